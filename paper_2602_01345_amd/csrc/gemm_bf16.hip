@@ -561,8 +561,8 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restric
 //   0: 128x128x64, 4 waves of 64x64, 2 LDS stages, two workgroups per CU
 //   1: 256x256x64, 8 waves of 128x64, 2 stages
 //   2: 256x128x64, 8 waves of 64x64, 3 stages
-//   3: 64x32x64, 2 waves of 32x32, 6 stages, staggered K walk          (M <= 64)
-//   4: 128x32x64, 4 waves of 32x32, 4 stages, staggered K walk         (M <= 256; M <= 512 for a narrow output and short K)
+//   3: 64x32x64, 2 waves of 32x32, 6 stages, staggered K walk          (head entropy only, M <= 64)
+//   4: 128x32x64, 4 waves of 32x32, 4 stages, staggered K walk         (head entropy only, M <= 256 or 512)
 //   5: 128x128x64, 8 waves of 64x32, 3 stages, one workgroup per CU (two waves per SIMD hide the LDS waits that
 //      four waves of 64x64 expose: 3-10 % faster at every shape measured)
 //   6: 256x256x32, 8 waves of 128x64, 3 stages
@@ -572,7 +572,9 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restric
 // every CU holds one, plus a fixed prologue/epilogue time.  Large tiles win when their tile count
 // fills whole rounds; the one-workgroup 128x128 kernel wins when there are few tiles (narrow
 // outputs, late blocks with few kept tokens).
+//   7: the few-rows kernels of gemm_rows_bf16.hip (chosen by their own plan, not by force)
 constexpr int kNumCfgs = 7;
+constexpr int kRowsCfg = 7;
 
 struct Candidate {
   int cfg, bm, bn;
@@ -599,18 +601,25 @@ double model_time(const Candidate& c, double slots, int M, int Nout, int K, bool
   return std::ceil(tiles / slots) * (t_tile + kFixed) * (K >= 4096 ? 0.8 : 1.0);
 }
 
-// Whether M rows of this projection go to the narrow-tile kernels (see pick_cfg).
+// Whether M rows of a prediction head go to the narrow-tile kernels (more workgroups for the weight stream).
 bool narrow_tiles(int M, int Nout, int K) { return M <= 256 || (M <= 512 && Nout < 4096 && K < 4096); }
 
-int pick_cfg(const nova_ctx* ctx, int M, int Nout, int K, double* t_out = nullptr, bool alone = true) {
+// Modelled time of the few-rows kernels: the weight stream, 3 us to start and end, 2.7 us per 64 rows (measured 3.6 ...
+// 24.5 us over 16 ... 256 rows and 2 ... 34 MB of weights, within 2 us), 3 us for the slice sums of a long K.
+double rows_time(int rows, int Nout, int K) {
+  return 3e-6 + 2.0 * Nout * K / 5e12 + 2.7e-6 * ((rows + 63) / 64) + (K >= 4096 ? 3e-6 : 0.0);
+}
+
+int pick_cfg(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64_t part_floats, double* t_out = nullptr,
+             bool alone = true) {
   if (ctx && ctx->gemm_cfg >= 0 && ctx->gemm_cfg < kNumCfgs) return ctx->gemm_cfg;
-  // few rows (the early, small scales): the weights are streamed once and the output has too few
-  // large tiles to occupy the CUs, so narrow tiles spread the weight stream over many workgroups
-  // (from 257 rows on only for a narrow output with a short K, the attention output projection: measured at 288 ...
-  // 512 rows, 128 x 32 tiles against 128 x 128: QKV 32-35 / 27 us, FFN1 32-39 / 25-27 us, FFN2 45-49 / 28-34 us
-  // (the latter with K slices), O-proj 17-19 / 23 us)
-  if (M <= 64) return 3;
-  if (narrow_tiles(M, Nout, K)) return 4;
+  if (mode == EPI_ENTROPY) {
+    if (M <= 64) return 3;
+    if (narrow_tiles(M, Nout, K)) return 4;
+  } else if (gemm_rows_plan(ctx ? ctx->num_cus : 256, mode, M, Nout, K, part_floats).rg) {
+    if (t_out) *t_out = rows_time(M, Nout, K);
+    return kRowsCfg;
+  }
   const double slots = ctx ? ctx->num_cus : 256;
   int best = 2;
   double best_t = 1e30;
@@ -629,10 +638,10 @@ struct Plan {
   int n;
   int m_base[2], m_end[2], cfg[2];
 };
-Plan plan_rows(const nova_ctx* ctx, int mode, int M, int Nout, int K) {
+Plan plan_rows(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64_t part_floats) {
   Plan p;
   double t_single = 1e30;
-  p.n = 1; p.m_base[0] = 0; p.m_end[0] = M; p.cfg[0] = pick_cfg(ctx, M, Nout, K, &t_single);
+  p.n = 1; p.m_base[0] = 0; p.m_end[0] = M; p.cfg[0] = pick_cfg(ctx, mode, M, Nout, K, part_floats, &t_single);
   const bool forced = ctx && ctx->gemm_cfg >= 0 && ctx->gemm_cfg < kNumCfgs;
   if (forced || mode == EPI_ENTROPY || M <= 512 || (ctx && ctx->gemm_parts == 0)) return p;   // one launch
   const int slots = ctx ? ctx->num_cus : 256;
@@ -641,14 +650,7 @@ Plan plan_rows(const nova_ctx* ctx, int mode, int M, int Nout, int K) {
     for (int rows = 1; rows * c.bm < M; ++rows) {         // tile rows in the first part
       const int m1 = rows * c.bm;
       double t_rest = 0.0;
-      const int cfg_rest = pick_cfg(ctx, M - m1, Nout, K, &t_rest, false);
-      if (narrow_tiles(M - m1, Nout, K)) {
-        // the narrow-tile kernels stream the weights once: measured 16 / 21 / 35 us for <= 128 / 256 / 512 rows of
-        // a 2048 x 8192 projection, in proportion to the weight bytes, never under 15 us
-        const int mr = M - m1;
-        const double w_time = 2.0 * Nout * (double)K / 3.2e12 * (mr <= 128 ? 1.0 : mr <= 256 ? 1.45 : 3.0);
-        t_rest = std::max(15e-6, 6e-6 + w_time) + (K >= 4096 ? 5e-6 : 0.0);
-      }
+      const int cfg_rest = pick_cfg(ctx, mode, M - m1, Nout, K, part_floats, &t_rest, false);
       const double t = model_time(c, slots, m1, Nout, K) + t_rest + 3e-6;
       if (t < best) {
         best = t;
@@ -664,6 +666,16 @@ Plan plan_rows(const nova_ctx* ctx, int mode, int M, int Nout, int K) {
 template <int MODE>
 hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W, int m_base, int M, int Nout, int K,
                        const EpiParams<bf16_t>& ep, int slots, int cus, int ksplit) {
+  if (cfg == kRowsCfg) {
+    const RowsPlan plan = gemm_rows_plan(cus, MODE, M - m_base, Nout, K, ep.part ? ep.part_floats : 0);
+    const hipError_t e = launch_gemm_rows_bf16(st, plan, plan.slices > 1 ? EPI_PARTIAL : MODE, A, W, m_base, M, Nout, K, ep);
+    if (e != hipSuccess || plan.slices == 1) return e;
+    if constexpr (MODE == EPI_RESIDUAL) {
+      const int64_t nvec = (int64_t)(M - m_base) * (Nout / 8);
+      gemm_reduce_kernel<MODE><<<(unsigned)((nvec + 255) / 256), 256, 0, st>>>(ep.part, plan.slices, m_base, M, Nout, ep);
+    }
+    return hipGetLastError();
+  }
   if constexpr (MODE == EPI_RESIDUAL) {
     // A long K and a narrow output with large tiles (the FFN down projection once few tokens are kept): the tiles
     // fill less than half of the CUs.  K is cut into 2 or 4 slices summed by as many workgroups per tile, fp32
@@ -688,30 +700,19 @@ hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W
       }
     }
   }
-  if constexpr (MODE == EPI_RESIDUAL || MODE == EPI_ATTN_OUT) {
-    // Few rows and a narrow output (the two projections back to C of the small scales and of row remainders): a
-    // tile column is one workgroup, too few to stream the weights at speed.  K is cut into slices summed by more
-    // workgroups (at least eight K steps per slice); a second small pass adds the slices and applies the epilogue.
-    const int wgs = ((M - m_base + (cfg == 3 ? 63 : 127)) / (cfg == 3 ? 64 : 128)) * ((Nout + 31) / 32);
-    if ((cfg == 3 || cfg == 4) && ep.part && wgs <= 128 && K >= 2048 && K % (4 * 64) == 0 && Nout % 8 == 0 &&
-        (int64_t)4 * (M - m_base) * Nout <= ep.part_floats) {
-      const int ks = 4;
-      const hipError_t e =
-          cfg == 3 ? launch_cfg<64, 32, 2, 1, 64, 6, true, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks)
-                   : launch_cfg<128, 32, 4, 1, 64, 4, true, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
-      if (e != hipSuccess) return e;
-      const int64_t nvec = (int64_t)(M - m_base) * (Nout / 8);
-      gemm_reduce_kernel<MODE><<<(unsigned)((nvec + 255) / 256), 256, 0, st>>>(ep.part, ks, m_base, M, Nout, ep);
-      return hipGetLastError();
-    }
-  }
   switch (cfg) {
     case 0: return launch_cfg<128, 128, 2, 2, 64, 2, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
     case 1: return launch_cfg<256, 256, 2, 4, 64, 2, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
-    case 3: return launch_cfg<64, 32, 2, 1, 64, 6, true, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
-    case 4: return launch_cfg<128, 32, 4, 1, 64, 4, true, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
     case 5: return launch_cfg<128, 128, 2, 4, 64, 3, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
     case 6: return launch_cfg<256, 256, 2, 4, 32, 3, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
+    case 3:
+      if constexpr (MODE == EPI_ENTROPY)
+        return launch_cfg<64, 32, 2, 1, 64, 6, true, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
+      [[fallthrough]];
+    case 4:
+      if constexpr (MODE == EPI_ENTROPY)
+        return launch_cfg<128, 32, 4, 1, 64, 4, true, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
+      [[fallthrough]];
     default: return launch_cfg<256, 128, 4, 2, 64, 3, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
   }
 }
@@ -719,7 +720,7 @@ hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W
 template <int MODE>
 hipError_t launch_mode(const nova_ctx* ctx, hipStream_t st, const bf16_t* A, const bf16_t* W, int M, int Nout,
                        int K, const EpiParams<bf16_t>& ep) {
-  const Plan p = plan_rows(ctx, MODE, M, Nout, K);
+  const Plan p = plan_rows(ctx, MODE, M, Nout, K, ep.part ? ep.part_floats : 0);
   for (int i = 0; i < p.n; ++i) {
     const int cus = ctx ? ctx->num_cus : 256;
     const hipError_t e = launch_part<MODE>(st, p.cfg[i], A, W, p.m_base[i], p.m_end[i], Nout, K, ep,
@@ -734,7 +735,7 @@ hipError_t launch_mode(const nova_ctx* ctx, hipStream_t st, const bf16_t* A, con
 
 // Output columns per tile of the configuration launch_gemm_bf16 uses for this shape.
 int gemm_bf16_tile_cols(const nova_ctx* ctx, int M, int Nout, int K) {
-  switch (pick_cfg(ctx, M, Nout, K)) {
+  switch (pick_cfg(ctx, EPI_ENTROPY, M, Nout, K, 0)) {
     case 0: case 5: return 128;
     case 1: case 6: return 256;
     case 3: case 4: return 32;

@@ -1,0 +1,306 @@
+// out = epilogue(A W^T) for few rows (the projections of the early, small scales and of row remainders): the weights
+// are read once and everything else is latency.
+//
+// The floor of such a projection is its weight stream, 2 Nout K bytes (0.4 ... 6.5 us at the rate of a large copy), plus
+// the launch (1.6 us inside a graph).  A kernel that walks K step by step through an LDS ring shared by the workgroup,
+// with a barrier per step and 20 KB in flight, takes 8 ... 17 us whatever the size.  Here:
+//  * The KW waves of a workgroup share one output tile (8 RG rows x 8 NG features) and split K among themselves: wave w
+//    takes the runs ("units") of 64 elements w, w + KW, ...  The narrow tile gives every projection enough workgroups
+//    to stream its weights from all over the chip, and no wave waits for another one until the end, when the partial
+//    sums meet once in LDS and are added in a fixed order.
+//  * A wave keeps S units in flight in an LDS ring of its own (global -> LDS loads of eight rows x 128 bytes, so that
+//    the eight lanes of a row ask for one line; operands loaded straight into the MFMA's register layout, 16 rows per
+//    16 lanes, cost one line look-up per lane: measured 1.3x slower with one row, 2x with 64).  No barrier: the wave
+//    waits for its own loads only.  Groups of eight rows that do not exist are not loaded.
+//  * The epilogue works on eight consecutive features of one row per thread, rows fastest, so that value-cache
+//    columns (key index minor) are written in runs of rows; its bias and residual are requested before the K walk.
+// Measured in a graph, weights from HBM, against the shared-ring kernel with 64 x 32 / 128 x 32 tiles (us): K = 1024,
+// Nout = 1024 / 3072 / 4096, one row 8.0 / 9.8 / 9.1 -> 3.5 / 4.5 / 4.7, 64 rows 8.2 / 9.9 / 9.4 -> 4.6 / 6.1 / 6.3,
+// 256 rows 8.9 / 10.4 / 10.3 -> 5.0 / 8.6 / 8.8; K = 2048, Nout = 8192, one row 13.8 -> 8.4 (4.9 TB/s with the launch
+// taken off), 64 rows 14.1 -> 12.3; K = 8192, Nout = 2048, one row 16.8 -> 8.7.
+#include "common.h"
+#include "epilogue.h"
+#include "nova_internal.h"
+
+namespace {
+
+typedef const __attribute__((address_space(1))) void* gptr_t;
+typedef __attribute__((address_space(3))) void* lptr_t;
+#define WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
+
+// s_waitcnt vmcnt(younger * LPU) for a wave-uniform younger in 0 .. MAXJ
+template <int MAXJ, int LPU>
+__device__ __forceinline__ void wait_younger(int younger) {
+  if constexpr (MAXJ == 0) {
+    WAIT_VMCNT(0);
+  } else {
+    if (younger == MAXJ) { WAIT_VMCNT(MAXJ * LPU); } else { wait_younger<MAXJ - 1, LPU>(younger); }
+  }
+}
+
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ f32x4v mfma16(bf16x8 a, bf16x8 b, f32x4v c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+
+// RG, NG: groups of eight rows / features of a tile (an MFMA tile is 16 x 16: with an odd count its other half is
+// whatever lies in LDS behind and is never used); KW: waves; S: units in flight per wave
+template <int RG, int NG, int KW, int S, int MODE>
+__global__ __launch_bounds__(KW* 64) void gemm_rows_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
+                                                            int M, int Nout, int K, int m_base, EpiParams<bf16_t> ep) {
+  constexpr int MT = (RG + 1) / 2, NF = (NG + 1) / 2;
+  constexpr int ROWS = MT * 16, LROWS = RG * 8, COLS = NG * 8, NT = KW * 64;
+  constexpr int COL8 = COLS / 8;                         // eight-feature groups per row: one thread each in the epilogue
+  constexpr int LPU = NG + RG;                       // 1 KB load instructions per unit
+  constexpr int SLOT = (NG + RG) * 1024;                 // rows 8 .. 15 of an odd group count are whatever follows: never used
+  constexpr int NO = (ROWS * COL8 + NT - 1) / NT;        // of which a thread takes this many
+  static_assert(S * LPU < 64, "vmcnt is a 6-bit counter");
+  __shared__ __attribute__((aligned(1024))) char lds[KW * S * SLOT + 1024];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n0 = blockIdx.x * COLS, m0 = m_base + blockIdx.y * LROWS;
+  if (ep.k_rows) {
+    // per-image keep counts: a tile without a live row has nothing to compute (the whole workgroup leaves together)
+    const int m_hi = min(m0 + LROWS, M);
+    bool live = false;
+    for (int b = m0 / ep.k; b * ep.k < m_hi; ++b)
+      live = live || max(m0 - b * ep.k, 0) < image_count(ep.k_rows, b, ep.k);
+    if (!live) return;
+  }
+
+  // ---- fills: instruction j of a unit drops 8 rows x 128 bytes into LDS; slot p of row r holds chunk p ^ ((r >> 1) & 7)
+  const int units_all = K / 64;                          // runs of 64 elements
+  const int slices = gridDim.z;                          // EPI_PARTIAL only: contiguous parts of the runs
+  const int u_lo = (int)((int64_t)units_all * blockIdx.z / slices) + wave;
+  const int n_units = ((int)((int64_t)units_all * (blockIdx.z + 1) / slices) - u_lo + KW - 1) / KW;   // of this wave
+  const int lr = lane >> 3, lp = lane & 7;
+  const bf16_t* pw[NG];
+  const bf16_t* pa[RG];
+#pragma unroll
+  for (int j = 0; j < NG; ++j) {
+    const int r = j * 8 + lr;
+    pw[j] = W + (int64_t)min(n0 + r, Nout - 1) * K + (lp ^ ((r >> 1) & 7)) * 8;
+  }
+#pragma unroll
+  for (int j = 0; j < RG; ++j) {
+    const int r = j * 8 + lr;
+    pa[j] = A + (int64_t)min(m0 + r, M - 1) * K + (lp ^ ((r >> 1) & 7)) * 8;
+  }
+  char* mine_lds = lds + wave * (S * SLOT);
+  auto issue = [&](int i) {
+    char* d = mine_lds + (i % S) * SLOT;
+    const int k0 = (u_lo + i * KW) * 64;
+#pragma unroll
+    for (int j = 0; j < NG; ++j) __builtin_amdgcn_global_load_lds((gptr_t)(pw[j] + k0), (lptr_t)(d + j * 1024), 16, 0, 0);
+#pragma unroll
+    for (int j = 0; j < RG; ++j) __builtin_amdgcn_global_load_lds((gptr_t)(pa[j] + k0), (lptr_t)(d + (NG + j) * 1024), 16, 0, 0);
+  };
+  // This thread's outputs: row m0 + o % ROWS, features n0 + 8 (o / ROWS) .. for o = tid, tid + NT, ...  Their bias,
+  // residual and gate are requested behind the first units; only the gathered residual's index, which its address
+  // waits for, goes ahead of them.  (vmcnt counts in order: the waits below are then for a few loads more than needed.)
+  constexpr bool HAS_RES = MODE == EPI_ATTN_OUT || MODE == EPI_RESIDUAL;
+  auto has_output = [&](int o) { return o < ROWS * COL8 && o % ROWS < LROWS && m0 + o % ROWS < M; };
+  bf16x8 bias[NO], res[HAS_RES ? NO : 1], gate[HAS_RES ? NO : 1];
+  int src[NO];
+#pragma unroll
+  for (int q = 0; q < NO; ++q) {
+    const int o = tid + q * NT;
+    src[q] = MODE == EPI_ATTN_OUT && has_output(o) ? ep.idx[m0 + o % ROWS] : 0;
+  }
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int i = 0; i < S; ++i)
+    if (i < n_units) issue(i);
+  asm volatile("" ::: "memory");
+#pragma unroll
+  for (int q = 0; q < NO; ++q) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      bias[q][e] = (bf16_t)0.f;
+      if (HAS_RES) { res[q][e] = (bf16_t)0.f; gate[q][e] = (bf16_t)1.f; }
+    }
+    const int o = tid + q * NT, row = m0 + o % ROWS, col = n0 + o / ROWS * 8;
+    if (MODE == EPI_PARTIAL || !has_output(o)) continue;
+    if (ep.bias) bias[q] = *reinterpret_cast<const bf16x8*>(ep.bias + col);
+    if constexpr (HAS_RES) {
+      int64_t roff = (int64_t)row * ep.ldo;
+      if (MODE == EPI_ATTN_OUT) roff = ((int64_t)(row / ep.k) * ep.Ntok + min(max(src[q], 0), ep.Ntok - 1)) * ep.C;
+      res[q] = *reinterpret_cast<const bf16x8*>(ep.res + roff + col);
+      if (ep.gate) gate[q] = *reinterpret_cast<const bf16x8*>(ep.gate + (int64_t)(row / ep.k) * ep.gate_pitch + col);
+    }
+  }
+  asm volatile("" ::: "memory");
+
+  const int r16 = lane & 15, kg = lane >> 4;
+  int off[2];                                            // byte offset of this lane's chunk of K step s in a 16-row tile
+#pragma unroll
+  for (int s = 0; s < 2; ++s) off[s] = r16 * 128 + (((s * 4 + kg) ^ ((r16 >> 1) & 7)) << 4);
+  f32x4v acc[MT][NF];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int f = 0; f < NF; ++f) acc[i][f] = f32x4v{0.f, 0.f, 0.f, 0.f};
+
+  for (int i = 0; i < n_units; ++i) {
+    // unit i has landed once at most the younger ones are in flight
+    const int younger = min(n_units - 1 - i, S - 1);
+    wait_younger<S - 1, LPU>(younger);
+    asm volatile("" ::: "memory");
+    const char* d = mine_lds + (i % S) * SLOT;
+    bf16x8 wf[2][NF], af[2][MT];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+#pragma unroll
+      for (int f = 0; f < NF; ++f) wf[s][f] = *reinterpret_cast<const bf16x8*>(d + f * 2048 + off[s]);
+#pragma unroll
+      for (int t = 0; t < MT; ++t) af[s][t] = *reinterpret_cast<const bf16x8*>(d + NG * 1024 + t * 2048 + off[s]);
+    }
+    if (i + S < n_units) {
+      __builtin_amdgcn_s_waitcnt(0xC07F);                // lgkmcnt(0): the slot has been read
+      asm volatile("" ::: "memory");
+      issue(i + S);
+    }
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) acc[t][f] = mfma16(wf[s][f], af[s][t], acc[t][f]);
+  }
+
+  // a lane holds features 4 kg .. 4 kg + 3 of row l % 16 of every tile
+#pragma unroll
+  for (int t = 0; t < MT; ++t)
+#pragma unroll
+    for (int f = 0; f < NF; ++f) *reinterpret_cast<f32x4v*>(mine_lds + ((f * 4 + kg) * ROWS + t * 16 + r16) * 16) = acc[t][f];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < NO; ++q) {
+    const int o = tid + q * NT, row = m0 + o % ROWS, col = n0 + o / ROWS * 8;
+    if (!has_output(o)) continue;
+    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < KW; ++w) {
+      const char* p = lds + w * (S * SLOT) + (2 * (o / ROWS) * ROWS + o % ROWS) * 16;
+      const f32x4v a = *reinterpret_cast<const f32x4v*>(p), b = *reinterpret_cast<const f32x4v*>(p + ROWS * 16);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { v[e] += a[e]; v[4 + e] += b[e]; }
+    }
+    if constexpr (MODE == EPI_PARTIAL) {
+      float* p = ep.part + ((int64_t)blockIdx.z * (M - m_base) + row - m_base) * Nout + col;
+      *reinterpret_cast<f32x4v*>(p) = f32x4v{v[0], v[1], v[2], v[3]};
+      *reinterpret_cast<f32x4v*>(p + 4) = f32x4v{v[4], v[5], v[6], v[7]};
+      continue;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += (float)bias[q][e];
+    bf16x8 y;
+    if constexpr (MODE == EPI_QKV) {
+      const int sel = col / ep.C, cf = col - sel * ep.C;   // C is a multiple of 64: eight features lie in one part and head
+      const float qs = sel == 0 ? ep.q_scale : 1.0f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) y[e] = (bf16_t)(v[e] * qs);
+      if (sel == 0) {
+        *reinterpret_cast<bf16x8*>(ep.out + (int64_t)row * ep.ldo + cf) = y;
+        continue;
+      }
+      const int b = row / ep.k, s = row - b * ep.k;
+      if (s >= image_count(ep.k_rows, b, ep.k)) continue;  // slots past an image's keep count append nothing
+      const int head = cf / ep.dh, d = cf - head * ep.dh;
+      const int64_t bh = (int64_t)b * ep.heads + head;
+      const int pos = image_prior(ep.kv_rows, b, ep.P) + s;
+      if (sel == 1) {
+        *reinterpret_cast<bf16x8*>(ep.kc + (bh * ep.cap + pos) * ep.dh + d) = y;
+      } else {
+        bf16_t* vp = ep.vc + (bh * ep.dh + d) * ep.cap + pos;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) vp[(int64_t)e * ep.cap] = y[e];
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        if (MODE == EPI_GELU) v[e] = gelu_erf(v[e]);
+        if (MODE == EPI_GELU_TANH) v[e] = gelu_tanh(v[e]);
+        if (MODE == EPI_PLAIN) v[e] *= ep.q_scale;
+        y[e] = (bf16_t)v[e];
+      }
+      if constexpr (HAS_RES) {                             // the projection (+ bias) is rounded before gate and residual
+        if (ep.gate) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) y[e] = (bf16_t)fmaf((float)gate[q][e], (float)y[e], (float)res[q][e]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) y[e] = (bf16_t)((float)y[e] + (float)res[q][e]);
+        }
+      }
+      *reinterpret_cast<bf16x8*>(ep.out + (int64_t)row * ep.ldo + col) = y;
+    }
+  }
+}
+
+template <int RG, int NG, int KW, int S, int MODE>
+hipError_t go(hipStream_t st, const bf16_t* A, const bf16_t* W, int m_base, int M, int Nout, int K, int slices,
+              const EpiParams<bf16_t>& ep) {
+  const dim3 grid(Nout / (NG * 8), (M - m_base + RG * 8 - 1) / (RG * 8), slices);
+  gemm_rows_kernel<RG, NG, KW, S, MODE><<<grid, KW * 64, 0, st>>>(A, W, M, Nout, K, m_base, ep);
+  return hipGetLastError();
+}
+
+template <int MODE>
+hipError_t by_plan(hipStream_t st, const RowsPlan& p, const bf16_t* A, const bf16_t* W, int m_base, int M, int Nout, int K,
+                   const EpiParams<bf16_t>& ep) {
+#define GO(RG_, NG_, KW_, S_) \
+  if (p.rg == RG_ && p.ng == NG_ && p.s == S_) return go<RG_, NG_, KW_, S_, MODE>(st, A, W, m_base, M, Nout, K, p.slices, ep)
+  GO(1, 1, 8, 4); GO(1, 2, 4, 4); GO(1, 4, 4, 4);
+  GO(2, 1, 8, 2); GO(2, 2, 4, 4); GO(2, 4, 4, 3);
+  GO(4, 1, 8, 3); GO(4, 2, 4, 3); GO(4, 4, 4, 4);
+  GO(8, 1, 4, 2); GO(8, 2, 4, 2); GO(8, 4, 4, 2); GO(8, 8, 4, 2); GO(8, 8, 4, 1);
+#undef GO
+  return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+// Tile and K slices for `rows` rows, or rg = 0 where the shared-ring kernels are faster.
+//  * The narrowest tile that needs no more workgroups than there are CUs: half of them leave CUs idle (64 rows,
+//    Nout = 3072, K = 1024: 96 workgroups 6.7 us, 192 6.1), twice as many fetch the rows twice as often (K = 2048,
+//    Nout = 6144: 192 workgroups 10.8 us, 384 15.0).  One tile shape has to do for up to 8 x 8 groups; beyond one
+//    workgroup per CU two of them still fit with one unit in flight each.
+//  * From 512 rows or two workgroups per CU on the 128- and 256-row tiles win (512 rows, K = 2048, Nout = 6144: 23.8
+//    against 27.8 us; at 256 rows 23.5 against 17.9).
+//  * A long K into few features (the FFN down projection) with 33 ... 128 rows: the tiles would fill a quarter of the
+//    CUs, so K is cut into four slices and a second small pass adds them (64 rows, K = 8192: 20 us uncut, 15.1 cut;
+//    with 16 rows 11.7 uncut, 12.9 cut; with 200 rows, K = 4096 10.6 uncut, 13.2 cut).
+RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K, int64_t part_floats) {
+  RowsPlan p = {};
+  if (mode == EPI_ENTROPY || rows > 512 || Nout % 64 != 0) return p;
+  const int rg = rows <= 8 ? 1 : rows <= 16 ? 2 : rows <= 32 ? 4 : 8;
+  const int row_tiles = (rows + 8 * rg - 1) / (8 * rg);
+  p.slices = 1;
+  if (mode == EPI_RESIDUAL && K >= 4096 && rows > 32 && rows <= 128 && (int64_t)4 * rows * Nout <= part_floats) p.slices = 4;
+  const int ng_max = rg == 8 ? 8 : 4;
+  int ng = 1;
+  while (ng < ng_max && row_tiles * (Nout / (8 * ng)) * p.slices > num_cus) ng *= 2;
+  const int wgs = row_tiles * (Nout / (8 * ng)) * p.slices;
+  if (rows > 64 && (wgs > 2 * num_cus || (wgs > num_cus && mode == EPI_RESIDUAL))) return p;
+  p.rg = rg;
+  p.ng = ng;
+  p.s = rg == 8 ? (ng == 8 && wgs > num_cus ? 1 : 2) : rg == 4 ? (ng == 4 ? 4 : 3) : rg == 2 ? (ng == 1 ? 2 : ng == 2 ? 4 : 3) : 4;
+  return p;
+}
+
+hipError_t launch_gemm_rows_bf16(hipStream_t st, const RowsPlan& p, int mode, const bf16_t* A, const bf16_t* W, int m_base,
+                                 int M, int Nout, int K, const EpiParams<bf16_t>& ep) {
+  switch (mode) {
+    case EPI_QKV: return by_plan<EPI_QKV>(st, p, A, W, m_base, M, Nout, K, ep);
+    case EPI_ATTN_OUT: return by_plan<EPI_ATTN_OUT>(st, p, A, W, m_base, M, Nout, K, ep);
+    case EPI_GELU: return by_plan<EPI_GELU>(st, p, A, W, m_base, M, Nout, K, ep);
+    case EPI_GELU_TANH: return by_plan<EPI_GELU_TANH>(st, p, A, W, m_base, M, Nout, K, ep);
+    case EPI_PLAIN: return by_plan<EPI_PLAIN>(st, p, A, W, m_base, M, Nout, K, ep);
+    case EPI_PARTIAL: return by_plan<EPI_PARTIAL>(st, p, A, W, m_base, M, Nout, K, ep);
+    case EPI_RESIDUAL: return by_plan<EPI_RESIDUAL>(st, p, A, W, m_base, M, Nout, K, ep);
+    default: return hipErrorInvalidValue;
+  }
+}

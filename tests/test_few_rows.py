@@ -1,0 +1,39 @@
+"""GPU parity of the few-rows projection kernels (csrc/gemm_rows_bf16.hip) against the oracle at the edges of their tiles:
+row counts around 8, 16, 32 and multiples of 64, a K with fewer runs of 64 than a workgroup has waves (C = 64, 320), every
+tile width the plan can pick, the long-K down projection with and without K slices.
+Tolerance: bf16 tensors max|d| / max|ref| <= 2e-2, as everywhere (the products and their sums are fp32)."""
+import pytest
+import torch
+
+import workloads as WL
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hx():
+    import harness
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU and the built libnova.so (no fallback)")
+    return harness
+
+
+def _block(B, grid, P, C, heads):
+    return WL.Workload("few", "bf16", B=B, C=C, heads=heads, L=1, V=64, keep_hi=.5, keep_lo=.5,
+                       scales=(WL.Scale(grid=grid, prev_grid=max(grid - 2, 1), kv_len=P),), seed=17)
+
+
+@pytest.mark.parametrize("C,heads", [(64, 1), (320, 5), (1024, 8)])
+@pytest.mark.parametrize("M", [1, 8, 9, 16, 17, 32, 33, 64, 65, 129, 257])
+def test_row_counts_around_the_tiles(hx, C, heads, M):
+    print(f"few rows C={C} M={M}", flush=True)
+    wl = _block(1, 17, 40, C, heads)
+    hx.check_block(hx.make_host_block(wl, 0, k=M), hx.BF16_TOL)
+
+
+@pytest.mark.parametrize("C,heads,M", [(2048, 16, 5), (2048, 16, 12), (2048, 16, 30), (2048, 16, 50), (2048, 16, 100),
+                                       (1920, 30, 72), (512, 8, 511), (1024, 8, 512)])
+def test_widths_and_long_k(hx, C, heads, M):
+    print(f"few rows C={C} M={M}", flush=True)
+    wl = _block(1, 23, 20, C, heads)
+    hx.check_block(hx.make_host_block(wl, 0, k=M), hx.BF16_TOL)
