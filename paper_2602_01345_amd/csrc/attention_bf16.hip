@@ -586,6 +586,11 @@ hipError_t launch_attention_bf16(const nova_ctx* ctx, hipStream_t st, const void
   const bf16_t* vc = static_cast<const bf16_t*>(vcv);
   bf16_t* out = static_cast<bf16_t*>(outv);
   const int dh = C / heads;
+  if (!ctx || (ctx->attn_cfg < 1 && ctx->attn_split < 2)) {     // neither shape nor split is forced
+    const int waves = attention_few_waves(ctx ? ctx->num_cus : 256, dh, B, k, heads, kv_total);
+    if (waves) return launch_attention_few_bf16(st, waves, qv, kcv, vcv, B, k, C, heads, cap, kv_total, outv, k_rows,
+                                                kv_rows, P, self_keys);
+  }
   // One group of 32 queries per wave (two workgroups per CU, so that one wave's softmax overlaps
   // another wave's MFMAs); two groups per wave (half the LDS reads per MFMA, one workgroup per
   // CU) can be forced for tuning.

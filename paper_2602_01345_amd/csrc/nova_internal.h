@@ -149,6 +149,12 @@ hipError_t launch_attention_bf16(const nova_ctx* ctx, hipStream_t st, const void
                                  int B, int k, int C, int heads, int cap, int kv_total, void* out,
                                  float* part_o, float* part_ml, int64_t part_floats, const int32_t* k_rows = nullptr,
                                  const int32_t* kv_rows = nullptr, int P = 0, int self_keys = 1);
+// attention_few_bf16.hip: the same for few queries (32-query workgroups of `waves` waves that split the keys);
+// attention_few_waves is 0 where attention_bf16.hip is faster
+int attention_few_waves(int slots, int dh, int B, int k, int heads, int kv_total);
+hipError_t launch_attention_few_bf16(hipStream_t st, int waves, const void* q, const void* kc, const void* vc, int B, int k, int C,
+                                     int heads, int cap, int kv_total, void* out, const int32_t* k_rows,
+                                     const int32_t* kv_rows, int P, int self_keys);
 // block_bf16.hip: MFMA path
 hipError_t launch_block_bf16(nova_ctx* ctx, hipStream_t st, const nova_block_shape& s,
                              const nova_block_weights& w, const nova_block_variant& var, const RowCounts& rc,
