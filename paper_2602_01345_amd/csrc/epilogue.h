@@ -15,6 +15,16 @@ enum EpiMode {
   EPI_PARTIAL = 7     // raw fp32 sums over one slice of K, [slice][M][Nout]; a reduce pass applies the real epilogue
 };
 
+// Division of 0 <= n < 2^31 by d >= 1 through inv = div_inv(d), made once on the host: the high half of n * inv is the
+// quotient or one less.
+inline uint32_t div_inv(int d) { return 0xFFFFFFFFu / (uint32_t)d; }
+__device__ __forceinline__ int div_by(int n, int d, uint32_t inv, int& rem) {
+  int q = (int)__umulhi((uint32_t)n, inv);
+  rem = n - q * d;
+  if (rem >= d) { ++q; rem -= d; }
+  return q;
+}
+
 template <typename T>
 struct EpiParams {
   const T* bias;        // [Nout] or nullptr
@@ -46,28 +56,31 @@ struct EpiParams {
   // floats), or nullptr to forbid slicing
   float* part;
   int64_t part_floats;
+  // bf16 kernels: div_inv(k) and log2(dh), set by launch_gemm_bf16
+  uint32_t k_inv;
+  int dh_log2;
+
+  // image (and slot in it) of a kept-token row
+  __device__ __forceinline__ int image(int row, int& slot) const { return div_by(row, k, k_inv, slot); }
+  __device__ __forceinline__ int image(int row) const { int slot; return image(row, slot); }
 };
 
-// Exact-form GELU 0.5 v (1 + erf(v / sqrt 2)).  erf through the rational approximation 7.1.26 of
-// Abramowitz & Stegun (|error| <= 1.5e-7, far below the bf16 / fp32 rounding of the result) on the
-// native reciprocal and exp2 units instead of the branchy library erff: this runs once per output
-// element of the FFN up-projection.
+// Exact-form GELU v Phi(v), Phi the normal distribution function, as v / (1 + 2^-z(v)): z is log2 of the odds
+// Phi(v) / Phi(-v), an odd function that v times a polynomial of degree 6 in v^2 meets so closely (fitted over
+// |v| <= 5.5, beyond which v / (1 + 2^-z) is v or 0 either way) that the result is off by at most 7e-8 before rounding
+// to fp32; the rational erf 7.1.26 of Abramowitz & Stegun, 2.1e-7 off, takes one instruction more.  This runs once
+// per output element of the FFN up-projection, where every instruction is 1.3 us of a round of 256 x 256 tiles.
 __device__ __forceinline__ float gelu_erf(float v) {
-  // GELU(v) = v Phi(v) = max(v, 0) - |v| h,  h = erfc(|v| / sqrt 2) / 2 = (poly(t) / 2) e^(-v^2 / 2),
-  // t = 1 / (1 + p |v| / sqrt 2): the 1/2 and the 1/sqrt 2 are folded into the constants
-  const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, fabsf(v), 1.0f));
-  float poly = fmaf(0.5f * 1.061405429f, t, 0.5f * -1.453152027f);
-  poly = fmaf(poly, t, 0.5f * 1.421413741f);
-  poly = fmaf(poly, t, 0.5f * -0.284496736f);
-  poly = fmaf(poly, t, 0.5f * 0.254829592f);
-  poly *= t;
-  const float w = v * 0.84932180028801904f;                 // sqrt(log2(e) / 2): e^(-v^2/2) = 2^(-w^2)
-  const float h = poly * __builtin_amdgcn_exp2f(-w * w);
-  // |v| h with the legacy multiply's 0 * inf = 0: an overflowed accumulator (v = +-inf, h = 0) saturates to
-  // +inf / 0 as the erf form does, instead of turning into NaN; NaN stays NaN
-  float tail;
-  asm("v_mul_legacy_f32 %0, |%1|, %2" : "=v"(tail) : "v"(v), "v"(h));
-  return fmaxf(v, 0.0f) - tail;
+  const float x = v * v;
+  float p = fmaf(5.21002386e-9f, x, -3.85050081e-7f);
+  p = fmaf(p, x, 1.14525110e-5f);
+  p = fmaf(p, x, -1.59389991e-4f);
+  p = fmaf(p, x, -9.55910802e-5f);
+  p = fmaf(p, x, 1.04838579e-1f);
+  p = fmaf(p, x, 2.30220720f);
+  const float s = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-v * p));
+  // an overflowed accumulator (v = -inf, s = 0) gives 0 and not NaN; a NaN comes through in s
+  return fmaxf(v, -3.0e38f) * s;
 }
 
 // tanh-form GELU 0.5 v (1 + tanh(z)), z = sqrt(2/pi) (v + 0.044715 v^3), written as v / (1 + e^(-2z)).

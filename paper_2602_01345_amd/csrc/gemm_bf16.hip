@@ -10,8 +10,15 @@
 //    lane-linear, the bank-conflict-avoiding XOR swizzle is applied on the global side: the
 //    lane that fills 16-byte slot p of row r fetches chunk p ^ ((r >> 1) & 7) of that row, and
 //    the MFMA operand reads look the chunk up at the same swizzled slot.
-//  * An NST-stage LDS ring (2 to 6 stages, per tile configuration): the loads of tiles t+1 .. t+NST-1 are in
-//    flight while tile t feeds the MFMAs; one bare barrier per K step with explicit vmcnt / lgkmcnt waits.
+//  * The 256 x 256 tile: two LDS buffers filled and freed in halves, the two waves of a SIMD alternating between the
+//    matrix cores and LDS (see the K loop).  Against one ring of K steps for all waves, same box, weights from HBM:
+//    4096 x 6912 x 2304 (QKV) 150 -> 124 us, 4096 x 9216 x 2304 (GELU) 225 -> 177, 8192 x 8192 x 8192 968 -> 833
+//    (1.14 -> 1.32 PFLOP/s; a large library product on the same card 1.40).
+//  * The smaller tiles: an NST-stage LDS ring (3 to 6 stages, per tile configuration): the loads of tiles
+//    t+1 .. t+NST-1 are in flight while tile t feeds the MFMAs; one bare barrier per K step with explicit
+//    vmcnt / lgkmcnt waits.
+//  * What surrounds the K loop is vector instructions at two waves per SIMD, some 4 ns each: bias and residual are
+//    what the accumulators start from, no epilogue goes through LDS, and no division is left in front of the first load.
 //  * Workgroup ids are remapped so that each XCD (ids are dealt round-robin to the 8 XCDs) works
 //    on a contiguous run of tiles, ordered in bands of 8 tile rows, so that the tiles in flight on
 //    one XCD form a compact rectangle and share A rows and W columns in that XCD's L2.
@@ -31,29 +38,38 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 // s_waitcnt with only vmcnt = n constrained (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
 #define WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
 
-// LDS byte offset of 16-byte chunk `c` of tile row `r`; a row holds BK elements (64 or 128 bytes).
+// 16 bytes per lane from base + lane_off + off (bytes; base and off wave-uniform) into 1 KB of LDS
+__device__ __forceinline__ void fill_lds(bf16_t* base, lptr_t dst, uint32_t lane_off, uint32_t off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(base, 0, 0x7FFFFFFF, 0x00020000), dst, 16,
+                                           lane_off, off, 0, 0);
+}
+
+// LDS byte offset of 16-byte chunk `c` of tile row `r`; a row holds 64 elements (128 bytes).
 // The XOR term changes with every group of rows that shares a bank window, so that 16 consecutive
 // rows reading the same chunk index hit 16 different 16-byte bank groups.
-template <int BK>
-__device__ __forceinline__ int swz(int r, int c) {
-  if (BK == 64) return r * 128 + ((c ^ ((r >> 1) & 7)) << 4);
-  return r * 64 + ((c ^ ((r >> 2) & 3)) << 4);
+__device__ __forceinline__ int swz(int r, int c) { return r * 128 + ((c ^ ((r >> 1) & 7)) << 4); }
+
+// Whether a workgroup walks several tiles (one workgroup per CU): the modes whose accumulators start from nothing but
+// the bias (a residual would have to wait for the previous tile's accumulators).
+constexpr bool persistent_tiles(bool stagger, int mode) {
+  return !stagger && (mode == EPI_QKV || mode == EPI_GELU || mode == EPI_GELU_TANH || mode == EPI_PLAIN);
 }
 
-// Whether a workgroup walks several tiles (one workgroup per CU): the modes whose epilogue needs no LDS, large
-// tiles only; with a residual the prefetched residual chunks of a wave's MFMA tiles must leave room in the
-// register file for the next tile's addresses (at most 4 MFMA tiles per wave).
-constexpr bool persistent_tiles(int mfma_tiles_per_wave, bool stagger, int mode) {
-  if (stagger) return false;
-  if (mode == EPI_GELU || mode == EPI_GELU_TANH || mode == EPI_PLAIN) return true;
-  return (mode == EPI_ATTN_OUT || mode == EPI_RESIDUAL) && mfma_tiles_per_wave <= 4;
-}
+// Workgroup id -> tile, with the divisions made on the host: a scalar division is some 30 dependent instructions, and
+// everything in front of a workgroup's first load is latency that nothing hides.
+struct TileMap {
+  int nblk, xcd_base, xcd_rem;             // tiles, tiles per XCD, XCDs with one more
+  int band_tiles, full_bands, last_rows;   // tiles per band of 8 tile rows, such bands, rows of the last, lower band
+  uint32_t band_inv, last_inv;             // div_inv of band_tiles / last_rows
+  int tiles_n, KT;                         // tile columns, K steps per workgroup
+};
 
-template <int BM, int BN, int WM, int WN, int BK, int NST, bool STAGGER, int MODE>
+// GATED (residual modes): the projection is multiplied by ep.gate before the residual is added
+template <int BM, int BN, int WM, int WN, int BK, int NST, bool STAGGER, int MODE, bool GATED>
 __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __restrict__ A,
                                                                 const bf16_t* __restrict__ W, int M, int Nout,
-                                                                int K, int m_base, int tiles_m, int tiles_n,
-                                                                int kslices, EpiParams<bf16_t> ep) {
+                                                                int K, int m_base, TileMap map,
+                                                                EpiParams<bf16_t> ep) {
   constexpr int NW = WM * WN;
   constexpr int TM = BM / WM / 32, TN = BN / WN / 32;      // MFMA tiles per wave
   constexpr int ROW_BYTES = BK * 2;
@@ -61,58 +77,79 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
   constexpr int RPI = 64 / CH;                             // tile rows filled by one wave load instruction
   constexpr int LA = BM / RPI / NW, LB = BN / RPI / NW;    // load instructions per wave per stage
   constexpr int LPW = LA + LB;
+  static_assert(BK == 64, "the swizzle is that of 128-byte rows");
   constexpr int KS = BK / 16;                              // MFMA K steps per stage
   constexpr int A_BYTES = BM * ROW_BYTES, B_BYTES = BN * ROW_BYTES, STAGE = A_BYTES + B_BYTES;
-  constexpr int CT_PITCH = BN + 8;                         // epilogue staging tile pitch (elements)
-  constexpr int CT_BYTES = BM * CT_PITCH * 2;
-  constexpr int LDS_BYTES = NST * STAGE > CT_BYTES ? NST * STAGE : CT_BYTES;
+  constexpr int LDS_BYTES = NST * STAGE;
   static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "tile rows must split over the waves");
   static_assert((NST - 2) * LPW < 64, "vmcnt is a 6-bit counter");
   __shared__ __attribute__((aligned(1024))) char lds[LDS_BYTES];
 
+  // all arguments in one round trip, not one per branch below that needs some
+  asm volatile("" ::"s"(A), "s"(W), "s"(M), "s"(Nout), "s"(K), "s"(m_base), "s"(map.xcd_base), "s"(map.xcd_rem),
+               "s"(map.band_tiles), "s"(map.full_bands), "s"(map.last_rows), "s"(map.band_inv), "s"(map.last_inv),
+               "s"(map.KT), "s"(ep.bias), "s"(ep.k_rows), "s"(ep.ldo));
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: LDS fill addresses stay scalar
   const int wm = wave / WN, wn = wave % WN;
 
   // ---- workgroup id -> tile, XCD-contiguous, M fastest -------------------------------
-  // kslices > 1 (EPI_PARTIAL only): the grid is kslices copies of the tile grid, copy s sums K slice s
+  // blockIdx.y: K slice (EPI_PARTIAL only)
   // PERSIST (the modes whose epilogue needs no LDS, large tiles): the grid is one workgroup per CU and a
   // workgroup takes the tiles L, L + gridDim.x, ...; the first K stages of its next tile are requested
   // before the epilogue of the current one, so their latency passes behind the epilogue.
-  constexpr bool PERSIST = persistent_tiles(BM / WM / 32 * (BN / WN / 32), STAGGER, MODE);
-  const int nblk = tiles_m * tiles_n;
-  const int kslice = PERSIST ? 0 : blockIdx.x / nblk;
-  int L = blockIdx.x - kslice * nblk;
+  constexpr bool PERSIST = persistent_tiles(STAGGER, MODE);
+  // PP: the two waves of a SIMD alternate between the matrix cores and LDS (see pp_loop below)
+  constexpr bool PP = BM == 256 && BN == 256 && BK == 64 && NST == 2 && WM == 2 && WN == 4;
+  // first tile row / column of MFMA tile i / jn of this wave
+  auto row_of = [&](int i) { return PP ? (i >> 1) * 128 + wm * 64 + (i & 1) * 32 : wm * (BM / WM) + i * 32; };
+  auto col_of = [&](int jn) { return PP ? jn * 128 + wn * 32 : wn * (BN / WN) + jn * 32; };
+  const int kslice = PERSIST ? 0 : blockIdx.y;
+  int L = blockIdx.x;
   // ---- global -> LDS: instruction i of this wave fills tile rows (i * NW + wave) * RPI + lane / CH
   const int lr = lane / CH, lp = lane % CH;
   const bf16_t* ga[LA];
   const bf16_t* gb[LB];
+  bf16_t *pp_a = nullptr, *pp_w = nullptr;                   // PP: the tile's first row / column and the lanes' offsets
+  uint32_t oa[PP ? LA : 1], ob[PP ? LB : 1];
   int tn = 0, m0 = 0, n0 = 0;
   auto set_tile = [&](int Lt) {
     // Lt -> tile, XCD-contiguous (gridDim.x is a multiple of 8 when a workgroup takes several tiles, so all of
     // them have its XCD's residue)
     const int xcd = Lt & 7, j = Lt >> 3;
-    const int base = nblk >> 3, rem = nblk & 7;
-    const int id = xcd * base + min(xcd, rem) + j;
-    // bands of GM tile rows, column by column inside a band: the workgroups an XCD runs at the same
-    // time then cover a compact GM x (slots / GM) rectangle and share A and W tiles in its L2
-    constexpr int GM = 8;
-    const int band = id / (GM * tiles_n), in_band = id - band * (GM * tiles_n);
-    const int first_m = band * GM, rows = min(tiles_m - first_m, GM);
-    tn = in_band / rows;
-    const int tm = first_m + (in_band - tn * rows);
+    const int id = xcd * map.xcd_base + min(xcd, map.xcd_rem) + j;
+    // bands of 8 tile rows, column by column inside a band: the workgroups an XCD runs at the same
+    // time then cover a compact 8 x (slots / 8) rectangle and share A and W tiles in its L2
+    int in_band = 0, tr = 0;
+    const int band = div_by(id, map.band_tiles, map.band_inv, in_band);
+    tn = div_by(in_band, map.last_rows, map.last_inv, tr);
+    const bool full = band < map.full_bands;
+    tn = full ? in_band >> 3 : tn;
+    const int tm = band * 8 + (full ? in_band & 7 : tr);
     m0 = m_base + tm * BM;                                 // this launch covers rows [m_base, M)
     n0 = tn * BN;
+    if constexpr (PP) {
+      pp_a = const_cast<bf16_t*>(A + (int64_t)m0 * K);
+      pp_w = const_cast<bf16_t*>(W + (int64_t)n0 * K);
+#pragma unroll
+      for (int i = 0; i < LA; ++i) {
+        const int r = (i * NW + wave) * RPI + lr;
+        const int c = (swz(r, lp) - r * ROW_BYTES);
+        oa[i] = (uint32_t)min(r, M - 1 - m0) * (uint32_t)(2 * K) + c;
+        ob[i] = (uint32_t)min(r, Nout - 1 - n0) * (uint32_t)(2 * K) + c;
+      }
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
       const int r = (i * NW + wave) * RPI + lr;
-      const int c = (swz<BK>(r, lp) - r * ROW_BYTES) >> 4;   // chunk of the row that lands in slot lp
+      const int c = (swz(r, lp) - r * ROW_BYTES) >> 4;   // chunk of the row that lands in slot lp
       ga[i] = A + (int64_t)min(m0 + r, M - 1) * K + c * 8;   // rows past the edge re-read the last row
     }
 #pragma unroll
     for (int i = 0; i < LB; ++i) {
       const int r = (i * NW + wave) * RPI + lr;
-      const int c = (swz<BK>(r, lp) - r * ROW_BYTES) >> 4;
+      const int c = (swz(r, lp) - r * ROW_BYTES) >> 4;
       gb[i] = W + (int64_t)min(n0 + r, Nout - 1) * K + c * 8;
     }
   };
@@ -144,31 +181,98 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
 
   f32x16 acc[TM][TN];
 
-  const int KT = K / BK / kslices;                         // K steps of this workgroup's slice
+  const int KT = map.KT;                                   // K steps of this workgroup's slice
   const int k_begin = kslice * KT * BK;
   // With few rows every tile column is streamed by one workgroup (or a few that share it), and all
   // of them would walk K in step: the same 128-byte slice of every weight row at the same time,
   // rows a power-of-two stride apart, i.e. a handful of memory channels.  Each tile column
   // therefore starts its (cyclic) walk over K at its own offset.
-  const int kt_first = STAGGER ? (int)(((int64_t)tn * KT) / tiles_n) : 0;
+  const int kt_first = STAGGER ? (int)(((int64_t)tn * KT) / map.tiles_n) : 0;
   auto k_of = [&](int t) { const int q = t + kt_first; return k_begin + (q >= KT ? q - KT : q) * BK; };
-  // prologue: NST-1 K stages in flight
-  auto prologue = [&]() {
+  // PP: half h of the tile's rows (part h) or columns (part 2 + h) at K step t into LDS buffer buf
+  auto pp_fill = [&](int part, int buf, int t) {
 #pragma unroll
-    for (int t = 0; t < NST - 1; ++t)
-      if (t < KT) issue(t, k_of(t), 0, LPW);
+    for (int i = 0; i < 2; ++i) {
+      const int j = (part & 1) * 2 + i;
+      char* d = lds + (part >> 1) * 65536 + buf * 32768 + (j * NW + wave) * RPI * ROW_BYTES;
+      fill_lds(part >> 1 ? pp_w : pp_a, (lptr_t)d, part >> 1 ? ob[j] : oa[j], (k_begin + t * BK) * 2);
+    }
   };
-  prologue();
+  // prologue: NST-1 K stages in flight (PP: one and three quarters)
+  auto prologue_first = [&]() {
+    if constexpr (PP) {
+      pp_fill(0, 0, 0); pp_fill(2, 0, 0); pp_fill(3, 0, 0); pp_fill(1, 0, 0);
+    } else {
+      issue(0, k_of(0), 0, LPW);
+    }
+  };
+  auto prologue_rest = [&]() {
+    if constexpr (PP) {
+      if (KT > 1) { pp_fill(0, 1, 1); pp_fill(2, 1, 1); pp_fill(3, 1, 1); }
+    } else {
+#pragma unroll
+      for (int t = 1; t < NST - 1; ++t)
+        if (t < KT) issue(t, k_of(t), 0, LPW);
+    }
+  };
 
+  // ---- what the accumulators start from: bias and residual row.  Requested ahead of the tile's second K stage, so
+  // that what waits for them does not wait for more than the first stage.
   const int half = lane >> 5, r32 = lane & 31;
-  const int arow0 = wm * (BM / WM) + r32;   // tile row of this lane's A operand in MFMA tile 0
-  const int brow0 = wn * (BN / WN) + r32;
+  constexpr bool HAS_RES = MODE == EPI_ATTN_OUT || MODE == EPI_RESIDUAL;
+  constexpr bool HAS_BIAS = MODE != EPI_PARTIAL && MODE != EPI_ENTROPY;
+  bf16x4 bvec[HAS_BIAS ? TN : 1][4];         // this lane's bias entries, packed
+  auto load_bias = [&]() {
+    if constexpr (HAS_BIAS) {
+#pragma unroll
+      for (int jn = 0; jn < TN; ++jn)
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4) bvec[jn][g4] = bf16x4{(bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f};
+      if (ep.bias) {
+#pragma unroll
+        for (int jn = 0; jn < TN; ++jn) {
+          // 32 columns are all inside or all outside (Nout is a multiple of 64): outside, some that are inside stand in
+          const bf16_t* bp = ep.bias + min(n0 + col_of(jn), Nout - 32) + 4 * half;
+#pragma unroll
+          for (int g4 = 0; g4 < 4; ++g4) bvec[jn][g4] = *reinterpret_cast<const bf16x4*>(bp + 8 * g4);
+        }
+      }
+    }
+  };
+  // residual row of this lane in MFMA tile row i (rows past the edge: the last one)
+  auto res_row = [&](int i) -> const bf16_t* {
+    const int row = min(m0 + row_of(i) + r32, M - 1);
+    int64_t roff = (int64_t)row * ep.ldo;
+    if (MODE == EPI_ATTN_OUT)
+      roff = ((int64_t)ep.image(row) * ep.Ntok + min(max(ep.idx[row], 0), ep.Ntok - 1)) * ep.C;
+    return ep.res + roff + n0 + 8 * half;
+  };
+  auto load_res = [&](u32x4* dst) {          // eight features of this lane's row: 16 gp + 8 half .. of a 32-column block
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const bf16_t* rp = res_row(i);
+#pragma unroll
+      for (int jn = 0; jn < TN; ++jn) {
+        const int c = n0 + col_of(jn) < Nout ? col_of(jn) : 0;        // columns past the edge: not used
+#pragma unroll
+        for (int gp = 0; gp < 2; ++gp) dst[(i * TN + jn) * 2 + gp] = *reinterpret_cast<const u32x4*>(rp + c + 16 * gp);
+      }
+    }
+  };
+  u32x4 rs[HAS_RES ? TM * TN * 2 : 1];
+  load_bias();
+  prologue_first();
+  if constexpr (HAS_RES) load_res(rs);
+  prologue_rest();
+
+  const int arow0 = row_of(0) + r32;   // tile row of this lane's A operand in MFMA tile 0
+  const int brow0 = col_of(0) + r32;
   // swizzled byte offsets of this lane's operand chunk for the 16-wide K steps of a stage
   int aoff[KS], boff[KS];
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
-    aoff[ks] = swz<BK>(arow0, ks * 2 + half);
-    boff[ks] = swz<BK>(brow0, ks * 2 + half);
+    aoff[ks] = swz(arow0, ks * 2 + half);
+    boff[ks] = swz(brow0, ks * 2 + half) + (PP ? 65536 : 0);
   }
   // Operand fragments are double buffered in registers and the schedule is pinned with
   // sched_barrier: the LDS reads of K step ks+1 are issued right after the first MFMA of K step
@@ -194,17 +298,122 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
 
   bool first_tile = true;
   for (;;) {   // tiles of this workgroup (one, unless PERSIST)
+  auto bias_of = [&](int jn, int r) {
+    if constexpr (MODE == EPI_ENTROPY) {
+      const int col = n0 + col_of(jn) + 8 * (r >> 2) + 4 * half + (r & 3);
+      return col >= Nout ? -INFINITY : (ep.bias ? (float)ep.bias[col] : 0.0f);   // -inf masks the edge
+    } else if constexpr (HAS_BIAS) {
+      return (float)bvec[jn][r >> 2][r & 3];
+    } else {
+      return 0.0f;
+    }
+  };
+  if constexpr (HAS_RES) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int jn = 0; jn < TN; ++jn)
+#pragma unroll
+        for (int gp = 0; gp < 2; ++gp) {
+          const u32x4 v = rs[(i * TN + jn) * 2 + gp];
+#pragma unroll
+          for (int w2 = 0; w2 < 2; ++w2) {   // eight consecutive features -> the lane's groups 2 gp and 2 gp + 1
+            const auto sw = __builtin_amdgcn_permlane32_swap(v[w2], v[2 + w2], false, false);
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+              const int r = (2 * gp + g) * 4 + 2 * w2;
+              acc[i][jn][r] = __uint_as_float(sw[g] << 16) + bias_of(jn, r);
+              acc[i][jn][r + 1] = __uint_as_float(sw[g] & 0xFFFF0000u) + bias_of(jn, r + 1);
+            }
+          }
+        }
+  } else {
+#pragma unroll
+    for (int jn = 0; jn < TN; ++jn)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float b = bias_of(jn, r);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) acc[i][jn][r] = b;
+      }
+  }
+  if constexpr (PP) {
+    // ---- 256 x 256 tile, K steps of 64, two LDS buffers, each filled and freed in halves of its rows and columns.
+    // A wave computes a 64 x 32 quadrant per phase (rows half x columns half), four phases per K step:
+    //   phase 1: read rows half 0, columns half 0 | quadrant 00     fill rows half 1 of step t + 1
+    //   phase 2: read columns half 1              | quadrant 01     fill rows half 0 of step t + 2
+    //   phase 3: read rows half 1                 | quadrant 11     fill columns half 0 of step t + 2
+    //   phase 4: nothing to read                  | quadrant 10     fill columns half 1 of step t + 2
+    // The waves of the upper row group run one barrier behind those of the lower one, so that of the two waves of a
+    // SIMD one issues its MFMAs while the other reads its next fragments.  A part is refilled a phase or more after
+    // the last reads of it were waited for in front of a barrier; it is read five phases later at the earliest,
+    // with five parts (80 KB of the CU's) still in flight.
+    bf16x8 fa[2][4], fb[2][4];
+    auto rd_a = [&](int h) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks)
+          fa[i][ks] = *reinterpret_cast<const bf16x8*>(lds + aoff[ks] + h * 16384 + i * 4096);
+    };
+    auto rd_b = [&](int h) {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+        fb[h][ks] = *reinterpret_cast<const bf16x8*>(lds + boff[ks] + h * 16384);
+    };
+    auto bar = [&]() {
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto quad = [&](int h, int jn) {
+      __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): the fragments are here, their LDS may be refilled
+      bar();
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) acc[2 * h + i][jn] = mfma32(fb[jn][ks], fa[i][ks], acc[2 * h + i][jn]);
+      __builtin_amdgcn_s_setprio(0);
+      bar();
+    };
+    if (!first_tile) { WAIT_VMCNT(0); } else if (KT > 1) { WAIT_VMCNT(10); } else { WAIT_VMCNT(4); }
+    first_tile = false;
+    bar();
+    if (wm == 1) bar();
+    for (int t = 0; t < KT; ++t) {
+      const int left = KT - 1 - t, buf = t & 1;   // K steps after this one
+      rd_a(0);
+      rd_b(0);
+      if (left >= 1) { pp_fill(1, buf ^ 1, t + 1); WAIT_VMCNT(10); } else { WAIT_VMCNT(2); }
+      quad(0, 0);
+      rd_b(1);
+      if (left >= 2) { pp_fill(0, buf, t + 2); WAIT_VMCNT(10); }
+      else if (left == 1) { WAIT_VMCNT(8); }
+      else { WAIT_VMCNT(0); }
+      quad(0, 1);
+      rd_a(1);
+      if (left >= 2) pp_fill(2, buf, t + 2);
+      quad(1, 1);
+      if (left >= 2) { pp_fill(3, buf, t + 2); WAIT_VMCNT(10); }
+      else if (left == 1) { WAIT_VMCNT(4); }
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) { aoff[ks] ^= 32768; boff[ks] ^= 32768; }
+      quad(1, 0);
+    }
+    if (wm == 0) bar();
+    if (PERSIST && (KT & 1)) {              // the next tile starts in buffer 0 again
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) { aoff[ks] ^= 32768; boff[ks] ^= 32768; }
+    }
+  } else {
   // wait for the first K stage.  After a prefetch the epilogue's own loads and stores are in flight as well and
   // the counter does not tell them apart: wait for everything.
   if (first_tile && KT >= NST - 1) { WAIT_VMCNT((NST - 2) * LPW); } else { WAIT_VMCNT(0); }
   first_tile = false;
   __syncthreads();
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int jn = 0; jn < TN; ++jn)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][jn][r] = 0.f;
   int stage = 0, fill = NST - 1;            // stage being computed / stage being refilled
   read_frags(0, 0, 0);
   for (int kt = 0; kt < KT; ++kt) {
@@ -242,30 +451,20 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
     stage = next;
     fill = fill + 1 == NST ? 0 : fill + 1;
   }
+  }
   if constexpr (MODE == EPI_ENTROPY) {
     // The accumulators (+ bias) are logits that never leave the chip: each lane reduces the columns
     // it holds of a token row to (max, S, T), the two half-waves and then the waves that share the
     // row merge their partials, and one (m, S, T) per row and column tile goes to memory.
     constexpr float kLog2e = 1.4426950408889634f;
     f32x4* lp = reinterpret_cast<f32x4*>(lds);           // [WN][BM]; the stage ring is free after the last barrier
-    float bias[TN][16];
-#pragma unroll
-    for (int jn = 0; jn < TN; ++jn)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int col = n0 + wn * (BN / WN) + jn * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-        bias[jn][r] = col >= Nout ? -INFINITY : (ep.bias ? (float)ep.bias[col] : 0.0f);   // -inf masks the edge
-      }
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       float m = -INFINITY;
 #pragma unroll
       for (int jn = 0; jn < TN; ++jn)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          acc[i][jn][r] += bias[jn][r];
-          m = fmaxf(m, acc[i][jn][r]);
-        }
+        for (int r = 0; r < 16; ++r) m = fmaxf(m, acc[i][jn][r]);
       float S = 0.0f, T = 0.0f;
       if (m != -INFINITY) {
 #pragma unroll
@@ -279,7 +478,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
           }
       }
       entropy_merge(m, S, T, __shfl_xor(m, 32, 64), __shfl_xor(S, 32, 64), __shfl_xor(T, 32, 64));
-      if (half == 0) lp[wn * BM + wm * (BM / WM) + i * 32 + r32] = f32x4{m, S, T, 0.0f};
+      if (half == 0) lp[wn * BM + row_of(i) + r32] = f32x4{m, S, T, 0.0f};
     }
     __syncthreads();
     for (int row = tid; row < BM; row += NW * 64) {
@@ -300,12 +499,12 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
     float* pp = ep.part + ((int64_t)kslice * (M - m_base) - m_base) * Nout;     // [slice][row - m_base][Nout]
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      const int row = m0 + wm * (BM / WM) + i * 32 + r32;
+      const int row = m0 + row_of(i) + r32;
 #pragma unroll
       for (int jn = 0; jn < TN; ++jn)
 #pragma unroll
         for (int g4 = 0; g4 < 4; ++g4) {
-          const int col = n0 + wn * (BN / WN) + jn * 32 + 8 * g4 + 4 * half;
+          const int col = n0 + col_of(jn) + 8 * g4 + 4 * half;
           if (row < M && col < Nout) {
             f32x4 v;
 #pragma unroll
@@ -315,108 +514,111 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
         }
     }
     return;
-  } else if constexpr (MODE != EPI_QKV) {
+  }
+  {
     const int em0 = m0, en0 = n0;            // origin of the tile whose accumulators are written out below
-    // ---- direct epilogue (everything but the QKV projection): no LDS staging.  A lane owns token l % 32
+    // ---- epilogue, without LDS staging.  A lane owns token l % 32
     // and, per register group g4, four consecutive features (8 g4 + 4 half ..); swapping the upper lanes'
     // group g4 with the lower lanes' group g4 + 1 (v_permlane32_swap) leaves every lane with eight
-    // consecutive features of its token: 16-byte residual / gate loads and one 16-byte store, and the two
-    // halves of the wave cover 32 contiguous bytes of each row.
-    constexpr bool HAS_RES = MODE == EPI_ATTN_OUT || MODE == EPI_RESIDUAL;
-    // The residual chunks are requested first, so that their latency (two dependent loads for the
-    // gathered residual) passes behind the conversion work.
-    bf16x8 rs[HAS_RES ? TM * TN * 2 : 1];
-    if constexpr (HAS_RES) {
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int row = em0 + wm * (BM / WM) + i * 32 + r32;
-        int64_t roff = (int64_t)row * ep.ldo;
-        if (MODE == EPI_ATTN_OUT && row < M)
-          roff = ((int64_t)(row / ep.k) * ep.Ntok + min(max(ep.idx[row], 0), ep.Ntok - 1)) * ep.C;
-#pragma unroll
-        for (int jn = 0; jn < TN; ++jn)
-#pragma unroll
-          for (int gp = 0; gp < 2; ++gp) {
-            const int col = en0 + wn * (BN / WN) + jn * 32 + 8 * (2 * gp + half);
-            if (row < M && col < Nout) rs[(i * TN + jn) * 2 + gp] = *reinterpret_cast<const bf16x8*>(ep.res + roff + col);
-          }
-      }
-    }
-    bf16x4 bvec[TN][4];                       // this lane's bias entries, packed
-#pragma unroll
-    for (int jn = 0; jn < TN; ++jn)
-#pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4) {
-        const int col = en0 + wn * (BN / WN) + jn * 32 + 8 * g4 + 4 * half;
-        bf16x4 bv = {(bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f};
-        if (ep.bias && col < Nout) bv = *reinterpret_cast<const bf16x4*>(ep.bias + col);
-        bvec[jn][g4] = bv;
-      }
+    // consecutive features of its token: one 16-byte store, and the two halves of the wave cover 32
+    // contiguous bytes of each row.  Bias and residual are in the accumulators already.  The value columns of the
+    // QKV projection (key index minor) need no swap: the lanes of a half wave hold consecutive tokens.
     bool more_tiles = false;
     if constexpr (PERSIST) {
       // Every wave has passed the last barrier of the K loop, nobody reads the ring any more: request the
-      // first stages of this workgroup's next tile now.  They are requested after the epilogue's own loads
-      // (loads complete in order, so those do not wait for the tile data) and land behind the conversion work.
-      if (L + (int)gridDim.x < nblk) {
+      // bias and the first stages of this workgroup's next tile now; they land behind the conversion work.
+      if (L + (int)gridDim.x < map.nblk) {
         more_tiles = true;
         L += gridDim.x;
         set_tile(L);
-        prologue();
+        load_bias();
+        prologue_first();
+        prologue_rest();
+      }
+    }
+    if constexpr (HAS_RES) {
+      if constexpr (GATED) {
+        // gated: r + g p as v + (g - 1)(v - r) with v = r + p, which is the ungated result where the gate is one
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          const bf16_t* rp = res_row(i) - 4 * half;
+          const bf16_t* gr = ep.gate + (int64_t)ep.image(min(em0 + row_of(i) + r32, M - 1)) * ep.gate_pitch + en0 + 4 * half;
+#pragma unroll
+          for (int jn = 0; jn < TN; ++jn) {
+            if (en0 + col_of(jn) >= Nout) continue;
+#pragma unroll
+            for (int g4 = 0; g4 < 4; ++g4) {
+              const bf16x4 r = *reinterpret_cast<const bf16x4*>(rp + col_of(jn) + 8 * g4);
+              const bf16x4 g = *reinterpret_cast<const bf16x4*>(gr + col_of(jn) + 8 * g4);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const float v = acc[i][jn][g4 * 4 + e];
+                acc[i][jn][g4 * 4 + e] = fmaf((float)g[e] - 1.0f, v - (float)r[e], v);
+              }
+            }
+          }
+        }
       }
     }
 #pragma unroll
-    for (int jn = 0; jn < TN; ++jn) {
-      const int cb = en0 + wn * (BN / WN) + jn * 32;                   // first feature of this 32-column block
-      float bias[16];
+    for (int i = 0; i < TM; ++i) {
+      const int row = em0 + row_of(i) + r32;
+      if (row < M) {
+        bf16_t* op = ep.out + (int64_t)row * ep.ldo + (MODE == EPI_QKV ? 0 : en0) + 8 * half;
+        int image = 0, pos = 0;
+        bool live = true;
+        if constexpr (MODE == EPI_QKV) {
+          int slot;
+          image = ep.image(row, slot);
+          live = slot < image_count(ep.k_rows, image, ep.k);         // slots past an image's keep count append nothing
+          pos = image_prior(ep.kv_rows, image, ep.P) + slot;
+        }
 #pragma unroll
-      for (int g4 = 0; g4 < 4; ++g4)
+        for (int jn = 0; jn < TN; ++jn) {
+          if (en0 + col_of(jn) >= Nout) continue;                     // wave-uniform
+          bf16_t* dst = op + col_of(jn);
+          float qs = MODE == EPI_PLAIN ? ep.q_scale : 1.0f;
+          if constexpr (MODE == EPI_QKV) {
+            // C and dh are multiples of 64: 32 columns lie in one part and one head
+            const int cb = en0 + col_of(jn), part = (cb >= ep.C) + (cb >= 2 * ep.C), cf = cb - part * ep.C;
+            const int head = cf >> ep.dh_log2, d = cf & (ep.dh - 1);
+            const int64_t bh = (int64_t)image * ep.heads + head;
+            if (part == 2) {
+              if (live) {
+                bf16_t* vp = ep.vc + (bh * ep.dh + d + 4 * half) * ep.cap + pos;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) bias[g4 * 4 + e] = (float)bvec[jn][g4][e];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int row = em0 + wm * (BM / WM) + i * 32 + r32;
-#pragma unroll
-        for (int gp = 0; gp < 2; ++gp) {                              // register groups (2 gp, 2 gp + 1)
-          u32x2 lo, hi;                                               // packed bf16 pairs of the two groups
-#pragma unroll
-          for (int g = 0; g < 2; ++g) {
-            bf16x4 o;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              float v = acc[i][jn][(2 * gp + g) * 4 + e] + bias[(2 * gp + g) * 4 + e];
-              if (MODE == EPI_GELU) v = gelu_erf(v);
-              if (MODE == EPI_GELU_TANH) v = gelu_tanh(v);
-              if (MODE == EPI_PLAIN) v *= ep.q_scale;
-              o[e] = (bf16_t)v;
-            }
-            (g == 0 ? lo : hi) = __builtin_bit_cast(u32x2, o);
-          }
-          u32x4 out16;
-#pragma unroll
-          for (int w2 = 0; w2 < 2; ++w2) {
-            const auto sw = __builtin_amdgcn_permlane32_swap(lo[w2], hi[w2], false, false);
-            out16[w2] = sw[0];          // lower lanes: own group 2 gp;       upper lanes: lower partner's group 2 gp + 1
-            out16[2 + w2] = sw[1];      // lower lanes: upper partner's 2 gp; upper lanes: own group 2 gp + 1
-          }
-          const int col = cb + 8 * (2 * gp + half);                   // eight consecutive features from here
-          if (row < M && col < Nout) {
-            if constexpr (HAS_RES) {
-              // the projection (+ bias) is rounded to bf16 before the gate and the residual are applied
-              const bf16x8 v = __builtin_bit_cast(bf16x8, out16);
-              const bf16x8 r = rs[(i * TN + jn) * 2 + gp];
-              bf16x8 o;
-              if (ep.gate) {
-                const bf16x8 gt = *reinterpret_cast<const bf16x8*>(ep.gate + (int64_t)(row / ep.k) * ep.gate_pitch + col);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o[e] = (bf16_t)fmaf((float)gt[e], (float)v[e], (float)r[e]);
-              } else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o[e] = (bf16_t)((float)v[e] + (float)r[e]);
+                for (int r = 0; r < 16; ++r) vp[(int64_t)(8 * (r >> 2) + (r & 3)) * ep.cap] = (bf16_t)acc[i][jn][r];
               }
-              *reinterpret_cast<bf16x8*>(ep.out + (int64_t)row * ep.ldo + col) = o;
-            } else {
-              *reinterpret_cast<u32x4*>(ep.out + (int64_t)row * ep.ldo + col) = out16;
+              continue;
             }
+            if (part == 0) qs = ep.q_scale;
+            dst = part == 0 ? op + cf : ep.kc + (bh * ep.cap + pos) * ep.dh + d + 8 * half;
+            if (part == 1 && !live) continue;
+          }
+#pragma unroll
+          for (int gp = 0; gp < 2; ++gp) {                            // register groups (2 gp, 2 gp + 1)
+            u32x2 lo, hi;                                             // packed bf16 pairs of the two groups
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+              bf16x4 o;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                float v = acc[i][jn][(2 * gp + g) * 4 + e];
+                if (MODE == EPI_GELU) v = gelu_erf(v);
+                if (MODE == EPI_GELU_TANH) v = gelu_tanh(v);
+                if (MODE == EPI_PLAIN || MODE == EPI_QKV) v *= qs;
+                o[e] = (bf16_t)v;
+              }
+              (g == 0 ? lo : hi) = __builtin_bit_cast(u32x2, o);
+            }
+            u32x4 out16;
+#pragma unroll
+            for (int w2 = 0; w2 < 2; ++w2) {
+              const auto sw = __builtin_amdgcn_permlane32_swap(lo[w2], hi[w2], false, false);
+              out16[w2] = sw[0];        // lower lanes: own group 2 gp;       upper lanes: lower partner's group 2 gp + 1
+              out16[2 + w2] = sw[1];    // lower lanes: upper partner's 2 gp; upper lanes: own group 2 gp + 1
+            }
+            *reinterpret_cast<u32x4*>(dst + 16 * gp) = out16;
           }
         }
       }
@@ -424,84 +626,6 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
     if (more_tiles) continue;
     return;
   }
-  break;   // the QKV projection: staged epilogue below
-  }
-  // ---- QKV epilogue, stage 1: accumulators (+ bias) -> bf16 tile in LDS, row-major (the value columns are
-  // written transposed, which needs the whole tile at hand) ---------------------------------------------
-  constexpr int NT = NW * 64;
-  constexpr int CPR = BN / 8;                       // chunks per tile row
-  constexpr int RPP = NT / CPR;                     // tile rows covered per pass
-  constexpr int NI = BM / RPP;                      // tile rows per thread
-  static_assert(NT % CPR == 0 && BM % RPP == 0, "chunk walk tiles the output tile");
-  bf16_t* ct = reinterpret_cast<bf16_t*>(lds);
-#pragma unroll
-  for (int jn = 0; jn < TN; ++jn)
-#pragma unroll
-    for (int g4 = 0; g4 < 4; ++g4) {
-      const int lc = wn * (BN / WN) + jn * 32 + 8 * g4 + 4 * half;   // first of 4 consecutive features
-      const int col = n0 + lc;
-      const float qs = col < ep.C ? ep.q_scale : 1.0f;   // query features (C is a multiple of 8: all four or none)
-      float bias[4] = {0.f, 0.f, 0.f, 0.f};
-      if (ep.bias && col < Nout) {
-        const bf16x4 bv = *reinterpret_cast<const bf16x4*>(ep.bias + col);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) bias[e] = (float)bv[e];
-      }
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int lrw = wm * (BM / WM) + i * 32 + r32;
-        bf16x4 o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = (bf16_t)((acc[i][jn][g4 * 4 + e] + bias[e]) * qs);
-        *reinterpret_cast<bf16x4*>(ct + lrw * CT_PITCH + lc) = o;
-      }
-    }
-  __syncthreads();
-
-  // ---- stage 2: 16-byte row chunks out of LDS, coalesced global stores ----------------------
-  // A thread keeps one column chunk and walks down the tile rows, so everything that depends on
-  // the column (q / key / value split, head, channel) is computed once.
-  {
-    const int cc = tid % CPR, r_first = tid / CPR;
-    const int col = n0 + cc * 8;
-    const int sel = col / ep.C, cf = col - sel * ep.C;
-    const int head = cf / ep.dh, d = cf - head * ep.dh;
-    if (col < Nout && sel != 2) {
-#pragma unroll
-      for (int it = 0; it < NI; ++it) {
-        const int lrw = r_first + it * RPP;
-        const int row = m0 + lrw;
-        if (row >= M) break;
-        const bf16x8 v = *reinterpret_cast<const bf16x8*>(ct + lrw * CT_PITCH + cc * 8);
-        if (sel == 0) {
-          *reinterpret_cast<bf16x8*>(ep.out + (int64_t)row * ep.ldo + cf) = v;
-        } else {
-          const int bb = row / ep.k, s = row - bb * ep.k;
-          if (s < image_count(ep.k_rows, bb, ep.k))      // slots past an image's keep count append nothing
-            *reinterpret_cast<bf16x8*>(ep.kc + (((int64_t)bb * ep.heads + head) * ep.cap +
-                                                image_prior(ep.kv_rows, bb, ep.P) + s) * ep.dh + d) = v;
-        }
-      }
-    }
-  }
-  if (MODE == EPI_QKV) {
-    // value columns: the cache is key-minor, so a thread keeps one tile row (token) and walks
-    // the value columns; consecutive lanes hold consecutive tokens -> consecutive addresses
-    const int v_lo = max(2 * ep.C - n0, 0);          // first tile column that is a value feature
-    const int v_hi = min(BN, Nout - n0);
-    if (v_hi > v_lo) {
-      constexpr int CG = NT / BM;                    // column groups walked in parallel
-      static_assert(NT % BM == 0, "one thread per tile row and column group");
-      const int lrw = tid % BM, cg = tid / BM;
-      const int row = m0 + lrw;
-      const int bb = row < M ? row / ep.k : 0, s = row - bb * ep.k;
-      if (row < M && s < image_count(ep.k_rows, bb, ep.k)) {
-        bf16_t* vrow = ep.vc + (int64_t)bb * ep.heads * ep.dh * ep.cap + image_prior(ep.kv_rows, bb, ep.P) + s;
-        const int cf0 = n0 - 2 * ep.C;               // value feature of tile column 0
-        for (int lc = v_lo + cg; lc < v_hi; lc += CG)
-          vrow[(int64_t)(cf0 + lc) * ep.cap] = ct[lrw * CT_PITCH + lc];   // (head * dh + d) * cap
-      }
-    }
   }
 }
 
@@ -509,14 +633,26 @@ template <int BM, int BN, int WM, int WN, int BK, int NST, bool STAGGER, int MOD
 hipError_t launch_cfg(hipStream_t st, const bf16_t* A, const bf16_t* W, int m_base, int M, int Nout, int K,
                       const EpiParams<bf16_t>& ep, int slots, int kslices = 1) {
   const int tiles_m = (M - m_base + BM - 1) / BM, tiles_n = (Nout + BN - 1) / BN;   // rows [m_base, M)
+  TileMap map;
+  map.nblk = tiles_m * tiles_n;
+  map.xcd_base = map.nblk / 8; map.xcd_rem = map.nblk % 8;
+  map.band_tiles = 8 * tiles_n; map.band_inv = div_inv(map.band_tiles);
+  map.full_bands = tiles_m / 8; map.last_rows = std::max(tiles_m % 8, 1); map.last_inv = div_inv(map.last_rows);
+  map.tiles_n = tiles_n; map.KT = K / BK / kslices;
   // the kernel's PERSIST modes walk several tiles per workgroup: one workgroup per CU then (a multiple of 8, so
   // that a workgroup's tiles share its XCD)
-  constexpr bool PERSIST = persistent_tiles(BM / WM / 32 * (BN / WN / 32), STAGGER, MODE);
-  int grid = tiles_m * tiles_n * kslices;
+  constexpr bool PERSIST = persistent_tiles(STAGGER, MODE);
+  int grid = map.nblk;
   // (not with per-image keep counts: a workgroup that finds its tile without a live row leaves at once)
   if (PERSIST && slots > 0 && slots % 8 == 0 && grid > slots && !ep.k_rows) grid = slots;
-  gemm_bf16_kernel<BM, BN, WM, WN, BK, NST, STAGGER, MODE><<<grid, WM * WN * 64, 0, st>>>(
-      A, W, M, Nout, K, m_base, tiles_m, tiles_n, kslices, ep);
+  if constexpr (MODE == EPI_ATTN_OUT || MODE == EPI_RESIDUAL) {
+    if (ep.gate) {
+      gemm_bf16_kernel<BM, BN, WM, WN, BK, NST, STAGGER, MODE, true><<<grid, WM * WN * 64, 0, st>>>(A, W, M, Nout, K, m_base, map, ep);
+      return hipGetLastError();
+    }
+  }
+  gemm_bf16_kernel<BM, BN, WM, WN, BK, NST, STAGGER, MODE, false><<<dim3(grid, kslices), WM * WN * 64, 0, st>>>(
+      A, W, M, Nout, K, m_base, map, ep);
   return hipGetLastError();
 }
 
@@ -542,63 +678,67 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restric
   for (int e = 0; e < 8; ++e) bias[e] = (bf16_t)0.f;
   if (ep.bias) bias = *reinterpret_cast<const bf16x8*>(ep.bias + col);
   int64_t roff = (int64_t)row * ep.ldo;
-  if (MODE == EPI_ATTN_OUT) roff = ((int64_t)(row / ep.k) * ep.Ntok + min(max(ep.idx[row], 0), ep.Ntok - 1)) * ep.C;
+  if (MODE == EPI_ATTN_OUT) roff = ((int64_t)ep.image(row) * ep.Ntok + min(max(ep.idx[row], 0), ep.Ntok - 1)) * ep.C;
   const bf16x8 r = *reinterpret_cast<const bf16x8*>(ep.res + roff + col);
   bf16x8 o;
   if (ep.gate) {
-    const bf16x8 gt = *reinterpret_cast<const bf16x8*>(ep.gate + (int64_t)(row / ep.k) * ep.gate_pitch + col);
+    const bf16x8 gt = *reinterpret_cast<const bf16x8*>(ep.gate + (int64_t)ep.image(row) * ep.gate_pitch + col);
 #pragma unroll
-    for (int e = 0; e < 8; ++e)      // the projection (+ bias) is rounded to bf16 first, as in the fused epilogue
-      o[e] = (bf16_t)fmaf((float)gt[e], (float)(bf16_t)(acc[e] + (float)bias[e]), (float)r[e]);
+    for (int e = 0; e < 8; ++e) o[e] = (bf16_t)fmaf((float)gt[e], acc[e] + (float)bias[e], (float)r[e]);
   } else {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = (bf16_t)((float)(bf16_t)(acc[e] + (float)bias[e]) + (float)r[e]);
+    for (int e = 0; e < 8; ++e) o[e] = (bf16_t)(acc[e] + (float)bias[e] + (float)r[e]);
   }
   *reinterpret_cast<bf16x8*>(ep.out + (int64_t)row * ep.ldo + col) = o;
 }
 
-// Tile configurations (NOVA_GEMM_CFG forces one, for tuning):
-//   0: 128x128x64, 4 waves of 64x64, 2 LDS stages, two workgroups per CU
-//   1: 256x256x64, 8 waves of 128x64, 2 stages
+// Tile configurations (NOVA_GEMM_CFG forces one, for tuning; numbers without a kernel mean 2):
+//   1: 256x256x64, 8 waves of 128x64 that alternate between the matrix cores and LDS
 //   2: 256x128x64, 8 waves of 64x64, 3 stages
 //   3: 64x32x64, 2 waves of 32x32, 6 stages, staggered K walk          (head entropy only, M <= 64)
 //   4: 128x32x64, 4 waves of 32x32, 4 stages, staggered K walk         (head entropy only, M <= 256 or 512)
 //   5: 128x128x64, 8 waves of 64x32, 3 stages, one workgroup per CU (two waves per SIMD hide the LDS waits that
 //      four waves of 64x64 expose: 3-10 % faster at every shape measured)
-//   6: 256x256x32, 8 waves of 128x64, 3 stages
-// Without a forced choice the launcher prices the candidates 2, 5 and 6 with a small model fitted
-// to measurements on MI355X (M = 1.6k..4.9k, N and K = 2k..8k): a launch takes
-// ceil(tiles / CUs) rounds, a round costs the tile's flops at the rate one workgroup sustains when
-// every CU holds one, plus a fixed prologue/epilogue time.  Large tiles win when their tile count
-// fills whole rounds; the one-workgroup 128x128 kernel wins when there are few tiles (narrow
-// outputs, late blocks with few kept tokens).
 //   7: the few-rows kernels of gemm_rows_bf16.hip (chosen by their own plan, not by force)
+// Without a forced choice the launcher prices 1, 2 and 5 with a model fitted to measurements on MI355X (300 ... 8192
+// rows, widths C of 1024 ... 2304, outputs of C, 3C and 4C features, K = C and 4C): a launch takes rounds of one tile
+// per CU; a round costs a fixed time (first loads, epilogue) and a time per element of K that grows with the share of
+// the CUs that are busy (they share L2, memory and power).  The fit is within 6 % (rms) of the measurements, and what
+// it chooses takes 0.1 % longer than the best of the three on average, 7 % at worst.
 constexpr int kNumCfgs = 7;
 constexpr int kRowsCfg = 7;
 
 struct Candidate {
   int cfg, bm, bn;
-  double rate;   // flop/s of one resident workgroup with all CUs busy
+  double launch, round, gelu;   // us per launch, per round, per round with a GELU
+  double k0, k1, k3;            // us per element of K in a round that fills a share f of the CUs: k0 + k1 f + k3 f^3
 };
 
-static const Candidate kCands[] = {{2, 256, 128, 3.3e12}, {5, 128, 128, 3.2e12}, {6, 256, 256, 3.6e12}};
-constexpr double kFixed = 8e-6;          // per round of workgroups: launch ramp, prologue, epilogue
+static const Candidate kCands[] = {{1, 256, 256, 5.1, 4.0, 2.1, 0.01621, -0.00149, 0.00964},
+                                   {2, 256, 128, 3.7, 2.7, 0.5, 0.01048, 0.00108, 0.00301},
+                                   {5, 128, 128, 3.1, 1.6, 0.0, 0.00591, 0.00119, 0.00168}};
 
-// Modelled time of one launch over M rows with candidate c: whole rounds over the CUs, each a tile's flops at the
-// candidate's sustained rate plus the fixed time.  A projection done by one launch of a single round that fills
-// only a fraction f of the CUs is shorter (the busy CUs share L2 and memory with fewer others): taken as
-// max(0.85, 1.1 f) of a whole round (`alone`).  Measured over the 32 blocks of the largest workload this helps the
-// K = 2048 projections; for the parts of a two-launch plan it misleads and is not applied.  K = 8192 has its own fit.
-double model_time(const Candidate& c, double slots, int M, int Nout, int K, bool alone = false) {
-  const double tiles = (double)((M + c.bm - 1) / c.bm) * ((Nout + c.bn - 1) / c.bn);
-  const double t_tile = 2.0 * c.bm * c.bn * K / c.rate;
-  if (alone && K < 4096 && tiles < slots)   // a whole projection that fills only a fraction of the CUs
-    return t_tile * std::max(0.85, std::min(1.0, 1.1 * tiles / slots)) + kFixed;
-  // K = 8192 (the FFN down projection), one partly filled round: measured 99 ... 131 us for 80 ... 256 tiles of
-  // 256 x 128 and 70 ... 79 us for 144 ... 256 tiles of 128 x 128, i.e. 0.8 of the fit above at a full round and
-  // a weak dependence on the fill
-  if (K >= 4096 && tiles < slots) return (t_tile + kFixed) * 0.8 * (0.65 + 0.35 * tiles / slots);
-  return std::ceil(tiles / slots) * (t_tile + kFixed) * (K >= 4096 ? 0.8 : 1.0);
+// K slices of a launch of `tiles` tiles (the FFN down projection once few tokens are kept: a long K and a narrow
+// output fill less than half of the CUs): 2 or 4 workgroups per tile, fp32 partial sums and a second pass.
+int k_slices(int cus, int mode, int tiles, int64_t rows, int Nout, int K, int64_t part_floats, int forced) {
+  if (mode != EPI_RESIDUAL || K < 4096 || forced == 0) return 1;
+  int ks = 1;
+  if (forced > 0) ks = forced;
+  else while (ks < 4 && tiles * ks * 2 <= cus) ks *= 2;
+  const bool fits = (ks == 2 || ks == 4) && K % (ks * 64) == 0 && K / (ks * 64) >= 16 && ks * rows * Nout <= part_floats;
+  return fits ? ks : 1;
+}
+
+// Modelled time (seconds) of one launch over M rows with candidate c.
+double model_time(const Candidate& c, int slots, int mode, int M, int Nout, int K, int64_t part_floats) {
+  const int tiles = ((M + c.bm - 1) / c.bm) * ((Nout + c.bn - 1) / c.bn);
+  const int ks = k_slices(slots, mode, tiles, M, Nout, K, part_floats, -1);
+  const int full = tiles * ks / slots, rest = tiles * ks % slots;
+  const double f = (double)rest / slots, fixed = c.round + (mode == EPI_GELU || mode == EPI_GELU_TANH ? c.gelu : 0.0);
+  double t = c.launch + full * (fixed + K / ks * (c.k0 + c.k1 + c.k3));
+  if (rest) t += fixed + K / ks * (c.k0 + c.k1 * f + c.k3 * f * f * f);
+  if (ks > 1) t += 2.5 + (ks * 4.0 + 4.0) * M * Nout / 5e6;
+  return t * 1e-6;
 }
 
 // Whether M rows of a prediction head go to the narrow-tile kernels (more workgroups for the weight stream).
@@ -610,8 +750,7 @@ double rows_time(int rows, int Nout, int K) {
   return 3e-6 + 2.0 * Nout * K / 5e12 + 2.7e-6 * ((rows + 63) / 64) + (K >= 4096 ? 3e-6 : 0.0);
 }
 
-int pick_cfg(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64_t part_floats, double* t_out = nullptr,
-             bool alone = true) {
+int pick_cfg(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64_t part_floats, double* t_out = nullptr) {
   if (ctx && ctx->gemm_cfg >= 0 && ctx->gemm_cfg < kNumCfgs) return ctx->gemm_cfg;
   if (mode == EPI_ENTROPY) {
     if (M <= 64) return 3;
@@ -620,11 +759,17 @@ int pick_cfg(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64_t part
     if (t_out) *t_out = rows_time(M, Nout, K);
     return kRowsCfg;
   }
-  const double slots = ctx ? ctx->num_cus : 256;
+  const int slots = ctx ? ctx->num_cus : 256;
   int best = 2;
   double best_t = 1e30;
+  // a prediction head's partials (16 bytes per row and column tile) that fit the static scratch with 256-column tiles
+  // only: those, in every entry point, so that the allocation-free one gives the same bits
+  const int64_t room = (int64_t)head_entropy_static_capacity() / 16;
+  const bool wide = mode == EPI_ENTROPY && (int64_t)M * ((Nout + 127) / 128) > room && (int64_t)M * ((Nout + 255) / 256) <= room;
   for (const Candidate& c : kCands) {
-    const double t = model_time(c, slots, M, Nout, K, alone);
+    if (wide && c.bn < 256) continue;
+    if (c.cfg == 1 && K > 1 << 21) continue;             // its tiles are addressed with 32-bit offsets
+    const double t = model_time(c, slots, mode, M, Nout, K, part_floats);
     if (t < best_t) { best_t = t; best = c.cfg; }
   }
   if (t_out) *t_out = best_t;
@@ -647,11 +792,15 @@ Plan plan_rows(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64_t pa
   const int slots = ctx ? ctx->num_cus : 256;
   double best = t_single * 0.97;                          // a second launch has to pay for itself
   for (const Candidate& c : kCands) {
-    for (int rows = 1; rows * c.bm < M; ++rows) {         // tile rows in the first part
-      const int m1 = rows * c.bm;
+    const int tiles_n = (Nout + c.bn - 1) / c.bn;
+    for (int rounds = 1;; ++rounds) {                     // rounds of the first part
+      const int64_t m1_all = (int64_t)rounds * slots / tiles_n * c.bm;
+      if (m1_all >= M) break;
+      const int m1 = (int)m1_all;
+      if (m1 == 0) continue;
       double t_rest = 0.0;
-      const int cfg_rest = pick_cfg(ctx, mode, M - m1, Nout, K, part_floats, &t_rest, false);
-      const double t = model_time(c, slots, m1, Nout, K) + t_rest + 3e-6;
+      const int cfg_rest = pick_cfg(ctx, mode, M - m1, Nout, K, part_floats, &t_rest);
+      const double t = model_time(c, slots, mode, m1, Nout, K, part_floats) + t_rest;
       if (t < best) {
         best = t;
         p.n = 2;
@@ -677,22 +826,16 @@ hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W
     return hipGetLastError();
   }
   if constexpr (MODE == EPI_RESIDUAL) {
-    // A long K and a narrow output with large tiles (the FFN down projection once few tokens are kept): the tiles
-    // fill less than half of the CUs.  K is cut into 2 or 4 slices summed by as many workgroups per tile, fp32
-    // partial sums go to the scratch buffer and the second pass adds them and applies the epilogue.  The scratch
-    // buffer holds 4 x rows x C floats, hence Nout == C and at most four slices.
-    if ((cfg == 2 || cfg == 5 || cfg == 6) && ep.part && ksplit != 0 && K >= 4096 && Nout == ep.C && Nout % 8 == 0) {
-      const int bm = cfg == 5 ? 128 : 256, bn = cfg == 6 ? 256 : 128, bk = cfg == 6 ? 32 : 64;
+    // see k_slices; the scratch buffer holds 4 x rows x C floats, hence Nout == C
+    if ((cfg == 1 || cfg == 2 || cfg == 5) && ep.part && Nout == ep.C && Nout % 8 == 0) {
+      const int bm = cfg == 5 ? 128 : 256, bn = cfg == 1 ? 256 : 128;
       const int tiles = ((M - m_base + bm - 1) / bm) * ((Nout + bn - 1) / bn);
-      int ks = 1;
-      if (ksplit > 0) ks = ksplit;
-      else while (ks < 4 && tiles * ks * 2 <= cus) ks *= 2;
-      if ((ks == 2 || ks == 4) && K % (ks * bk) == 0 && K / (ks * bk) >= 16 &&
-          (int64_t)ks * (M - m_base) * Nout <= ep.part_floats) {
+      const int ks = k_slices(cus, MODE, tiles, M - m_base, Nout, K, ep.part_floats, ksplit);
+      if (ks > 1) {
         hipError_t e;
-        if (cfg == 2) e = launch_cfg<256, 128, 4, 2, 64, 3, false, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
-        else if (cfg == 5) e = launch_cfg<128, 128, 2, 4, 64, 3, false, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
-        else e = launch_cfg<256, 256, 2, 4, 32, 3, false, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
+        if (cfg == 1) e = launch_cfg<256, 256, 2, 4, 64, 2, false, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
+        else if (cfg == 2) e = launch_cfg<256, 128, 4, 2, 64, 3, false, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
+        else e = launch_cfg<128, 128, 2, 4, 64, 3, false, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
         if (e != hipSuccess) return e;
         const int64_t nvec = (int64_t)(M - m_base) * (Nout / 8);
         gemm_reduce_kernel<MODE><<<(unsigned)((nvec + 255) / 256), 256, 0, st>>>(ep.part, ks, m_base, M, Nout, ep);
@@ -701,10 +844,8 @@ hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W
     }
   }
   switch (cfg) {
-    case 0: return launch_cfg<128, 128, 2, 2, 64, 2, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
     case 1: return launch_cfg<256, 256, 2, 4, 64, 2, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
     case 5: return launch_cfg<128, 128, 2, 4, 64, 3, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
-    case 6: return launch_cfg<256, 256, 2, 4, 32, 3, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
     case 3:
       if constexpr (MODE == EPI_ENTROPY)
         return launch_cfg<64, 32, 2, 1, 64, 6, true, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
@@ -736,15 +877,17 @@ hipError_t launch_mode(const nova_ctx* ctx, hipStream_t st, const bf16_t* A, con
 // Output columns per tile of the configuration launch_gemm_bf16 uses for this shape.
 int gemm_bf16_tile_cols(const nova_ctx* ctx, int M, int Nout, int K) {
   switch (pick_cfg(ctx, EPI_ENTROPY, M, Nout, K, 0)) {
-    case 0: case 5: return 128;
-    case 1: case 6: return 256;
+    case 1: return 256;
     case 3: case 4: return 32;
     default: return 128;
   }
 }
 
 hipError_t launch_gemm_bf16(const nova_ctx* ctx, hipStream_t st, int mode, const void* A, const void* W, int M,
-                            int Nout, int K, const EpiParams<bf16_t>& ep) {
+                            int Nout, int K, const EpiParams<bf16_t>& params) {
+  EpiParams<bf16_t> ep = params;
+  ep.k_inv = ep.k > 0 ? div_inv(ep.k) : 0;
+  ep.dh_log2 = ep.dh == 128 ? 7 : 6;
   const bf16_t* a = static_cast<const bf16_t*>(A);
   const bf16_t* w = static_cast<const bf16_t*>(W);
   switch (mode) {

@@ -126,9 +126,9 @@ __global__ __launch_bounds__(KW* 64) void gemm_rows_kernel(const bf16_t* __restr
     if (ep.bias) bias[q] = *reinterpret_cast<const bf16x8*>(ep.bias + col);
     if constexpr (HAS_RES) {
       int64_t roff = (int64_t)row * ep.ldo;
-      if (MODE == EPI_ATTN_OUT) roff = ((int64_t)(row / ep.k) * ep.Ntok + min(max(src[q], 0), ep.Ntok - 1)) * ep.C;
+      if (MODE == EPI_ATTN_OUT) roff = ((int64_t)ep.image(row) * ep.Ntok + min(max(src[q], 0), ep.Ntok - 1)) * ep.C;
       res[q] = *reinterpret_cast<const bf16x8*>(ep.res + roff + col);
-      if (ep.gate) gate[q] = *reinterpret_cast<const bf16x8*>(ep.gate + (int64_t)(row / ep.k) * ep.gate_pitch + col);
+      if (ep.gate) gate[q] = *reinterpret_cast<const bf16x8*>(ep.gate + (int64_t)ep.image(row) * ep.gate_pitch + col);
     }
   }
   asm volatile("" ::: "memory");
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(KW* 64) void gemm_rows_kernel(const bf16_t* __restr
     for (int e = 0; e < 8; ++e) v[e] += (float)bias[q][e];
     bf16x8 y;
     if constexpr (MODE == EPI_QKV) {
-      const int sel = col / ep.C, cf = col - sel * ep.C;   // C is a multiple of 64: eight features lie in one part and head
+      const int sel = (col >= ep.C) + (col >= 2 * ep.C), cf = col - sel * ep.C;   // C is a multiple of 64: eight features lie in one part and head
       const float qs = sel == 0 ? ep.q_scale : 1.0f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) y[e] = (bf16_t)(v[e] * qs);
@@ -206,9 +206,10 @@ __global__ __launch_bounds__(KW* 64) void gemm_rows_kernel(const bf16_t* __restr
         *reinterpret_cast<bf16x8*>(ep.out + (int64_t)row * ep.ldo + cf) = y;
         continue;
       }
-      const int b = row / ep.k, s = row - b * ep.k;
+      int s;
+      const int b = ep.image(row, s);
       if (s >= image_count(ep.k_rows, b, ep.k)) continue;  // slots past an image's keep count append nothing
-      const int head = cf / ep.dh, d = cf - head * ep.dh;
+      const int head = cf >> ep.dh_log2, d = cf & (ep.dh - 1);
       const int64_t bh = (int64_t)b * ep.heads + head;
       const int pos = image_prior(ep.kv_rows, b, ep.P) + s;
       if (sel == 1) {
@@ -226,13 +227,13 @@ __global__ __launch_bounds__(KW* 64) void gemm_rows_kernel(const bf16_t* __restr
         if (MODE == EPI_PLAIN) v[e] *= ep.q_scale;
         y[e] = (bf16_t)v[e];
       }
-      if constexpr (HAS_RES) {                             // the projection (+ bias) is rounded before gate and residual
+      if constexpr (HAS_RES) {
         if (ep.gate) {
 #pragma unroll
-          for (int e = 0; e < 8; ++e) y[e] = (bf16_t)fmaf((float)gate[q][e], (float)y[e], (float)res[q][e]);
+          for (int e = 0; e < 8; ++e) y[e] = (bf16_t)fmaf((float)gate[q][e], v[e], (float)res[q][e]);
         } else {
 #pragma unroll
-          for (int e = 0; e < 8; ++e) y[e] = (bf16_t)((float)y[e] + (float)res[q][e]);
+          for (int e = 0; e < 8; ++e) y[e] = (bf16_t)(v[e] + (float)res[q][e]);
         }
       }
       *reinterpret_cast<bf16x8*>(ep.out + (int64_t)row * ep.ldo + col) = y;
