@@ -1,6 +1,8 @@
 // fp32 path of the pruned block (Sec. 3.3, "Residual Cache Reuse", first equation,
 // evaluated on the kept rows): plain, LDS-tiled fp32 kernels for small fp32 models.
 // It exists for correctness at full fp32 precision; the matrix-core path is block_bf16.hip.
+#include <algorithm>
+
 #include "common.h"
 #include "epilogue.h"
 #include "nova_internal.h"
@@ -8,32 +10,63 @@
 namespace {
 
 constexpr int kTile = 16;
+constexpr int kStepK = 64;                 // elements of K per step
+constexpr int kPitch = kStepK + 4;         // 16-byte reads of sixteen rows hit all banks once
 
-// out[m][n] = sum_k A[m][k] * W[n][k]  (+ epilogue); A [M, K] row-major, W [Nout, K] row-major
+// out[m][n] = sum_k A[m][k] * W[n][k]  (+ epilogue); A [M, K] row-major, W [Nout, K] row-major.
+// One thread per output element, K in ascending order.  These launches are a few workgroups that wait for memory: the
+// next 64 elements of K are requested before the current ones are used, so K = 256 costs one exposed latency and four
+// pairs of barriers where steps of 16 cost sixteen of each (128 x 64, K = 256: 9.9 -> 5.4 us).
 template <int MODE>
 __global__ __launch_bounds__(kTile* kTile) void gemm_f32_kernel(const float* __restrict__ A,
                                                                 const float* __restrict__ W, int M, int Nout,
                                                                 int K, EpiParams<float> ep) {
-  __shared__ float As[kTile][kTile + 1];
-  __shared__ float Ws[kTile][kTile + 1];
+  __shared__ __attribute__((aligned(16))) float As[kTile][kPitch];
+  __shared__ __attribute__((aligned(16))) float Ws[kTile][kPitch];
   const int tx = threadIdx.x % kTile, ty = threadIdx.x / kTile;
   const int row = blockIdx.y * kTile + ty;
   const int col = blockIdx.x * kTile + tx;
-  float acc = 0.f;
-  for (int k0 = 0; k0 < K; k0 += kTile) {
-    const int ar = blockIdx.y * kTile + ty, wr = blockIdx.x * kTile + ty, kk = k0 + tx;
-    As[ty][tx] = (ar < M && kk < K) ? A[(int64_t)ar * K + kk] : 0.f;
-    Ws[ty][tx] = (wr < Nout && kk < K) ? W[(int64_t)wr * K + kk] : 0.f;
-    __syncthreads();
+  const int wr = blockIdx.x * kTile + ty;            // the weight row this thread loads for the tile
+  const float* ap = A + (int64_t)min(row, M - 1) * K;
+  const float* wp = W + (int64_t)min(wr, Nout - 1) * K;
+  constexpr int NL = kStepK / kTile;
+  float a[NL], w[NL];
+  auto request = [&](int k0) {
 #pragma unroll
-    for (int i = 0; i < kTile; ++i) acc = fmaf(As[ty][i], Ws[tx][i], acc);
+    for (int i = 0; i < NL; ++i) {
+      const int kk = k0 + tx + i * kTile;
+      a[i] = kk < K ? ap[kk] : 0.f;
+      w[i] = kk < K ? wp[kk] : 0.f;
+    }
+  };
+  request(0);
+  float acc = 0.f;
+  for (int k0 = 0; k0 < K; k0 += kStepK) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      As[ty][tx + i * kTile] = a[i];
+      Ws[ty][tx + i * kTile] = w[i];
+    }
+    __syncthreads();
+    if (k0 + kStepK < K) request(k0 + kStepK);
+#pragma unroll
+    for (int i = 0; i < kStepK; i += 4) {
+      const f32x4 av = *reinterpret_cast<const f32x4*>(&As[ty][i]), wv = *reinterpret_cast<const f32x4*>(&Ws[tx][i]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = fmaf(av[e], wv[e], acc);
+    }
     __syncthreads();
   }
   if (row < M && col < Nout) epilogue_store<float, MODE>(ep, row, col, acc);
 }
 
-// One wave per (query row m, head).  Scores of all P+k cached keys are kept in LDS.
-__global__ __launch_bounds__(NOVA_WAVE) void attention_f32_kernel(const float* __restrict__ q,
+// One workgroup per (query row m, head), its waves splitting the keys and then the channels.  Scores of all P+k cached
+// keys are kept in LDS.  Bound by latency: with one wave per query and head 128 queries of 4 heads (dh = 16) over 552 keys
+// took 31.9 us, one scalar load after the other; now 7.1 us.
+constexpr int kAttnWaves = 4;
+constexpr int kChannels = 4;               // channels of V a wave sums at a time
+
+__global__ __launch_bounds__(kAttnWaves* NOVA_WAVE) void attention_f32_kernel(const float* __restrict__ q,
                                                                   const float* __restrict__ kc,
                                                                   const float* __restrict__ vc, int k, int C,
                                                                   int heads, int dh, int cap, int kv_total_uniform,
@@ -41,48 +74,80 @@ __global__ __launch_bounds__(NOVA_WAVE) void attention_f32_kernel(const float* _
                                                                   const int32_t* __restrict__ k_rows,
                                                                   const int32_t* __restrict__ kv_rows, int P,
                                                                   int self_keys) {
-  extern __shared__ float sc[];            // [kv_total] scores, then [dh] the query
-  const int lane = threadIdx.x;
+  extern __shared__ float sc[];            // [kv_total] scores, then the waves' maxima and sums
+  constexpr int NT = kAttnWaves * NOVA_WAVE;
+  const int tid = threadIdx.x, lane = tid & (NOVA_WAVE - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / NOVA_WAVE);
   const int m = blockIdx.x, head = blockIdx.y;
   const int b = m / k;
   // per-image keep counts: a slot past its image's count gets zeros; an image's keys are its own prior rows plus
   // its own kept rows (never more than the uniform total the LDS was sized for)
   const int kq = image_count(k_rows, b, k);
   if (m - b * k >= kq) {
-    for (int d = lane; d < dh; d += NOVA_WAVE) out[(int64_t)m * C + head * dh + d] = 0.0f;
+    for (int d = tid; d < dh; d += NT) out[(int64_t)m * C + head * dh + d] = 0.0f;
     return;
   }
   const int kv_total = self_keys && (k_rows || kv_rows) ? image_prior(kv_rows, b, P) + kq : kv_total_uniform;
-  float* qs = sc + kv_total;
+  float* red = sc + kv_total;
   const int64_t bh = (int64_t)b * heads + head;
   const float* K = kc + bh * cap * dh;
   const float* V = vc + bh * dh * (int64_t)cap;
-  for (int d = lane; d < dh; d += NOVA_WAVE) qs[d] = q[(int64_t)m * C + head * dh + d];
-  __syncthreads();
+  const float* qr = q + (int64_t)m * C + head * dh;      // the same for all threads: scalar loads
   float mx = -INFINITY;
-  for (int j = lane; j < kv_total; j += NOVA_WAVE) {
+  for (int j = tid; j < kv_total; j += NT) {
+    const float* kr = K + (int64_t)j * dh;
     float s = 0.f;
-    for (int d = 0; d < dh; ++d) s = fmaf(qs[d], K[(int64_t)j * dh + d], s);
+    int d = 0;
+    for (; d + 16 <= dh; d += 16) {
+      float v[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) v[e] = kr[d + e];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s = fmaf(qr[d + e], v[e], s);
+    }
+    for (; d < dh; ++d) s = fmaf(qr[d], kr[d], s);
     s *= scale;
     sc[j] = s;
     mx = fmaxf(mx, s);
   }
   mx = wave_max(mx);
+  if (lane == 0) red[wave] = mx;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kAttnWaves; ++w) mx = fmaxf(mx, red[w]);
   float z = 0.f;
-  for (int j = lane; j < kv_total; j += NOVA_WAVE) {
-    float e = expf(sc[j] - mx);
+  for (int j = tid; j < kv_total; j += NT) {
+    const float e = expf(sc[j] - mx);
     sc[j] = e;
     z += e;
   }
   z = wave_sum(z);
+  if (lane == 0) red[kAttnWaves + wave] = z;
   __syncthreads();
-  for (int d = 0; d < dh; ++d) {
-    float a = 0.f;
-    for (int j = lane; j < kv_total; j += NOVA_WAVE) a = fmaf(sc[j], V[(int64_t)d * cap + j], a);
-    a = wave_sum(a);
-    if (lane == 0) out[(int64_t)m * C + head * dh + d] = a / z;
+  z = 0.f;
+#pragma unroll
+  for (int w = 0; w < kAttnWaves; ++w) z += red[kAttnWaves + w];
+  for (int d0 = wave * kChannels; d0 < dh; d0 += kAttnWaves * kChannels) {
+    float a[kChannels] = {};
+    const float* vr[kChannels];
+#pragma unroll
+    for (int c = 0; c < kChannels; ++c) vr[c] = V + (int64_t)min(d0 + c, dh - 1) * cap;
+#pragma unroll 4
+    for (int j = lane; j < kv_total; j += NOVA_WAVE) {
+      const float p = sc[j];
+#pragma unroll
+      for (int c = 0; c < kChannels; ++c) a[c] = fmaf(p, vr[c][j], a[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < kChannels; ++c) {
+      const float s = wave_sum(a[c]);
+      if (lane == 0 && d0 + c < dh) out[(int64_t)m * C + head * dh + d0 + c] = s / z;
+    }
   }
 }
+
+// LDS of attention_f32_kernel: the scores, and dh floats or what the waves exchange
+size_t attention_f32_lds(int kv_total, int dh) { return (size_t)(kv_total + std::max(dh, 2 * kAttnWaves)) * sizeof(float); }
 
 template <int MODE>
 void gemm(hipStream_t st, const float* A, const float* W, int M, int Nout, int K, const EpiParams<float>& ep) {
@@ -132,10 +197,10 @@ hipError_t launch_block_f32(nova_ctx* ctx, hipStream_t st, const nova_block_shap
   }
 
   const int kv_total = s.kv_len + s.k;
-  const size_t lds = (size_t)(kv_total + dh) * sizeof(float);
+  const size_t lds = attention_f32_lds(kv_total, dh);
   {
     StageTimer t(ctx, st, NOVA_STAGE_ATTENTION);
-    attention_f32_kernel<<<dim3(M, s.heads), NOVA_WAVE, lds, st>>>(q, kc, vc, s.k, C, s.heads, dh, s.kv_capacity,
+    attention_f32_kernel<<<dim3(M, s.heads), kAttnWaves * NOVA_WAVE, lds, st>>>(q, kc, vc, s.k, C, s.heads, dh, s.kv_capacity,
                                                                    kv_total, var.qk_norm ? 1.0f : 1.0f / sqrtf((float)dh), attn,
                                                                    rc.k_rows, rc.kv_rows, s.kv_len, 1);
   }
@@ -151,8 +216,8 @@ hipError_t launch_block_f32(nova_ctx* ctx, hipStream_t st, const nova_block_shap
     if (e != hipSuccess) return e;
     ep.bias = static_cast<const float*>(var.b_cq); ep.out = q; ep.ldo = C; ep.gate = nullptr;
     gemm<EPI_PLAIN>(st, u, static_cast<const float*>(var.w_cq), M, C, C, ep);
-    const size_t lds_t = (size_t)(var.text_len + dh) * sizeof(float);
-    attention_f32_kernel<<<dim3(M, s.heads), NOVA_WAVE, lds_t, st>>>(
+    const size_t lds_t = attention_f32_lds(var.text_len, dh);
+    attention_f32_kernel<<<dim3(M, s.heads), kAttnWaves * NOVA_WAVE, lds_t, st>>>(
         q, static_cast<const float*>(var.k_text), static_cast<const float*>(var.v_text), s.k, C, s.heads, dh,
         var.text_capacity, var.text_len, 1.0f / sqrtf((float)dh), attn, rc.k_rows, nullptr, 0, 0);
     ep.bias = static_cast<const float*>(var.b_co); ep.out = x1; ep.ldo = C; ep.res = x1;
