@@ -104,25 +104,30 @@ __global__ __launch_bounds__(kWavesPerBlock* NOVA_WAVE) void entropy_kernel(
 }
 
 // Scale mean entropy of one image per workgroup: mean[b] = (sum_i H[b, i]) / N with a fixed summation order
-// (thread t adds its contiguous share of the elements in index order, then a fixed tree over the threads), so the
+// (thread t adds elements t, t + 1024, ..., then a fixed tree over the threads), so the
 // result is the same bits on every run: the layer-linkage ratio turns it into an integer keep count.  A NaN
-// entropy gives NaN.
-constexpr int kMeanThreads = 256;
+// entropy gives NaN.  One latency for up to 4096 tokens: 256 threads that add contiguous shares one load after the
+// other take 4.0 us for 4096, this 3.1.
+constexpr int kMeanThreads = 1024;
 __global__ __launch_bounds__(kMeanThreads) void row_mean_kernel(const float* __restrict__ H, int64_t rows_per_batch,
                                                                 float* __restrict__ mean) {
-  __shared__ float part[kMeanThreads];
+  __shared__ float part[kMeanThreads / NOVA_WAVE];
   const float* h = H + (int64_t)blockIdx.x * rows_per_batch;
   float s = 0.0f;
-  const int64_t ipt = (rows_per_batch + kMeanThreads - 1) / kMeanThreads;
-  const int64_t i0 = std::min<int64_t>(threadIdx.x * ipt, rows_per_batch), i1 = std::min<int64_t>(i0 + ipt, rows_per_batch);
-  for (int64_t i = i0; i < i1; ++i) s += h[i];
-  part[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = kMeanThreads / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) part[threadIdx.x] += part[threadIdx.x + o];
-    __syncthreads();
+  for (int64_t i = threadIdx.x; i < rows_per_batch; i += 4 * kMeanThreads) {
+    float v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = i + u * kMeanThreads < rows_per_batch ? h[i + u * kMeanThreads] : 0.0f;
+    s += (v[0] + v[1]) + (v[2] + v[3]);
   }
-  if (threadIdx.x == 0) mean[blockIdx.x] = part[0] / (float)rows_per_batch;
+  s = wave_sum(s);
+  if ((threadIdx.x & (NOVA_WAVE - 1)) == 0) part[threadIdx.x / NOVA_WAVE] = s;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  float t = 0.0f;
+#pragma unroll
+  for (int w = 0; w < kMeanThreads / NOVA_WAVE; ++w) t += part[w];
+  mean[blockIdx.x] = t / (float)rows_per_batch;
 }
 
 template <typename T, int CH>

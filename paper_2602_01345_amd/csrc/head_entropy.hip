@@ -10,15 +10,36 @@
 
 namespace {
 
-__global__ __launch_bounds__(256) void head_entropy_combine_kernel(const f32x4* __restrict__ part, int tiles_n,
-                                                                   int M, float* __restrict__ H) {
-  const int row = blockIdx.x * blockDim.x + threadIdx.x;
-  if (row >= M) return;
-  const f32x4 a = part[row];
-  float m = a[0], S = a[1], T = a[2];
-  for (int t = 1; t < tiles_n; ++t) {
-    const f32x4 b = part[(int64_t)t * M + row];
-    entropy_merge(m, S, T, b[0], b[1], b[2]);
+// A workgroup merges the partials of 64 rows: four waves take every fourth column tile, four loads in flight each, and
+// meet in LDS.  (One thread per row that loads a partial, merges it and loads the next is one memory latency per tile:
+// 16 tiles of 8192 rows 7.2 us, now 4.7.)
+constexpr int kCombineRows = 64, kCombineGroups = 4;
+
+__global__ __launch_bounds__(kCombineRows* kCombineGroups) void head_entropy_combine_kernel(
+    const f32x4* __restrict__ part, int tiles_n, int M, float* __restrict__ H) {
+  __shared__ f32x4 meet[kCombineGroups][kCombineRows];
+  const int r = threadIdx.x % kCombineRows, g = threadIdx.x / kCombineRows;
+  const int row = blockIdx.x * kCombineRows + r;
+  const f32x4* p = part + min(row, M - 1);
+  float m = 0.0f, S = 0.0f, T = 0.0f;
+  for (int t = g; t < tiles_n; t += 4 * kCombineGroups) {
+    f32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = p[(int64_t)min(t + u * kCombineGroups, tiles_n - 1) * M];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (t + u == g) { m = v[0][0]; S = v[0][1]; T = v[0][2]; }     // the group's first tile
+      else if (t + u * kCombineGroups < tiles_n) entropy_merge(m, S, T, v[u][0], v[u][1], v[u][2]);
+    }
+  }
+  meet[g][r] = f32x4{m, S, T, 0.0f};
+  __syncthreads();
+  if (g != 0 || row >= M) return;
+#pragma unroll
+  for (int w = 1; w < kCombineGroups; ++w) {
+    if (w >= tiles_n) break;               // a group without a tile
+    const f32x4 v = meet[w][r];
+    entropy_merge(m, S, T, v[0], v[1], v[2]);
   }
   float h = logf(S) + T / S;
   h = h < 0.0f ? 0.0f : h;
@@ -79,7 +100,7 @@ hipError_t launch_head_entropy(const nova_ctx* ctx, hipStream_t st, const void* 
   hipError_t e = launch_gemm_bf16(ctx, st, EPI_ENTROPY, hidden, w_head, M, V, C, ep);
   if (e != hipSuccess) return e;
   const int bn = gemm_bf16_tile_cols(ctx, M, V, C);
-  head_entropy_combine_kernel<<<(M + 255) / 256, 256, 0, st>>>(ep.ent_part, (V + bn - 1) / bn, M, H);
+  head_entropy_combine_kernel<<<(M + kCombineRows - 1) / kCombineRows, kCombineRows * kCombineGroups, 0, st>>>(ep.ent_part, (V + bn - 1) / bn, M, H);
   if (mean) return launch_row_mean(st, H, rows_per_batch, batch, mean);
   return hipGetLastError();
 }
