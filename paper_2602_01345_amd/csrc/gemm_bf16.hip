@@ -744,10 +744,13 @@ double model_time(const Candidate& c, int slots, int mode, int M, int Nout, int 
 // Whether M rows of a prediction head go to the narrow-tile kernels (more workgroups for the weight stream).
 bool narrow_tiles(int M, int Nout, int K) { return M <= 256 || (M <= 512 && Nout < 4096 && K < 4096); }
 
-// Modelled time of the few-rows kernels: the weight stream, 3 us to start and end, 2.7 us per 64 rows (measured 3.6 ...
-// 24.5 us over 16 ... 256 rows and 2 ... 34 MB of weights, within 2 us), 3 us for the slice sums of a long K.
-double rows_time(int rows, int Nout, int K) {
-  return 3e-6 + 2.0 * Nout * K / 5e12 + 2.7e-6 * ((rows + 63) / 64) + (K >= 4096 ? 3e-6 : 0.0);
+// Modelled time of the few-rows kernels: what the busiest CU loads at 75 GB/s, half of the weights at the rate of a large
+// copy, 2.5 us to start and end, 3 us for the slice sums (measured 4.2 ... 22 us over 64 ... 1024 rows and 2 ... 38 MB
+// of weights; within 2 us but for a long K, where it is up to 8 us too much).
+double rows_time(const RowsPlan& p, int cus, int rows, int Nout, int K) {
+  const int wgs = (rows + 8 * p.rg - 1) / (8 * p.rg) * (Nout / (8 * p.ng)) * p.slices;
+  const double bytes = (double)((wgs + cus - 1) / cus) * 16.0 * (p.rg + p.ng) * K / p.slices;
+  return 2.5e-6 + bytes / 75e9 + (double)Nout * K / 5e12 + (p.slices > 1 ? 3e-6 : 0.0);
 }
 
 int pick_cfg(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64_t part_floats, double* t_out = nullptr) {
@@ -755,11 +758,13 @@ int pick_cfg(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64_t part
   if (mode == EPI_ENTROPY) {
     if (M <= 64) return 3;
     if (narrow_tiles(M, Nout, K)) return 4;
-  } else if (gemm_rows_plan(ctx ? ctx->num_cus : 256, mode, M, Nout, K, part_floats).rg) {
-    if (t_out) *t_out = rows_time(M, Nout, K);
-    return kRowsCfg;
   }
   const int slots = ctx ? ctx->num_cus : 256;
+  const RowsPlan rows = gemm_rows_plan(slots, mode, M, Nout, K, part_floats);      // rg = 0 for a prediction head
+  if (rows.rg) {
+    if (t_out) *t_out = rows_time(rows, slots, M, Nout, K);
+    return kRowsCfg;
+  }
   int best = 2;
   double best_t = 1e30;
   // a prediction head's partials (16 bytes per row and column tile) that fit the static scratch with 256-column tiles

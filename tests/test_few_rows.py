@@ -37,3 +37,10 @@ def test_widths_and_long_k(hx, C, heads, M):
     print(f"few rows C={C} M={M}", flush=True)
     wl = _block(1, 23, 20, C, heads)
     hx.check_block(hx.make_host_block(wl, 0, k=M), hx.BF16_TOL)
+
+
+@pytest.mark.parametrize("C,heads,k", [(1024, 8, 257), (1024, 8, 511), (512, 8, 600)])
+def test_one_workgroup_per_cu_beyond_512_rows(hx, C, heads, k):
+    print(f"few rows C={C} M={2 * k}", flush=True)
+    wl = _block(2, 25, 20, C, heads)
+    hx.check_block(hx.make_host_block(wl, 0, k=k), hx.BF16_TOL)
