@@ -53,13 +53,38 @@ __device__ __forceinline__ int image_prior(const int32_t* __restrict__ kv_rows, 
   return v < 0 ? 0 : (v > P ? P : v);
 }
 
+// Wave-wide sum / maximum on the DPP cross-lane paths of the vector ALU (quads, half rows, rows of 16, then the two
+// row broadcasts), read back from lane 63 as a wave-uniform scalar: six dependent vector instructions and no trip
+// through the LDS crossbar, which is what a butterfly of lane shuffles costs six times over.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_or(float v, float identity) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(identity), __float_as_int(v), CTRL, ROW_MASK, 0xF, false));
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, NOVA_WAVE);
-  return v;
+  v += dpp_or<0xB1, 0xF>(v, 0.0f);          // quad_perm [1,0,3,2]
+  v += dpp_or<0x4E, 0xF>(v, 0.0f);          // quad_perm [2,3,0,1]
+  v += dpp_or<0x141, 0xF>(v, 0.0f);         // row_half_mirror
+  v += dpp_or<0x140, 0xF>(v, 0.0f);         // row_mirror: every lane holds the sum of its row of 16
+  v += dpp_or<0x142, 0xA>(v, 0.0f);         // row_bcast15 into rows 1 and 3
+  v += dpp_or<0x143, 0xC>(v, 0.0f);         // row_bcast31 into rows 2 and 3: lane 63 holds the total
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, NOVA_WAVE));
-  return v;
+  v = fmaxf(v, dpp_or<0xB1, 0xF>(v, -INFINITY));
+  v = fmaxf(v, dpp_or<0x4E, 0xF>(v, -INFINITY));
+  v = fmaxf(v, dpp_or<0x141, 0xF>(v, -INFINITY));
+  v = fmaxf(v, dpp_or<0x140, 0xF>(v, -INFINITY));
+  v = fmaxf(v, dpp_or<0x142, 0xA>(v, -INFINITY));
+  v = fmaxf(v, dpp_or<0x143, 0xC>(v, -INFINITY));
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+// Division of 0 <= n < 2^31 by d >= 1 through inv = div_inv(d), made once on the host: the high half of n * inv is the
+// quotient or one less.
+inline uint32_t div_inv(int d) { return 0xFFFFFFFFu / (uint32_t)(d > 0 ? d : 1); }
+__device__ __forceinline__ int div_by(int n, int d, uint32_t inv, int& rem) {
+  int q = (int)__umulhi((uint32_t)n, inv);
+  rem = n - q * d;
+  if (rem >= d) { ++q; rem -= d; }
+  return q;
 }

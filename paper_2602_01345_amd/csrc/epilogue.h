@@ -15,16 +15,6 @@ enum EpiMode {
   EPI_PARTIAL = 7     // raw fp32 sums over one slice of K, [slice][M][Nout]; a reduce pass applies the real epilogue
 };
 
-// Division of 0 <= n < 2^31 by d >= 1 through inv = div_inv(d), made once on the host: the high half of n * inv is the
-// quotient or one less.
-inline uint32_t div_inv(int d) { return 0xFFFFFFFFu / (uint32_t)d; }
-__device__ __forceinline__ int div_by(int n, int d, uint32_t inv, int& rem) {
-  int q = (int)__umulhi((uint32_t)n, inv);
-  rem = n - q * d;
-  if (rem >= d) { ++q; rem -= d; }
-  return q;
-}
-
 template <typename T>
 struct EpiParams {
   const T* bias;        // [Nout] or nullptr
