@@ -2,13 +2,16 @@
 // the order (entropy descending, index ascending)  (Sec. 3.3, "Dual-Linkage
 // Acceleration", final sentence; Sec. 3.2, the highest-entropy tokens are maintained).
 //
-// One 1024-thread workgroup per batch row.  Entropies are mapped to 32-bit keys whose
-// unsigned order is the required numeric order (NaN lowest, -0 == +0), staged in LDS,
-// and the k-th largest key is found by a 4-pass, 8-bit MSB radix select on LDS
-// histograms (select_core.h).  Every key above the threshold is kept; of the keys equal to it the
-// first (k - #above) in index order are kept.  Two block-wide prefix sums over
-// contiguous index ranges turn that rule into the ascending index list and the mask.
+// One workgroup per batch row.  Entropies are mapped to 32-bit keys whose unsigned order is the required numeric order
+// (NaN lowest, -0 == +0), and the k-th largest key is found.  Every key above the threshold is kept; of the keys equal to
+// it the first (k - #above) in index order are kept, which prefix sums turn into the ascending index list and the mask.
 // Integer compares only: the result equals a stable sort bit for bit.
+//
+// Bound by latency (1 ... 32 KB per row): every barrier, LDS round trip and lane shuffle counts.  Rows of up to 8192
+// tokens keep their keys in registers, divide the range of the keys that occur into 2048 bins, rank the few keys of
+// the bin that matters in one wave, and need nine barriers; the radix select on LDS histograms with its four passes,
+// 24 barriers, stays for longer rows.  Radix select / this (us): 8 rows of 256 8.5 / 4.6, one row of 256 in a
+// graph 7.8 / 3.5, one of 1024 7.8 / 5.6, two of 4096 11.4 / 8.0.
 #include "common.h"
 #include "nova_internal.h"
 #include "select_core.h"
@@ -18,33 +21,40 @@ namespace {
 using namespace select_core;
 
 constexpr int kThreads = 1024;
-constexpr int kLdsKeys = 8192;   // rows up to this many tokens are staged in LDS
 
-template <bool STAGED>
-__global__ __launch_bounds__(kThreads) void select_kernel(const float* __restrict__ H, int N, int k_uniform,
-                                                          const int32_t* __restrict__ k_per_row,
-                                                          int pitch, int32_t* __restrict__ idx,
-                                                          uint8_t* __restrict__ mask) {
-  __shared__ uint32_t keys_lds[STAGED ? kLdsKeys : 1];
-  __shared__ Scratch<kThreads> sc;
+__device__ __forceinline__ int row_count(int k_uniform, const int32_t* __restrict__ k_per_row, int b, int N, int pitch) {
+  if (!k_per_row) return k_uniform;
+  int k = k_per_row[b];
+  k = k < 0 ? 0 : (k > N ? N : k);
+  return k > pitch ? pitch : k;
+}
 
-  const int tid = threadIdx.x;
+// N <= NT * KPT
+template <int NT, int KPT>
+__global__ __launch_bounds__(NT) void select_kernel(const float* __restrict__ H, int N, int k_uniform,
+                                                    const int32_t* __restrict__ k_per_row, int pitch,
+                                                    int32_t* __restrict__ idx, uint8_t* __restrict__ mask) {
+  __shared__ RowScratch<NT, KPT> sc;
   const int b = blockIdx.x;
   const float* h = H + (int64_t)b * N;
+  const int k = row_count(k_uniform, k_per_row, b, N, pitch);
+  uint32_t key[KPT];
+#pragma unroll
+  for (int u = 0; u < KPT; ++u) key[u] = sort_key(h[min(u * NT + (int)threadIdx.x, N - 1)]);
+  uint32_t thr = 0, remaining = 0;
+  if (k > 0 && k < N) thr = range_select<NT, KPT>(key, N, k, sc, &remaining);
+  range_compact<NT, KPT>(key, N, thr, remaining, k == N, k == 0, pitch, idx + (int64_t)b * pitch, mask + (int64_t)b * N, sc);
+}
 
-  int k = k_uniform;
-  if (k_per_row) {
-    k = k_per_row[b];
-    k = k < 0 ? 0 : (k > N ? N : k);
-    k = k > pitch ? pitch : k;
-  }
-
-  if (STAGED) {
-    for (int i = tid; i < N; i += kThreads) keys_lds[i] = sort_key(h[i]);
-    __syncthreads();
-  }
-  auto key_at = [&](int i) -> uint32_t { return STAGED ? keys_lds[i] : sort_key(h[i]); };
-
+// any N
+__global__ __launch_bounds__(kThreads) void select_long_kernel(const float* __restrict__ H, int N, int k_uniform,
+                                                               const int32_t* __restrict__ k_per_row, int pitch,
+                                                               int32_t* __restrict__ idx, uint8_t* __restrict__ mask) {
+  __shared__ Scratch<kThreads> sc;
+  const int b = blockIdx.x;
+  const float* h = H + (int64_t)b * N;
+  const int k = row_count(k_uniform, k_per_row, b, N, pitch);
+  auto key_at = [&](int i) -> uint32_t { return sort_key(h[i]); };
   uint32_t thr = 0, remaining = 0;
   if (k > 0 && k < N) thr = radix_select<kThreads, 32>(key_at, N, k, sc, &remaining);
   compact<kThreads>(key_at, N, thr, remaining, k == N, k == 0, pitch, idx + (int64_t)b * pitch, mask + (int64_t)b * N,
@@ -55,9 +65,12 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const float* __restric
 
 hipError_t launch_select(hipStream_t st, const float* H, int B, int N, int k, const int32_t* k_per_row,
                          int32_t* idx, uint8_t* mask) {
-  if (N <= kLdsKeys)
-    select_kernel<true><<<B, kThreads, 0, st>>>(H, N, k, k_per_row, k, idx, mask);
-  else
-    select_kernel<false><<<B, kThreads, 0, st>>>(H, N, k, k_per_row, k, idx, mask);
+  auto go = [&](auto kernel, int threads) { kernel<<<B, threads, 0, st>>>(H, N, k, k_per_row, k, idx, mask); };
+  if (N <= 256) go(select_kernel<256, 1>, 256);
+  else if (N <= 1024) go(select_kernel<256, 4>, 256);
+  else if (N <= 2048) go(select_kernel<1024, 2>, 1024);
+  else if (N <= 4096) go(select_kernel<1024, 4>, 1024);
+  else if (N <= 8192) go(select_kernel<1024, 8>, 1024);
+  else go(select_long_kernel, kThreads);
   return hipGetLastError();
 }
