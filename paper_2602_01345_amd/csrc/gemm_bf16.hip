@@ -695,16 +695,18 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restric
 // Tile configurations (NOVA_GEMM_CFG forces one, for tuning; numbers without a kernel mean 2):
 //   1: 256x256x64, 8 waves of 128x64 that alternate between the matrix cores and LDS
 //   2: 256x128x64, 8 waves of 64x64, 3 stages
+//   6: 192x128x64, 8 waves of 96x32, 3 stages: one round where 256x128 leaves too many CUs idle and 128x128 needs a
+//      second round (1640 rows, K = 1024, 3072 features 17.3 -> 15.7 us; 1100 rows, 4096 features 19.2 -> 16.2)
 //   3: 64x32x64, 2 waves of 32x32, 6 stages, staggered K walk          (head entropy only, M <= 64)
 //   4: 128x32x64, 4 waves of 32x32, 4 stages, staggered K walk         (head entropy only, M <= 256 or 512)
 //   5: 128x128x64, 8 waves of 64x32, 3 stages, one workgroup per CU (two waves per SIMD hide the LDS waits that
 //      four waves of 64x64 expose: 3-10 % faster at every shape measured)
 //   7: the few-rows kernels of gemm_rows_bf16.hip (chosen by their own plan, not by force)
-// Without a forced choice the launcher prices 1, 2 and 5 with a model fitted to measurements on MI355X (300 ... 8192
+// Without a forced choice the launcher prices 1, 2, 5 and 6 with a model fitted to measurements on MI355X (300 ... 8192
 // rows, widths C of 1024 ... 2304, outputs of C, 3C and 4C features, K = C and 4C): a launch takes rounds of one tile
 // per CU; a round costs a fixed time (first loads, epilogue) and a time per element of K that grows with the share of
-// the CUs that are busy (they share L2, memory and power).  The fit is within 6 % (rms) of the measurements, and what
-// it chooses takes 0.1 % longer than the best of the three on average, 7 % at worst.
+// the CUs that are busy (they share L2, memory and power).  The fit is within 5 % (rms) of the measurements, and what
+// it chooses takes 0.03 % longer than the best of the four on average, 4 % at worst (launches without K slices).
 constexpr int kNumCfgs = 7;
 constexpr int kRowsCfg = 7;
 
@@ -714,9 +716,10 @@ struct Candidate {
   double k0, k1, k3;            // us per element of K in a round that fills a share f of the CUs: k0 + k1 f + k3 f^3
 };
 
-static const Candidate kCands[] = {{1, 256, 256, 5.1, 4.0, 2.1, 0.01621, -0.00149, 0.00964},
-                                   {2, 256, 128, 3.7, 2.7, 0.5, 0.01048, 0.00108, 0.00301},
-                                   {5, 128, 128, 3.1, 1.6, 0.0, 0.00591, 0.00119, 0.00168}};
+static const Candidate kCands[] = {{1, 256, 256, 4.3, 5.0, 2.0, 0.01580, -0.00114, 0.01000},
+                                   {2, 256, 128, 3.4, 2.8, 0.6, 0.01072, 0.00005, 0.00404},
+                                   {6, 192, 128, 2.4, 3.2, 0.6, 0.00784, 0.00200, 0.00151},
+                                   {5, 128, 128, 2.7, 1.9, 0.0, 0.00603, 0.00112, 0.00152}};
 
 // K slices of a launch of `tiles` tiles (the FFN down projection once few tokens are kept: a long K and a narrow
 // output fill less than half of the CUs): 2 or 4 workgroups per tile, fp32 partial sums and a second pass.
@@ -832,14 +835,15 @@ hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W
   }
   if constexpr (MODE == EPI_RESIDUAL) {
     // see k_slices; the scratch buffer holds 4 x rows x C floats, hence Nout == C
-    if ((cfg == 1 || cfg == 2 || cfg == 5) && ep.part && Nout == ep.C && Nout % 8 == 0) {
-      const int bm = cfg == 5 ? 128 : 256, bn = cfg == 1 ? 256 : 128;
+    if ((cfg == 1 || cfg == 2 || cfg == 5 || cfg == 6) && ep.part && Nout == ep.C && Nout % 8 == 0) {
+      const int bm = cfg == 5 ? 128 : cfg == 6 ? 192 : 256, bn = cfg == 1 ? 256 : 128;
       const int tiles = ((M - m_base + bm - 1) / bm) * ((Nout + bn - 1) / bn);
       const int ks = k_slices(cus, MODE, tiles, M - m_base, Nout, K, ep.part_floats, ksplit);
       if (ks > 1) {
         hipError_t e;
         if (cfg == 1) e = launch_cfg<256, 256, 2, 4, 64, 2, false, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
         else if (cfg == 2) e = launch_cfg<256, 128, 4, 2, 64, 3, false, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
+        else if (cfg == 6) e = launch_cfg<192, 128, 2, 4, 64, 3, false, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
         else e = launch_cfg<128, 128, 2, 4, 64, 3, false, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
         if (e != hipSuccess) return e;
         const int64_t nvec = (int64_t)(M - m_base) * (Nout / 8);
@@ -851,6 +855,7 @@ hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W
   switch (cfg) {
     case 1: return launch_cfg<256, 256, 2, 4, 64, 2, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
     case 5: return launch_cfg<128, 128, 2, 4, 64, 3, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
+    case 6: return launch_cfg<192, 128, 2, 4, 64, 3, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
     case 3:
       if constexpr (MODE == EPI_ENTROPY)
         return launch_cfg<64, 32, 2, 1, 64, 6, true, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
