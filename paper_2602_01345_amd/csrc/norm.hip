@@ -58,6 +58,17 @@ __global__ __launch_bounds__(kWavesPerBlock* NOVA_WAVE) void gather_ln_kernel(
       const int vi = u * NOVA_WAVE + lane;
       if (vi < nvec) v[u].load(p + vi * VN);
     }
+    // the modulation vectors are requested with the row, not behind its sums
+    VT a[U], g[U];
+    if (shift) {
+      const T* sh = shift + (int64_t)image * mod_pitch;
+      const T* sc = scale + (int64_t)image * mod_pitch;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int vi = u * NOVA_WAVE + lane;
+        if (vi < nvec) { a[u].load(sh + vi * VN); g[u].load(sc + vi * VN); }
+      }
+    }
     float sum = 0.f;
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -74,17 +85,14 @@ __global__ __launch_bounds__(kWavesPerBlock* NOVA_WAVE) void gather_ln_kernel(
         for (int e = 0; e < VN; ++e) { float d = v[u].get(e) - mean; sq = fmaf(d, d, sq); }
       }
     const float rstd = 1.0f / sqrtf(wave_sum(sq) / (float)C + kEps);
-    const T* sh = shift ? shift + (int64_t)image * mod_pitch : nullptr;
-    const T* sc = shift ? scale + (int64_t)image * mod_pitch : nullptr;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int vi = u * NOVA_WAVE + lane;
       if (vi < nvec) {
         VT o;
         if (shift) {
-          VT a, g; a.load(sh + vi * VN); g.load(sc + vi * VN);
 #pragma unroll
-          for (int e = 0; e < VN; ++e) o.set(e, fmaf((v[u].get(e) - mean) * rstd, 1.0f + g.get(e), a.get(e)));
+          for (int e = 0; e < VN; ++e) o.set(e, fmaf((v[u].get(e) - mean) * rstd, 1.0f + g[u].get(e), a[u].get(e)));
         } else {
 #pragma unroll
           for (int e = 0; e < VN; ++e) o.set(e, (v[u].get(e) - mean) * rstd);
