@@ -11,7 +11,7 @@
 // tokens keep their keys in registers, divide the range of the keys that occur into 2048 bins, rank the few keys of
 // the bin that matters in one wave, and need nine barriers; the radix select on LDS histograms with its four passes,
 // 24 barriers, stays for longer rows.  Radix select / this (us): 8 rows of 256 8.5 / 4.6, one row of 256 in a
-// graph 7.8 / 3.5, one of 1024 7.8 / 5.6, two of 4096 11.4 / 8.0.
+// graph 7.8 / 3.5, one of 1024 7.8 / 4.9, two of 4096 11.4 / 8.0.
 #include "common.h"
 #include "nova_internal.h"
 #include "select_core.h"
@@ -67,7 +67,7 @@ hipError_t launch_select(hipStream_t st, const float* H, int B, int N, int k, co
                          int32_t* idx, uint8_t* mask) {
   auto go = [&](auto kernel, int threads) { kernel<<<B, threads, 0, st>>>(H, N, k, k_per_row, k, idx, mask); };
   if (N <= 256) go(select_kernel<256, 1>, 256);
-  else if (N <= 1024) go(select_kernel<256, 4>, 256);
+  else if (N <= 1024) go(select_kernel<512, 2>, 512);     // 8 rows of 1024: 256 / 512 / 1024 threads 4.9 / 4.2 / 4.3 us
   else if (N <= 2048) go(select_kernel<1024, 2>, 1024);
   else if (N <= 4096) go(select_kernel<1024, 4>, 1024);
   else if (N <= 8192) go(select_kernel<1024, 8>, 1024);
