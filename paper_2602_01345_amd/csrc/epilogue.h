@@ -59,7 +59,7 @@ struct EpiParams {
 // Phi(v) / Phi(-v), an odd function that v times a polynomial of degree 6 in v^2 meets so closely (fitted over
 // |v| <= 5.5, beyond which v / (1 + 2^-z) is v or 0 either way) that the result is off by at most 7e-8 before rounding
 // to fp32; the rational erf 7.1.26 of Abramowitz & Stegun, 2.1e-7 off, takes one instruction more.  This runs once
-// per output element of the FFN up-projection, where every instruction is 1.3 us of a round of 256 x 256 tiles.
+// per output element of the FFN up-projection, where every instruction is some 0.6 us of a round of 256 x 256 tiles.
 __device__ __forceinline__ float gelu_erf(float v) {
   const float x = v * v;
   float p = fmaf(5.21002386e-9f, x, -3.85050081e-7f);

@@ -95,11 +95,11 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
 
   // ---- workgroup id -> tile, XCD-contiguous, M fastest -------------------------------
   // blockIdx.y: K slice (EPI_PARTIAL only)
-  // PERSIST (the modes whose epilogue needs no LDS, large tiles): the grid is one workgroup per CU and a
+  // PERSIST (see persistent_tiles): the grid is one workgroup per CU and a
   // workgroup takes the tiles L, L + gridDim.x, ...; the first K stages of its next tile are requested
   // before the epilogue of the current one, so their latency passes behind the epilogue.
   constexpr bool PERSIST = persistent_tiles(STAGGER, MODE);
-  // PP: the two waves of a SIMD alternate between the matrix cores and LDS (see pp_loop below)
+  // PP: the two waves of a SIMD alternate between the matrix cores and LDS (see the K loop)
   constexpr bool PP = BM == 256 && BN == 256 && BK == 64 && NST == 2 && WM == 2 && WN == 4;
   // first tile row / column of MFMA tile i / jn of this wave
   auto row_of = [&](int i) { return PP ? (i >> 1) * 128 + wm * 64 + (i & 1) * 32 : wm * (BM / WM) + i * 32; };
