@@ -55,22 +55,25 @@ struct EpiParams {
   __device__ __forceinline__ int image(int row) const { int slot; return image(row, slot); }
 };
 
-// Exact-form GELU v Phi(v), Phi the normal distribution function, as v / (1 + 2^-z(v)): z is log2 of the odds
-// Phi(v) / Phi(-v), an odd function that v times a polynomial of degree 6 in v^2 meets so closely (fitted over
-// |v| <= 5.5, beyond which v / (1 + 2^-z) is v or 0 either way) that the result is off by at most 7e-8 before rounding
-// to fp32; the rational erf 7.1.26 of Abramowitz & Stegun, 2.1e-7 off, takes one instruction more.  This runs once
-// per output element of the FFN up-projection, where every instruction is some 0.6 us of a round of 256 x 256 tiles.
+// Exact-form GELU v Phi(v) = max(v, 0) - |v| h, h = Phi(-|v|) = E(t) e^(-v^2 / 2) with t = 1 / (1 + 0.4 |v|) and a
+// polynomial E of degree 6 without a constant term (the form of Abramowitz & Stegun 7.1.26, fitted here to h itself).
+// The factor e^(-v^2 / 2) keeps the left tail right on its own scale, down to where fp32 ends: off by at most 1.3e-4 of
+// the value for v in (-6, 0), 5e-4 to -8, 2.2e-3 to -13; nowhere off by more than 2.1e-8 before rounding to fp32.  (A
+// form v s(v) with s fitted in absolute terms takes two instructions less and loses the tail: 4 % at -5, all of it at -6.)
+// This runs once per output element of the FFN up-projection, where every instruction is some 0.6 us of a round of
+// 256 x 256 tiles.
 __device__ __forceinline__ float gelu_erf(float v) {
-  const float x = v * v;
-  float p = fmaf(5.21002386e-9f, x, -3.85050081e-7f);
-  p = fmaf(p, x, 1.14525110e-5f);
-  p = fmaf(p, x, -1.59389991e-4f);
-  p = fmaf(p, x, -9.55910802e-5f);
-  p = fmaf(p, x, 1.04838579e-1f);
-  p = fmaf(p, x, 2.30220720f);
-  const float s = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-v * p));
-  // an overflowed accumulator (v = -inf, s = 0) gives 0 and not NaN; a NaN comes through in s
-  return fmaxf(v, -3.0e38f) * s;
+  const float t = __builtin_amdgcn_rcpf(fmaf(0.4f, fabsf(v), 1.0f));
+  float p = fmaf(5.58479467e-2f, t, -2.52587740e-1f);
+  p = fmaf(p, t, 3.36451671e-1f);
+  p = fmaf(p, t, 1.56750284e-2f);
+  p = fmaf(p, t, 1.87767675e-1f);
+  p = fmaf(p, t, 1.56845430e-1f);
+  p *= t;
+  const float w = v * 0.84932180028801904f;                 // sqrt(log2(e) / 2): e^(-v^2/2) = 2^(-w^2)
+  const float h = p * __builtin_amdgcn_exp2f(-w * w);
+  // an overflowed accumulator (v = +-inf, h = 0) gives +inf / 0 and not NaN; a NaN comes through in h
+  return fmaf(-fminf(fabsf(v), 3.0e38f), h, fmaxf(v, 0.0f));
 }
 
 // tanh-form GELU 0.5 v (1 + tanh(z)), z = sqrt(2/pi) (v + 0.044715 v^3), written as v / (1 + e^(-2z)).
