@@ -17,8 +17,11 @@
 //  * The smaller tiles: an NST-stage LDS ring (3 to 6 stages, per tile configuration): the loads of tiles
 //    t+1 .. t+NST-1 are in flight while tile t feeds the MFMAs; one bare barrier per K step with explicit
 //    vmcnt / lgkmcnt waits.
-//  * What surrounds the K loop is vector instructions at two waves per SIMD, some 4 ns each: bias and residual are
-//    what the accumulators start from, no epilogue goes through LDS, and no division is left in front of the first load.
+//  * What surrounds the K loop is vector instructions at two waves per SIMD, some 4 ns each: the accumulators start from
+//    the bias, no epilogue goes through LDS, and no division is left in front of the first load.
+//    (That is K / 16 roundings at the bias's magnitude, 2^-28 K |bias| at most: nothing next to the rounding to bf16.)
+//  * The projection p is summed apart from the residual r and meets it once, as p + r or fma(gate, p, r), as in the few-rows
+//    kernels and the second pass of a K-sliced launch: a zero gate leaves r, and a large r costs p no bits.
 //  * Workgroup ids are remapped so that each XCD (ids are dealt round-robin to the 8 XCDs) works
 //    on a contiguous run of tiles, ordered in bands of 8 tile rows, so that the tiles in flight on
 //    one XCD form a compact rectangle and share A rows and W columns in that XCD's L2.
@@ -49,8 +52,8 @@ __device__ __forceinline__ void fill_lds(bf16_t* base, lptr_t dst, uint32_t lane
 // rows reading the same chunk index hit 16 different 16-byte bank groups.
 __device__ __forceinline__ int swz(int r, int c) { return r * 128 + ((c ^ ((r >> 1) & 7)) << 4); }
 
-// Whether a workgroup walks several tiles (one workgroup per CU): the modes whose accumulators start from nothing but
-// the bias (a residual would have to wait for the previous tile's accumulators).
+// Whether a workgroup walks several tiles (one workgroup per CU): the modes without a residual (the next tile's would
+// have to wait for the registers that this tile's is held in).
 constexpr bool persistent_tiles(bool stagger, int mode) {
   return !stagger && (mode == EPI_QKV || mode == EPI_GELU || mode == EPI_GELU_TANH || mode == EPI_PLAIN);
 }
@@ -216,8 +219,9 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
     }
   };
 
-  // ---- what the accumulators start from: bias and residual row.  Requested ahead of the tile's second K stage, so
-  // that what waits for them does not wait for more than the first stage.
+  // ---- bias (what the accumulators start from) and residual row, requested ahead of the tile's second K stage, so that
+  // what waits for them does not wait for more than the first stage.  The residual waits in registers for the epilogue;
+  // PP has none to spare and requests it there, all but the kept index that its address takes.
   const int half = lane >> 5, r32 = lane & 31;
   constexpr bool HAS_RES = MODE == EPI_ATTN_OUT || MODE == EPI_RESIDUAL;
   constexpr bool HAS_BIAS = MODE != EPI_PARTIAL && MODE != EPI_ENTROPY;
@@ -240,16 +244,22 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
     }
   };
   // residual row of this lane in MFMA tile row i (rows past the edge: the last one)
+  int kept[MODE == EPI_ATTN_OUT ? TM : 1];
+  if constexpr (MODE == EPI_ATTN_OUT) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i) kept[i] = ep.idx[min(m0 + row_of(i) + r32, M - 1)];
+  }
   auto res_row = [&](int i) -> const bf16_t* {
     const int row = min(m0 + row_of(i) + r32, M - 1);
     int64_t roff = (int64_t)row * ep.ldo;
-    if (MODE == EPI_ATTN_OUT)
-      roff = ((int64_t)ep.image(row) * ep.Ntok + min(max(ep.idx[row], 0), ep.Ntok - 1)) * ep.C;
+    if constexpr (MODE == EPI_ATTN_OUT)
+      roff = ((int64_t)ep.image(row) * ep.Ntok + min(max(kept[i], 0), ep.Ntok - 1)) * ep.C;
     return ep.res + roff + n0 + 8 * half;
   };
-  auto load_res = [&](u32x4* dst) {          // eight features of this lane's row: 16 gp + 8 half .. of a 32-column block
+  auto load_res = [&](u32x4* dst, int lo, int hi) {          // eight features of this lane's row: 16 gp + 8 half .. of a 32-column block
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
+      if (i < lo || i >= hi) continue;
       const bf16_t* rp = res_row(i);
 #pragma unroll
       for (int jn = 0; jn < TN; ++jn) {
@@ -262,7 +272,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
   u32x4 rs[HAS_RES ? TM * TN * 2 : 1];
   load_bias();
   prologue_first();
-  if constexpr (HAS_RES) load_res(rs);
+  if constexpr (HAS_RES && !PP) load_res(rs, 0, TM);
   prologue_rest();
 
   const int arow0 = row_of(0) + r32;   // tile row of this lane's A operand in MFMA tile 0
@@ -308,35 +318,14 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
       return 0.0f;
     }
   };
-  if constexpr (HAS_RES) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+  for (int jn = 0; jn < TN; ++jn)
 #pragma unroll
-      for (int jn = 0; jn < TN; ++jn)
+    for (int r = 0; r < 16; ++r) {
+      const float b = bias_of(jn, r);
 #pragma unroll
-        for (int gp = 0; gp < 2; ++gp) {
-          const u32x4 v = rs[(i * TN + jn) * 2 + gp];
-#pragma unroll
-          for (int w2 = 0; w2 < 2; ++w2) {   // eight consecutive features -> the lane's groups 2 gp and 2 gp + 1
-            const auto sw = __builtin_amdgcn_permlane32_swap(v[w2], v[2 + w2], false, false);
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-              const int r = (2 * gp + g) * 4 + 2 * w2;
-              acc[i][jn][r] = __uint_as_float(sw[g] << 16) + bias_of(jn, r);
-              acc[i][jn][r + 1] = __uint_as_float(sw[g] & 0xFFFF0000u) + bias_of(jn, r + 1);
-            }
-          }
-        }
-  } else {
-#pragma unroll
-    for (int jn = 0; jn < TN; ++jn)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float b = bias_of(jn, r);
-#pragma unroll
-        for (int i = 0; i < TM; ++i) acc[i][jn][r] = b;
-      }
-  }
+      for (int i = 0; i < TM; ++i) acc[i][jn][r] = b;
+    }
   if constexpr (PP) {
     // ---- 256 x 256 tile, K steps of 64, two LDS buffers, each filled and freed in halves of its rows and columns.
     // A wave computes a 64 x 32 quadrant per phase (rows half x columns half), four phases per K step:
@@ -521,8 +510,8 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
     // and, per register group g4, four consecutive features (8 g4 + 4 half ..); swapping the upper lanes'
     // group g4 with the lower lanes' group g4 + 1 (v_permlane32_swap) leaves every lane with eight
     // consecutive features of its token: one 16-byte store, and the two halves of the wave cover 32
-    // contiguous bytes of each row.  Bias and residual are in the accumulators already.  The value columns of the
-    // QKV projection (key index minor) need no swap: the lanes of a half wave hold consecutive tokens.
+    // contiguous bytes of each row.  The value columns of the QKV projection (key index minor) need no swap: the
+    // lanes of a half wave hold consecutive tokens.
     bool more_tiles = false;
     if constexpr (PERSIST) {
       // Every wave has passed the last barrier of the K loop, nobody reads the ring any more: request the
@@ -536,33 +525,59 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
         prologue_rest();
       }
     }
-    if constexpr (HAS_RES) {
-      if constexpr (GATED) {
-        // gated: r + g p as v + (g - 1)(v - r) with v = r + p, which is the ungated result where the gate is one
+    // p -> p + r or fma(gate, p, r) for MFMA tile row i.  The gates, and PP's residual with them, come one tile row
+    // ahead (registers for more there are none); PP's residual alone comes whole.
+    u32x4 gate[GATED ? TM * TN * 2 : 1];
+    auto load_gate = [&](int i) {
+      const bf16_t* gr = ep.gate + (int64_t)ep.image(min(em0 + row_of(i) + r32, M - 1)) * ep.gate_pitch + en0 + 8 * half;
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const bf16_t* rp = res_row(i) - 4 * half;
-          const bf16_t* gr = ep.gate + (int64_t)ep.image(min(em0 + row_of(i) + r32, M - 1)) * ep.gate_pitch + en0 + 4 * half;
+      for (int jn = 0; jn < TN; ++jn) {
+        const int c = en0 + col_of(jn) < Nout ? col_of(jn) : 0;       // columns past the edge: not used
 #pragma unroll
-          for (int jn = 0; jn < TN; ++jn) {
-            if (en0 + col_of(jn) >= Nout) continue;
+        for (int gp = 0; gp < 2; ++gp) gate[(i * TN + jn) * 2 + gp] = *reinterpret_cast<const u32x4*>(gr + c + 16 * gp);
+      }
+    };
+    // eight consecutive features of a row -> the lane's groups 2 gp and 2 gp + 1
+    auto spread = [&](const u32x4& v, float (&f)[8]) {
 #pragma unroll
-            for (int g4 = 0; g4 < 4; ++g4) {
-              const bf16x4 r = *reinterpret_cast<const bf16x4*>(rp + col_of(jn) + 8 * g4);
-              const bf16x4 g = *reinterpret_cast<const bf16x4*>(gr + col_of(jn) + 8 * g4);
+      for (int w2 = 0; w2 < 2; ++w2) {
+        const auto sw = __builtin_amdgcn_permlane32_swap(v[w2], v[2 + w2], false, false);
 #pragma unroll
-              for (int e = 0; e < 4; ++e) {
-                const float v = acc[i][jn][g4 * 4 + e];
-                acc[i][jn][g4 * 4 + e] = fmaf((float)g[e] - 1.0f, v - (float)r[e], v);
-              }
-            }
-          }
+        for (int g = 0; g < 2; ++g) {
+          f[g * 4 + 2 * w2] = __uint_as_float(sw[g] << 16);
+          f[g * 4 + 2 * w2 + 1] = __uint_as_float(sw[g] & 0xFFFF0000u);
         }
       }
+    };
+    auto add_residual = [&](int i) {
+      if constexpr (GATED) {
+        if (i + 1 < TM) {
+          if constexpr (PP) load_res(rs, i + 1, i + 2);
+          load_gate(i + 1);
+        }
+      }
+#pragma unroll
+      for (int jn = 0; jn < TN; ++jn)
+#pragma unroll
+        for (int gp = 0; gp < 2; ++gp) {
+          float r[8], g[8];
+          spread(rs[(i * TN + jn) * 2 + gp], r);
+          if constexpr (GATED) spread(gate[(i * TN + jn) * 2 + gp], g);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float v = acc[i][jn][gp * 8 + e];
+            acc[i][jn][gp * 8 + e] = GATED ? fmaf(g[e], v, r[e]) : v + r[e];
+          }
+        }
+    };
+    if constexpr (HAS_RES) {
+      if constexpr (PP) load_res(rs, 0, GATED ? 1 : TM);
+      if constexpr (GATED) load_gate(0);
     }
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       const int row = em0 + row_of(i) + r32;
+      if constexpr (HAS_RES) add_residual(i);
       if (row < M) {
         bf16_t* op = ep.out + (int64_t)row * ep.ldo + (MODE == EPI_QKV ? 0 : en0) + 8 * half;
         int image = 0, pos = 0;
