@@ -159,11 +159,11 @@ __global__ __launch_bounds__(NW * 64) void attention_few_kernel(
     for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, s[kb][r]);
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, NOVA_WAVE));   // finite: every tile holds a valid key
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, NOVA_WAVE));   // -inf where every score of the tile is
     // the reference moves when some query's maximum lies above it (always on the wave's first tile)
     if (__any(tmax > m_run)) {
       const float m_new = fmaxf(m_run, tmax);
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
       l_run *= alpha;
 #pragma unroll
       for (int d = 0; d < DB; ++d)
@@ -171,12 +171,14 @@ __global__ __launch_bounds__(NW * 64) void attention_few_kernel(
         for (int r = 0; r < 16; ++r) o[d][r] *= alpha;
       m_run = m_new;
     }
+    // keys whose scores are all -inf weigh nothing: another wave may hold the finite ones
+    const float m_ref = m_run == -INFINITY ? 0.f : m_run;
     bf16x8 p[KG];
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const float e = __builtin_amdgcn_exp2f(s[kb][r] - m_run);
+        const float e = __builtin_amdgcn_exp2f(s[kb][r] - m_ref);
         l_run += e;
         p[kb * 2 + (r >> 3)][r & 7] = (bf16_t)e;
       }
@@ -234,7 +236,7 @@ __global__ __launch_bounds__(NW * 64) void attention_few_kernel(
     f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const float f = __builtin_amdgcn_exp2f(part_m[w][qr] - m);     // a wave without a tile: reference -inf, weight 0
+      const float f = __builtin_amdgcn_exp2f(part_m[w][qr] - m);     // a wave without a finite score: reference -inf, weight 0
       l = fmaf(f, part_l[w][qr], l);
       const char* pw = lds + w * TILE + (2 * d8 * BQ + qr) * 16;
       a0 += f * *reinterpret_cast<const f32x4*>(pw);

@@ -1,7 +1,7 @@
 """GPU parity of the few-queries attention kernel (csrc/attention_few_bf16.hip) against the oracle where it can go wrong: fewer
 key tiles than waves, keys that end on, one before and one behind a tile, queries that end on and next to a block of 32, four
 and eight waves, both head sizes, scores spread over tens of nats (the softmax reference moves in every wave), images with
-counts of their own (one with none).  Tolerance: bf16 tensors max|d| / max|ref| <= 2e-2, as everywhere."""
+counts of their own (one with none), waves none of whose keys has a finite score.  Tolerance: bf16 tensors max|d| / max|ref| <= 2e-2, as everywhere."""
 import pytest
 import torch
 
@@ -47,3 +47,17 @@ def test_images_with_their_own_counts(hx, C, heads):
     print(f"few queries, per-image counts C={C}", flush=True)
     hb = hx.make_host_block(_wl(3, 300, C, heads), 0)
     hx.check_block_rows(hb, [100, 0, 33], [300, 17, 64], hx.BF16_TOL)
+
+
+@pytest.mark.parametrize("C,heads", [(128, 2), (256, 2)])
+@pytest.mark.parametrize("P", [200, 700])                                    # four and eight waves
+def test_keys_whose_scores_overflow_weigh_nothing(hx, C, heads, P):
+    """Behind the first 64 prior keys every prior key scores -inf (about -3e39 before fp32 ends): whole tiles, and all tiles
+    of some waves, without a finite score."""
+    print(f"few queries, scores of -inf C={C} P={P}", flush=True)
+    hb = hx.make_host_block(_wl(2, P, C, heads), 0, k=32)
+    dh = C // heads
+    hb.weights["w_qkv"][:C:dh] = 0.0                                         # the first query channel of every head is 64
+    hb.weights["b_qkv"][:C:dh] = 64.0
+    hb.k_prior[:, 64:, ::dh] = -3.0e38
+    hx.check_block(hb, hx.BF16_TOL)
