@@ -535,7 +535,7 @@ hipError_t launch_cfg(const nova_ctx* ctx, hipStream_t st, const bf16_t* q, cons
   // The partial workspace holds part_floats / (BQ * DH) partial results.
   constexpr float kSolo = 1.8f;
   int n_whole = items, nsplit = 1;
-  if (part_o && part_ml) {
+  if (part_o && part_ml && !(ctx && ctx->attn_split == 1)) {
     const int cus = slots / OCC;
     const int rest = items % slots;                       // items of the last round (0: nothing to cut)
     auto usable = [&](int s, int cut) {                   // every run owns at least one tile; partials fit
@@ -586,7 +586,7 @@ hipError_t launch_attention_bf16(const nova_ctx* ctx, hipStream_t st, const void
   const bf16_t* vc = static_cast<const bf16_t*>(vcv);
   bf16_t* out = static_cast<bf16_t*>(outv);
   const int dh = C / heads;
-  if (!ctx || (ctx->attn_cfg < 1 && ctx->attn_split < 2)) {     // neither shape nor split is forced
+  if (!ctx || (ctx->attn_cfg < 1 && ctx->attn_split < 1)) {     // neither shape nor runs are forced
     const int waves = attention_few_waves(ctx ? ctx->num_cus : 256, dh, B, k, heads, kv_total);
     if (waves) return launch_attention_few_bf16(st, waves, qv, kcv, vcv, B, k, C, heads, cap, kv_total, outv, k_rows,
                                                 kv_rows, P, self_keys);

@@ -50,6 +50,25 @@ def test_images_with_their_own_counts(hx, C, heads):
 
 
 @pytest.mark.parametrize("C,heads", [(128, 2), (256, 2)])
+def test_one_forced_run_is_the_many_query_kernel_uncut(hx, C, heads, monkeypatch):
+    """NOVA_ATTN_SPLIT=1 reaches csrc/attention_bf16.hip without key runs, whatever the size: the bits of its default
+    workgroup shape forced (too few key tiles here for the launcher to cut any)."""
+    from paper_2602_01345_amd import Nova
+    print(f"forced uncut attention C={C}", flush=True)
+    hb = hx.make_host_block(_wl(2, 700, C, heads), 0, k=70)
+    outs = []
+    for knob in ("NOVA_ATTN_SPLIT", "NOVA_ATTN_CFG"):
+        with monkeypatch.context() as m:
+            m.setenv(knob, "1")
+            m.setattr(hx, "_NOVA", Nova(0))            # the knobs are read when a context is created
+            runner, st, x = hx.to_gpu(hb)
+            runner.run_block(st, x)
+            torch.cuda.synchronize()
+            outs.append(st.y_kept.clone())
+    assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("C,heads", [(128, 2), (256, 2)])
 @pytest.mark.parametrize("P", [200, 700])                                    # four and eight waves
 def test_keys_whose_scores_overflow_weigh_nothing(hx, C, heads, P):
     """Behind the first 64 prior keys every prior key scores -inf (about -3e39 before fp32 ends): whole tiles, and all tiles
