@@ -27,6 +27,7 @@
 //    one XCD form a compact rectangle and share A rows and W columns in that XCD's L2.
 #include "common.h"
 #include "epilogue.h"
+#include "gemm_plan.h"
 #include "nova_internal.h"
 
 namespace {
@@ -705,134 +706,6 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restric
     for (int e = 0; e < 8; ++e) o[e] = (bf16_t)(acc[e] + (float)bias[e] + (float)r[e]);
   }
   *reinterpret_cast<bf16x8*>(ep.out + (int64_t)row * ep.ldo + col) = o;
-}
-
-// Tile configurations (NOVA_GEMM_CFG forces one, for tuning; numbers without a kernel mean 2):
-//   1: 256x256x64, 8 waves of 128x64 that alternate between the matrix cores and LDS
-//   2: 256x128x64, 8 waves of 64x64, 3 stages
-//   6: 192x128x64, 8 waves of 96x32, 3 stages: one round where 256x128 leaves too many CUs idle and 128x128 needs a
-//      second round (1640 rows, K = 1024, 3072 features 17.3 -> 15.7 us; 1100 rows, 4096 features 19.2 -> 16.2)
-//   3: 64x32x64, 2 waves of 32x32, 6 stages, staggered K walk          (head entropy only, M <= 64)
-//   4: 128x32x64, 4 waves of 32x32, 4 stages, staggered K walk         (head entropy only, M <= 256 or 512)
-//   5: 128x128x64, 8 waves of 64x32, 3 stages, one workgroup per CU (two waves per SIMD hide the LDS waits that
-//      four waves of 64x64 expose: 3-10 % faster at every shape measured)
-//   7: the few-rows kernels of gemm_rows_bf16.hip (chosen by their own plan, not by force)
-// Without a forced choice the launcher prices 1, 2, 5 and 6 with a model fitted to measurements on MI355X (300 ... 8192
-// rows, widths C of 1024 ... 2304, outputs of C, 3C and 4C features, K = C and 4C): a launch takes rounds of one tile
-// per CU; a round costs a fixed time (first loads, epilogue) and a time per element of K that grows with the share of
-// the CUs that are busy (they share L2, memory and power).  The fit is within 5 % (rms) of the measurements, and what
-// it chooses takes 0.03 % longer than the best of the four on average, 4 % at worst (launches without K slices).
-constexpr int kNumCfgs = 7;
-constexpr int kRowsCfg = 7;
-
-struct Candidate {
-  int cfg, bm, bn;
-  double launch, round, gelu;   // us per launch, per round, per round with a GELU
-  double k0, k1, k3;            // us per element of K in a round that fills a share f of the CUs: k0 + k1 f + k3 f^3
-};
-
-static const Candidate kCands[] = {{1, 256, 256, 4.3, 5.0, 2.0, 0.01580, -0.00114, 0.01000},
-                                   {2, 256, 128, 3.4, 2.8, 0.6, 0.01072, 0.00005, 0.00404},
-                                   {6, 192, 128, 2.4, 3.2, 0.6, 0.00784, 0.00200, 0.00151},
-                                   {5, 128, 128, 2.7, 1.9, 0.0, 0.00603, 0.00112, 0.00152}};
-
-// K slices of a launch of `tiles` tiles (the FFN down projection once few tokens are kept: a long K and a narrow
-// output fill less than half of the CUs): 2 or 4 workgroups per tile, fp32 partial sums and a second pass.
-int k_slices(int cus, int mode, int tiles, int64_t rows, int Nout, int K, int64_t part_floats, int forced) {
-  if (mode != EPI_RESIDUAL || K < 4096 || forced == 0) return 1;
-  int ks = 1;
-  if (forced > 0) ks = forced;
-  else while (ks < 4 && tiles * ks * 2 <= cus) ks *= 2;
-  const bool fits = (ks == 2 || ks == 4) && K % (ks * 64) == 0 && K / (ks * 64) >= 16 && ks * rows * Nout <= part_floats;
-  return fits ? ks : 1;
-}
-
-// Modelled time (seconds) of one launch over M rows with candidate c.
-double model_time(const Candidate& c, int slots, int mode, int M, int Nout, int K, int64_t part_floats) {
-  const int tiles = ((M + c.bm - 1) / c.bm) * ((Nout + c.bn - 1) / c.bn);
-  const int ks = k_slices(slots, mode, tiles, M, Nout, K, part_floats, -1);
-  const int full = tiles * ks / slots, rest = tiles * ks % slots;
-  const double f = (double)rest / slots, fixed = c.round + (mode == EPI_GELU || mode == EPI_GELU_TANH ? c.gelu : 0.0);
-  double t = c.launch + full * (fixed + K / ks * (c.k0 + c.k1 + c.k3));
-  if (rest) t += fixed + K / ks * (c.k0 + c.k1 * f + c.k3 * f * f * f);
-  if (ks > 1) t += 2.5 + (ks * 4.0 + 4.0) * M * Nout / 5e6;
-  return t * 1e-6;
-}
-
-// Whether M rows of a prediction head go to the narrow-tile kernels (more workgroups for the weight stream).
-bool narrow_tiles(int M, int Nout, int K) { return M <= 256 || (M <= 512 && Nout < 4096 && K < 4096); }
-
-// Modelled time of the few-rows kernels: what the busiest CU loads at 75 GB/s, half of the weights at the rate of a large
-// copy, 2.5 us to start and end, 3 us for the slice sums (measured 4.2 ... 22 us over 64 ... 1024 rows and 2 ... 38 MB
-// of weights; within 2 us but for a long K, where it is up to 8 us too much).
-double rows_time(const RowsPlan& p, int cus, int rows, int Nout, int K) {
-  const int wgs = (rows + 8 * p.rg - 1) / (8 * p.rg) * (Nout / (8 * p.ng)) * p.slices;
-  const double bytes = (double)((wgs + cus - 1) / cus) * 16.0 * (p.rg + p.ng) * K / p.slices;
-  return 2.5e-6 + bytes / 75e9 + (double)Nout * K / 5e12 + (p.slices > 1 ? 3e-6 : 0.0);
-}
-
-int pick_cfg(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64_t part_floats, double* t_out = nullptr) {
-  if (ctx && ctx->gemm_cfg >= 0 && ctx->gemm_cfg < kNumCfgs) return ctx->gemm_cfg;
-  if (mode == EPI_ENTROPY) {
-    if (M <= 64) return 3;
-    if (narrow_tiles(M, Nout, K)) return 4;
-  }
-  const int slots = ctx ? ctx->num_cus : 256;
-  const RowsPlan rows = gemm_rows_plan(slots, mode, M, Nout, K, part_floats);      // rg = 0 for a prediction head
-  if (rows.rg) {
-    if (t_out) *t_out = rows_time(rows, slots, M, Nout, K);
-    return kRowsCfg;
-  }
-  int best = 2;
-  double best_t = 1e30;
-  // a prediction head's partials (16 bytes per row and column tile) that fit the static scratch with 256-column tiles
-  // only: those, in every entry point, so that the allocation-free one gives the same bits
-  const int64_t room = (int64_t)head_entropy_static_capacity() / 16;
-  const bool wide = mode == EPI_ENTROPY && (int64_t)M * ((Nout + 127) / 128) > room && (int64_t)M * ((Nout + 255) / 256) <= room;
-  for (const Candidate& c : kCands) {
-    if (wide && c.bn < 256) continue;
-    if (c.cfg == 1 && K > 1 << 21) continue;             // its tiles are addressed with 32-bit offsets
-    const double t = model_time(c, slots, mode, M, Nout, K, part_floats);
-    if (t < best_t) { best_t = t; best = c.cfg; }
-  }
-  if (t_out) *t_out = best_t;
-  return best;
-}
-
-// A launch plan: one configuration for all rows, or two launches -- typically (nearly) whole rounds of large
-// tiles over the first rows and the best single configuration for the rows left over, so that only a small
-// remainder pays for a ragged last round.  Returns the number of parts; part i covers rows [m_base[i], m_end[i]) with cfg[i].
-struct Plan {
-  int n;
-  int m_base[2], m_end[2], cfg[2];
-};
-Plan plan_rows(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64_t part_floats) {
-  Plan p;
-  double t_single = 1e30;
-  p.n = 1; p.m_base[0] = 0; p.m_end[0] = M; p.cfg[0] = pick_cfg(ctx, mode, M, Nout, K, part_floats, &t_single);
-  const bool forced = ctx && ctx->gemm_cfg >= 0 && ctx->gemm_cfg < kNumCfgs;
-  if (forced || mode == EPI_ENTROPY || M <= 512 || (ctx && ctx->gemm_parts == 0)) return p;   // one launch
-  const int slots = ctx ? ctx->num_cus : 256;
-  double best = t_single * 0.97;                          // a second launch has to pay for itself
-  for (const Candidate& c : kCands) {
-    const int tiles_n = (Nout + c.bn - 1) / c.bn;
-    for (int rounds = 1;; ++rounds) {                     // rounds of the first part
-      const int64_t m1_all = (int64_t)rounds * slots / tiles_n * c.bm;
-      if (m1_all >= M) break;
-      const int m1 = (int)m1_all;
-      if (m1 == 0) continue;
-      double t_rest = 0.0;
-      const int cfg_rest = pick_cfg(ctx, mode, M - m1, Nout, K, part_floats, &t_rest);
-      const double t = model_time(c, slots, mode, m1, Nout, K, part_floats) + t_rest;
-      if (t < best) {
-        best = t;
-        p.n = 2;
-        p.m_base[0] = 0; p.m_end[0] = m1; p.cfg[0] = c.cfg;
-        p.m_base[1] = m1; p.m_end[1] = M; p.cfg[1] = cfg_rest;
-      }
-    }
-  }
-  return p;
 }
 
 template <int MODE>

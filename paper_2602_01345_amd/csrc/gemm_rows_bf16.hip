@@ -264,36 +264,6 @@ hipError_t by_plan(hipStream_t st, const RowsPlan& p, const bf16_t* A, const bf1
 
 }  // namespace
 
-// Tile and K slices for `rows` rows, or rg = 0 where the shared-ring kernels are faster.
-//  * The narrowest tile that needs no more workgroups than there are CUs: half of them leave CUs idle (64 rows,
-//    Nout = 3072, K = 1024: 96 workgroups 6.7 us, 192 6.1), twice as many fetch the rows twice as often (K = 2048,
-//    Nout = 6144: 192 workgroups 10.8 us, 384 15.0).  One tile shape has to do for up to 8 x 8 groups; beyond one
-//    workgroup per CU two of them still fit with one unit in flight each.
-//  * One workgroup per CU beats the 128- and 256-row tiles at any row count (1024 rows, Nout = 1024: K = 1024 8.4
-//    against 11.1 us, K = 4096 16.4 against 22.9; 640 rows 7.4 / 14.7 against 11.0 / 17.3).  Two per CU do up to 512 rows
-//    (512 rows, K = 1024, Nout = 3072: 10.2 against 10.5; 820 rows, Nout = 1920 = K: 17.8 against 17.2), but not with a
-//    long K (400 rows, K = 9216, Nout = 2304: 30 against 27).
-//  * A long K into few features (the FFN down projection) with 33 ... 128 rows: the tiles would fill a quarter of the
-//    CUs, so K is cut into four slices and a second small pass adds them (64 rows, K = 8192: 20 us uncut, 15.1 cut;
-//    with 16 rows 11.7 uncut, 12.9 cut; with 200 rows, K = 4096 10.6 uncut, 13.2 cut).
-RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K, int64_t part_floats) {
-  RowsPlan p = {};
-  if (mode == EPI_ENTROPY || Nout % 64 != 0) return p;
-  const int rg = rows <= 8 ? 1 : rows <= 16 ? 2 : rows <= 32 ? 4 : 8;
-  const int row_tiles = (rows + 8 * rg - 1) / (8 * rg);
-  p.slices = 1;
-  if (mode == EPI_RESIDUAL && K >= 4096 && rows > 32 && rows <= 128 && (int64_t)4 * rows * Nout <= part_floats) p.slices = 4;
-  const int ng_max = rg == 8 ? 8 : 4;
-  int ng = 1;
-  while (ng < ng_max && row_tiles * (Nout / (8 * ng)) * p.slices > num_cus) ng *= 2;
-  const int wgs = row_tiles * (Nout / (8 * ng)) * p.slices;
-  if (rows > 64 && wgs > (mode == EPI_RESIDUAL || rows > 512 ? num_cus : 2 * num_cus)) return p;
-  p.rg = rg;
-  p.ng = ng;
-  p.s = rg == 8 ? (ng == 8 && wgs > num_cus ? 1 : 2) : rg == 4 ? (ng == 4 ? 4 : 3) : rg == 2 ? (ng == 1 ? 2 : ng == 2 ? 4 : 3) : 4;
-  return p;
-}
-
 hipError_t launch_gemm_rows_bf16(hipStream_t st, const RowsPlan& p, int mode, const bf16_t* A, const bf16_t* W, int m_base,
                                  int M, int Nout, int K, const EpiParams<bf16_t>& ep) {
   switch (mode) {

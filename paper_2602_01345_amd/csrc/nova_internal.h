@@ -115,12 +115,11 @@ hipError_t launch_block_f32(nova_ctx* ctx, hipStream_t st, const nova_block_shap
 template <typename T> struct EpiParams;
 hipError_t launch_gemm_bf16(const nova_ctx* ctx, hipStream_t st, int mode, const void* A, const void* W, int M,
                             int Nout, int K, const EpiParams<__bf16>& ep);
-// gemm_rows_bf16.hip: the same for few rows [m_base, M).  The plan's rg is 0 where the shape is better served by
-// gemm_bf16.hip; slices > 1 (EPI_RESIDUAL only): launch with EPI_PARTIAL, then add the slices
+// gemm_rows_bf16.hip: the same for few rows [m_base, M), by a plan of gemm_plan.h.  The plan's rg is 0 where the shape is
+// better served by gemm_bf16.hip; slices > 1 (EPI_RESIDUAL only): launch with EPI_PARTIAL, then add the slices
 struct RowsPlan {
   int rg, ng, s, slices;   // groups of 8 rows / 8 features per tile, units in flight per wave, K slices
 };
-RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K, int64_t part_floats);
 hipError_t launch_gemm_rows_bf16(hipStream_t st, const RowsPlan& plan, int mode, const __bf16* A, const __bf16* W, int m_base,
                                  int M, int Nout, int K, const EpiParams<__bf16>& ep);
 int gemm_bf16_tile_cols(const nova_ctx* ctx, int M, int Nout, int K);
