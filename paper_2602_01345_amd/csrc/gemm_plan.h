@@ -65,6 +65,9 @@ static const Candidate kCands[] = {{1, 256, 256, 4.3, 5.0, 2.0, 0.01580, -0.0011
                                    {6, 192, 128, 2.4, 3.2, 0.6, 0.00784, 0.00200, 0.00151},
                                    {5, 128, 128, 2.7, 1.9, 0.0, 0.00603, 0.00112, 0.00152}};
 
+// Configuration 1 addresses its tiles with 32-bit offsets: 255 rows of 2 K bytes and the offset along K stay below 2^31.
+inline bool tile_fits(int cfg, int K) { return cfg != 1 || K <= 1 << 21; }
+
 // K slices of a launch of `tiles` tiles (the FFN down projection once few tokens are kept: a long K and a narrow
 // output fill less than half of the CUs): 2 or 4 workgroups per tile, fp32 partial sums and a second pass.
 inline int k_slices(int cus, int mode, int tiles, int64_t rows, int Nout, int K, int64_t part_floats, int forced) {
@@ -101,7 +104,7 @@ inline double rows_time(const RowsPlan& p, int cus, int rows, int Nout, int K) {
 }
 
 inline int pick_cfg(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64_t part_floats, double* t_out = nullptr) {
-  if (ctx && ctx->gemm_cfg >= 0 && ctx->gemm_cfg < kNumCfgs) return ctx->gemm_cfg;
+  if (ctx && ctx->gemm_cfg >= 0 && ctx->gemm_cfg < kNumCfgs) return tile_fits(ctx->gemm_cfg, K) ? ctx->gemm_cfg : 2;
   if (mode == EPI_ENTROPY) {
     if (M <= 64) return 3;
     if (narrow_tiles(M, Nout, K)) return 4;
@@ -120,7 +123,7 @@ inline int pick_cfg(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64
   const bool wide = mode == EPI_ENTROPY && (int64_t)M * ((Nout + 127) / 128) > room && (int64_t)M * ((Nout + 255) / 256) <= room;
   for (const Candidate& c : kCands) {
     if (wide && c.bn < 256) continue;
-    if (c.cfg == 1 && K > 1 << 21) continue;             // its tiles are addressed with 32-bit offsets
+    if (!tile_fits(c.cfg, K)) continue;
     const double t = model_time(c, slots, mode, M, Nout, K, part_floats);
     if (t < best_t) { best_t = t; best = c.cfg; }
   }
@@ -144,6 +147,7 @@ inline Plan plan_rows(const nova_ctx* ctx, int mode, int M, int Nout, int K, int
   const int slots = ctx ? ctx->num_cus : 256;
   double best = t_single * 0.97;                          // a second launch has to pay for itself
   for (const Candidate& c : kCands) {
+    if (!tile_fits(c.cfg, K)) continue;
     const int tiles_n = (Nout + c.bn - 1) / c.bn;
     for (int rounds = 1;; ++rounds) {                     // rounds of the first part
       const int64_t m1_all = (int64_t)rounds * slots / tiles_n * c.bm;

@@ -1,0 +1,34 @@
+// Prints what csrc/gemm_plan.h plans on 256 compute units (tests/test_gemm_plan.py): one line per request of
+// mode M Nout K part_floats gemm_cfg gemm_parts gemm_ksplit on standard input, for every part of the plan
+// rows:cfg:tiles:slices, the few-rows kernels as rows:7:workgroups:slices.
+#include <cstdio>
+
+#include "gemm_plan.h"
+
+size_t head_entropy_static_capacity() { return NOVA_HEAD_ENTROPY_STATIC_BYTES; }
+
+int main() {
+  long long part;
+  int mode, M, Nout, K, cfg, parts, ksplit;
+  while (scanf("%d %d %d %d %lld %d %d %d", &mode, &M, &Nout, &K, &part, &cfg, &parts, &ksplit) == 8) {
+    nova_ctx c{};
+    c.num_cus = 256;
+    c.gemm_cfg = cfg;
+    c.gemm_parts = parts;
+    const Plan p = plan_rows(&c, mode, M, Nout, K, part);
+    for (int i = 0; i < p.n; ++i) {
+      const int rows = p.m_end[i] - p.m_base[i];
+      if (p.cfg[i] == kRowsCfg) {
+        const RowsPlan r = gemm_rows_plan(256, mode, rows, Nout, K, part);
+        printf("%d:7:%d:%d ", rows, (rows + 8 * r.rg - 1) / (8 * r.rg) * (Nout / (8 * r.ng)), r.slices);
+        continue;
+      }
+      const Candidate* t = &kCands[1];
+      for (const Candidate& q : kCands)
+        if (q.cfg == p.cfg[i]) t = &q;
+      const int tiles = (rows + t->bm - 1) / t->bm * ((Nout + t->bn - 1) / t->bn);
+      printf("%d:%d:%d:%d ", rows, p.cfg[i], tiles, k_slices(256, mode, tiles, rows, Nout, K, part, ksplit));
+    }
+    printf("\n");
+  }
+}

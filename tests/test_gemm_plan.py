@@ -1,0 +1,40 @@
+"""The launch plans of csrc/gemm_plan.h on the CPU, compiled for the host alone (gemm_plan_probe.cpp)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2602_01345_amd", "csrc")
+QKV, ATTN_OUT, GELU, RESIDUAL = 0, 1, 2, 3             # EpiMode of csrc/epilogue.h
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plan") / "probe")
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    subprocess.run([hipcc, "--offload-arch=gfx950", "--offload-host-only", "-std=c++20", "-x", "hip", "-I" + CSRC,
+                    os.path.join(HERE, "gemm_plan_probe.cpp"), "-o", exe], check=True, capture_output=True)
+
+    def ask(mode, M, Nout, K, part_floats=10 ** 9, cfg=-1, parts=-1, ksplit=-1):
+        """[(rows, configuration, tiles or workgroups, K slices)] of the launches"""
+        r = subprocess.run([exe], input=f"{mode} {M} {Nout} {K} {part_floats} {cfg} {parts} {ksplit}\n", text=True,
+                           check=True, capture_output=True)
+        return [tuple(int(v) for v in p.split(":")) for p in r.stdout.split()]
+    return ask
+
+
+@pytest.mark.parametrize("K", [(1 << 21) + 64, 1 << 22, 1 << 23])
+@pytest.mark.parametrize("M,Nout", [(600, 16384), (2049, 8192), (4097, 16384), (9000, 8192)])
+def test_the_tile_with_32_bit_offsets_stops_where_they_end(plan, M, Nout, K):
+    """255 rows of 2 K bytes and the offset along K of the 256 x 256 tile have to stay below 2^31 bytes: neither one launch,
+    nor the parts of two, nor a forced choice may take it beyond K = 2^21."""
+    for cfg in (-1, 1):
+        parts = plan(RESIDUAL, M, Nout, K, cfg=cfg)
+        assert all(c != 1 for _, c, _, _ in parts), parts
+        assert sum(p[0] for p in parts) == M
+
+
+def test_the_tile_with_32_bit_offsets_up_to_there(plan):
+    assert plan(RESIDUAL, 2049, 8192, 1 << 21, cfg=1)[0][1] == 1
