@@ -64,3 +64,13 @@ def test_grid_lists_match_the_workloads():
             t = grids.index(s.grid)
             assert s.kv_len == sum(g * g for g in grids[:t]), name
             assert s.prev_grid == grids[t - 1], name
+
+
+def test_stream_handle_without_torchs_private_function(monkeypatch):
+    import types
+
+    import torch
+    from paper_2602_01345_amd import binding
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    assert binding._stream() == 77
