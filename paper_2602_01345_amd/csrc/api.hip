@@ -26,7 +26,8 @@ int shape_error(const nova_block_shape* s) {
     if (s->C % 64 != 0 || (dh != 64 && dh != 128) || s->kv_capacity % 64 != 0) return NOVA_ERR_UNSUPPORTED;
   } else {
     if (s->C % 4 != 0 || dh > 256) return NOVA_ERR_UNSUPPORTED;
-    // the fp32 attention keeps one score per cached key (plus the query) in 64 KiB of LDS
+    // the fp32 attention keeps one score per cached key in LDS, and behind them dh floats or the eight that its waves
+    // exchange: 64 KiB, and up to 28 bytes more with heads of fewer than eight channels (a CU has 160 KiB)
     if ((int64_t)s->kv_len + s->k + dh > 16384) return NOVA_ERR_UNSUPPORTED;
   }
   if ((int64_t)s->B * s->k * (int64_t)s->C * s->ffn_mult > (int64_t)1 << 40) return NOVA_ERR_UNSUPPORTED;

@@ -672,10 +672,8 @@ hipError_t launch_cfg(hipStream_t st, const bf16_t* A, const bf16_t* W, int m_ba
   return hipGetLastError();
 }
 
-// Second pass of a K-sliced launch: out = residual-epilogue(sum of the slices + bias) for rows [m_base, M);
-// MODE is EPI_RESIDUAL (residual row = output row) or EPI_ATTN_OUT (residual row gathered through the kept indices).
+// Second pass of a K-sliced launch (EPI_RESIDUAL): out = residual + gate (sum of the slices + bias) for rows [m_base, M).
 // One thread per 8 output features.
-template <int MODE>
 __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restrict__ part, int kslices, int m_base,
                                                           int M, int Nout, EpiParams<bf16_t> ep) {
   const int cpr = Nout / 8;
@@ -693,9 +691,7 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restric
 #pragma unroll
   for (int e = 0; e < 8; ++e) bias[e] = (bf16_t)0.f;
   if (ep.bias) bias = *reinterpret_cast<const bf16x8*>(ep.bias + col);
-  int64_t roff = (int64_t)row * ep.ldo;
-  if (MODE == EPI_ATTN_OUT) roff = ((int64_t)ep.image(row) * ep.Ntok + min(max(ep.idx[row], 0), ep.Ntok - 1)) * ep.C;
-  const bf16x8 r = *reinterpret_cast<const bf16x8*>(ep.res + roff + col);
+  const bf16x8 r = *reinterpret_cast<const bf16x8*>(ep.res + (int64_t)row * ep.ldo + col);
   bf16x8 o;
   if (ep.gate) {
     const bf16x8 gt = *reinterpret_cast<const bf16x8*>(ep.gate + (int64_t)ep.image(row) * ep.gate_pitch + col);
@@ -717,7 +713,7 @@ hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W
     if (e != hipSuccess || plan.slices == 1) return e;
     if constexpr (MODE == EPI_RESIDUAL) {
       const int64_t nvec = (int64_t)(M - m_base) * (Nout / 8);
-      gemm_reduce_kernel<MODE><<<(unsigned)((nvec + 255) / 256), 256, 0, st>>>(ep.part, plan.slices, m_base, M, Nout, ep);
+      gemm_reduce_kernel<<<(unsigned)((nvec + 255) / 256), 256, 0, st>>>(ep.part, plan.slices, m_base, M, Nout, ep);
     }
     return hipGetLastError();
   }
@@ -735,7 +731,7 @@ hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W
         else e = launch_cfg<128, 128, 2, 4, 64, 3, false, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
         if (e != hipSuccess) return e;
         const int64_t nvec = (int64_t)(M - m_base) * (Nout / 8);
-        gemm_reduce_kernel<MODE><<<(unsigned)((nvec + 255) / 256), 256, 0, st>>>(ep.part, ks, m_base, M, Nout, ep);
+        gemm_reduce_kernel<<<(unsigned)((nvec + 255) / 256), 256, 0, st>>>(ep.part, ks, m_base, M, Nout, ep);
         return hipGetLastError();
       }
     }

@@ -56,7 +56,7 @@ __global__ __launch_bounds__(kThreads) void select_long_kernel(const float* __re
   const int k = row_count(k_uniform, k_per_row, b, N, pitch);
   auto key_at = [&](int i) -> uint32_t { return sort_key(h[i]); };
   uint32_t thr = 0, remaining = 0;
-  if (k > 0 && k < N) thr = radix_select<kThreads, 32>(key_at, N, k, sc, &remaining);
+  if (k > 0 && k < N) thr = radix_select<kThreads>(key_at, N, k, sc, &remaining);
   compact<kThreads>(key_at, N, thr, remaining, k == N, k == 0, pitch, idx + (int64_t)b * pitch, mask + (int64_t)b * N,
                     sc.wave_sums);
 }

@@ -16,11 +16,13 @@ __device__ __forceinline__ uint32_t sort_key(float h) {
   return (b & 0x80000000u) ? ~b : (b | 0x80000000u);    // -inf -> 0x007fffff > 0
 }
 
-// LDS scratch of one workgroup of NT threads; COPIES counters per histogram bin (32 = one per LDS bank)
-template <int NT, int COPIES = 32>
+constexpr int kCopies = 32;              // counters per histogram bin: one per LDS bank
+
+// LDS scratch of one workgroup of NT threads
+template <int NT>
 struct Scratch {
   uint32_t hist[256];
-  uint32_t hist_banked[256 * COPIES];    // [bin][copy]: copy = lane % COPIES
+  uint32_t hist_banked[256 * kCopies];   // [bin][copy]: copy = lane % kCopies
   uint32_t wave_sums[NT / NOVA_WAVE];
   uint32_t bin, remaining;
 };
@@ -54,14 +56,12 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* w
 // The k-th largest of the N keys key_at(0..N-1), 0 < k < N, by a 4-pass, 8-bit MSB radix select on LDS histograms:
 // returns the threshold key; *remaining_out = how many of the keys equal to it are kept (the first ones in index
 // order).  Keys of one image share their leading bits, so in the first passes nearly all keys fall into one or two
-// bins: a single histogram would serialise its atomics on one address.  Each bin therefore has COPIES counters (32:
-// one per LDS bank) and a lane adds to the counter of its own bank; the counters are summed (and cleared) after the
-// pass.  Called by all NT threads of the workgroup.
-template <int NT, int COPIES, typename KeyAt>
-__device__ __forceinline__ uint32_t radix_select(KeyAt key_at, int N, int k, Scratch<NT, COPIES>& sc,
-                                                 uint32_t* remaining_out) {
-  constexpr int kCopies = COPIES;
-  static_assert(NT == 256 || NT == 1024, "the counter sum below gives NT / 256 threads to every bin");
+// bins: a single histogram would serialise its atomics on one address.  Each bin therefore has kCopies counters and a
+// lane adds to the counter of its own bank; the counters are summed (and cleared) after the pass.  Called by all NT
+// threads of the workgroup.
+template <int NT, typename KeyAt>
+__device__ __forceinline__ uint32_t radix_select(KeyAt key_at, int N, int k, Scratch<NT>& sc, uint32_t* remaining_out) {
+  static_assert(NT % 256 == 0 && NT <= 1024, "the counter sum below gives NT / 256 threads to every bin");
   constexpr int TPB = NT / 256;          // threads per bin in the counter sum
   const int tid = threadIdx.x;
   const int lane = tid & (NOVA_WAVE - 1);
@@ -77,7 +77,7 @@ __device__ __forceinline__ uint32_t radix_select(KeyAt key_at, int N, int k, Scr
     }
     __syncthreads();
     {
-      // TPB threads per bin, COPIES / TPB counters each (walked from a bin-dependent start, so that the lanes of a
+      // TPB threads per bin, kCopies / TPB counters each (walked from a bin-dependent start, so that the lanes of a
       // wave touch all banks); the counters are left at zero for the next pass
       constexpr int CPT = kCopies / TPB;
       const int bin = tid / TPB, q = tid % TPB;
