@@ -12,7 +12,8 @@ namespace {
 constexpr int kWavesPerBlock = 4;
 constexpr float kEps = 1e-6f;
 
-// U: vectors per lane, a row of at most U * 64 vectors is kept in registers; 0: any row, three passes
+// U: vectors per lane, a row of at most U * 64 vectors is kept in registers (every count up to eight has its kernel: with
+// modulation eight vectors are 96 registers); 0: any row, three passes
 template <typename T, int U>
 __global__ __launch_bounds__(kWavesPerBlock* NOVA_WAVE) void gather_ln_kernel(
     const T* __restrict__ src, const int32_t* __restrict__ idx, int M, int k, uint32_t k_inv, int N, int C,
@@ -150,9 +151,12 @@ void launch_t(hipStream_t st, const void* src, const int32_t* idx, int M, int k,
   switch (vecs) {
     case 1: return go(gather_ln_kernel<T, 1>);
     case 2: return go(gather_ln_kernel<T, 2>);
-    case 3: case 4: return go(gather_ln_kernel<T, 4>);
+    case 3: return go(gather_ln_kernel<T, 3>);
+    case 4: return go(gather_ln_kernel<T, 4>);
     case 5: return go(gather_ln_kernel<T, 5>);
-    case 6: case 7: case 8: return go(gather_ln_kernel<T, 8>);
+    case 6: return go(gather_ln_kernel<T, 6>);
+    case 7: return go(gather_ln_kernel<T, 7>);
+    case 8: return go(gather_ln_kernel<T, 8>);
     default: return go(gather_ln_kernel<T, 0>);
   }
 }
