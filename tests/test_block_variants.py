@@ -50,6 +50,31 @@ def test_variants_bf16(hx, variant, C, heads):
     _say(f"   errors {errs}")
 
 
+@pytest.mark.parametrize("cfg", ["1", "2", "5", "6"])
+@pytest.mark.parametrize("C,heads", [(128, 2), (256, 2)])
+def test_all_variants_bf16_on_every_tile(hx, cfg, C, heads, monkeypatch):
+    """The sizes above go to the few-rows kernels; here to every tile configuration of the projections."""
+    from paper_2602_01345_amd import Nova
+    monkeypatch.setenv("NOVA_GEMM_CFG", cfg)
+    monkeypatch.setattr(hx, "_NOVA", Nova(0))          # the knob is read when a context is created
+    _say(f"all variants bf16 C={C} tile {cfg}")
+    wl = _custom("bf16", B=2, grid=17, prev=13, P=100, C=C, heads=heads)
+    hx.check_block(hx.make_host_block(wl, 0, k=150, variant=set(ALL)), hx.BF16_TOL)
+
+
+@pytest.mark.parametrize("cfg,ksplit", [("1", "2"), ("2", "4"), ("5", "2"), ("6", "4"), (None, None)])
+def test_gated_sum_of_k_slices(hx, cfg, ksplit, monkeypatch):
+    """The down projection (K = 4096) cut into slices whose sum is gated; unforced, 1100 rows get four slices."""
+    from paper_2602_01345_amd import Nova
+    for name, v in (("NOVA_GEMM_CFG", cfg), ("NOVA_GEMM_KSPLIT", ksplit)):
+        if v is not None:
+            monkeypatch.setenv(name, v)
+    monkeypatch.setattr(hx, "_NOVA", Nova(0))
+    _say(f"gated K slices tile {cfg} slices {ksplit}")
+    wl = _custom("bf16", B=2, grid=24, prev=18, P=70, C=1024, heads=8)
+    hx.check_block(hx.make_host_block(wl, 0, k=550, variant={"ada", "gelu_tanh"}), hx.BF16_TOL, rows=[1])
+
+
 @pytest.mark.parametrize("k", [1, 289])
 def test_variants_bf16_single_and_all_rows(hx, k):
     wl = _custom("bf16", B=2, grid=17, prev=13, P=0 if k == 289 else 64, C=128, heads=2)

@@ -38,3 +38,25 @@ def test_the_tile_with_32_bit_offsets_stops_where_they_end(plan, M, Nout, K):
 
 def test_the_tile_with_32_bit_offsets_up_to_there(plan):
     assert plan(RESIDUAL, 2049, 8192, 1 << 21, cfg=1)[0][1] == 1
+
+
+def _part_floats(M, C):
+    return min(4 * M * C, 128 * 256 * 256)             # K-slice scratch of the block's workspace
+
+
+def test_sizes_of_the_gpu_tests_reach_what_they_test(plan):
+    import test_gpu_parity as G
+    M, C = 2 * G.TWO_LAUNCHES_K, 768
+    assert len(plan(GELU, M, 4 * C, C)) == 2 and len(plan(GELU, M, 4 * C, C, parts=0)) == 1
+    (_, cfg, tiles, _), = plan(GELU, 2 * G.MANY_TILES_K, 4 * C, C)
+    assert cfg != 7 and tiles > 256
+    for M, slices in ((1100, 4), (1400, 4), (3100, 1)):                    # the down projection of C = 1024
+        (_, cfg, _, got), = plan(RESIDUAL, M, 1024, 4096, _part_floats(M, 1024))
+        assert cfg != 7 and got == slices, (M, cfg, got)
+        for forced in (2, 4):
+            (_, _, _, got), = plan(RESIDUAL, M, 1024, 4096, _part_floats(M, 1024), ksplit=forced)
+            assert got == (forced if forced * M * 1024 <= _part_floats(M, 1024) else 1), (M, forced, got)
+    for cfg in (1, 2, 5, 6):                           # forced tiles take few rows away from the few-rows kernels
+        assert plan(ATTN_OUT, 260, 1024, 1024, cfg=cfg)[0][1] == cfg
+        assert plan(RESIDUAL, 260, 1024, 4096, _part_floats(260, 1024), cfg=cfg, ksplit=2)[0][3] == 2
+    assert plan(QKV, 300, 384, 128)[0][1] == 7         # and unforced they go there

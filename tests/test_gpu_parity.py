@@ -341,10 +341,16 @@ def test_probe_kernels_report_their_work(hx):
     assert float(sink) == 0.0
 
 
+@pytest.mark.parametrize("attn_cfg", [None, "1"])
 @pytest.mark.parametrize("P,k", [(0, 1), (0, 40), (3, 61), (64, 64), (127, 1), (500, 289)])
-def test_block_bf16_key_range_edges(hx, P, k):
-    """No prior keys at all, one partial key tile, exact tile multiples, a one-key ragged tail."""
-    _say(f"block bf16 P={P} k={k}")
+def test_block_bf16_key_range_edges(hx, P, k, attn_cfg, monkeypatch):
+    """No prior keys at all, one partial key tile, exact tile multiples, a one-key ragged tail; in the few-queries
+    kernel, which such sizes go to, and in the many-queries kernel's default workgroup shape."""
+    if attn_cfg:
+        from paper_2602_01345_amd import Nova
+        monkeypatch.setenv("NOVA_ATTN_CFG", attn_cfg)
+        monkeypatch.setattr(hx, "_NOVA", Nova(0))
+    _say(f"block bf16 P={P} k={k} attention {attn_cfg}")
     wl = _custom("bf16", B=2, grid=17, prev=13, P=P, C=128, heads=2)
     hb = hx.make_host_block(wl, 0, k=k)
     errs = hx.check_block(hb, hx.BF16_TOL)
@@ -352,12 +358,12 @@ def test_block_bf16_key_range_edges(hx, P, k):
 
 
 @pytest.mark.parametrize("dh_case", [(128, 2), (256, 2)])
-@pytest.mark.parametrize("forced_split", [0, 3])
+@pytest.mark.parametrize("forced_split", [0, 1, 3])
 def test_block_bf16_peaked_attention_with_rising_scores(hx, dh_case, forced_split, monkeypatch):
     """Sharply peaked attention whose largest score keeps rising along the keys: the query projection is scaled
     up (scores spread over tens of nats) and the prior keys grow in length with their position, so that the
-    softmax reference point of the kernel has to move several times while it walks the key tiles, also inside
-    the runs of a split item."""
+    softmax reference point of the kernel has to move several times while it walks the key tiles (few-queries kernel;
+    1: many-queries kernel, uncut), also inside the runs of a split item (3)."""
     C, heads = dh_case
     if forced_split:
         from paper_2602_01345_amd import Nova
@@ -399,12 +405,11 @@ def test_block_bf16_forced_key_splits(hx, split, monkeypatch):
 
 
 @pytest.mark.parametrize("knob,value", [("NOVA_ATTN_CFG", "2"), ("NOVA_ATTN_CFG", "3"), ("NOVA_ATTN_CFG", "4"),
-                                        ("NOVA_GEMM_CFG", "0"), ("NOVA_GEMM_CFG", "1"), ("NOVA_GEMM_CFG", "2"),
-                                        ("NOVA_GEMM_CFG", "5"), ("NOVA_GEMM_CFG", "6"), ("NOVA_GEMM_PARTS", "0"),
-                                        ("NOVA_GEMM_PERSIST", "0")])
+                                        ("NOVA_GEMM_CFG", "1"), ("NOVA_GEMM_CFG", "2"), ("NOVA_GEMM_CFG", "5"),
+                                        ("NOVA_GEMM_CFG", "6")])
 def test_block_bf16_with_every_tuning_knob(hx, knob, value, monkeypatch):
     """The kernel shapes that only an environment knob selects (other attention workgroup shapes, every GEMM tile
-    configuration forced, no two-launch row plans, one workgroup per tile) compute the same block."""
+    configuration forced) compute the same block."""
     from paper_2602_01345_amd import Nova
     monkeypatch.setenv(knob, value)
     monkeypatch.setattr(hx, "_NOVA", Nova(0))          # the knobs are read when a context is created
@@ -413,6 +418,25 @@ def test_block_bf16_with_every_tuning_knob(hx, knob, value, monkeypatch):
         wl = _custom("bf16", B=2, grid=17, prev=13, P=P, C=C, heads=heads)
         errs = hx.check_block(hx.make_host_block(wl, 0, k=k), hx.BF16_TOL)
         _say(f"   C={C}: errors {errs}")
+
+
+# 2 x k rows of width 768 whose up-projection goes out as two launches / as more tiles than compute units (held to that by
+# tests/test_gemm_plan.py)
+TWO_LAUNCHES_K, MANY_TILES_K = 1360, 1300
+
+
+@pytest.mark.parametrize("knob,k", [(None, TWO_LAUNCHES_K), ("NOVA_GEMM_PARTS", TWO_LAUNCHES_K),
+                                    (None, MANY_TILES_K), ("NOVA_GEMM_PERSIST", MANY_TILES_K)])
+def test_block_bf16_two_launch_plans_and_tile_walks(hx, knob, k, monkeypatch):
+    """The up-projection as two launches and as one, and with workgroups that walk several tiles and without."""
+    if knob:
+        from paper_2602_01345_amd import Nova
+        monkeypatch.setenv(knob, "0")
+        monkeypatch.setattr(hx, "_NOVA", Nova(0))
+    _say(f"block bf16 k={k} {knob}=0")
+    wl = _custom("bf16", B=2, grid=37, prev=28, P=60, C=768, heads=12)
+    errs = hx.check_block(hx.make_host_block(wl, 0, k=k), hx.BF16_TOL, rows=[1])
+    _say(f"   errors {errs}")
 
 
 @pytest.mark.parametrize("cfg", [None, "2", "6"])
@@ -435,15 +459,15 @@ def test_block_bf16_value_append_at_every_alignment(hx, cfg, monkeypatch):
 @pytest.mark.parametrize("ksplit", ["0", "2", "4", None])
 def test_block_bf16_ffn_down_projection_with_k_slices(hx, ksplit, monkeypatch):
     """The FFN down projection with large tiles and K = 4096 cut into 2 or 4 slices (fp32 partial sums, second
-    pass), forced on, forced off, and as the launcher chooses (600 rows: slices; 1400 rows: none)."""
+    pass), forced on, forced off, and as the launcher chooses (1100 and 1400 rows: four slices; 3100: none)."""
     from paper_2602_01345_amd import Nova
     if ksplit is not None:
         monkeypatch.setenv("NOVA_GEMM_KSPLIT", ksplit)
         monkeypatch.setattr(hx, "_NOVA", Nova(0))
     _say(f"block bf16 C=1024 F=4096, K slices of the down projection: {ksplit}")
-    for k in (300, 700):
-        wl = _custom("bf16", B=2, grid=28, prev=20, P=500, C=1024, heads=8)
-        errs = hx.check_block(hx.make_host_block(wl, 0, k=k), hx.BF16_TOL)
+    for k in (550, 700, 1550):
+        wl = _custom("bf16", B=2, grid=40, prev=32, P=100, C=1024, heads=8)
+        errs = hx.check_block(hx.make_host_block(wl, 0, k=k), hx.BF16_TOL, rows=[1])
         _say(f"   M={2 * k}: errors {errs}")
 
 

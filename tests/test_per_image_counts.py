@@ -16,11 +16,16 @@ def _wl(dtype, B, grid, prev, P, C, heads, seed=9):
                        scales=(WL.Scale(grid=grid, prev_grid=prev, kv_len=P),), seed=seed)
 
 
+@pytest.mark.parametrize("attn_cfg", [None, "1"])             # few-queries kernel, many-queries kernel
 @pytest.mark.parametrize("C,heads", [(128, 2), (256, 2)])                       # dh = 64 and dh = 128
 @pytest.mark.parametrize("k_rows,kv_rows", [([150, 0, 289], [100, 37, 64]), ([1, 37, 200], [0, 100, 1]),
                                             ([289, 289, 289], [100, 100, 100])])
-def test_block_bf16_per_image_counts(C, heads, k_rows, kv_rows):
-    print(f"per-image counts bf16 C={C} heads={heads} k={k_rows} kv={kv_rows}", flush=True)
+def test_block_bf16_per_image_counts(C, heads, k_rows, kv_rows, attn_cfg, monkeypatch):
+    if attn_cfg:
+        from paper_2602_01345_amd import Nova
+        monkeypatch.setenv("NOVA_ATTN_CFG", attn_cfg)
+        monkeypatch.setattr(Hn, "_NOVA", Nova(0))
+    print(f"per-image counts bf16 C={C} heads={heads} k={k_rows} kv={kv_rows} attention {attn_cfg}", flush=True)
     hb = Hn.make_host_block(_wl("bf16", 3, 17, 13, 100, C, heads), 0)
     errs = Hn.check_block_rows(hb, k_rows, kv_rows, Hn.BF16_TOL)
     print(f"   errors {errs}", flush=True)
