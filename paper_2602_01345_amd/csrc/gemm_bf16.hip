@@ -12,7 +12,7 @@
 //    the MFMA operand reads look the chunk up at the same swizzled slot.
 //  * The 256 x 256 tile: two LDS buffers filled and freed in halves, the two waves of a SIMD alternating between the
 //    matrix cores and LDS (see the K loop).  Against one ring of K steps for all waves, same box, weights from HBM:
-//    4096 x 6912 x 2304 (QKV) 150 -> 124 us, 4096 x 9216 x 2304 (GELU) 225 -> 177, 8192 x 8192 x 8192 968 -> 833
+//    4096 x 6912 x 2304 (QKV) 150 -> 124 us, 4096 x 9216 x 2304 (GELU) 225 -> 180, 8192 x 8192 x 8192 968 -> 833
 //    (1.14 -> 1.32 PFLOP/s; a large library product on the same card 1.40).
 //  * The smaller tiles: an NST-stage LDS ring (3 to 6 stages, per tile configuration): the loads of tiles
 //    t+1 .. t+NST-1 are in flight while tile t feeds the MFMAs; one bare barrier per K step with explicit
@@ -406,6 +406,11 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
   __syncthreads();
   int stage = 0, fill = NST - 1;            // stage being computed / stage being refilled
   read_frags(0, 0, 0);
+  // A loop body of 0.8 KB that every wave fetches in step: where it lies in the 64-byte lines of the instruction cache moves
+  // a launch by up to 4 % and changes with every edit around it (192 x 128 tiles, 3280 x 2048 rows x features, K = 8192:
+  // 174.9 us where the compiler happened to put it well, 184.2 where not, 174.7 with its first line aligned; 256 x 128
+  // 133.9 / 135.0 / 131.3).  The 256 x 256 tile's loop does not mind.
+  asm volatile(".p2align 6");
   for (int kt = 0; kt < KT; ++kt) {
     // the stage refilled now was read during the previous iteration and freed by its barrier
     const bool more = kt + NST - 1 < KT;
