@@ -257,7 +257,8 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
       roff = ((int64_t)ep.image(row) * ep.Ntok + min(max(kept[i], 0), ep.Ntok - 1)) * ep.C;
     return ep.res + roff + n0 + 8 * half;
   };
-  auto load_res = [&](u32x4* dst, int lo, int hi) {          // eight features of this lane's row: 16 gp + 8 half .. of a 32-column block
+  // eight features of this lane's row in MFMA tile rows lo .. hi - 1: 16 gp + 8 half .. of a 32-column block
+  auto load_res = [&](u32x4* dst, int lo, int hi) {
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       if (i < lo || i >= hi) continue;
