@@ -681,11 +681,11 @@ hipError_t launch_cfg(hipStream_t st, const bf16_t* A, const bf16_t* W, int m_ba
 // Second pass of a K-sliced launch (EPI_RESIDUAL): out = residual + gate (sum of the slices + bias) for rows [m_base, M).
 // One thread per 8 output features.
 __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restrict__ part, int kslices, int m_base,
-                                                          int M, int Nout, EpiParams<bf16_t> ep) {
+                                                          int M, int Nout, uint32_t cpr_inv, EpiParams<bf16_t> ep) {
   const int cpr = Nout / 8;
-  const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (v >= (int64_t)(M - m_base) * cpr) return;
-  const int row = m_base + (int)(v / cpr), col = (int)(v % cpr) * 8;
+  int c8;
+  const int row = m_base + div_by(blockIdx.x * 256 + threadIdx.x, cpr, cpr_inv, c8), col = c8 * 8;
+  if (row >= M) return;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   for (int s = 0; s < kslices; ++s) {
     const float* p = part + ((int64_t)s * (M - m_base) + row - m_base) * Nout + col;
@@ -715,13 +715,7 @@ hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W
                        const EpiParams<bf16_t>& ep, int slots, int cus, int ksplit) {
   if (cfg == kRowsCfg) {
     const RowsPlan plan = gemm_rows_plan(cus, MODE, M - m_base, Nout, K, ep.part ? ep.part_floats : 0);
-    const hipError_t e = launch_gemm_rows_bf16(st, plan, plan.slices > 1 ? EPI_PARTIAL : MODE, A, W, m_base, M, Nout, K, ep);
-    if (e != hipSuccess || plan.slices == 1) return e;
-    if constexpr (MODE == EPI_RESIDUAL) {
-      const int64_t nvec = (int64_t)(M - m_base) * (Nout / 8);
-      gemm_reduce_kernel<<<(unsigned)((nvec + 255) / 256), 256, 0, st>>>(ep.part, plan.slices, m_base, M, Nout, ep);
-    }
-    return hipGetLastError();
+    return launch_gemm_rows_bf16(st, plan, MODE, A, W, m_base, M, Nout, K, ep);
   }
   if constexpr (MODE == EPI_RESIDUAL) {
     // see k_slices; the scratch buffer holds 4 x rows x C floats, hence Nout == C
@@ -737,7 +731,7 @@ hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W
         else e = launch_cfg<128, 128, 2, 4, 64, 3, false, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
         if (e != hipSuccess) return e;
         const int64_t nvec = (int64_t)(M - m_base) * (Nout / 8);
-        gemm_reduce_kernel<<<(unsigned)((nvec + 255) / 256), 256, 0, st>>>(ep.part, ks, m_base, M, Nout, ep);
+        gemm_reduce_kernel<<<(unsigned)((nvec + 255) / 256), 256, 0, st>>>(ep.part, ks, m_base, M, Nout, div_inv(Nout / 8), ep);
         return hipGetLastError();
       }
     }

@@ -6,34 +6,48 @@
 #include "epilogue.h"
 #include "nova_internal.h"
 
-// Tile and K slices for `rows` rows, or rg = 0 where the shared-ring kernels are faster.
-//  * The narrowest tile that needs no more workgroups than there are CUs: half of them leave CUs idle (64 rows,
-//    Nout = 3072, K = 1024: 96 workgroups 6.7 us, 192 6.1), twice as many fetch the rows twice as often (K = 2048,
-//    Nout = 6144: 192 workgroups 10.8 us, 384 15.0).  One tile shape has to do for up to 8 x 8 groups; beyond one
-//    workgroup per CU two of them still fit with one unit in flight each.
+// Tile of the few-rows kernels for `rows` rows, or rg = 0 where the shared-ring kernels are faster.
+//  * A tile of rg groups of eight rows and ng groups of eight features loads (rg + ng) groups and computes rg ng, so of
+//    the tiles that give every CU one workgroup the one nearest to a square loads least: the rule is the fewest groups
+//    on the busiest CU.  Against the narrowest tile over all rows at once (us, weights from HBM): 64 rows, Nout = 1024,
+//    K = 1024 / 4096 64 x 8 3.9 / 8.9 (K cut into four slices), 16 x 16 3.0 / 6.7; 128 rows 64 x 8 4.0 / 10.1 (cut),
+//    32 x 16 3.3 / 8.3; 64 rows, Nout = 3072 64 x 16 5.4, 32 x 32 4.9.  Cutting K and adding the slices in a second pass
+//    is worth it nowhere any more but for 128 rows of K = 8192 (18.1 against 18.6, not counting what its launch costs
+//    behind cold caches).
+//  * Equal counts: the wider tile (more rows in flight per weight row), the taller with a long K (100 rows, K = 4096,
+//    Nout = 1024: 32 x 16 6.9, 16 x 32 7.8; K = 1024 3.27, 3.24).
+//  * Up to eight rows the weights are all there is to load, and several small workgroups per CU stream them best
+//    (K = 2048, Nout = 8192, two rows: 8 x 8 8.2, 8 x 16 8.7, 8 x 32 8.9; K = 1024, Nout = 3072: 8 x 8 4.0, 8 x 16 3.6).
 //  * One workgroup per CU beats the 128- and 256-row tiles at any row count (1024 rows, Nout = 1024: K = 1024 8.4
 //    against 11.1 us, K = 4096 16.4 against 22.9; 640 rows 7.4 / 14.7 against 11.0 / 17.3).  Two per CU do up to 512 rows
 //    (512 rows, K = 1024, Nout = 3072: 10.2 against 10.5; 820 rows, Nout = 1920 = K: 17.8 against 17.2), but not with a
 //    long K (400 rows, K = 9216, Nout = 2304: 30 against 27).
-//  * A long K into few features (the FFN down projection) with 33 ... 128 rows: the tiles would fill a quarter of the
-//    CUs, so K is cut into four slices and a second small pass adds them (64 rows, K = 8192: 20 us uncut, 15.1 cut;
-//    with 16 rows 11.7 uncut, 12.9 cut; with 200 rows, K = 4096 10.6 uncut, 13.2 cut).
-inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K, int64_t part_floats) {
-  RowsPlan p = {};
-  if (mode == EPI_ENTROPY || Nout % 64 != 0) return p;
-  const int rg = rows <= 8 ? 1 : rows <= 16 ? 2 : rows <= 32 ? 4 : 8;
-  const int row_tiles = (rows + 8 * rg - 1) / (8 * rg);
-  p.slices = 1;
-  if (mode == EPI_RESIDUAL && K >= 4096 && rows > 32 && rows <= 128 && (int64_t)4 * rows * Nout <= part_floats) p.slices = 4;
-  const int ng_max = rg == 8 ? 8 : 4;
-  int ng = 1;
-  while (ng < ng_max && row_tiles * (Nout / (8 * ng)) * p.slices > num_cus) ng *= 2;
-  const int wgs = row_tiles * (Nout / (8 * ng)) * p.slices;
-  if (rows > 64 && wgs > (mode == EPI_RESIDUAL || rows > 512 ? num_cus : 2 * num_cus)) return p;
-  p.rg = rg;
-  p.ng = ng;
-  p.s = rg == 8 ? (ng == 8 && wgs > num_cus ? 1 : 2) : rg == 4 ? (ng == 4 ? 4 : 3) : rg == 2 ? (ng == 1 ? 2 : ng == 2 ? 4 : 3) : 4;
-  return p;
+// The kernels: groups of eight rows, of eight features, waves, units in flight per wave, workgroups that fit a CU.
+#define NOVA_ROWS_TILES(T)                                                          \
+  T(1, 1, 4, 4, 2) T(1, 1, 8, 4, 2) T(1, 2, 4, 4, 2) T(1, 4, 4, 4, 2) T(2, 1, 4, 4, 2) \
+  T(2, 2, 4, 4, 2) T(2, 4, 4, 3, 2) T(4, 2, 4, 3, 2) T(4, 4, 4, 2, 2) T(4, 8, 4, 2, 1) \
+  T(8, 4, 4, 2, 1) T(8, 8, 4, 2, 1) T(8, 8, 4, 1, 2)
+inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K, int64_t) {
+  RowsPlan best = {};
+  if (mode == EPI_ENTROPY || Nout % 64 != 0 || K > 1 << 23) return best;    // 64 rows of 2 K bytes: 32-bit offsets
+  const bool weights_only = rows <= 8 && (K > 1536 || Nout <= 8 * num_cus) && Nout <= 32 * num_cus;
+  const int max_per_cu = mode == EPI_RESIDUAL || rows > 512 ? 1 : 2;
+  int64_t least = INT64_MAX;
+  auto consider = [&](const RowsPlan& t, int fit) {
+    if (t.rg * t.ng == 1 ? t.kw != (K > 2048 ? 8 : 4) : weights_only) return;       // a long K over twice the waves
+    const int64_t wgs = (int64_t)((rows + 8 * t.rg - 1) / (8 * t.rg)) * (Nout / (8 * t.ng));
+    const int64_t per_cu = (wgs + num_cus - 1) / num_cus;
+    if (rows > 64 && per_cu > std::min(fit, max_per_cu)) return;                     // up to 64 rows: in turns
+    const int64_t groups = per_cu * (t.rg + t.ng);
+    if (groups < least || (groups == least && (K >= 4096 ? t.rg > best.rg : t.ng > best.ng))) {
+      least = groups;
+      best = t;
+    }
+  };
+#define CONSIDER(RG, NG, KW, S, FIT) consider({RG, NG, KW, S, 1}, FIT);
+  NOVA_ROWS_TILES(CONSIDER)
+#undef CONSIDER
+  return best;
 }
 
 // Tile configurations (NOVA_GEMM_CFG forces one, for tuning; numbers without a kernel mean 2):
@@ -95,12 +109,12 @@ inline double model_time(const Candidate& c, int slots, int mode, int M, int Nou
 inline bool narrow_tiles(int M, int Nout, int K) { return M <= 256 || (M <= 512 && Nout < 4096 && K < 4096); }
 
 // Modelled time of the few-rows kernels: what the busiest CU loads at 75 GB/s, half of the weights at the rate of a large
-// copy, 2.5 us to start and end, 3 us for the slice sums (measured 4.2 ... 22 us over 64 ... 1024 rows and 2 ... 38 MB
-// of weights; within 2 us but for a long K, where it is up to 8 us too much).
+// copy, 2.1 us to start and end (measured 3.0 ... 22 us over 64 ... 1024 rows and 2 ... 38 MB of weights; within 2 us but
+// for a long K, where it is up to 8 us too much).
 inline double rows_time(const RowsPlan& p, int cus, int rows, int Nout, int K) {
-  const int wgs = (rows + 8 * p.rg - 1) / (8 * p.rg) * (Nout / (8 * p.ng)) * p.slices;
-  const double bytes = (double)((wgs + cus - 1) / cus) * 16.0 * (p.rg + p.ng) * K / p.slices;
-  return 2.5e-6 + bytes / 75e9 + (double)Nout * K / 5e12 + (p.slices > 1 ? 3e-6 : 0.0);
+  const int wgs = (rows + 8 * p.rg - 1) / (8 * p.rg) * (Nout / (8 * p.ng));
+  const double bytes = (double)((wgs + cus - 1) / cus) * 16.0 * (p.rg + p.ng) * K;
+  return 2.1e-6 + bytes / 75e9 + (double)Nout * K / 5e12;
 }
 
 inline int pick_cfg(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64_t part_floats, double* t_out = nullptr) {

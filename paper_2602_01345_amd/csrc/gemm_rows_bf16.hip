@@ -11,22 +11,30 @@
 //  * A wave keeps S units in flight in an LDS ring of its own (global -> LDS loads of eight rows x 128 bytes, so that
 //    the eight lanes of a row ask for one line; operands loaded straight into the MFMA's register layout, 16 rows per
 //    16 lanes, cost one line look-up per lane: measured 1.3x slower with one row, 2x with 64).  No barrier: the wave
-//    waits for its own loads only.  Groups of eight rows that do not exist are not loaded.
+//    waits for its own loads only.
+//  * What surrounds the K walk is one lone wave per SIMD, some 5 cycles an instruction: no division (two of 64 bits to
+//    divide K over slices were 0.4 us of every launch), the arguments in one round trip, loads whose addresses are one
+//    lane offset and a scalar, no accumulation registers to move out of.
 //  * The epilogue works on eight consecutive features of one row per thread, rows fastest, so that value-cache
 //    columns (key index minor) are written in runs of rows; its bias and residual are requested before the K walk.
-// Measured in a graph, weights from HBM, against the shared-ring kernel with 64 x 32 / 128 x 32 tiles (us): K = 1024,
-// Nout = 1024 / 3072 / 4096, one row 8.0 / 9.8 / 9.1 -> 3.5 / 4.5 / 4.7, 64 rows 8.2 / 9.9 / 9.4 -> 4.6 / 6.1 / 6.3,
-// 256 rows 8.9 / 10.4 / 10.3 -> 5.0 / 8.6 / 8.8; K = 2048, Nout = 8192, one row 13.8 -> 8.4 (4.9 TB/s with the launch
-// taken off), 64 rows 14.1 -> 12.3; K = 8192, Nout = 2048, one row 16.8 -> 8.7.
+// Measured in a graph, weights from HBM (us; with the divisions and 64-row tiles whatever the width / now / a stream of the
+// same bytes): K = 1024, Nout = 1024 / 3072 / 4096, one row 3.1 / 4.2 / 4.5 -> 2.7 / 3.6 / 3.9 (- / 2.9 / 3.3), 64 rows
+// 4.3 / 5.9 / 6.1 -> 3.0 / 4.9 / 5.1; K = 4096, Nout = 1024, one row 4.8 -> 4.4, 64 rows 9.3 -> 6.7.
 #include "common.h"
 #include "epilogue.h"
+#include "gemm_plan.h"
 #include "nova_internal.h"
 
 namespace {
 
-typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 #define WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
+
+// 16 bytes per lane from base + lane_off + off (bytes; base and off wave-uniform) into 1 KB of LDS
+__device__ __forceinline__ void fill_lds(const bf16_t* base, char* dst, uint32_t lane_off, uint32_t off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, 0x7FFFFFFF, 0x00020000), (lptr_t)dst, 16, lane_off, off, 0, 0);
+}
 
 // s_waitcnt vmcnt(younger * LPU) for a wave-uniform younger in 0 .. MAXJ
 template <int MAXJ, int LPU>
@@ -47,8 +55,8 @@ __device__ __forceinline__ f32x4v mfma16(bf16x8 a, bf16x8 b, f32x4v c) {
 // RG, NG: groups of eight rows / features of a tile (an MFMA tile is 16 x 16: with an odd count its other half is
 // whatever lies in LDS behind and is never used); KW: waves; S: units in flight per wave
 template <int RG, int NG, int KW, int S, int MODE>
-__global__ __launch_bounds__(KW* 64) void gemm_rows_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ W,
-                                                            int M, int Nout, int K, int m_base, EpiParams<bf16_t> ep) {
+__global__ __launch_bounds__(KW* 64) __attribute__((amdgpu_waves_per_eu(KW * S * (NG + RG) <= 79 ? 2 : 1))) void gemm_rows_kernel(
+    const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int Nout, int K, int m_base, EpiParams<bf16_t> ep) {
   constexpr int MT = (RG + 1) / 2, NF = (NG + 1) / 2;
   constexpr int ROWS = MT * 16, LROWS = RG * 8, COLS = NG * 8, NT = KW * 64;
   constexpr int COL8 = COLS / 8;                         // eight-feature groups per row: one thread each in the epilogue
@@ -58,6 +66,9 @@ __global__ __launch_bounds__(KW* 64) void gemm_rows_kernel(const bf16_t* __restr
   static_assert(S * LPU < 64, "vmcnt is a 6-bit counter");
   __shared__ __attribute__((aligned(1024))) char lds[KW * S * SLOT + 1024];
 
+  // all arguments in one round trip, not one per branch below that needs some
+  asm volatile("" ::"s"(A), "s"(W), "s"(M), "s"(Nout), "s"(K), "s"(m_base), "s"(ep.bias), "s"(ep.out),
+               "s"(ep.ldo), "s"(ep.k), "s"(ep.k_inv), "s"(ep.k_rows), "s"(ep.res), "s"(ep.idx), "s"(ep.Ntok), "s"(ep.gate));
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n0 = blockIdx.x * COLS, m0 = m_base + blockIdx.y * LROWS;
@@ -65,37 +76,33 @@ __global__ __launch_bounds__(KW* 64) void gemm_rows_kernel(const bf16_t* __restr
     // per-image keep counts: a tile without a live row has nothing to compute (the whole workgroup leaves together)
     const int m_hi = min(m0 + LROWS, M);
     bool live = false;
-    for (int b = m0 / ep.k; b * ep.k < m_hi; ++b)
+    for (int b = ep.image(m0); b * ep.k < m_hi; ++b)
       live = live || max(m0 - b * ep.k, 0) < image_count(ep.k_rows, b, ep.k);
     if (!live) return;
   }
 
   // ---- fills: instruction j of a unit drops 8 rows x 128 bytes into LDS; slot p of row r holds chunk p ^ ((r >> 1) & 7)
-  const int units_all = K / 64;                          // runs of 64 elements
-  const int slices = gridDim.z;                          // EPI_PARTIAL only: contiguous parts of the runs
-  const int u_lo = (int)((int64_t)units_all * blockIdx.z / slices) + wave;
-  const int n_units = ((int)((int64_t)units_all * (blockIdx.z + 1) / slices) - u_lo + KW - 1) / KW;   // of this wave
+  const int n_units = (K / 64 - wave + KW - 1) / KW;     // runs of 64 elements of this wave: wave, wave + KW, ...
   const int lr = lane >> 3, lp = lane & 7;
-  const bf16_t* pw[NG];
-  const bf16_t* pa[RG];
+  const bf16_t* Ab = A + (int64_t)m0 * K;
+  const bf16_t* Wb = W + (int64_t)n0 * K;
+  // byte offsets from the tile's first row (32 bits: gemm_rows_plan keeps K that short); rows past the last one re-read it
+  uint32_t ow[2], oa[RG];
 #pragma unroll
-  for (int j = 0; j < NG; ++j) {
-    const int r = j * 8 + lr;
-    pw[j] = W + (int64_t)min(n0 + r, Nout - 1) * K + (lp ^ ((r >> 1) & 7)) * 8;
-  }
+  for (int j = 0; j < 2; ++j) ow[j] = (uint32_t)lr * (uint32_t)(2 * K) + ((lp ^ (lr >> 1) ^ (j * 4)) << 4);
 #pragma unroll
   for (int j = 0; j < RG; ++j) {
     const int r = j * 8 + lr;
-    pa[j] = A + (int64_t)min(m0 + r, M - 1) * K + (lp ^ ((r >> 1) & 7)) * 8;
+    oa[j] = (uint32_t)min(r, M - 1 - m0) * (uint32_t)(2 * K) + ((lp ^ ((r >> 1) & 7)) << 4);
   }
   char* mine_lds = lds + wave * (S * SLOT);
   auto issue = [&](int i) {
     char* d = mine_lds + (i % S) * SLOT;
-    const int k0 = (u_lo + i * KW) * 64;
+    const uint32_t k0 = (uint32_t)(wave + i * KW) * 128;
 #pragma unroll
-    for (int j = 0; j < NG; ++j) __builtin_amdgcn_global_load_lds((gptr_t)(pw[j] + k0), (lptr_t)(d + j * 1024), 16, 0, 0);
+    for (int j = 0; j < NG; ++j) fill_lds(Wb, d + j * 1024, ow[j & 1], k0 + (uint32_t)(j * 16 * K));
 #pragma unroll
-    for (int j = 0; j < RG; ++j) __builtin_amdgcn_global_load_lds((gptr_t)(pa[j] + k0), (lptr_t)(d + (NG + j) * 1024), 16, 0, 0);
+    for (int j = 0; j < RG; ++j) fill_lds(Ab, d + (NG + j) * 1024, oa[j], k0);
   };
   // This thread's outputs: row m0 + o % ROWS, features n0 + 8 (o / ROWS) .. for o = tid, tid + NT, ...  Their bias,
   // residual and gate are requested behind the first units; only the gathered residual's index, which its address
@@ -122,7 +129,7 @@ __global__ __launch_bounds__(KW* 64) void gemm_rows_kernel(const bf16_t* __restr
       if (HAS_RES) { res[q][e] = (bf16_t)0.f; gate[q][e] = (bf16_t)1.f; }
     }
     const int o = tid + q * NT, row = m0 + o % ROWS, col = n0 + o / ROWS * 8;
-    if (MODE == EPI_PARTIAL || !has_output(o)) continue;
+    if (!has_output(o)) continue;
     if (ep.bias) bias[q] = *reinterpret_cast<const bf16x8*>(ep.bias + col);
     if constexpr (HAS_RES) {
       int64_t roff = (int64_t)row * ep.ldo;
@@ -188,12 +195,6 @@ __global__ __launch_bounds__(KW* 64) void gemm_rows_kernel(const bf16_t* __restr
 #pragma unroll
       for (int e = 0; e < 4; ++e) { v[e] += a[e]; v[4 + e] += b[e]; }
     }
-    if constexpr (MODE == EPI_PARTIAL) {
-      float* p = ep.part + ((int64_t)blockIdx.z * (M - m_base) + row - m_base) * Nout + col;
-      *reinterpret_cast<f32x4v*>(p) = f32x4v{v[0], v[1], v[2], v[3]};
-      *reinterpret_cast<f32x4v*>(p + 4) = f32x4v{v[4], v[5], v[6], v[7]};
-      continue;
-    }
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] += (float)bias[q][e];
     bf16x8 y;
@@ -242,9 +243,9 @@ __global__ __launch_bounds__(KW* 64) void gemm_rows_kernel(const bf16_t* __restr
 }
 
 template <int RG, int NG, int KW, int S, int MODE>
-hipError_t go(hipStream_t st, const bf16_t* A, const bf16_t* W, int m_base, int M, int Nout, int K, int slices,
+hipError_t go(hipStream_t st, const bf16_t* A, const bf16_t* W, int m_base, int M, int Nout, int K,
               const EpiParams<bf16_t>& ep) {
-  const dim3 grid(Nout / (NG * 8), (M - m_base + RG * 8 - 1) / (RG * 8), slices);
+  const dim3 grid(Nout / (NG * 8), (M - m_base + RG * 8 - 1) / (RG * 8));
   gemm_rows_kernel<RG, NG, KW, S, MODE><<<grid, KW * 64, 0, st>>>(A, W, M, Nout, K, m_base, ep);
   return hipGetLastError();
 }
@@ -252,12 +253,9 @@ hipError_t go(hipStream_t st, const bf16_t* A, const bf16_t* W, int m_base, int 
 template <int MODE>
 hipError_t by_plan(hipStream_t st, const RowsPlan& p, const bf16_t* A, const bf16_t* W, int m_base, int M, int Nout, int K,
                    const EpiParams<bf16_t>& ep) {
-#define GO(RG_, NG_, KW_, S_) \
-  if (p.rg == RG_ && p.ng == NG_ && p.s == S_) return go<RG_, NG_, KW_, S_, MODE>(st, A, W, m_base, M, Nout, K, p.slices, ep)
-  GO(1, 1, 8, 4); GO(1, 2, 4, 4); GO(1, 4, 4, 4);
-  GO(2, 1, 8, 2); GO(2, 2, 4, 4); GO(2, 4, 4, 3);
-  GO(4, 1, 8, 3); GO(4, 2, 4, 3); GO(4, 4, 4, 4);
-  GO(8, 1, 4, 2); GO(8, 2, 4, 2); GO(8, 4, 4, 2); GO(8, 8, 4, 2); GO(8, 8, 4, 1);
+#define GO(RG, NG, KW, S, FIT) \
+  if (p.rg == RG && p.ng == NG && p.kw == KW && p.s == S) return go<RG, NG, KW, S, MODE>(st, A, W, m_base, M, Nout, K, ep);
+  NOVA_ROWS_TILES(GO)
 #undef GO
   return hipErrorInvalidValue;
 }
@@ -272,7 +270,6 @@ hipError_t launch_gemm_rows_bf16(hipStream_t st, const RowsPlan& p, int mode, co
     case EPI_GELU: return by_plan<EPI_GELU>(st, p, A, W, m_base, M, Nout, K, ep);
     case EPI_GELU_TANH: return by_plan<EPI_GELU_TANH>(st, p, A, W, m_base, M, Nout, K, ep);
     case EPI_PLAIN: return by_plan<EPI_PLAIN>(st, p, A, W, m_base, M, Nout, K, ep);
-    case EPI_PARTIAL: return by_plan<EPI_PARTIAL>(st, p, A, W, m_base, M, Nout, K, ep);
     case EPI_RESIDUAL: return by_plan<EPI_RESIDUAL>(st, p, A, W, m_base, M, Nout, K, ep);
     default: return hipErrorInvalidValue;
   }

@@ -116,9 +116,10 @@ template <typename T> struct EpiParams;
 hipError_t launch_gemm_bf16(const nova_ctx* ctx, hipStream_t st, int mode, const void* A, const void* W, int M,
                             int Nout, int K, const EpiParams<__bf16>& ep);
 // gemm_rows_bf16.hip: the same for few rows [m_base, M), by a plan of gemm_plan.h.  The plan's rg is 0 where the shape is
-// better served by gemm_bf16.hip; slices > 1 (EPI_RESIDUAL only): launch with EPI_PARTIAL, then add the slices
+// better served by gemm_bf16.hip
 struct RowsPlan {
-  int rg, ng, s, slices;   // groups of 8 rows / 8 features per tile, units in flight per wave, K slices
+  int rg, ng, kw, s;       // groups of 8 rows / 8 features per tile, waves, units in flight per wave
+  int slices;              // K slices: 1, these kernels do not cut K over workgroups
 };
 hipError_t launch_gemm_rows_bf16(hipStream_t st, const RowsPlan& plan, int mode, const __bf16* A, const __bf16* W, int m_base,
                                  int M, int Nout, int K, const EpiParams<__bf16>& ep);
