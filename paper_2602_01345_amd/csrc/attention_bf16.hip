@@ -586,7 +586,8 @@ hipError_t launch_attention_bf16(const nova_ctx* ctx, hipStream_t st, const void
   const bf16_t* vc = static_cast<const bf16_t*>(vcv);
   bf16_t* out = static_cast<bf16_t*>(outv);
   const int dh = C / heads;
-  if (!ctx || (ctx->attn_cfg < 1 && ctx->attn_split < 1)) {     // neither shape nor runs are forced
+  // neither shape nor runs are forced; the few-queries kernel addresses a head's value cache with 32 bits
+  if ((!ctx || (ctx->attn_cfg < 1 && ctx->attn_split < 1)) && cap <= 1 << 22) {
     const int waves = attention_few_waves(ctx ? ctx->num_cus : 256, dh, B, k, heads, kv_total);
     if (waves) return launch_attention_few_bf16(st, waves, qv, kcv, vcv, B, k, C, heads, cap, kv_total, outv, k_rows,
                                                 kv_rows, P, self_keys);

@@ -16,13 +16,18 @@
 
 namespace {
 
-typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
 #define WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+
+// 16 bytes per lane from base + lane_off + off (bytes; base and off wave-uniform) into 1 KB of LDS
+__device__ __forceinline__ void fill_lds(const bf16_t* base, char* dst, uint32_t lane_off, uint32_t off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, 0x7FFFFFFF, 0x00020000), (lptr_t)dst, 16, lane_off, off, 0, 0);
 }
 
 // MFMA row i of a 32-key block reads this key, so that a lane ends up holding runs of eight consecutive keys, the
@@ -43,10 +48,10 @@ __device__ __forceinline__ int swz(int r, int c) {
 constexpr int BQ = 32;               // queries per workgroup
 
 template <int DH, int NW>
-__global__ __launch_bounds__(NW * 64) void attention_few_kernel(
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) void attention_few_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ kc, const bf16_t* __restrict__ vc, int k, int C, int heads,
-    int cap, int kv_total_uniform, int nqb, bf16_t* __restrict__ out, const int32_t* __restrict__ k_rows,
-    const int32_t* __restrict__ kv_rows, int P, int self_keys) {
+    int cap, int kv_total_uniform, int nqb, uint32_t nqb_inv, uint32_t heads_inv, bf16_t* __restrict__ out,
+    const int32_t* __restrict__ k_rows, const int32_t* __restrict__ kv_rows, int P, int self_keys) {
   constexpr int KT = 4096 / DH;                  // keys per tile
   constexpr int KB = KT / 32;                    // 32-key blocks per tile
   constexpr int KROWB = DH * 2, VROWB = KT * 2;  // bytes per row of the K tile (a key) and of the V tile (a channel)
@@ -56,14 +61,17 @@ __global__ __launch_bounds__(NW * 64) void attention_few_kernel(
   __shared__ __attribute__((aligned(1024))) char lds[NW * TILE];
   __shared__ float part_m[NW][BQ], part_l[NW][BQ];
 
+  // all arguments in one round trip, not one per branch below that needs some
+  asm volatile("" ::"s"(q), "s"(kc), "s"(vc), "s"(k), "s"(C), "s"(heads), "s"(cap), "s"(kv_total_uniform), "s"(nqb),
+               "s"(nqb_inv), "s"(heads_inv), "s"(out), "s"(k_rows), "s"(kv_rows), "s"(P), "s"(self_keys));
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int half = lane >> 5, col = lane & 31;
   // the query blocks of one (image, head) go to one XCD (workgroups are dealt to the 8 XCDs in turn): shared K / V in its L2
   const int n = gridDim.x, xcd = blockIdx.x & 7;
   const int item = xcd * (n >> 3) + min(xcd, n & 7) + (blockIdx.x >> 3);
-  const int bh = item / nqb, qb = item - bh * nqb;
-  const int b = bh / heads, head = bh - b * heads;
+  int qb, head;
+  const int bh = div_by(item, nqb, nqb_inv, qb), b = div_by(bh, heads, heads_inv, head);
   const bf16_t* Kg = kc + (int64_t)bh * cap * DH;          // [cap][DH]
   const bf16_t* Vg = vc + (int64_t)bh * DH * (int64_t)cap; // [DH][cap]
   const int kq = image_count(k_rows, b, k);
@@ -79,30 +87,28 @@ __global__ __launch_bounds__(NW * 64) void attention_few_kernel(
   const int ntiles = (kv_total + KT - 1) / KT;
   char* sk = lds + wave * TILE;
   char* sv = sk + TILE / 2;
-  int koff[LK], voff[LV];                                  // element offsets from the tile origin
+  // byte offsets of the lanes' 16-byte chunks in load instruction i (rows i * 64 / chunks per row ..): the swizzle repeats
+  // after KV_ / VV instructions, the rest of the address is wave-uniform
+  constexpr int KC = KROWB / 16, VC = VROWB / 16;          // 16-byte chunks per row
+  constexpr int KR = 64 / KC, VR = 64 / VC;                // rows per instruction
+  constexpr int KV_ = KROWB == 256 ? 4 : 2, VV = VROWB == 128 ? 2 : 1;
+  uint32_t koff[KV_], voff[VV];
   {
-    constexpr int KC = KROWB / 16, VC = VROWB / 16;        // 16-byte chunks per row
     const int kr = lane / KC, kp = lane % KC, vr = lane / VC, vp = lane % VC;
 #pragma unroll
-    for (int i = 0; i < LK; ++i) {
-      const int r = i * (64 / KC) + kr;
-      koff[i] = r * DH + ((swz<KROWB>(r, kp) - r * KROWB) >> 4) * 8;
-    }
+    for (int i = 0; i < KV_; ++i) koff[i] = swz<KROWB>(i * KR + kr, kp) - i * KR * KROWB;
 #pragma unroll
-    for (int i = 0; i < LV; ++i) {
-      const int r = i * (64 / VC) + vr;
-      voff[i] = r * cap + ((swz<VROWB>(r, vp) - r * VROWB) >> 4) * 8;
-    }
+    for (int i = 0; i < VV; ++i) voff[i] = (uint32_t)vr * (uint32_t)(2 * cap) + (swz<VROWB>(i * VR + vr, vp) - (i * VR + vr) * VROWB);
   }
   auto issue_k = [&](int t) {
+    const bf16_t* Kt = Kg + (int64_t)t * KT * DH;
 #pragma unroll
-    for (int i = 0; i < LK; ++i)
-      __builtin_amdgcn_global_load_lds((gptr_t)(Kg + (int64_t)t * KT * DH + koff[i]), (lptr_t)(sk + i * 1024), 16, 0, 0);
+    for (int i = 0; i < LK; ++i) fill_lds(Kt, sk + i * 1024, koff[i % KV_], i * KR * KROWB);
   };
   auto issue_v = [&](int t) {
+    const bf16_t* Vt = Vg + t * KT;
 #pragma unroll
-    for (int i = 0; i < LV; ++i)
-      __builtin_amdgcn_global_load_lds((gptr_t)(Vg + t * KT + voff[i]), (lptr_t)(sv + i * 1024), 16, 0, 0);
+    for (int i = 0; i < LV; ++i) fill_lds(Vt, sv + i * 1024, voff[i % VV], (uint32_t)(i * VR) * (uint32_t)(2 * cap));
   };
   // query fragments first: the first score MFMA needs them together with the first K tile
   bf16x8 qf[KSTEPS];
@@ -213,6 +219,22 @@ __global__ __launch_bounds__(NW * 64) void attention_few_kernel(
 
   // ---- merge of the waves' partial results --------------------------------------------------------------------
   const float l_tot = l_run + __shfl_xor(l_run, 32, NOVA_WAVE);
+  if constexpr (NW == 1) {
+    // nothing to merge: a lane holds four consecutive channels of its query per register group
+    const float inv = 1.0f / l_tot;
+    if (col < live) {
+#pragma unroll
+      for (int d = 0; d < DB; ++d)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          bf16x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = (bf16_t)(o[d][r4 * 4 + e] * inv);
+          *reinterpret_cast<bf16x4*>(ob + (int64_t)col * C + d * 32 + r4 * 8 + half * 4) = v;
+        }
+    }
+    return;
+  }
   if (half == 0) { part_m[wave][col] = m_run; part_l[wave][col] = l_tot; }
   // [channel / 4][query] of four channels each, in the wave's own tile (nothing of it is in flight or unread any more)
 #pragma unroll
@@ -264,7 +286,7 @@ __global__ __launch_bounds__(NW * 64) void attention_few_kernel(
 int attention_few_waves(int slots, int dh, int B, int k, int heads, int kv_total) {
   const int64_t grid = (int64_t)B * heads * ((k + BQ - 1) / BQ);
   const int tiles = (kv_total + 4096 / dh - 1) / (4096 / dh);
-  if (grid <= slots && tiles <= 8 * 12) return tiles > 4 ? 8 : 4;
+  if (grid <= slots && tiles <= 8 * 12) return tiles > 4 ? 8 : tiles > 1 ? 4 : 1;
   return grid <= 2 * slots && tiles <= 4 * 3 ? 4 : 0;
 }
 
@@ -275,10 +297,10 @@ hipError_t launch_attention_few_bf16(hipStream_t st, int waves, const void* q, c
   const bf16_t *qt = static_cast<const bf16_t*>(q), *kt = static_cast<const bf16_t*>(kc), *vt = static_cast<const bf16_t*>(vc);
   bf16_t* ot = static_cast<bf16_t*>(out);
 #define GO(DH_, NW_)                                                                                                  \
-  attention_few_kernel<DH_, NW_><<<grid, NW_ * 64, 0, st>>>(qt, kt, vt, k, C, heads, cap, kv_total, nqb, ot, k_rows, \
-                                                            kv_rows, P, self_keys)
-  if (C / heads == 64) { if (waves == 8) GO(64, 8); else GO(64, 4); }
-  else { if (waves == 8) GO(128, 8); else GO(128, 4); }
+  attention_few_kernel<DH_, NW_><<<grid, NW_ * 64, 0, st>>>(qt, kt, vt, k, C, heads, cap, kv_total, nqb, div_inv(nqb), \
+                                                            div_inv(heads), ot, k_rows, kv_rows, P, self_keys)
+  if (C / heads == 64) { if (waves == 8) GO(64, 8); else if (waves == 4) GO(64, 4); else GO(64, 1); }
+  else { if (waves == 8) GO(128, 8); else if (waves == 4) GO(128, 4); else GO(128, 1); }
 #undef GO
   return hipGetLastError();
 }

@@ -50,6 +50,14 @@ def test_images_with_their_own_counts(hx, C, heads):
 
 
 @pytest.mark.parametrize("C,heads", [(128, 2), (256, 2)])
+def test_one_tile_of_keys_with_counts(hx, C, heads):
+    """At most one tile of keys (64 at dh = 64, 32 at dh = 128): a single wave per workgroup, which writes its output itself."""
+    print(f"few queries, one tile, per-image counts C={C}", flush=True)
+    hb = hx.make_host_block(_wl(4, 12, C, heads, grid=9), 0, k=20)
+    hx.check_block_rows(hb, [20, 0, 1, 7], [12, 5, 0, 3], hx.BF16_TOL)
+
+
+@pytest.mark.parametrize("C,heads", [(128, 2), (256, 2)])
 def test_one_forced_run_is_the_many_query_kernel_uncut(hx, C, heads, monkeypatch):
     """NOVA_ATTN_SPLIT=1 reaches csrc/attention_bf16.hip without key runs, whatever the size: the bits of its default
     workgroup shape forced (too few key tiles here for the launcher to cut any)."""
