@@ -137,6 +137,13 @@ int nova_entropy(nova_ctx* ctx, void* stream, const void* logits, int logits_dty
                  int64_t rows_per_batch, int batch, int V, int64_t row_stride_elems,
                  float* entropy, float* mean_entropy);
 
+/* nova_entropy of n_blocks tensors of one shape, stride and dtype (the logits of a step's blocks) in as few launches as
+ * one tensor takes: logits, entropy and mean_entropy (NULL: no means) are HOST arrays of n_blocks device pointers, read
+ * before the call returns.  The results are those of n_blocks calls, bit for bit.  n_blocks == 0 is a no-op. */
+int nova_entropy_blocks(nova_ctx* ctx, void* stream, int n_blocks, const void* const* logits, int logits_dtype,
+                        int64_t rows_per_batch, int batch, int V, int64_t row_stride_elems,
+                        float* const* entropy, float* const* mean_entropy);
+
 /*
  * Token entropy of a bitwise token head (a token is d independent binary choices, as in the
  * Infinity backbones of Sec. 4; entropy equation of Sec. 3.3 on the product distribution):
@@ -202,6 +209,12 @@ int nova_head_entropy_static(nova_ctx* ctx, void* stream, const void* hidden, co
  */
 int nova_select(nova_ctx* ctx, void* stream, const float* entropy, int B, int N, int k,
                 const int32_t* k_per_row, int32_t* kept_idx, uint8_t* keep_mask);
+
+/* nova_select of n_blocks arrays of one shape in one launch: entropy, kept_idx and keep_mask are HOST arrays of n_blocks
+ * device pointers, k a HOST array of the blocks' keep counts (all read before the call returns); kept_idx[i] is
+ * [B, k[i]].  n_blocks == 0 is a no-op. */
+int nova_select_blocks(nova_ctx* ctx, void* stream, int n_blocks, const float* const* entropy, int B, int N,
+                       const int32_t* k, int32_t* const* kept_idx, uint8_t* const* keep_mask);
 
 /*
  * One transformer block on the kept tokens only (Sec. 3.3, "Residual Cache Reuse",

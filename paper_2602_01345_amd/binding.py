@@ -108,6 +108,10 @@ def load_library() -> C.CDLL:
     lib.nova_workspace_bytes.restype = C.c_size_t
     lib.nova_entropy.argtypes = [vp, vp, vp, i32, i64, i32, i32, i64, vp, vp]
     lib.nova_select.argtypes = [vp, vp, vp, i32, i32, i32, vp, vp, vp]
+    lib.nova_entropy_blocks.argtypes = [vp, vp, i32, vp, i32, i64, i32, i32, i64, vp, vp]
+    lib.nova_entropy_blocks.restype = i32
+    lib.nova_select_blocks.argtypes = [vp, vp, i32, vp, i32, i32, vp, vp, vp]
+    lib.nova_select_blocks.restype = i32
     lib.nova_entropy_bits.argtypes = [vp, vp, vp, i32, i64, i32, i32, vp, vp]
     lib.nova_entropy_bits.restype = i32
     lib.nova_head_entropy_workspace_bytes.argtypes = [i64, i32, i32]
@@ -158,6 +162,10 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
         return None
     assert t.is_cuda and t.is_contiguous(), "device-resident contiguous tensors only"
     return t.data_ptr()
+
+
+def _ptrs(ts: Sequence[torch.Tensor]) -> "C.Array":
+    return (C.c_void_p * len(ts))(*[_ptr(t) for t in ts])
 
 
 # The current stream's handle without a Stream object around it (0.3 against 2.7 us): with small kernels the calls below
@@ -261,6 +269,20 @@ class Nova:
                                    logits.stride(1), _ptr(entropy), _ptr(mean))
         self._check(rc, "nova_entropy")
 
+    # -- nova_entropy_blocks --------------------------------------------------------
+    def entropy_blocks(self, logits: Sequence[torch.Tensor], entropy: Sequence[torch.Tensor],
+                       mean: Optional[Sequence[torch.Tensor]] = None):
+        """entropy() of every tensor of a list; tensors of one shape, stride and dtype share their launches."""
+        a = logits[0]
+        if any(t.shape != a.shape or t.stride(1) != a.stride(1) or t.dtype != a.dtype for t in logits):
+            for i, t in enumerate(logits):
+                self.entropy(t, entropy[i], None if mean is None else mean[i])
+            return
+        B, N, V = a.shape
+        rc = self.lib.nova_entropy_blocks(self.ctx, _stream(), len(logits), _ptrs(logits), _dtype_code(a), N, B, V,
+                                          a.stride(1), _ptrs(entropy), None if mean is None else _ptrs(mean))
+        self._check(rc, "nova_entropy_blocks")
+
     # -- nova_entropy_bits ----------------------------------------------------------
     def entropy_bits(self, bit_logits: torch.Tensor, entropy: torch.Tensor, mean: Optional[torch.Tensor] = None):
         """bit_logits [B, N, d, 2] (f32|bf16) -> entropy [B, N] f32 (and mean [B] f32)."""
@@ -300,6 +322,16 @@ class Nova:
         rc = self.lib.nova_select(self.ctx, _stream(), _ptr(entropy), B, N, k, _ptr(k_per_row),
                                   _ptr(kept_idx), _ptr(keep_mask))
         self._check(rc, "nova_select")
+
+    # -- nova_select_blocks ---------------------------------------------------------
+    def select_blocks(self, entropy: Sequence[torch.Tensor], k: Sequence[int], kept_idx: Sequence[torch.Tensor],
+                      keep_mask: Sequence[torch.Tensor]):
+        """select() of every tensor of a list of [B, N] entropies, each with its own k, in one launch."""
+        B, N = entropy[0].shape
+        assert all(t.shape == (B, N) for t in entropy)
+        rc = self.lib.nova_select_blocks(self.ctx, _stream(), len(entropy), _ptrs(entropy), B, N,
+                                         (C.c_int32 * len(k))(*[int(v) for v in k]), _ptrs(kept_idx), _ptrs(keep_mask))
+        self._check(rc, "nova_select_blocks")
 
     # -- nova_pruned_block ----------------------------------------------------------
     def workspace_bytes(self, shape: BlockShape) -> int:

@@ -205,12 +205,27 @@ int nova_entropy(nova_ctx* ctx, void* stream, const void* logits, int logits_dty
   if (rows_per_batch < 0 || batch < 0 || V < 1 || row_stride_elems < V) return NOVA_ERR_INVALID_ARG;
   if (rows_per_batch == 0 || batch == 0) return NOVA_OK;
   if (!logits || !entropy) return NOVA_ERR_INVALID_ARG;
+  return nova_entropy_blocks(ctx, stream, 1, &logits, logits_dtype, rows_per_batch, batch, V, row_stride_elems, &entropy,
+                             mean_entropy ? &mean_entropy : nullptr);
+}
+
+int nova_entropy_blocks(nova_ctx* ctx, void* stream, int n_blocks, const void* const* logits, int logits_dtype,
+                        int64_t rows_per_batch, int batch, int V, int64_t row_stride_elems, float* const* entropy,
+                        float* const* mean_entropy) {
+  if (!ctx) return NOVA_ERR_INVALID_ARG;
+  if (!valid_dtype(logits_dtype)) return NOVA_ERR_UNSUPPORTED;
+  if (n_blocks < 0 || rows_per_batch < 0 || batch < 0 || V < 1 || row_stride_elems < V) return NOVA_ERR_INVALID_ARG;
+  if (n_blocks == 0 || rows_per_batch == 0 || batch == 0) return NOVA_OK;
+  if (!logits || !entropy) return NOVA_ERR_INVALID_ARG;
   if (rows_per_batch * batch > ((int64_t)1 << 31) - 8) return NOVA_ERR_UNSUPPORTED;
-  if ((reinterpret_cast<uintptr_t>(logits) % esize(logits_dtype)) != 0) return NOVA_ERR_INVALID_ARG;
+  for (int i = 0; i < n_blocks; ++i) {
+    if (!logits[i] || !entropy[i] || (mean_entropy && !mean_entropy[i])) return NOVA_ERR_INVALID_ARG;
+    if ((reinterpret_cast<uintptr_t>(logits[i]) % esize(logits_dtype)) != 0) return NOVA_ERR_INVALID_ARG;
+  }
   if (int rc = set_device(ctx)) return rc;
   StageTimer timer(ctx, static_cast<hipStream_t>(stream), NOVA_STAGE_ENTROPY);
-  hipError_t e = launch_entropy(static_cast<hipStream_t>(stream), ctx->num_cus, logits, logits_dtype, rows_per_batch, batch, V,
-                                row_stride_elems, entropy, mean_entropy);
+  hipError_t e = launch_entropy(static_cast<hipStream_t>(stream), ctx->num_cus, n_blocks, logits, logits_dtype, rows_per_batch,
+                                batch, V, row_stride_elems, entropy, mean_entropy);
   return e == hipSuccess ? NOVA_OK : NOVA_ERR_HIP;
 }
 
@@ -284,7 +299,24 @@ int nova_select(nova_ctx* ctx, void* stream, const float* entropy, int B, int N,
   if (!entropy || !keep_mask || (k > 0 && !kept_idx)) return NOVA_ERR_INVALID_ARG;
   if (int rc = set_device(ctx)) return rc;
   StageTimer timer(ctx, static_cast<hipStream_t>(stream), NOVA_STAGE_SELECT);
-  hipError_t e = launch_select(static_cast<hipStream_t>(stream), entropy, B, N, k, k_per_row, kept_idx, keep_mask);
+  hipError_t e = launch_select(static_cast<hipStream_t>(stream), 1, &entropy, B, N, &k, k_per_row, &kept_idx, &keep_mask);
+  return e == hipSuccess ? NOVA_OK : NOVA_ERR_HIP;
+}
+
+int nova_select_blocks(nova_ctx* ctx, void* stream, int n_blocks, const float* const* entropy, int B, int N, const int32_t* k,
+                       int32_t* const* kept_idx, uint8_t* const* keep_mask) {
+  if (!ctx) return NOVA_ERR_INVALID_ARG;
+  if (n_blocks < 0 || B < 0 || N < 0 || (n_blocks > 0 && !k)) return NOVA_ERR_INVALID_ARG;
+  for (int i = 0; i < n_blocks; ++i)
+    if (k[i] < 0 || k[i] > N) return NOVA_ERR_INVALID_ARG;
+  if (N > 65536) return NOVA_ERR_UNSUPPORTED;
+  if (n_blocks == 0 || B == 0 || N == 0) return NOVA_OK;
+  if (!entropy || !kept_idx || !keep_mask) return NOVA_ERR_INVALID_ARG;
+  for (int i = 0; i < n_blocks; ++i)
+    if (!entropy[i] || !keep_mask[i] || (k[i] > 0 && !kept_idx[i])) return NOVA_ERR_INVALID_ARG;
+  if (int rc = set_device(ctx)) return rc;
+  StageTimer timer(ctx, static_cast<hipStream_t>(stream), NOVA_STAGE_SELECT);
+  hipError_t e = launch_select(static_cast<hipStream_t>(stream), n_blocks, entropy, B, N, k, nullptr, kept_idx, keep_mask);
   return e == hipSuccess ? NOVA_OK : NOVA_ERR_HIP;
 }
 

@@ -22,10 +22,25 @@ namespace {
 
 using namespace entropy_core;
 
+// The tensors of a launch, one set per blockIdx.y: a whole step's blocks go through one launch, since each of them alone
+// is mostly launch, ramp and tail (a step of 16 blocks of 2048 rows of 4096 bf16 logits: 16 launches 105 us, one 67).
+template <int NB>
+struct EntropyBatch {
+  const void* logits[NB];
+  float* H[NB];
+};
+template <int NB>
+struct MeanBatch {
+  const float* H[NB];
+  float* mean[NB];
+};
+
 // Any shape: one row per wave, lanes past the row's end masked.
-template <typename T, int CH>
+template <typename T, int CH, int NB>
 __global__ __launch_bounds__(kWavesPerBlock* NOVA_WAVE) void entropy_generic_kernel(
-    const T* __restrict__ logits, int64_t rows, int V, int64_t stride, float* __restrict__ H, int vec_ok) {
+    EntropyBatch<NB> batch, int64_t rows, int V, int64_t stride, int vec_ok) {
+  const T* __restrict__ logits = static_cast<const T*>(batch.logits[blockIdx.y]);
+  float* __restrict__ H = batch.H[blockIdx.y];
   using VT = Vec16<T>;
   constexpr int VN = VT::N;
   const int lane = threadIdx.x & (NOVA_WAVE - 1);
@@ -92,9 +107,11 @@ __global__ __launch_bounds__(kWavesPerBlock* NOVA_WAVE) void entropy_generic_ker
 
 
 // Regular rows: each wave walks rows  w, w + nwaves, ...  (entropy_core.h: walk_rows).
-template <typename T, int CH>
-__global__ __launch_bounds__(kWavesPerBlock* NOVA_WAVE) void entropy_kernel(
-    const T* __restrict__ logits, int64_t rows, int nchunk, int64_t stride, float* __restrict__ H) {
+template <typename T, int CH, int NB>
+__global__ __launch_bounds__(kWavesPerBlock* NOVA_WAVE) void entropy_kernel(EntropyBatch<NB> batch, int64_t rows, int nchunk,
+                                                                             int64_t stride) {
+  const T* __restrict__ logits = static_cast<const T*>(batch.logits[blockIdx.y]);
+  float* __restrict__ H = batch.H[blockIdx.y];
   const int lane = threadIdx.x & (NOVA_WAVE - 1);
   const int64_t w0 = (int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / NOVA_WAVE;
   const int64_t nwaves = (int64_t)gridDim.x * kWavesPerBlock;
@@ -109,10 +126,10 @@ __global__ __launch_bounds__(kWavesPerBlock* NOVA_WAVE) void entropy_kernel(
 // entropy gives NaN.  One latency for up to 4096 tokens: 256 threads that add contiguous shares one load after the
 // other take 4.0 us for 4096, this 3.1.
 constexpr int kMeanThreads = 1024;
-__global__ __launch_bounds__(kMeanThreads) void row_mean_kernel(const float* __restrict__ H, int64_t rows_per_batch,
-                                                                float* __restrict__ mean) {
+template <int NB>
+__global__ __launch_bounds__(kMeanThreads) void row_mean_kernel(MeanBatch<NB> batch, int64_t rows_per_batch) {
   __shared__ float part[kMeanThreads / NOVA_WAVE];
-  const float* h = H + (int64_t)blockIdx.x * rows_per_batch;
+  const float* __restrict__ h = batch.H[blockIdx.y] + (int64_t)blockIdx.x * rows_per_batch;
   float s = 0.0f;
   for (int64_t i = threadIdx.x; i < rows_per_batch; i += 4 * kMeanThreads) {
     float v[4];
@@ -127,49 +144,65 @@ __global__ __launch_bounds__(kMeanThreads) void row_mean_kernel(const float* __r
   float t = 0.0f;
 #pragma unroll
   for (int w = 0; w < kMeanThreads / NOVA_WAVE; ++w) t += part[w];
-  mean[blockIdx.x] = t / (float)rows_per_batch;
+  batch.mean[blockIdx.y][blockIdx.x] = t / (float)rows_per_batch;
 }
 
-template <typename T, int CH>
-void launch_regular(hipStream_t st, int num_cus, const T* logits, int64_t rows, int nchunk, int64_t stride, float* H) {
-  // at most kWavesPerSimd resident waves per SIMD, each walking several rows
-  const int64_t max_blocks = (int64_t)num_cus * 4 * kWavesPerSimd / kWavesPerBlock;
-  const unsigned grid = (unsigned)std::min<int64_t>((rows + kWavesPerBlock - 1) / kWavesPerBlock, max_blocks);
-  entropy_kernel<T, CH><<<grid, kWavesPerBlock * NOVA_WAVE, 0, st>>>(logits, rows, nchunk, stride, H);
-}
-
-template <typename T>
-hipError_t launch_t(hipStream_t st, int num_cus, const T* logits, int64_t rows_per_batch, int batch, int V,
-                    int64_t stride, float* H, float* mean) {
+// `n` tensors of the same shape and alignment, at most NB
+template <typename T, int NB>
+void launch_t(hipStream_t st, int num_cus, int n, const void* const* logits, int64_t rows, int V, int64_t stride, float* const* H) {
   constexpr int VN = Vec16<T>::N;
-  const int64_t rows = rows_per_batch * batch;
-  const int vec_ok = ((reinterpret_cast<uintptr_t>(logits) & 15) == 0) &&
-                     ((stride * (int64_t)sizeof(T)) % 16 == 0);
+  EntropyBatch<NB> batch = {};
+  for (int i = 0; i < n; ++i) { batch.logits[i] = logits[i]; batch.H[i] = H[i]; }
+  const int vec_ok = ((reinterpret_cast<uintptr_t>(logits[0]) & 15) == 0) && ((stride * (int64_t)sizeof(T)) % 16 == 0);
   const int per_sweep = NOVA_WAVE * VN;            // elements one 16-byte vector per lane covers
+  const int64_t per_row = (rows + kWavesPerBlock - 1) / kWavesPerBlock;
   if (vec_ok && V % per_sweep == 0) {
-    const int sweeps = V / per_sweep;
-    if (sweeps % 4 == 0) launch_regular<T, 4>(st, num_cus, logits, rows, sweeps / 4, stride, H);
-    else if (sweeps % 2 == 0) launch_regular<T, 2>(st, num_cus, logits, rows, sweeps / 2, stride, H);
-    else launch_regular<T, 1>(st, num_cus, logits, rows, sweeps, stride, H);
+    // at most kWavesPerSimd resident waves per SIMD over all tensors, each walking several rows
+    const int64_t max_blocks = std::max<int64_t>((int64_t)num_cus * 4 * kWavesPerSimd / kWavesPerBlock / n, 1);
+    const dim3 grid((unsigned)std::min<int64_t>(per_row, max_blocks), n);
+    const int sweeps = V / per_sweep, block = kWavesPerBlock * NOVA_WAVE;
+    if (sweeps % 4 == 0) entropy_kernel<T, 4, NB><<<grid, block, 0, st>>>(batch, rows, sweeps / 4, stride);
+    else if (sweeps % 2 == 0) entropy_kernel<T, 2, NB><<<grid, block, 0, st>>>(batch, rows, sweeps / 2, stride);
+    else entropy_kernel<T, 1, NB><<<grid, block, 0, st>>>(batch, rows, sweeps, stride);
   } else {
-    const unsigned grid = (unsigned)((rows + kWavesPerBlock - 1) / kWavesPerBlock);
-    entropy_generic_kernel<T, 8><<<grid, kWavesPerBlock * NOVA_WAVE, 0, st>>>(logits, rows, V, stride, H, vec_ok);
+    const dim3 grid((unsigned)per_row, n);
+    entropy_generic_kernel<T, 8, NB><<<grid, kWavesPerBlock * NOVA_WAVE, 0, st>>>(batch, rows, V, stride, vec_ok);
   }
-  if (mean) return launch_row_mean(st, H, rows_per_batch, batch, mean);
-  return hipGetLastError();
+}
+
+template <int NB>
+void launch_mean(hipStream_t st, int n, const float* const* H, int64_t rows_per_batch, int batch_rows, float* const* mean) {
+  MeanBatch<NB> batch = {};
+  for (int i = 0; i < n; ++i) { batch.H[i] = H[i]; batch.mean[i] = mean[i]; }
+  row_mean_kernel<NB><<<dim3(batch_rows, n), kMeanThreads, 0, st>>>(batch, rows_per_batch);
 }
 
 }  // namespace
 
 hipError_t launch_row_mean(hipStream_t st, const float* H, int64_t rows_per_batch, int batch, float* mean) {
-  row_mean_kernel<<<batch, kMeanThreads, 0, st>>>(H, rows_per_batch, mean);
+  launch_mean<1>(st, 1, &H, rows_per_batch, batch, &mean);
   return hipGetLastError();
 }
 
-hipError_t launch_entropy(hipStream_t st, int num_cus, const void* logits, int dtype, int64_t rows_per_batch,
-                          int batch, int V, int64_t stride, float* H, float* mean) {
-  if (dtype == NOVA_BF16)
-    return launch_t<bf16_t>(st, num_cus, static_cast<const bf16_t*>(logits), rows_per_batch, batch, V, stride, H,
-                            mean);
-  return launch_t<float>(st, num_cus, static_cast<const float*>(logits), rows_per_batch, batch, V, stride, H, mean);
+hipError_t launch_entropy(hipStream_t st, int num_cus, int n, const void* const* logits, int dtype, int64_t rows_per_batch,
+                          int batch, int V, int64_t stride, float* const* H, float* const* mean) {
+  const int64_t rows = rows_per_batch * batch;
+  for (int i = 0; i < n;) {
+    // a run of tensors of one alignment: the kernel is chosen as for each of them alone
+    int run = 1;
+    const bool aligned = (reinterpret_cast<uintptr_t>(logits[i]) & 15) == 0;
+    while (run < kMaxBatch && i + run < n && ((reinterpret_cast<uintptr_t>(logits[i + run]) & 15) == 0) == aligned) ++run;
+    auto go = [&](auto one, auto many) { run == 1 ? one() : many(); };
+    if (dtype == NOVA_BF16)
+      go([&] { launch_t<bf16_t, 1>(st, num_cus, 1, logits + i, rows, V, stride, H + i); },
+         [&] { launch_t<bf16_t, kMaxBatch>(st, num_cus, run, logits + i, rows, V, stride, H + i); });
+    else
+      go([&] { launch_t<float, 1>(st, num_cus, 1, logits + i, rows, V, stride, H + i); },
+         [&] { launch_t<float, kMaxBatch>(st, num_cus, run, logits + i, rows, V, stride, H + i); });
+    if (mean)
+      go([&] { launch_mean<1>(st, 1, H + i, rows_per_batch, batch, mean + i); },
+         [&] { launch_mean<kMaxBatch>(st, run, H + i, rows_per_batch, batch, mean + i); });
+    i += run;
+  }
+  return hipGetLastError();
 }

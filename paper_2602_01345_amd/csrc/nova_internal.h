@@ -50,9 +50,11 @@ struct StageTimer {
   }
 };
 
-// entropy.hip
-hipError_t launch_entropy(hipStream_t st, int num_cus, const void* logits, int dtype, int64_t rows_per_batch,
-                          int batch, int V, int64_t stride, float* H, float* mean);
+// Tensors per launch of the calls that take several blocks' tensors at once (a table in the kernel's arguments).
+constexpr int kMaxBatch = 32;
+// entropy.hip: n tensors of one shape; mean may be nullptr
+hipError_t launch_entropy(hipStream_t st, int num_cus, int n, const void* const* logits, int dtype, int64_t rows_per_batch,
+                          int batch, int V, int64_t stride, float* const* H, float* const* mean);
 // entropy.hip: mean[b] = mean of H[b, 0..rows_per_batch), summed in a fixed order (bit-reproducible)
 hipError_t launch_row_mean(hipStream_t st, const float* H, int64_t rows_per_batch, int batch, float* mean);
 // select.hip
@@ -64,8 +66,9 @@ hipError_t launch_probe_mfma(hipStream_t st, int num_cus, int iters, float* sink
 hipError_t launch_probe_mfma_data(hipStream_t st, int num_cus, const void* src, int iters, float* sink);
 hipError_t launch_entropy_bits(hipStream_t st, const void* logits, int dtype, int64_t rows_per_batch, int batch,
                                int d, float* H, float* mean);
-hipError_t launch_select(hipStream_t st, const float* H, int B, int N, int k, const int32_t* k_per_row,
-                         int32_t* idx, uint8_t* mask);
+// select.hip: n sets of rows; k_per_row (n = 1 only) may be nullptr
+hipError_t launch_select(hipStream_t st, int n, const float* const* H, int B, int N, const int* k, const int32_t* k_per_row,
+                         int32_t* const* idx, uint8_t* const* mask);
 // merge.hip
 hipError_t launch_merge(hipStream_t st, int dtype, int interp, int B, int C, int h, int w, int hp, int wp, int k,
                         const void* x, const void* y, const int32_t* idx, const uint8_t* mask,

@@ -60,6 +60,7 @@ class ScalePlan:
     cache_new: List[Optional[torch.Tensor]]
     cache_prev: List[Optional[torch.Tensor]]
     graph: Optional[torch.cuda.CUDAGraph] = None
+    entropies: Optional[List[torch.Tensor]] = None     # per block [B, N] (a pruned scale); entropy is the last block's
 
 
 class ImageRunner:
@@ -132,14 +133,17 @@ class ImageRunner:
             else:
                 idx = [torch.empty((B, max(k, 1)), dtype=torch.int32, device=dev) for k in ks]
                 mask = [torch.empty((B, N), dtype=torch.uint8, device=dev) for _ in ks]
+            H = None if dense else list(torch.empty((self.L, B, N), dtype=torch.float32, device=dev))
+            out = [torch.empty((B, N, C), dtype=self.dtype, device=dev) for _ in ks]
             plan = ScalePlan(
                 t=t, grid=g, prev_grid=prev_grid if prev_cache[0] is not None else g, k=ks, kv_len=list(kv),
                 x=torch.empty((B, N, C), dtype=self.dtype, device=dev),
                 logits=None if dense else logits[t],
-                entropy=None if dense else torch.empty((B, N), dtype=torch.float32, device=dev),
-                idx=idx, mask=mask,
-                y=[torch.empty((B, max(k, 1), C), dtype=self.dtype, device=dev) for k in ks],
-                out=[torch.empty((B, N, C), dtype=self.dtype, device=dev) for _ in ks],
+                entropy=None if dense else H[-1], entropies=H, idx=idx, mask=mask,
+                # every token kept and no residual cache: the block writes the scale's output itself
+                y=out if dense and not keep else
+                  [torch.empty((B, max(k, 1), C), dtype=self.dtype, device=dev) for k in ks],
+                out=out,
                 cache_new=[torch.empty((B, N, C), dtype=self.dtype, device=dev) if keep else None for _ in ks],
                 cache_prev=list(prev_cache))
             for j, k in enumerate(ks):
@@ -158,16 +162,17 @@ class ImageRunner:
         n, g = self.nova, plan.grid
         N = g * g
         x = plan.x
+        if plan.logits is not None:
+            n.entropy_blocks([plan.logits[j] for j in range(self.L)], plan.entropies)
+            n.select_blocks(plan.entropies, plan.k, plan.idx, plan.mask)
         for j in range(self.L):
             k = plan.k[j]
-            if plan.logits is not None:
-                n.entropy(plan.logits[j], plan.entropy)
-                n.select(plan.entropy, k, plan.idx[j], plan.mask[j])
             shape = BlockShape(self.code, self.B, N, self.C, self.heads, plan.kv_len[j], self.cap, k, self.ffn_mult)
             n.pruned_block_variant(shape, self.weights[j], self.variants[j], x, plan.idx[j], self.k_cache[j],
                                    self.v_cache[j], plan.y[j], self._workspace)
-            n.merge_cache_interp(self.interp, g, g, plan.prev_grid, plan.prev_grid, k, x, plan.y[j], plan.idx[j],
-                                 plan.mask[j], plan.cache_prev[j], plan.out[j], plan.cache_new[j])
+            if plan.y[j] is not plan.out[j]:
+                n.merge_cache_interp(self.interp, g, g, plan.prev_grid, plan.prev_grid, k, x, plan.y[j], plan.idx[j],
+                                     plan.mask[j], plan.cache_prev[j], plan.out[j], plan.cache_new[j])
             x = plan.out[j]
         return x
 
@@ -204,49 +209,57 @@ class ImageRunner:
         N = g * g
         dense = k_table is None and ratio_t is None
         dev = self.device
-        H = torch.empty((B, N), dtype=torch.float32, device=dev)
-        mean = torch.empty(B, dtype=torch.float32, device=dev)
-        mask = torch.empty((B, N), dtype=torch.uint8, device=dev)
-        idx = torch.empty((B, N), dtype=torch.int32, device=dev)
+        # the blocks' logits are inputs of the scale: all their entropies and means at once, and the selections with them
+        # where the counts are known
+        means = list(torch.empty((self.L, B), dtype=torch.float32, device=dev))
+        mean = means[-1]
+        masks = list(torch.empty((1 if k_table is None else self.L, B, N), dtype=torch.uint8, device=dev))
+        idx_bufs = list(torch.empty((1 if k_table is None else self.L, B, N), dtype=torch.int32, device=dev))
         if dense:
-            idx.copy_(torch.arange(N, dtype=torch.int32, device=dev).expand(B, N))
-            mask.fill_(1)
+            Hs = list(torch.empty((1, B, N), dtype=torch.float32, device=dev))
+            idx_bufs[0].copy_(torch.arange(N, dtype=torch.int32, device=dev).expand(B, N))
+            masks[0].fill_(1)
+        else:
+            Hs = list(torch.empty((self.L, B, N), dtype=torch.float32, device=dev))
+            n.entropy_blocks([logits[j] for j in range(self.L)], Hs, means)
+            if ratio_t is None:
+                n.select_blocks(Hs, [int(k_table[j]) for j in range(self.L)], idx_bufs, masks)
         ks: List[int] = []
         outs: List[torch.Tensor] = []
         caches: List[torch.Tensor] = []
         ents: List[torch.Tensor] = []
         idxs: List[torch.Tensor] = []
-        have_mean = False
+        have_mean = not dense
         for j in range(self.L):
             k_rows = None                             # per-image counts of this block (device), controller mode only
+            H, idx, mask = Hs[0 if dense else j], idx_bufs[0 if k_table is None else j], masks[0 if k_table is None else j]
             if dense:
                 k = N
                 if logits is not None and j == self.L - 1:
                     n.entropy(logits[j], H, mean)
                     have_mean = True
-            else:
-                n.entropy(logits[j], H, mean)
-                have_mean = True
-                if ratio_t is not None:
-                    # per-image counts, on the device from here to the merge: row pitch N
-                    n.layer_ratio(mean, self._state, ratio_t, j + 1, N, self._ratio_tj, self._k_row)
-                    k, k_rows = N, self._k_row
-                else:
-                    k, k_rows = int(k_table[j]), None
+            elif ratio_t is not None:
+                # per-image counts, on the device from here to the merge: row pitch N
+                n.layer_ratio(means[j], self._state, ratio_t, j + 1, N, self._ratio_tj, self._k_row)
+                k, k_rows = N, self._k_row
                 n.select(H, k, idx, mask, k_per_row=k_rows)
+            else:
+                k = int(k_table[j])
             shape = self._shape(N, j, k)
             self._ensure_workspace(shape)
-            y = torch.empty((B, max(k, 1), C), dtype=self.dtype, device=dev)
             out = torch.empty((B, N, C), dtype=self.dtype, device=dev)
+            # every token kept and no residual cache: the block writes the scale's output itself
+            whole = dense and not keep_cache
+            y = out if whole else torch.empty((B, max(k, 1), C), dtype=self.dtype, device=dev)
             cache_new = torch.empty((B, N, C), dtype=self.dtype, device=dev) if keep_cache else None
             # the block reads and advances the per-image cache lengths (equal to kv_len as long as every image
             # has kept the same number of tokens)
             n.pruned_block_rows(shape, self.weights[j], self.variants[j], k_rows, self.kv_rows[j], self.kv_rows[j], x,
                                 idx, self.k_cache[j], self.v_cache[j], y, self._workspace)
             pg = self.cache_grid if self.cache[j] is not None else g
-            if k_rows is None:
+            if k_rows is None and not whole:
                 n.merge_cache_interp(self.interp, g, g, pg, pg, k, x, y, idx, mask, self.cache[j], out, cache_new)
-            else:
+            elif not whole:
                 n.merge_cache_rows(self.interp, g, g, pg, pg, k, k_rows, x, y, idx, mask, self.cache[j], out, cache_new)
             self.kv_len[j] += k
             if inspect:

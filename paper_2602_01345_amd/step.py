@@ -2,7 +2,9 @@
 
 For every block j:  nova_entropy -> nova_select -> nova_pruned_block -> nova_merge_cache,
 all enqueued on the current stream with no host synchronisation in between (the keep
-count k_j is an input).  This module only owns device buffers and call order.
+count k_j is an input).  The entropies and selections read the blocks' logits only, inputs of the step like the
+keep counts, so a step takes them for all blocks first, in one launch each (nova_entropy_blocks, nova_select_blocks).
+This module only owns device buffers and call order.
 """
 from __future__ import annotations
 
@@ -97,14 +99,22 @@ class StepRunner:
         return st.out
 
     def run_step(self, x: torch.Tensor, overlap_selection: bool = False) -> torch.Tensor:
-        """All blocks of the step.  A block's entropy and selection read only that block's logits (an input of the
+        """All blocks of the step: entropies and selections of all of them, then block after block.  A block's entropy and selection read only that block's logits (an input of the
         step), so with overlap_selection they are enqueued one block ahead on a second stream (default priority)
         and run next to the previous block's gather and QKV projection.  The results are the same launches on the
         same data either way.  Measured gain on the largest workload: 0.2 % (the entropy kernel fills the CUs, so
         the two streams mostly take turns); off by default."""
-        if not overlap_selection or len(self.blocks) < 2:
+        if len(self.blocks) < 2:
             for st in self.blocks:
                 x = self.run_block(st, x)
+            return x
+        if not overlap_selection:
+            bs = self.blocks
+            self.nova.entropy_blocks([st.logits for st in bs], [st.entropy for st in bs])
+            self.nova.select_blocks([st.entropy for st in bs], [st.k for st in bs], [st.kept_idx for st in bs],
+                                    [st.keep_mask for st in bs])
+            for st in bs:
+                x = self._block_and_merge(st, x)
             return x
         main = torch.cuda.current_stream()
         if self._side is None:
