@@ -22,6 +22,9 @@ LIB = os.path.join(HERE, "libnova.so")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC", "-Wall", "-Wno-unused-function",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # the first 14 words of a kernel's arguments arrive in registers with the wave: no round trip to memory (0.2 us behind a
+    # cold scalar cache) before the first address; the block of 64 rows of 1024 in a graph 37.4 -> 36.4 us
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",
 ]
 
 
