@@ -63,8 +63,10 @@ inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K,
 // Without a forced choice the launcher prices 1, 2, 5 and 6 with a model fitted to measurements on MI355X (300 ... 8192
 // rows, widths C of 1024 ... 2304, outputs of C, 3C and 4C features, K = C and 4C): a launch takes rounds of one tile
 // per CU; a round costs a fixed time (first loads, epilogue) and a time per element of K that grows with the share of
-// the CUs that are busy (they share L2, memory and power).  The fit is within 5 % (rms) of the measurements, and what
-// it chooses takes 0.03 % longer than the best of the four on average, 4 % at worst (launches without K slices).
+// the CUs that are busy (they share L2, memory and power).  Fitted to 330 shapes (500 ... 6144 rows) for the choice, not
+// for the times (within 8 %, rms): what it chooses takes 0.16 % longer than the best of the four on average, 6.6 % at
+// worst (launches without K slices); the constants before, fitted when the smaller tiles' loads took 64-bit addresses,
+// 0.29 % and 18 %.
 constexpr int kNumCfgs = 7;
 constexpr int kRowsCfg = 7;
 
@@ -74,13 +76,15 @@ struct Candidate {
   double k0, k1, k3;            // us per element of K in a round that fills a share f of the CUs: k0 + k1 f + k3 f^3
 };
 
-static const Candidate kCands[] = {{1, 256, 256, 4.3, 5.0, 2.0, 0.01580, -0.00114, 0.01000},
-                                   {2, 256, 128, 3.4, 2.8, 0.6, 0.01072, 0.00005, 0.00404},
-                                   {6, 192, 128, 2.4, 3.2, 0.6, 0.00784, 0.00200, 0.00151},
-                                   {5, 128, 128, 2.7, 1.9, 0.0, 0.00603, 0.00112, 0.00152}};
+static const Candidate kCands[] = {{1, 256, 256, 6.3, 3.1, 3.5, 0.01641, 0.00352, 0.00571},
+                                   {2, 256, 128, 1.8, 2.0, 2.3, 0.00883, 0.00519, 0.0},
+                                   {6, 192, 128, 2.9, 0.1, 1.7, 0.00760, 0.00444, 0.0},
+                                   {5, 128, 128, 2.5, 0.1, 1.2, 0.00604, 0.00332, 0.0}};
 
-// Configuration 1 addresses its tiles with 32-bit offsets: 255 rows of 2 K bytes and the offset along K stay below 2^31.
-inline bool tile_fits(int cfg, int K) { return cfg != 1 || K <= 1 << 21; }
+// Up to this K the lanes' 32-bit offsets into a tile do: 255 rows of 2 K bytes and the offset along K stay below 2^31.
+// Beyond it configuration 2 takes 64-bit addresses; the staggered ones (3, 4) always do.
+constexpr int kNearK = 1 << 21;
+inline bool tile_fits(int cfg, int K) { return (cfg != 1 && cfg != 5 && cfg != 6) || K <= kNearK; }
 
 // K slices of a launch of `tiles` tiles (the FFN down projection once few tokens are kept: a long K and a narrow
 // output fill less than half of the CUs): 2 or 4 workgroups per tile, fp32 partial sums and a second pass.

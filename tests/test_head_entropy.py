@@ -146,3 +146,21 @@ def test_entropy_bits_edge_values():
                                     H2.data_ptr(), None)
     torch.cuda.synchronize()
     assert np.allclose(H2.cpu().numpy(), O.bitwise_entropy(Hn.f64(view)), rtol=1e-5)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("C", [1 << 21, (1 << 21) + 64])   # the widest tokens with 32-bit offsets into a tile, and beyond
+def test_head_entropy_of_very_wide_tokens(C):
+    # 600 of the features are not zero, the first and the last among them; the others add exact zeros
+    B, N, V, live = 1, 300, 100, 600
+    small, w_small, b = _case(B, N, live, V, seed=11)
+    cols = torch.from_numpy(np.random.default_rng(1).choice(C, size=live, replace=False))
+    cols[0], cols[1] = 0, C - 1
+    assert len(set(cols.tolist())) == live
+    print(f"head entropy C={C}", flush=True)
+    hidden = torch.zeros(B, N, C, dtype=torch.bfloat16)
+    hidden[:, :, cols] = small
+    w = torch.zeros(V, C, dtype=torch.bfloat16)
+    w[:, cols] = w_small
+    got, _ = _run(hidden, w, b)
+    assert _ok(got, O.head_entropy(Hn.f64(small), Hn.f64(w_small), Hn.f64(b)))
