@@ -60,10 +60,10 @@ inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K,
 //   5: 128x128x64, 8 waves of 64x32, 3 stages, one workgroup per CU (two waves per SIMD hide the LDS waits that
 //      four waves of 64x64 expose: 3-10 % faster at every shape measured)
 //   7: the few-rows kernels of gemm_rows_bf16.hip (chosen by gemm_rows_plan, not by force)
-// Without a forced choice the launcher prices 1, 2, 5 and 6 with a model fitted to measurements on MI355X (300 ... 8192
+// Without a forced choice the launcher prices 1, 2, 5 and 6 with a model fitted to measurements on MI355X (300 ... 6144
 // rows, widths C of 1024 ... 2304, outputs of C, 3C and 4C features, K = C and 4C): a launch takes rounds of one tile
 // per CU; a round costs a fixed time (first loads, epilogue) and a time per element of K that grows with the share of
-// the CUs that are busy (they share L2, memory and power).  Fitted to 330 shapes (500 ... 6144 rows) for the choice, not
+// the CUs that are busy (they share L2, memory and power).  Fitted to some 330 shapes for the choice, not
 // for the times (within 8 %, rms): what it chooses takes 0.16 % longer than the best of the four on average, 6.6 % at
 // worst (launches without K slices); the constants before, fitted when the smaller tiles' loads took 64-bit addresses,
 // 0.29 % and 18 %.
