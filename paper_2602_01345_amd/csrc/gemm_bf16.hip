@@ -670,7 +670,7 @@ hipError_t launch_cfg(hipStream_t st, const bf16_t* A, const bf16_t* W, int m_ba
   if (PERSIST && slots > 0 && slots % 8 == 0 && grid > slots && !ep.k_rows) grid = slots;
   if constexpr (MODE == EPI_ATTN_OUT || MODE == EPI_RESIDUAL) {
     if (ep.gate) {
-      gemm_bf16_kernel<BM, BN, WM, WN, BK, NST, STAGGER, MODE, true><<<grid, WM * WN * 64, 0, st>>>(A, W, M, Nout, K, m_base, map, ep);
+      gemm_bf16_kernel<BM, BN, WM, WN, BK, NST, STAGGER, MODE, true, FAR><<<grid, WM * WN * 64, 0, st>>>(A, W, M, Nout, K, m_base, map, ep);
       return hipGetLastError();
     }
   }
@@ -726,7 +726,8 @@ hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W
       const int ks = k_slices(cus, MODE, tiles, M - m_base, Nout, K, ep.part_floats, ksplit);
       if (ks > 1) {
         hipError_t e;
-        if (cfg == 1) e = launch_cfg<256, 256, 2, 4, 64, 2, false, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
+        if (far_tile(K)) e = launch_cfg<256, 128, 4, 2, 64, 3, false, EPI_PARTIAL, true>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
+        else if (cfg == 1) e = launch_cfg<256, 256, 2, 4, 64, 2, false, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
         else if (cfg == 2) e = launch_cfg<256, 128, 4, 2, 64, 3, false, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
         else if (cfg == 6) e = launch_cfg<192, 128, 2, 4, 64, 3, false, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
         else e = launch_cfg<128, 128, 2, 4, 64, 3, false, EPI_PARTIAL>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
@@ -737,9 +738,14 @@ hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W
       }
     }
   }
-  if (K > kNearK && cfg != 3 && cfg != 4) {
-    // a prediction head of very wide tokens; projections have weights of at least K / 4 rows, which no memory holds
-    if constexpr (MODE == EPI_ENTROPY)
+  if constexpr (MODE == EPI_ENTROPY) {
+    if (cfg == 3) return launch_cfg<64, 32, 2, 1, 64, 6, true, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
+    if (cfg == 4) return launch_cfg<128, 32, 4, 1, 64, 4, true, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
+  }
+  if (far_tile(K)) {
+    // the FFN down projection of a very wide FFN and a prediction head of very wide tokens; K of the other projections is
+    // the width itself, and C x C weights of more than 8 TB are in no memory
+    if constexpr (MODE == EPI_RESIDUAL || MODE == EPI_ENTROPY)
       return launch_cfg<256, 128, 4, 2, 64, 3, false, MODE, true>(st, A, W, m_base, M, Nout, K, ep, slots);
     else
       return hipErrorInvalidValue;
@@ -748,14 +754,6 @@ hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W
     case 1: return launch_cfg<256, 256, 2, 4, 64, 2, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
     case 5: return launch_cfg<128, 128, 2, 4, 64, 3, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
     case 6: return launch_cfg<192, 128, 2, 4, 64, 3, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
-    case 3:
-      if constexpr (MODE == EPI_ENTROPY)
-        return launch_cfg<64, 32, 2, 1, 64, 6, true, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
-      [[fallthrough]];
-    case 4:
-      if constexpr (MODE == EPI_ENTROPY)
-        return launch_cfg<128, 32, 4, 1, 64, 4, true, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
-      [[fallthrough]];
     default: return launch_cfg<256, 128, 4, 2, 64, 3, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
   }
 }

@@ -82,9 +82,11 @@ static const Candidate kCands[] = {{1, 256, 256, 6.3, 3.1, 3.5, 0.01641, 0.00352
                                    {5, 128, 128, 2.5, 0.1, 1.2, 0.00604, 0.00332, 0.0}};
 
 // Up to this K the lanes' 32-bit offsets into a tile do: 255 rows of 2 K bytes and the offset along K stay below 2^31.
-// Beyond it configuration 2 takes 64-bit addresses; the staggered ones (3, 4) always do.
+// Beyond it configuration 2 takes 64-bit addresses, K slices among them, and stands in for 1, 5 and 6; the staggered ones
+// (3, 4) of a prediction head always do.  The FFN down projection gets there with few features and a wide FFN.
 constexpr int kNearK = 1 << 21;
 inline bool tile_fits(int cfg, int K) { return (cfg != 1 && cfg != 5 && cfg != 6) || K <= kNearK; }
+inline bool far_tile(int K) { return K > kNearK; }
 
 // K slices of a launch of `tiles` tiles (the FFN down projection once few tokens are kept: a long K and a narrow
 // output fill less than half of the CUs): 2 or 4 workgroups per tile, fp32 partial sums and a second pass.

@@ -1,6 +1,8 @@
 // Prints what csrc/gemm_plan.h plans on 256 compute units (tests/test_gemm_plan.py): one line per request of
 // mode M Nout K part_floats gemm_cfg gemm_parts gemm_ksplit on standard input, for every part of the plan
-// rows:cfg:tiles:slices, the few-rows kernels as rows:7:workgroups:slices.
+// rows:cfg:tiles:slices:reach, the few-rows kernels as rows:7:workgroups:slices:reach.  Reach: the byte offsets into a tile
+// end below it (its rows of 2 K bytes), 0 where the kernel takes 64-bit addresses instead.
+#include <algorithm>
 #include <cstdio>
 
 #include "gemm_plan.h"
@@ -20,14 +22,16 @@ int main() {
       const int rows = p.m_end[i] - p.m_base[i];
       if (p.cfg[i] == kRowsCfg) {
         const RowsPlan r = gemm_rows_plan(256, mode, rows, Nout, K, part);
-        printf("%d:7:%d:%d ", rows, (rows + 8 * r.rg - 1) / (8 * r.rg) * (Nout / (8 * r.ng)), r.slices);
+        printf("%d:7:%d:%d:%lld ", rows, (rows + 8 * r.rg - 1) / (8 * r.rg) * (Nout / (8 * r.ng)), r.slices,
+               8LL * std::max(r.rg, r.ng) * 2 * K);
         continue;
       }
       const Candidate* t = &kCands[1];
       for (const Candidate& q : kCands)
         if (q.cfg == p.cfg[i]) t = &q;
       const int tiles = (rows + t->bm - 1) / t->bm * ((Nout + t->bn - 1) / t->bn);
-      printf("%d:%d:%d:%d ", rows, p.cfg[i], tiles, k_slices(256, mode, tiles, rows, Nout, K, part, ksplit));
+      printf("%d:%d:%d:%d:%lld ", rows, p.cfg[i], tiles, k_slices(256, mode, tiles, rows, Nout, K, part, ksplit),
+             far_tile(K) ? 0 : 2LL * std::max(t->bm, t->bn) * K);
     }
     printf("\n");
   }

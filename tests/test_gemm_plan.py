@@ -17,11 +17,12 @@ def plan(tmp_path_factory):
     subprocess.run([hipcc, "--offload-arch=gfx950", "--offload-host-only", "-std=c++20", "-x", "hip", "-I" + CSRC,
                     os.path.join(HERE, "gemm_plan_probe.cpp"), "-o", exe], check=True, capture_output=True)
 
-    def ask(mode, M, Nout, K, part_floats=10 ** 9, cfg=-1, parts=-1, ksplit=-1):
-        """[(rows, configuration, tiles or workgroups, K slices)] of the launches"""
+    def ask(mode, M, Nout, K, part_floats=10 ** 9, cfg=-1, parts=-1, ksplit=-1, reach=False):
+        """[(rows, configuration, tiles or workgroups, K slices)] of the launches, with reach=True the end of each
+        launch's 32-bit offsets behind them (0: 64-bit addresses)"""
         r = subprocess.run([exe], input=f"{mode} {M} {Nout} {K} {part_floats} {cfg} {parts} {ksplit}\n", text=True,
                            check=True, capture_output=True)
-        return [tuple(int(v) for v in p.split(":")) for p in r.stdout.split()]
+        return [tuple(int(v) for v in p.split(":"))[:5 if reach else 4] for p in r.stdout.split()]
     return ask
 
 
@@ -34,6 +35,23 @@ def test_the_tile_with_32_bit_offsets_stops_where_they_end(plan, M, Nout, K):
         parts = plan(RESIDUAL, M, Nout, K, cfg=cfg)
         assert all(c != 1 for _, c, _, _ in parts), parts
         assert sum(p[0] for p in parts) == M
+
+
+@pytest.mark.parametrize("M,Nout,K", [(m, 64, k) for m in (1, 64, 200, 300, 600, 5000) for k in
+                                      (1 << 21, (1 << 21) + 256, (1 << 22) + 4096, 1 << 23, (1 << 23) + 2048)] +
+                         [(600, 2048, 2049 * 2048), (1100, 2048, 2049 * 2048), (2100, 2048, 1025 * 2048)])
+def test_no_launch_leaves_its_32_bit_offsets(plan, M, Nout, K):
+    """The FFN down projection of few features and a very wide FFN, cut into K slices or not: every launch's offsets stay
+    below 2^31 - 1 bytes, the length its buffer loads are bounded by, or it takes 64-bit addresses."""
+    cut = 0
+    for cfg in (-1, 0, 1, 2, 3, 4, 5, 6):
+        for ksplit in (-1, 0, 2, 4):
+            parts = plan(RESIDUAL, M, Nout, K, _part_floats(M, Nout), cfg=cfg, ksplit=ksplit, reach=True)
+            assert sum(p[0] for p in parts) == M
+            assert all(p[4] < (1 << 31) - 1 for p in parts), (cfg, ksplit, parts)
+            assert K <= 1 << 21 or all(p[1] == 7 or p[4] == 0 for p in parts), (cfg, ksplit, parts)
+            cut += any(p[3] > 1 for p in parts)
+    assert cut or 2 * M * Nout > _part_floats(M, Nout)
 
 
 def test_the_tile_with_32_bit_offsets_up_to_there(plan):
