@@ -22,6 +22,8 @@
 //    against 11.1 us, K = 4096 16.4 against 22.9; 640 rows 7.4 / 14.7 against 11.0 / 17.3).  Two per CU do up to 512 rows
 //    (512 rows, K = 1024, Nout = 3072: 10.2 against 10.5; 820 rows, Nout = 1920 = K: 17.8 against 17.2), but not with a
 //    long K (400 rows, K = 9216, Nout = 2304: 30 against 27).
+//  * A tile's rows of 2 K bytes are addressed with 32-bit offsets: 64 of them up to K = 2^23, 8 up to 2^26 (the down
+//    projection of 64 features, K = 2^23 + 2048, 5 / 200 rows: 3.9 / 4.4 ms, 256 x 128 tiles in K slices 20.5 / 25.7).
 // The kernels: groups of eight rows, of eight features, waves, units in flight per wave, workgroups that fit a CU.
 #define NOVA_ROWS_TILES(T)                                                          \
   T(1, 1, 4, 4, 2) T(1, 1, 8, 4, 2) T(1, 2, 4, 4, 2) T(1, 4, 4, 4, 2) T(2, 1, 4, 4, 2) \
@@ -29,11 +31,12 @@
   T(8, 4, 4, 2, 1) T(8, 8, 4, 2, 1) T(8, 8, 4, 1, 2)
 inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K, int64_t) {
   RowsPlan best = {};
-  if (mode == EPI_ENTROPY || Nout % 64 != 0 || K > 1 << 23) return best;    // 64 rows of 2 K bytes: 32-bit offsets
+  if (mode == EPI_ENTROPY || Nout % 64 != 0) return best;
   const bool weights_only = rows <= 8 && (K > 1536 || Nout <= 8 * num_cus) && Nout <= 32 * num_cus;
   const int max_per_cu = mode == EPI_RESIDUAL || rows > 512 ? 1 : 2;
   int64_t least = INT64_MAX;
   auto consider = [&](const RowsPlan& t, int fit) {
+    if ((int64_t)std::max(t.rg, t.ng) * 16 * K > 1 << 30) return;                    // see the last rule above
     if (t.rg * t.ng == 1 ? t.kw != (K > 2048 ? 8 : 4) : weights_only) return;       // a long K over twice the waves
     const int64_t wgs = (int64_t)((rows + 8 * t.rg - 1) / (8 * t.rg)) * (Nout / (8 * t.ng));
     const int64_t per_cu = (wgs + num_cus - 1) / num_cus;

@@ -54,6 +54,13 @@ def test_no_launch_leaves_its_32_bit_offsets(plan, M, Nout, K):
     assert cut or 2 * M * Nout > _part_floats(M, Nout)
 
 
+@pytest.mark.parametrize("K,few", [(1 << 23, True), ((1 << 23) + 2048, True), (1 << 26, True), ((1 << 26) + 64, False)])
+def test_few_rows_keep_their_kernels_while_a_tile_fits(plan, K, few):
+    """Eight rows of 2 K bytes are within 32-bit offsets up to K = 2^26: no reason to leave the few-rows kernels before."""
+    for M in (1, 8, 64, 200):
+        assert [p[1] == 7 for p in plan(RESIDUAL, M, 64, K, _part_floats(M, 64))] == [few], (M, K)
+
+
 def test_the_tile_with_32_bit_offsets_up_to_there(plan):
     assert plan(RESIDUAL, 2049, 8192, 1 << 21, cfg=1)[0][1] == 1
 

@@ -49,7 +49,8 @@ def test_ring_tiles(monkeypatch, F, variant, ksplit):
     _check(monkeypatch, 300, F, variant, CFG=2, KSPLIT=ksplit)
 
 
-@pytest.mark.parametrize("M", [5, 300])
-@pytest.mark.parametrize("F", [1 << 23, (1 << 23) + 2048])
-def test_unforced(monkeypatch, M, F):
+@pytest.mark.parametrize("M,F", [(5, 1 << 23), (300, 1 << 23), (5, (1 << 23) + 2048), (300, (1 << 23) + 2048),
+                                 (300, (1 << 24) + 2048), (5, 1 << 26)])
+def test_few_rows_tiles(monkeypatch, M, F):
+    """Smaller tiles of the few-rows kernels as K grows: 64 rows or features end at 2^23, 32 at 2^24, 8 at 2^26."""
     _check(monkeypatch, M, F)
