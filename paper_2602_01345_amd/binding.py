@@ -168,6 +168,13 @@ def _ptrs(ts: Sequence[torch.Tensor]) -> "C.Array":
     return (C.c_void_p * len(ts))(*[_ptr(t) for t in ts])
 
 
+def _check_lengths(n: int, **lists):
+    """Host arrays the library reads n entries of."""
+    for name, ts in lists.items():
+        if ts is not None and len(ts) < n:
+            raise ValueError(f"{name}: {len(ts)} entries for {n} blocks")
+
+
 # The current stream's handle without a Stream object around it (0.3 against 2.7 us): with small kernels the calls below
 # are what a step waits for.  Not part of torch's public interface, so a torch without it takes the public way.
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
@@ -273,6 +280,9 @@ class Nova:
     def entropy_blocks(self, logits: Sequence[torch.Tensor], entropy: Sequence[torch.Tensor],
                        mean: Optional[Sequence[torch.Tensor]] = None):
         """entropy() of every tensor of a list; tensors of one shape, stride and dtype share their launches."""
+        _check_lengths(len(logits), entropy=entropy, mean=mean)
+        if len(logits) == 0:
+            return
         a = logits[0]
         if any(t.shape != a.shape or t.stride(1) != a.stride(1) or t.dtype != a.dtype for t in logits):
             for i, t in enumerate(logits):
@@ -327,6 +337,9 @@ class Nova:
     def select_blocks(self, entropy: Sequence[torch.Tensor], k: Sequence[int], kept_idx: Sequence[torch.Tensor],
                       keep_mask: Sequence[torch.Tensor]):
         """select() of every tensor of a list of [B, N] entropies, each with its own k, in one launch."""
+        _check_lengths(len(entropy), k=k, kept_idx=kept_idx, keep_mask=keep_mask)
+        if len(entropy) == 0:
+            return
         B, N = entropy[0].shape
         assert all(t.shape == (B, N) for t in entropy)
         rc = self.lib.nova_select_blocks(self.ctx, _stream(), len(entropy), _ptrs(entropy), B, N,
