@@ -8,9 +8,12 @@
 // pruned tokens: a wave whose mask byte says "kept" leaves at once) followed by one wave per kept slot s, which
 // copies row s of the block's output to token kept_idx[b, s] -- so nobody has to look up where in the kept
 // list a token sits.  What a wave does is scalar work without a division (the quotients come from the host): with
-// 64-bit divisions in every lane 9 rows of 1024 took 1.82 us in a graph, 1.70 without (a launch alone 1.57).  Per-image keep counts: slots past an image's count (or holding -1) leave at once.
+// 64-bit divisions in every lane 9 rows of 1024 took 1.82 us in a graph, 1.70 without (a launch alone 1.57).  Per-image
+// keep counts: slots past an image's count (or holding -1) leave at once.
 // The bilinear taps (half-pixel centres) are wave-uniform and evaluated in fp32.  Other interpolation
 // kernels (nearest cell, cubic convolution) go through a generic separable-taps kernel further down.
+#include <algorithm>
+
 #include "common.h"
 #include "nova_internal.h"
 
@@ -295,21 +298,27 @@ hipError_t launch_t(hipStream_t st, int interp, int B, int C, int h, int w, int 
   };
   g.ny_inv = nearest_inv(hp, h);
   g.nx_inv = nearest_inv(wp, w);
-  const unsigned grid = (unsigned)((int64_t)B * g.per_image);
-  const T* xt = static_cast<const T*>(x);
-  const T* yt = static_cast<const T*>(y);
-  const T* ct = static_cast<const T*>(cache_prev);
-  T* ot = static_cast<T*>(out);
-  T* nt = static_cast<T*>(cache_new);
-  if (interp == NOVA_INTERP_NEAREST)
-    merge_taps_kernel<T, 1><<<grid, kWavesPerBlock * NOVA_WAVE, 0, st>>>(g, C, h, w, hp, wp, k, xt, yt, idx, mask, ct,
-                                                                       ot, nt, k_rows);
-  else if (interp == NOVA_INTERP_BICUBIC)
-    merge_taps_kernel<T, 4><<<grid, kWavesPerBlock * NOVA_WAVE, 0, st>>>(g, C, h, w, hp, wp, k, xt, yt, idx, mask, ct,
-                                                                       ot, nt, k_rows);
-  else
-    merge_kernel<T><<<grid, kWavesPerBlock * NOVA_WAVE, 0, st>>>(g, C, h, w, hp, wp, k, xt, yt, idx, mask, ct, ot, nt,
-                                                                 k_rows);
+  constexpr int threads = kWavesPerBlock * NOVA_WAVE;
+  // a launch has fewer than 2^32 threads: images beyond that (some 16 million of up to four tokens) take another one
+  const int most = (int)std::max<int64_t>(UINT32_MAX / threads / g.per_image, 1);
+  const int64_t N = (int64_t)h * w, np = (int64_t)hp * wp;
+  for (int b = 0; b < B; b += std::min(most, B - b)) {
+    const unsigned grid = (unsigned)((int64_t)std::min(most, B - b) * g.per_image);
+    const T* xt = static_cast<const T*>(x) + b * N * C;
+    const T* yt = y ? static_cast<const T*>(y) + (int64_t)b * k * C : nullptr;
+    const T* ct = cache_prev ? static_cast<const T*>(cache_prev) + b * np * C : nullptr;
+    T* ot = static_cast<T*>(out) + b * N * C;
+    T* nt = cache_new ? static_cast<T*>(cache_new) + b * N * C : nullptr;
+    const int32_t* it = idx ? idx + (int64_t)b * k : nullptr;
+    const int32_t* kt = k_rows ? k_rows + b : nullptr;
+    const uint8_t* mt = mask + b * N;
+    if (interp == NOVA_INTERP_NEAREST)
+      merge_taps_kernel<T, 1><<<grid, threads, 0, st>>>(g, C, h, w, hp, wp, k, xt, yt, it, mt, ct, ot, nt, kt);
+    else if (interp == NOVA_INTERP_BICUBIC)
+      merge_taps_kernel<T, 4><<<grid, threads, 0, st>>>(g, C, h, w, hp, wp, k, xt, yt, it, mt, ct, ot, nt, kt);
+    else
+      merge_kernel<T><<<grid, threads, 0, st>>>(g, C, h, w, hp, wp, k, xt, yt, it, mt, ct, ot, nt, kt);
+  }
   return hipGetLastError();
 }
 

@@ -91,3 +91,27 @@ def test_interp_argument_errors(hx):
         assert e.value.code == -1
     torch.cuda.synchronize()
     assert bool((out == 5.0).all())
+
+
+@pytest.mark.parametrize("k", [0, 1])
+def test_more_images_than_one_launch_has_waves_for(hx, k):
+    """A workgroup per image of one token and 2^24 - 1 workgroups of 256 threads in a launch: the images around that are
+    right, with per-image counts (none kept where k = 1 and the image's number is odd)."""
+    B, C, last = (1 << 24) + 3, 8, (1 << 24) - 1
+    print(f"merge B={B} k={k}", flush=True)
+    ends = torch.tensor([0, 1, last - 1, last, last + 1, B - 1], device="cuda")
+    row = torch.arange(B, device="cuda")
+    x = (row % 97).to(torch.bfloat16)[:, None, None].expand(B, 1, C).contiguous()
+    prev = (row % 89).to(torch.bfloat16)[:, None, None].expand(B, 1, C).contiguous()
+    y = (row % 83 + 500).to(torch.bfloat16)[:, None, None].expand(B, 1, C).contiguous()
+    kept = (1 - row % 2) * k
+    mask = kept.to(torch.uint8)[:, None].contiguous()
+    idx = torch.zeros((B, 1), dtype=torch.int32, device="cuda")
+    out, cn = torch.full_like(x, float("nan")), torch.full_like(x, float("nan"))
+    counts = kept.to(torch.int32) if k else None
+    hx.nova().merge_cache_rows(0, 1, 1, 1, 1, k, counts, x, y, idx, mask, prev, out, cn)
+    torch.cuda.synchronize()
+    ref = torch.where(kept[:, None, None] > 0, y.float(), x.float() + prev.float())
+    assert torch.equal(out[ends].float(), ref[ends]) and torch.equal(out, ref.to(torch.bfloat16))
+    ref = torch.where(kept[:, None, None] > 0, y.float() - x.float(), prev.float())
+    assert torch.equal(cn[ends].float(), ref[ends].to(torch.bfloat16).float()) and torch.equal(cn, ref.to(torch.bfloat16))
