@@ -38,6 +38,14 @@ template <> struct Vec16<bf16_t> {
   __device__ __forceinline__ void set(int i, float x) { v[i] = (bf16_t)x; }
 };
 
+// Global -> LDS: 16 bytes per lane from base + lane_off + off (bytes; base and off wave-uniform) into 1 KB of LDS at dst.
+// Offsets have 32 bits and are bounded at 2^31 - 1: loads from there on give zeros.
+typedef __attribute__((address_space(3))) void* lptr_t;
+__device__ __forceinline__ void fill_lds(const bf16_t* base, char* dst, uint32_t lane_off, uint32_t off) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, 0x7FFFFFFF, 0x00020000), (lptr_t)dst, 16, lane_off, off, 0, 0);
+}
+
 // Per-image keep counts (the reduction ratios of Sec. 3.3, "Dual-Linkage Acceleration", are per instance): the
 // kept rows of image b are slots [0, k_b) of its kpitch-row segment, and it holds its own number of prior K/V rows.
 // Null pointers mean "uniform": every image keeps kpitch rows / holds P prior rows.  Values are clamped, so a

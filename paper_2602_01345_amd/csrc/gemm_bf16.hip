@@ -33,7 +33,6 @@
 namespace {
 
 typedef const __attribute__((address_space(1))) void* gptr_t;
-typedef __attribute__((address_space(3))) void* lptr_t;
 
 __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
@@ -41,12 +40,6 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 
 // s_waitcnt with only vmcnt = n constrained (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
 #define WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
-
-// 16 bytes per lane from base + lane_off + off (bytes; base and off wave-uniform) into 1 KB of LDS
-__device__ __forceinline__ void fill_lds(bf16_t* base, lptr_t dst, uint32_t lane_off, uint32_t off) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(base, 0, 0x7FFFFFFF, 0x00020000), dst, 16,
-                                           lane_off, off, 0, 0);
-}
 
 // LDS byte offset of 16-byte chunk `c` of tile row `r`; a row holds 64 elements (128 bytes).
 // The XOR term changes with every group of rows that shares a bank window, so that 16 consecutive
@@ -115,7 +108,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
   const int lr = lane / CH, lp = lane % CH;
   const bf16_t* ga[FAR ? LA : 1];
   const bf16_t* gb[FAR ? LB : 1];
-  bf16_t *tile_a = nullptr, *tile_w = nullptr;               // the tile's first row / column and the lanes' offsets
+  const bf16_t *tile_a = nullptr, *tile_w = nullptr;               // the tile's first row / column and the lanes' offsets
   uint32_t oa[LA], ob[LB];
   int tn = 0, m0 = 0, n0 = 0;
   auto set_tile = [&](int Lt) {
@@ -133,8 +126,8 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
     const int tm = band * 8 + (full ? in_band & 7 : tr);
     m0 = m_base + tm * BM;                                 // this launch covers rows [m_base, M)
     n0 = tn * BN;
-    tile_a = const_cast<bf16_t*>(A + (int64_t)m0 * K);
-    tile_w = const_cast<bf16_t*>(W + (int64_t)n0 * K);
+    tile_a = A + (int64_t)m0 * K;
+    tile_w = W + (int64_t)n0 * K;
     // byte offset of the chunk of row r that lands in slot lp; rows past the edge re-read the last row
 #pragma unroll
     for (int i = 0; i < LA; ++i) {
@@ -173,14 +166,14 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
       if (i >= lo && i < hi) {
         char* d = sa + (i * NW + wave) * RPI * ROW_BYTES;
         if constexpr (FAR) __builtin_amdgcn_global_load_lds((gptr_t)(ga[i] + k0), (lptr_t)d, 16, 0, 0);
-        else fill_lds(tile_a, (lptr_t)d, oa[i], k0 * 2);
+        else fill_lds(tile_a, d, oa[i], k0 * 2);
       }
 #pragma unroll
     for (int i = 0; i < LB; ++i)
       if (LA + i >= lo && LA + i < hi) {
         char* d = sb + (i * NW + wave) * RPI * ROW_BYTES;
         if constexpr (FAR) __builtin_amdgcn_global_load_lds((gptr_t)(gb[i] + k0), (lptr_t)d, 16, 0, 0);
-        else fill_lds(tile_w, (lptr_t)d, ob[i], k0 * 2);
+        else fill_lds(tile_w, d, ob[i], k0 * 2);
       }
   };
 
@@ -200,7 +193,7 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
     for (int i = 0; i < 2; ++i) {
       const int j = (part & 1) * 2 + i;
       char* d = lds + (part >> 1) * 65536 + buf * 32768 + (j * NW + wave) * RPI * ROW_BYTES;
-      fill_lds(part >> 1 ? tile_w : tile_a, (lptr_t)d, part >> 1 ? ob[j] : oa[j], (k_begin + t * BK) * 2);
+      fill_lds(part >> 1 ? tile_w : tile_a, d, part >> 1 ? ob[j] : oa[j], (k_begin + t * BK) * 2);
     }
   };
   // prologue: NST-1 K stages in flight (PP: one and three quarters)
@@ -715,7 +708,7 @@ template <int MODE>
 hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W, int m_base, int M, int Nout, int K,
                        const EpiParams<bf16_t>& ep, int slots, int cus, int ksplit) {
   if (cfg == kRowsCfg) {
-    const RowsPlan plan = gemm_rows_plan(cus, MODE, M - m_base, Nout, K, ep.part ? ep.part_floats : 0);
+    const RowsPlan plan = gemm_rows_plan(cus, MODE, M - m_base, Nout, K);
     return launch_gemm_rows_bf16(st, plan, MODE, A, W, m_base, M, Nout, K, ep);
   }
   if constexpr (MODE == EPI_RESIDUAL) {

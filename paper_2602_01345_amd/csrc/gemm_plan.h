@@ -29,7 +29,7 @@
   T(1, 1, 4, 4, 2) T(1, 1, 8, 4, 2) T(1, 2, 4, 4, 2) T(1, 4, 4, 4, 2) T(2, 1, 4, 4, 2) \
   T(2, 2, 4, 4, 2) T(2, 4, 4, 3, 2) T(4, 2, 4, 3, 2) T(4, 4, 4, 2, 2) T(4, 8, 4, 2, 1) \
   T(8, 4, 4, 2, 1) T(8, 8, 4, 2, 1) T(8, 8, 4, 1, 2)
-inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K, int64_t) {
+inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K) {
   RowsPlan best = {};
   if (mode == EPI_ENTROPY || Nout % 64 != 0) return best;
   const bool weights_only = rows <= 8 && (K > 1536 || Nout <= 8 * num_cus) && Nout <= 32 * num_cus;
@@ -47,7 +47,7 @@ inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K,
       best = t;
     }
   };
-#define CONSIDER(RG, NG, KW, S, FIT) consider({RG, NG, KW, S, 1}, FIT);
+#define CONSIDER(RG, NG, KW, S, FIT) consider({RG, NG, KW, S}, FIT);
   NOVA_ROWS_TILES(CONSIDER)
 #undef CONSIDER
   return best;
@@ -133,7 +133,7 @@ inline int pick_cfg(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64
     if (narrow_tiles(M, Nout, K)) return 4;
   }
   const int slots = ctx ? ctx->num_cus : 256;
-  const RowsPlan rows = gemm_rows_plan(slots, mode, M, Nout, K, part_floats);      // rg = 0 for a prediction head
+  const RowsPlan rows = gemm_rows_plan(slots, mode, M, Nout, K);      // rg = 0 for a prediction head
   if (rows.rg) {
     if (t_out) *t_out = rows_time(rows, slots, M, Nout, K);
     return kRowsCfg;

@@ -27,14 +27,7 @@
 
 namespace {
 
-typedef __attribute__((address_space(3))) void* lptr_t;
 #define WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(0x0F70 | ((n) & 15) | (((n) >> 4) << 14))
-
-// 16 bytes per lane from base + lane_off + off (bytes; base and off wave-uniform) into 1 KB of LDS
-__device__ __forceinline__ void fill_lds(const bf16_t* base, char* dst, uint32_t lane_off, uint32_t off) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(
-      __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, 0x7FFFFFFF, 0x00020000), (lptr_t)dst, 16, lane_off, off, 0, 0);
-}
 
 // s_waitcnt vmcnt(younger * LPU) for a wave-uniform younger in 0 .. MAXJ
 template <int MAXJ, int LPU>

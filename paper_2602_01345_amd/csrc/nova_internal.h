@@ -122,7 +122,6 @@ hipError_t launch_gemm_bf16(const nova_ctx* ctx, hipStream_t st, int mode, const
 // better served by gemm_bf16.hip
 struct RowsPlan {
   int rg, ng, kw, s;       // groups of 8 rows / 8 features per tile, waves, units in flight per wave
-  int slices;              // K slices: 1, these kernels do not cut K over workgroups
 };
 hipError_t launch_gemm_rows_bf16(hipStream_t st, const RowsPlan& plan, int mode, const __bf16* A, const __bf16* W, int m_base,
                                  int M, int Nout, int K, const EpiParams<__bf16>& ep);
