@@ -1,7 +1,7 @@
 // Prints what csrc/gemm_plan.h plans on 256 compute units (tests/test_gemm_plan.py): one line per request of
 // mode M Nout K part_floats gemm_cfg gemm_parts gemm_ksplit on standard input, for every part of the plan
-// rows:cfg:tiles:slices:reach, the few-rows kernels, which do not cut K, as rows:7:workgroups:1:reach.  Reach: the byte
-// offsets into a tile end below it (its rows of 2 K bytes), 0 where the kernel takes 64-bit addresses instead.
+// rows:cfg:tiles:slices:reach, the few-rows kernels, which do not cut K, as rows:7:workgroups:1:reach:rg:ng:kw:s.  Reach:
+// the byte offsets into a tile end below it (its rows of 2 K bytes), 0 where the kernel takes 64-bit addresses instead.
 #include <algorithm>
 #include <cstdio>
 
@@ -22,8 +22,8 @@ int main() {
       const int rows = p.m_end[i] - p.m_base[i];
       if (p.cfg[i] == kRowsCfg) {
         const RowsPlan r = gemm_rows_plan(256, mode, rows, Nout, K);
-        printf("%d:7:%d:1:%lld ", rows, (rows + 8 * r.rg - 1) / (8 * r.rg) * (Nout / (8 * r.ng)),
-               8LL * std::max(r.rg, r.ng) * 2 * K);
+        printf("%d:7:%d:1:%lld:%d:%d:%d:%d ", rows, (rows + 8 * r.rg - 1) / (8 * r.rg) * (Nout / (8 * r.ng)),
+               8LL * std::max(r.rg, r.ng) * 2 * K, r.rg, r.ng, r.kw, r.s);
         continue;
       }
       const Candidate* t = &kCands[1];

@@ -1,5 +1,6 @@
 """The launch plans of csrc/gemm_plan.h on the CPU, compiled for the host alone (gemm_plan_probe.cpp)."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -23,6 +24,15 @@ def plan(tmp_path_factory):
         r = subprocess.run([exe], input=f"{mode} {M} {Nout} {K} {part_floats} {cfg} {parts} {ksplit}\n", text=True,
                            check=True, capture_output=True)
         return [tuple(int(v) for v in p.split(":"))[:5 if reach else 4] for p in r.stdout.split()]
+
+    def few_rows_tiles(sizes):
+        """{(mode, rg, ng, kw, s)} of the few-rows launches of blocks of (C, M)"""
+        asked = [(mode, f"{mode} {M} {N * C} {K * C} {_part_floats(M, C)} -1 -1 -1\n") for C, M in sizes
+                 for mode, N, K in ((QKV, 3, 1), (ATTN_OUT, 1, 1), (GELU, 4, 1), (RESIDUAL, 1, 4))]
+        r = subprocess.run([exe], input="".join(q for _, q in asked), text=True, check=True, capture_output=True)
+        return {(mode, *(int(v) for v in p.split(":")[5:])) for (mode, _), line in zip(asked, r.stdout.split("\n"))
+                for p in line.split() if p.split(":")[1] == "7"}
+    ask.few_rows_tiles = few_rows_tiles
     return ask
 
 
@@ -67,6 +77,17 @@ def test_the_tile_with_32_bit_offsets_up_to_there(plan):
 
 def _part_floats(M, C):
     return min(4 * M * C, 128 * 256 * 256)             # K-slice scratch of the block's workspace
+
+
+def test_sizes_of_the_gpu_tests_reach_every_few_rows_tile(plan):
+    """Every tile of csrc/gemm_plan.h, in every projection that picks it over the widths of up to 2496 with up to 1100 rows."""
+    import test_few_rows as F
+    tested = plan.few_rows_tiles(F.SIZES)
+    with open(os.path.join(CSRC, "gemm_plan.h")) as f:
+        tiles = {tuple(int(v) for v in t.split(",")[:4]) for t in re.findall(r" T\((\d+(?:, \d+){4})\)", f.read())}
+    assert len(tiles) == 13 and {t[1:] for t in tested} == tiles
+    picked = plan.few_rows_tiles([(C, M) for C in range(64, 2560, 64) for M in [*range(1, 66), *range(66, 1100, 11)]])
+    assert picked <= tested, picked - tested
 
 
 def test_sizes_of_the_gpu_tests_reach_what_they_test(plan):

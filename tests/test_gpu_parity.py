@@ -210,8 +210,8 @@ def test_block_f32_rows_wider_than_the_layer_norm_register_path(hx):
 
 @pytest.mark.parametrize("k", [1, 40, 100])
 def test_block_bf16_few_rows_long_ffn(hx, k):
-    """Few kept rows and an FFN hidden width of 4096: the down projection sums K in slices over several
-    workgroups and a second pass adds the slices (M = 2, 80, 200 rows)."""
+    """Few kept rows and an FFN hidden width of 4096: the waves of a few-rows workgroup split the long K of the down
+    projection (M = 2, 80, 200 rows)."""
     _say(f"block bf16 C=1024 F=4096 k={k}")
     wl = _custom("bf16", B=2, grid=10, prev=7, P=64, C=1024, heads=8)
     errs = hx.check_block(hx.make_host_block(wl, 0, k=k), hx.BF16_TOL)
