@@ -75,6 +75,17 @@ def test_the_tile_with_32_bit_offsets_up_to_there(plan):
     assert plan(RESIDUAL, 2049, 8192, 1 << 21, cfg=1)[0][1] == 1
 
 
+@pytest.mark.parametrize("mode,M,C,cfg,slices", [(QKV, 1500, 1920, 1, 1), (GELU, 1500, 1920, 1, 1), (QKV, 1500, 2048, 1, 1),
+                                                 (GELU, 1500, 2048, 1, 1), (QKV, 3072, 1024, 1, 1), (QKV, 4096, 768, 1, 1),
+                                                 (GELU, 4096, 768, 1, 1), (RESIDUAL, 1800, 1024, 5, 2)])
+def test_tiles_are_priced_with_weights_from_memory(plan, mode, M, C, cfg, slices):
+    """One round of wide tiles against two of narrow ones, which read the weights more often: blocks of these sizes are 3 to
+    7 % slower with what launches on weights in L2 would choose."""
+    N, K = {QKV: (3 * C, C), GELU: (4 * C, C), RESIDUAL: (C, 4 * C)}[mode]
+    (_, got, _, ks), = plan(mode, M, N, K, _part_floats(M, C))
+    assert (got, ks) == (cfg, slices)
+
+
 def _part_floats(M, C):
     return min(4 * M * C, 128 * 256 * 256)             # K-slice scratch of the block's workspace
 
