@@ -16,8 +16,11 @@
 //    behind cold caches).
 //  * Equal counts: the wider tile (more rows in flight per weight row), the taller with a long K (100 rows, K = 4096,
 //    Nout = 1024: 32 x 16 6.9, 16 x 32 7.8; K = 1024 3.27, 3.24).
-//  * Up to eight rows the weights are all there is to load, and several small workgroups per CU stream them best
-//    (K = 2048, Nout = 8192, two rows: 8 x 8 8.2, 8 x 16 8.7, 8 x 32 8.9; K = 1024, Nout = 3072: 8 x 8 4.0, 8 x 16 3.6).
+//  * Up to eight rows the weights are all there is to load, and the smallest workgroups stream them best where every CU
+//    gets as many of them: one, or with a longer K two to four (K = 2048, Nout = 8192, two rows: 8 x 8 8.2, 8 x 16 8.7,
+//    8 x 32 8.9; K = 1024, Nout = 3072: 8 x 8 4.0, 8 x 16 3.6).  Uneven, the rule above is better (a block of eight rows of
+//    C = 2304: 8 x 16 in place of 288 workgroups of 8 x 8 out of K = 2304 / 9216 -1.1 / -3.1 us, 8 x 32 in place of 864
+//    -1.5; C = 1920, 8 x 32 in place of 960 -0.9).
 //  * One workgroup per CU beats the 128- and 256-row tiles at any row count (1024 rows, Nout = 1024: K = 1024 8.4
 //    against 11.1 us, K = 4096 16.4 against 22.9; 640 rows 7.4 / 14.7 against 11.0 / 17.3).  Two per CU do up to 512 rows
 //    (512 rows, K = 1024, Nout = 3072: 10.2 against 10.5; 820 rows, Nout = 1920 = K: 17.8 against 17.2), but not with a
@@ -32,7 +35,7 @@
 inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K) {
   RowsPlan best = {};
   if (mode == EPI_ENTROPY || Nout % 64 != 0) return best;
-  const bool weights_only = rows <= 8 && (K > 1536 || Nout <= 8 * num_cus) && Nout <= 32 * num_cus;
+  const bool weights_only = rows <= 8 && (Nout <= 8 * num_cus || (K > 1536 && Nout % (8 * num_cus) == 0 && Nout <= 32 * num_cus));
   const int max_per_cu = mode == EPI_RESIDUAL || rows > 512 ? 1 : 2;
   int64_t least = INT64_MAX;
   auto consider = [&](const RowsPlan& t, int fit) {

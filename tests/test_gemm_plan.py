@@ -71,6 +71,14 @@ def test_few_rows_keep_their_kernels_while_a_tile_fits(plan, K, few):
         assert [p[1] == 7 for p in plan(RESIDUAL, M, 64, K, _part_floats(M, 64))] == [few], (M, K)
 
 
+def test_eight_rows_of_features_that_divide_unevenly(plan):
+    """288 or 864 workgroups of 8 x 8 give some CUs one more than others: wider tiles, one workgroup per CU at most."""
+    for M in (1, 8):
+        assert plan.few_rows_tiles([(2304, M)]) == {(QKV, 1, 4, 4, 4), (ATTN_OUT, 1, 2, 4, 4), (GELU, 1, 2, 4, 4),
+                                                    (RESIDUAL, 1, 2, 4, 4)}
+        assert plan.few_rows_tiles([(2048, M)]) == {(mode, 1, 1, 8 if mode == RESIDUAL else 4, 4) for mode in range(4)}
+
+
 def test_the_tile_with_32_bit_offsets_up_to_there(plan):
     assert plan(RESIDUAL, 2049, 8192, 1 << 21, cfg=1)[0][1] == 1
 
