@@ -13,9 +13,10 @@
 //    K = 1024 / 4096 64 x 8 3.9 / 8.9 (K cut into four slices), 16 x 16 3.0 / 6.7; 128 rows 64 x 8 4.0 / 10.1 (cut),
 //    32 x 16 3.3 / 8.3; 64 rows, Nout = 3072 64 x 16 5.4, 32 x 32 4.9.  Cutting K and adding the slices in a second pass
 //    is worth it nowhere any more but for 128 rows of K = 8192 (18.1 against 18.6, not counting what its launch costs
-//    behind cold caches).
-//  * Equal counts: the wider tile (more rows in flight per weight row), the taller with a long K (100 rows, K = 4096,
-//    Nout = 1024: 32 x 16 6.9, 16 x 32 7.8; K = 1024 3.27, 3.24).
+//    behind cold caches) and 48 ... 64 rows of K = 12288 (a block of 64 rows of C = 3072 94.1 against 97.8).
+//  * Equal counts: the taller tile, which fetches the weights less often, with a long K or many weights (64 x 32 for
+//    32 x 64: 64 rows, K = 2304 into 6912 -1.6 us; 200 rows, C = 1920 = K -2.5; 100 rows, K = 4096, Nout = 1024 32 x 16 6.9,
+//    16 x 32 7.8), else the wider one, more rows in flight per weight row (a block of 256 rows of C = 512 26.5, 27.3).
 //  * Up to eight rows the weights are all there is to load, and the smallest workgroups stream them best where every CU
 //    gets as many of them: one, or with a longer K two to four (K = 2048, Nout = 8192, two rows: 8 x 8 8.2, 8 x 16 8.7,
 //    8 x 32 8.9; K = 1024, Nout = 3072: 8 x 8 4.0, 8 x 16 3.6).  Uneven, the rule above is better (a block of eight rows of
@@ -36,6 +37,7 @@ inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K)
   RowsPlan best = {};
   if (mode == EPI_ENTROPY || Nout % 64 != 0) return best;
   const bool weights_only = rows <= 8 && (Nout <= 8 * num_cus || (K > 1536 && Nout % (8 * num_cus) == 0 && Nout <= 32 * num_cus));
+  const bool tall = K >= 4096 || (K >= 1536 && Nout >= 1536);
   const int max_per_cu = mode == EPI_RESIDUAL || rows > 512 ? 1 : 2;
   int64_t least = INT64_MAX;
   auto consider = [&](const RowsPlan& t, int fit) {
@@ -45,7 +47,7 @@ inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K)
     const int64_t per_cu = (wgs + num_cus - 1) / num_cus;
     if (rows > 64 && per_cu > std::min(fit, max_per_cu)) return;                     // up to 64 rows: in turns
     const int64_t groups = per_cu * (t.rg + t.ng);
-    if (groups < least || (groups == least && (K >= 4096 ? t.rg > best.rg : t.ng > best.ng))) {
+    if (groups < least || (groups == least && (tall ? t.rg > best.rg : t.ng > best.ng))) {
       least = groups;
       best = t;
     }
