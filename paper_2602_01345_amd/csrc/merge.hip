@@ -4,7 +4,7 @@
 // output minus input everywhere.
 //
 // Bandwidth-bound streaming kernel.  One wave64 owns one row of C channels and moves it in 16-byte vectors; all
-// loads of a sweep are issued before the first use.  The launch has, image by image, one wave per token (it serves the
+// loads of a sweep are issued before the first use.  The launch has one wave per token (it serves the
 // pruned tokens: a wave whose mask byte says "kept" leaves at once) followed by one wave per kept slot s, which
 // copies row s of the block's output to token kept_idx[b, s] -- so nobody has to look up where in the kept
 // list a token sits.  What a wave does is scalar work without a division (the quotients come from the host): with
@@ -39,10 +39,16 @@ __device__ __forceinline__ Taps axis_taps(int dst, int n_in, float ratio) {
   return t;
 }
 
+// From this many tokens on the launch goes image by image, else the tokens of all images come first: the longer waves, they
+// hide under the copies (bilinear, half kept, tokens first / by image: 4 x 256 rows of 1920 6.8 / 7.1 us, 16 x 256 of 2304
+// 22.5 / 23.9; 8 x 1024 of 2304 38.7 / 38.6, nearest 37.0 / 35.8; 2 x 4096 of 2048 32.5 / 31.0).
+constexpr int kImageTokens = 1024;
+
 // Quotients made once on the host.
 struct MergeGrid {
-  int per_image;                  // workgroups per image: waves for its tokens, then for its kept slots
-  uint32_t per_image_inv, w_inv;  // div_inv of per_image / of the grid's width
+  int tok_blocks, slot_blocks;    // workgroups per image for its tokens / its kept slots
+  int group_blocks, group_toks;   // per group of images, one or all: workgroups, those of them for tokens, which come first
+  uint32_t group_inv, tok_inv, slot_inv, w_inv;   // div_inv of group_blocks, tok_blocks, slot_blocks, the grid's width
   float ry, rx;                   // (rows, columns of the prior grid) / (of this one)
   uint32_t ny_inv, nx_inv;        // nearest cell: div_inv of twice the rows / columns, 0 where its products need 64 bits
 };
@@ -55,14 +61,17 @@ struct MergeItem {
 __device__ __forceinline__ MergeItem merge_item(const MergeGrid& g, int N, int k, const int32_t* __restrict__ idx,
                                                 const uint8_t* __restrict__ mask, const int32_t* __restrict__ k_rows) {
   MergeItem it = {0, -1, -1};
-  int block;
-  it.b = div_by(blockIdx.x, g.per_image, g.per_image_inv, block);
-  const uint32_t item = (uint32_t)block * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x / NOVA_WAVE);
-  if (item < (uint32_t)N) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / NOVA_WAVE);
+  int in_group, block;
+  it.b = div_by(blockIdx.x, g.group_blocks, g.group_inv, in_group);
+  if (in_group < g.group_toks) {
+    it.b += div_by(in_group, g.tok_blocks, g.tok_inv, block);
+    const int i = block * kWavesPerBlock + wave;
     // kept tokens are written by their slot's wave (with k == 0 there are no slots: every token takes this path)
-    if (!mask[(int64_t)it.b * N + item] || k == 0) it.tok = (int)item;
-  } else if (item - N < (uint32_t)k) {
-    const int s = (int)(item - N);
+    if (i < N && (!mask[(int64_t)it.b * N + i] || k == 0)) it.tok = i;
+  } else {
+    it.b += div_by(in_group - g.group_toks, g.slot_blocks, g.slot_inv, block);
+    const int s = block * kWavesPerBlock + wave;
     const int64_t slot = (int64_t)it.b * k + s;
     const int t = s < image_count(k_rows, it.b, k) ? idx[slot] : -1;
     if (t >= 0 && t < N) { it.tok = t; it.slot = slot; }
@@ -292,8 +301,10 @@ hipError_t launch_t(hipStream_t st, int interp, int B, int C, int h, int w, int 
                     const void* y, const int32_t* idx, const uint8_t* mask, const void* cache_prev, void* out,
                     void* cache_new, const int32_t* k_rows) {
   MergeGrid g;
-  g.per_image = (int)(((int64_t)h * w + k + kWavesPerBlock - 1) / kWavesPerBlock);
-  g.per_image_inv = div_inv(g.per_image);
+  g.tok_blocks = (int)(((int64_t)h * w + kWavesPerBlock - 1) / kWavesPerBlock);
+  g.slot_blocks = (k + kWavesPerBlock - 1) / kWavesPerBlock;
+  g.tok_inv = div_inv(g.tok_blocks);
+  g.slot_inv = div_inv(g.slot_blocks);
   g.w_inv = div_inv(w);
   g.ry = (float)hp / (float)h;
   g.rx = (float)wp / (float)w;
@@ -303,11 +314,17 @@ hipError_t launch_t(hipStream_t st, int interp, int B, int C, int h, int w, int 
   g.ny_inv = nearest_inv(hp, h);
   g.nx_inv = nearest_inv(wp, w);
   constexpr int threads = kWavesPerBlock * NOVA_WAVE;
-  // a launch has fewer than 2^32 threads: images beyond that (some 16 million of up to four tokens) take another one
-  const int most = (int)std::max<int64_t>(UINT32_MAX / threads / g.per_image, 1);
+  // a launch has fewer than 2^32 threads: images beyond that (from 8 million of up to four tokens on) take another one
+  const int64_t per_image = (int64_t)g.tok_blocks + g.slot_blocks;
+  const int most = (int)std::max<int64_t>(UINT32_MAX / threads / per_image, 1);
   const int64_t N = (int64_t)h * w, np = (int64_t)hp * wp;
   for (int b = 0; b < B; b += std::min(most, B - b)) {
-    const unsigned grid = (unsigned)((int64_t)std::min(most, B - b) * g.per_image);
+    const int images = std::min(most, B - b);
+    const unsigned grid = (unsigned)(images * per_image);
+    const int group = N >= kImageTokens ? 1 : images;
+    g.group_blocks = (int)(group * per_image);
+    g.group_inv = div_inv(g.group_blocks);
+    g.group_toks = group * g.tok_blocks;
     const T* xt = static_cast<const T*>(x) + b * N * C;
     const T* yt = y ? static_cast<const T*>(y) + (int64_t)b * k * C : nullptr;
     const T* ct = cache_prev ? static_cast<const T*>(cache_prev) + b * np * C : nullptr;
