@@ -73,7 +73,7 @@ inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K)
 // per CU; a round costs a fixed time (first loads, epilogue) and a time per element of K that grows with the share of
 // the CUs that are busy (they share L2, memory and power).  Fitted for the choice, not for the times, to whole blocks
 // whose weights come from memory as a model's do, with and without K slices and in one launch or two: what it chooses is
-// 0.09 % of the block's time from the best on average, 4 % at worst (426 sizes; 0.1 % and 7 % on the half of them that a
+// 0.08 % of the block's time from the best on average, 4 % at worst (426 sizes; 0.1 % and 7 % on the half of them that a
 // fit leaves out).  A fit to launches that find their weights in L2 makes a single round of 256 x 256 tiles too dear
 // against two of smaller ones, which fetch the weights more often: 0.25 %, and blocks up to 7 % slower (1500 rows,
 // C = 1920 / 2048 226 / 237 us, with this one 212 / 228; 1800 rows, C = 1024 126 and 120).
@@ -86,10 +86,10 @@ struct Candidate {
   double k0, k1, k3;            // us per element of K in a round that fills a share f of the CUs: k0 + k1 f + k3 f^3
 };
 
-static const Candidate kCands[] = {{1, 256, 256, 3.5, 5.3, 2.1, 0.01805, -0.00097, 0.00601},
-                                   {2, 256, 128, 2.4, 3.2, 0.7, 0.00993, -0.00009, 0.00405},
-                                   {6, 192, 128, 2.7, 2.8, 0.6, 0.00767, 0.00187, 0.00168},
-                                   {5, 128, 128, 2.1, 1.1, 0.1, 0.00649, 0.00126, 0.00183}};
+static const Candidate kCands[] = {{1, 256, 256, 3.5, 5.4, 1.8, 0.01806, -0.00115, 0.00630},
+                                   {2, 256, 128, 2.4, 3.1, 0.7, 0.00974, -0.00010, 0.00433},
+                                   {6, 192, 128, 2.5, 2.7, 0.6, 0.00778, 0.00189, 0.00153},
+                                   {5, 128, 128, 2.2, 1.1, 0.1, 0.00649, 0.00120, 0.00165}};
 
 // Up to this K the lanes' 32-bit offsets into a tile do: 255 rows of 2 K bytes and the offset along K stay below 2^31.
 // Beyond it configuration 2 takes 64-bit addresses, K slices among them, and stands in for 1, 5 and 6; the staggered ones
@@ -117,7 +117,7 @@ inline double model_time(const Candidate& c, int slots, int mode, int M, int Nou
   const double f = (double)rest / slots, fixed = c.round + (mode == EPI_GELU || mode == EPI_GELU_TANH ? c.gelu : 0.0);
   double t = c.launch + full * (fixed + K / ks * (c.k0 + c.k1 + c.k3));
   if (rest) t += fixed + K / ks * (c.k0 + c.k1 * f + c.k3 * f * f * f);
-  if (ks > 1) t += 2.3 + (ks * 4.0 + 4.0) * M * Nout / 6.3e6;
+  if (ks > 1) t += 2.5 + (ks * 4.0 + 4.0) * M * Nout / 5.9e6;
   // in four slices a launch of 192 x 128 tiles takes either time, at random (60 tiles, K = 6144: 26 or 33 us)
   if (ks == 4 && c.cfg == 6) t += K / ks * 0.0011;
   return t * 1e-6;

@@ -90,7 +90,8 @@ def test_the_tile_with_32_bit_offsets_up_to_there(plan):
 
 @pytest.mark.parametrize("mode,M,C,cfg,slices", [(QKV, 1500, 1920, 1, 1), (GELU, 1500, 1920, 1, 1), (QKV, 1500, 2048, 1, 1),
                                                  (GELU, 1500, 2048, 1, 1), (QKV, 3072, 1024, 1, 1), (QKV, 4096, 768, 1, 1),
-                                                 (GELU, 4096, 768, 1, 1), (RESIDUAL, 1800, 1024, 5, 2)])
+                                                 (GELU, 4096, 768, 1, 1), (RESIDUAL, 1800, 1024, 5, 2),
+                                                 (RESIDUAL, 2048, 1024, 5, 2)])
 def test_tiles_are_priced_with_weights_from_memory(plan, mode, M, C, cfg, slices):
     """One round of wide tiles against two of narrow ones, which read the weights more often: blocks of these sizes are 3 to
     7 % slower with what launches on weights in L2 would choose."""
