@@ -137,9 +137,11 @@ int nova_entropy(nova_ctx* ctx, void* stream, const void* logits, int logits_dty
                  int64_t rows_per_batch, int batch, int V, int64_t row_stride_elems,
                  float* entropy, float* mean_entropy);
 
-/* nova_entropy of n_blocks tensors of one shape, stride and dtype (the logits of a step's blocks) in as few launches as
- * one tensor takes: logits, entropy and mean_entropy (NULL: no means) are HOST arrays of n_blocks device pointers, read
- * before the call returns.  The results are those of n_blocks calls, bit for bit.  n_blocks == 0 is a no-op. */
+/* nova_entropy of n_blocks tensors of one shape, stride and dtype (the logits of a step's blocks) in shared launches: up
+ * to 32 neighbours of the list that are all 16-byte aligned, or all not, take as many launches as one tensor (two lists of
+ * different alignment are better passed in two calls than mixed).  logits, entropy and mean_entropy (NULL: no means) are
+ * HOST arrays of n_blocks device pointers, read before the call returns.  The results are those of n_blocks calls, bit for
+ * bit.  n_blocks == 0 is a no-op. */
 int nova_entropy_blocks(nova_ctx* ctx, void* stream, int n_blocks, const void* const* logits, int logits_dtype,
                         int64_t rows_per_batch, int batch, int V, int64_t row_stride_elems,
                         float* const* entropy, float* const* mean_entropy);
@@ -210,8 +212,8 @@ int nova_head_entropy_static(nova_ctx* ctx, void* stream, const void* hidden, co
 int nova_select(nova_ctx* ctx, void* stream, const float* entropy, int B, int N, int k,
                 const int32_t* k_per_row, int32_t* kept_idx, uint8_t* keep_mask);
 
-/* nova_select of n_blocks arrays of one shape in one launch: entropy, kept_idx and keep_mask are HOST arrays of n_blocks
- * device pointers, k a HOST array of the blocks' keep counts (all read before the call returns); kept_idx[i] is
+/* nova_select of n_blocks arrays of one shape, up to 32 per launch: entropy, kept_idx and keep_mask are HOST arrays of
+ * n_blocks device pointers, k a HOST array of the blocks' keep counts (all read before the call returns); kept_idx[i] is
  * [B, k[i]].  n_blocks == 0 is a no-op. */
 int nova_select_blocks(nova_ctx* ctx, void* stream, int n_blocks, const float* const* entropy, int B, int N,
                        const int32_t* k, int32_t* const* kept_idx, uint8_t* const* keep_mask);

@@ -279,7 +279,8 @@ class Nova:
     # -- nova_entropy_blocks --------------------------------------------------------
     def entropy_blocks(self, logits: Sequence[torch.Tensor], entropy: Sequence[torch.Tensor],
                        mean: Optional[Sequence[torch.Tensor]] = None):
-        """entropy() of every tensor of a list; tensors of one shape, stride and dtype share their launches."""
+        """entropy() of every tensor of a list; tensors of one shape, stride and dtype share launches (32 neighbours of
+        one alignment each), a list that mixes them takes one call per tensor."""
         _check_lengths(len(logits), entropy=entropy, mean=mean)
         if len(logits) == 0:
             return
@@ -336,7 +337,7 @@ class Nova:
     # -- nova_select_blocks ---------------------------------------------------------
     def select_blocks(self, entropy: Sequence[torch.Tensor], k: Sequence[int], kept_idx: Sequence[torch.Tensor],
                       keep_mask: Sequence[torch.Tensor]):
-        """select() of every tensor of a list of [B, N] entropies, each with its own k, in one launch."""
+        """select() of every tensor of a list of [B, N] entropies, each with its own k, 32 of them per launch."""
         _check_lengths(len(entropy), k=k, kept_idx=kept_idx, keep_mask=keep_mask)
         if len(entropy) == 0:
             return

@@ -22,8 +22,10 @@ LIB = os.path.join(HERE, "libnova.so")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++20", "-fPIC", "-Wall", "-Wno-unused-function",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-    # the first 14 words of a kernel's arguments arrive in registers with the wave: no round trip to memory (0.2 us behind a
-    # cold scalar cache) before the first address; the block of 64 rows of 1024 in a graph 37.4 -> 36.4 us
+    # up to 14 words of a kernel's arguments in front of its first by-value struct arrive in registers with the wave: no round
+    # trip to memory (0.2 us behind a cold scalar cache) before the first address.  All 14: LayerNorm, attention (12 or 13 the
+    # unit-length rescaling, fp32 attention and bitwise entropies), 8 the bf16 projections, none the merge and the batched
+    # entropies, means and selections, whose tables come first.  The block of 64 rows of 1024 in a graph 37.4 -> 36.4 us
     "-mllvm", "-amdgpu-kernarg-preload-count=14",
 ]
 

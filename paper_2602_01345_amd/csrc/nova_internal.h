@@ -23,7 +23,8 @@ struct nova_ctx {
   std::vector<ProfRecord> prof;
   int gemm_cfg;   // >= 0 forces one GEMM tile configuration (environment NOVA_GEMM_CFG, for tuning)
   int attn_cfg;   // >= 1: likewise a workgroup shape of attention_bf16.hip (NOVA_ATTN_CFG)
-  int attn_split; // >= 1: attention_bf16.hip, 1: no item cut into key runs, else the items of the last round into that many (NOVA_ATTN_SPLIT)
+  // >= 1: attention_bf16.hip, 1: no item cut into key runs, else the items of the last round into that many (NOVA_ATTN_SPLIT)
+  int attn_split;
   int gemm_parts; // 0 forbids splitting a GEMM's rows over two launches (NOVA_GEMM_PARTS)
   int gemm_persist; // 0: one workgroup per tile always (NOVA_GEMM_PERSIST); else one workgroup per CU walks several tiles
   int gemm_ksplit;  // 0: never cut K of the large-tile FFN down projection into slices; 2 / 4: always (NOVA_GEMM_KSPLIT)

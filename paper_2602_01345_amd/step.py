@@ -3,7 +3,7 @@
 For every block j:  nova_entropy -> nova_select -> nova_pruned_block -> nova_merge_cache,
 all enqueued on the current stream with no host synchronisation in between (the keep
 count k_j is an input).  The entropies and selections read the blocks' logits only, inputs of the step like the
-keep counts, so a step takes them for all blocks first, in one launch each (nova_entropy_blocks, nova_select_blocks).
+keep counts, so a step takes them for all blocks first, up to 32 per launch (nova_entropy_blocks, nova_select_blocks).
 This module only owns device buffers and call order.
 """
 from __future__ import annotations

@@ -1,7 +1,8 @@
 """GPU parity of the few-queries attention kernel (csrc/attention_few_bf16.hip) against the oracle where it can go wrong: fewer
-key tiles than waves, keys that end on, one before and one behind a tile, queries that end on and next to a block of 32, four
-and eight waves, both head sizes, scores spread over tens of nats (the softmax reference moves in every wave), images with
-counts of their own (one with none), waves none of whose keys has a finite score.  Tolerance: bf16 tensors max|d| / max|ref| <= 2e-2, as everywhere."""
+key tiles than waves, keys that end on, one before and one behind a tile, queries that end on and next to a block of 32, one,
+four and eight waves, both head sizes, scores spread over tens of nats (the softmax reference moves in every wave), images
+with counts of their own (one with none), waves none of whose keys has a finite score.
+Tolerance: bf16 tensors max|d| / max|ref| <= 2e-2, as everywhere."""
 import pytest
 import torch
 
