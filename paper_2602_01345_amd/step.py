@@ -99,11 +99,12 @@ class StepRunner:
         return st.out
 
     def run_step(self, x: torch.Tensor, overlap_selection: bool = False) -> torch.Tensor:
-        """All blocks of the step: entropies and selections of all of them, then block after block.  A block's entropy and selection read only that block's logits (an input of the
-        step), so with overlap_selection they are enqueued one block ahead on a second stream (default priority)
-        and run next to the previous block's gather and QKV projection.  The results are the same launches on the
-        same data either way.  Measured gain on the largest workload: 0.2 % (the entropy kernel fills the CUs, so
-        the two streams mostly take turns); off by default."""
+        """All blocks of the step: entropies and selections of all of them, then block after block.  With
+        overlap_selection each block's entropy and selection, which read that block's logits only, are launches of
+        their own instead, enqueued one block ahead on a second stream (default priority) next to the previous
+        block's gather and QKV projection.  The values are the same either way.  Off by default: on the largest
+        workload a step takes 20.7 ms with it and 20.3 without (the launches of single blocks are mostly ramp and
+        tail, and the entropy kernel fills the CUs, so the two streams mostly take turns)."""
         if len(self.blocks) < 2:
             for st in self.blocks:
                 x = self.run_block(st, x)
