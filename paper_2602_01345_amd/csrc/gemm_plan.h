@@ -18,10 +18,12 @@
 //    32 x 64: 64 rows, K = 2304 into 6912 -1.6 us; 200 rows, C = 1920 = K -2.5; 100 rows, K = 4096, Nout = 1024 32 x 16 6.9,
 //    16 x 32 7.8), else the wider one, more rows in flight per weight row (a block of 256 rows of C = 512 26.5, 27.3).
 //  * Up to eight rows the weights are all there is to load, and the smallest workgroups stream them best where every CU
-//    gets as many of them: one, or with a longer K two to four (K = 2048, Nout = 8192, two rows: 8 x 8 8.2, 8 x 16 8.7,
-//    8 x 32 8.9; K = 1024, Nout = 3072: 8 x 8 4.0, 8 x 16 3.6).  Uneven, the rule above is better (a block of eight rows of
-//    C = 2304: 8 x 16 in place of 288 workgroups of 8 x 8 out of K = 2304 / 9216 -1.1 / -3.1 us, 8 x 32 in place of 864
-//    -1.5; C = 1920, 8 x 32 in place of 960 -0.9).
+//    gets as many of them: one (K = 4096, Nout = 1024, one row: 8 x 16 1.0 us more), with K > 1536 two to four (one row,
+//    K = 2048, Nout = 8192: 8 x 16 / 8 x 32 0.6 / 0.9 more; K = 1536, Nout = 6144: 0.1 more / 0.1 less; K = 1024, Nout = 4096:
+//    0.3 less / the same).  Uneven, the rule above is better (a block of eight rows of C = 2304: 8 x 16 in place of 288
+//    workgroups of 8 x 8 out of K = 2304 / 9216 -1.1 / -3.1 us, 8 x 32 in place of 864 -1.5; C = 1920, 8 x 32 in place of 960
+//    -0.9).  They have eight waves with K > 2048 (one / eight rows, K = 3072: -0.5 / 0 against four, K = 6144 -1.0 / -0.2, but
+//    K = 2048, Nout = 8192 +1.3 / +0.9).
 //  * One workgroup per CU beats the 128- and 256-row tiles at any row count (1024 rows, Nout = 1024: K = 1024 8.4
 //    against 11.1 us, K = 4096 16.4 against 22.9; 640 rows 7.4 / 14.7 against 11.0 / 17.3).  Two per CU do up to 512 rows
 //    (512 rows, K = 1024, Nout = 3072: 10.2 against 10.5; 820 rows, Nout = 1920 = K: 17.8 against 17.2), but not with a
