@@ -14,6 +14,7 @@
 //    matrix cores and LDS (see the K loop).  Against one ring of K steps for all waves, same box, weights from HBM:
 //    4096 x 6912 x 2304 (QKV) 150 -> 124 us, 4096 x 9216 x 2304 (GELU) 225 -> 180, 8192 x 8192 x 8192 968 -> 833
 //    (1.14 -> 1.32 PFLOP/s; a large library product on the same card 1.40).
+//    192 x 256 alternates in the same way, where it fills the CUs better (gemm_plan.h).
 //  * The smaller tiles: an NST-stage LDS ring (3 to 6 stages, per tile configuration): the loads of tiles
 //    t+1 .. t+NST-1 are in flight while tile t feeds the MFMAs; one bare barrier per K step with explicit
 //    vmcnt / lgkmcnt waits.
@@ -78,7 +79,10 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
   static_assert(BK == 64, "the swizzle is that of 128-byte rows");
   constexpr int KS = BK / 16;                              // MFMA K steps per stage
   constexpr int A_BYTES = BM * ROW_BYTES, B_BYTES = BN * ROW_BYTES, STAGE = A_BYTES + B_BYTES;
-  constexpr int LDS_BYTES = NST * STAGE;
+  // PP: the two waves of a SIMD alternate between the matrix cores and LDS (see the K loop); PP3: in three phases
+  constexpr bool PP3 = BM == 192 && BN == 256 && NST == 2 && WM == 2 && WN == 4;
+  constexpr bool PP = PP3 || (BM == 256 && BN == 256 && NST == 2 && WM == 2 && WN == 4);
+  constexpr int LDS_BYTES = PP ? 131072 : NST * STAGE;
   static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "tile rows must split over the waves");
   static_assert((NST - 2) * LPW < 64, "vmcnt is a 6-bit counter");
   __shared__ __attribute__((aligned(1024))) char lds[LDS_BYTES];
@@ -97,10 +101,8 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
   // workgroup takes the tiles L, L + gridDim.x, ...; the first K stages of its next tile are requested
   // before the epilogue of the current one, so their latency passes behind the epilogue.
   constexpr bool PERSIST = persistent_tiles(STAGGER, MODE);
-  // PP: the two waves of a SIMD alternate between the matrix cores and LDS (see the K loop)
-  constexpr bool PP = BM == 256 && BN == 256 && BK == 64 && NST == 2 && WM == 2 && WN == 4;
   // first tile row / column of MFMA tile i / jn of this wave
-  auto row_of = [&](int i) { return PP ? (i >> 1) * 128 + wm * 64 + (i & 1) * 32 : wm * (BM / WM) + i * 32; };
+  auto row_of = [&](int i) { return PP3 ? i * 64 + wm * 32 : PP ? (i >> 1) * 128 + wm * 64 + (i & 1) * 32 : wm * (BM / WM) + i * 32; };
   auto col_of = [&](int jn) { return PP ? jn * 128 + wn * 32 : wn * (BN / WN) + jn * 32; };
   const int kslice = PERSIST ? 0 : blockIdx.y;
   int L = blockIdx.x;
@@ -196,16 +198,29 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
       fill_lds(part >> 1 ? tile_w : tile_a, d, part >> 1 ? ob[j] : oa[j], (k_begin + t * BK) * 2);
     }
   };
-  // prologue: NST-1 K stages in flight (PP: one and three quarters)
+  // PP3: 64 rows (part 0 ... 2) or all columns (part 3) of the tile at K step t into LDS buffer buf
+  auto pp3_fill = [&](int part, int buf, int t) {
+#pragma unroll
+    for (int j = 0; j < (part == 3 ? 4 : 1); ++j) {
+      const int i = part == 3 ? j : part;
+      char* d = lds + (part == 3 ? 65536 : 0) + buf * 32768 + (i * NW + wave) * RPI * ROW_BYTES;
+      fill_lds(part == 3 ? tile_w : tile_a, d, part == 3 ? ob[i] : oa[i], (k_begin + t * BK) * 2);
+    }
+  };
+  // prologue: NST-1 K stages in flight (PP: one and three quarters, PP3: two but for 64 rows)
   auto prologue_first = [&]() {
-    if constexpr (PP) {
+    if constexpr (PP3) {
+      pp3_fill(3, 0, 0); pp3_fill(0, 0, 0); pp3_fill(1, 0, 0); pp3_fill(2, 0, 0);
+    } else if constexpr (PP) {
       pp_fill(0, 0, 0); pp_fill(2, 0, 0); pp_fill(3, 0, 0); pp_fill(1, 0, 0);
     } else {
       issue(0, k_of(0), 0, LPW);
     }
   };
   auto prologue_rest = [&]() {
-    if constexpr (PP) {
+    if constexpr (PP3) {
+      if (KT > 1) { pp3_fill(3, 1, 1); pp3_fill(0, 1, 1); pp3_fill(1, 1, 1); }
+    } else if constexpr (PP) {
       if (KT > 1) { pp_fill(0, 1, 1); pp_fill(2, 1, 1); pp_fill(3, 1, 1); }
     } else {
 #pragma unroll
@@ -353,17 +368,61 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
       asm volatile("" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
     };
-    auto quad = [&](int h, int jn) {
+    // between two barriers: the products of MFMA tiles (i0, j0) and (i1, j1), rows' fragments a0 and a1
+    auto products = [&](int i0, int j0, int a0, int i1, int j1, int a1) {
       __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): the fragments are here, their LDS may be refilled
       bar();
       __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks)
-#pragma unroll
-        for (int i = 0; i < 2; ++i) acc[2 * h + i][jn] = mfma32(fb[jn][ks], fa[i][ks], acc[2 * h + i][jn]);
+      for (int ks = 0; ks < 4; ++ks) {
+        acc[i0][j0] = mfma32(fb[j0][ks], fa[a0][ks], acc[i0][j0]);
+        acc[i1][j1] = mfma32(fb[j1][ks], fa[a1][ks], acc[i1][j1]);
+      }
       __builtin_amdgcn_s_setprio(0);
       bar();
     };
+    auto toggle = [&]() {                     // to the other LDS buffer
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) { aoff[ks] ^= 32768; boff[ks] ^= 32768; }
+    };
+    if constexpr (PP3) {
+      // 192 x 256 tile: three phases per K step, 64 rows (32 of them the wave's) x all columns each: eight products a phase as
+      // above, and all columns are read in the first.
+      //   phase 1: read columns, rows 0 .. 63   fill rows 128 .. 191 of step t + 1
+      //   phase 2: read rows 64 .. 127          fill columns and rows 0 .. 63 of step t + 2
+      //   phase 3: read rows 128 .. 191         fill rows 64 .. 127 of step t + 2
+      // What a phase reads, both wave groups have read in front of the barrier that the next phase's fills come behind; the
+      // wait in a phase is for what the next one reads, requested four phases before.
+      auto rd = [&](int i) {
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) fa[0][ks] = *reinterpret_cast<const bf16x8*>(lds + aoff[ks] + i * 8192);
+      };
+      if (!first_tile) { WAIT_VMCNT(0); } else if (KT > 1) { WAIT_VMCNT(8); } else { WAIT_VMCNT(2); }
+      first_tile = false;
+      bar();
+      if (wm == 1) bar();
+      for (int t = 0; t < KT; ++t) {
+        const int left = KT - 1 - t, buf = t & 1;   // K steps after this one
+        rd(0);
+        rd_b(0);
+        rd_b(1);
+        if (left >= 1) { pp3_fill(2, buf ^ 1, t + 1); WAIT_VMCNT(8); } else { WAIT_VMCNT(1); }
+        products(0, 0, 0, 0, 1, 0);
+        rd(1);
+        if (left >= 2) { pp3_fill(3, buf, t + 2); pp3_fill(0, buf, t + 2); WAIT_VMCNT(12); }
+        else if (left == 1) { WAIT_VMCNT(7); }
+        else { WAIT_VMCNT(0); }
+        products(1, 0, 0, 1, 1, 0);
+        rd(2);
+        if (left >= 2) { pp3_fill(1, buf, t + 2); WAIT_VMCNT(8); }
+        else if (left == 1) { WAIT_VMCNT(2); }
+        toggle();
+        products(2, 0, 0, 2, 1, 0);
+      }
+      if (wm == 0) bar();
+      if (PERSIST && (KT & 1)) toggle();            // the next tile starts in buffer 0 again
+    } else {
+    auto quad = [&](int h, int jn) { products(2 * h, jn, 0, 2 * h + 1, jn, 1); };
     if (!first_tile) { WAIT_VMCNT(0); } else if (KT > 1) { WAIT_VMCNT(10); } else { WAIT_VMCNT(4); }
     first_tile = false;
     bar();
@@ -384,14 +443,11 @@ __global__ __launch_bounds__(WM* WN * 64) void gemm_bf16_kernel(const bf16_t* __
       quad(1, 1);
       if (left >= 2) { pp_fill(3, buf, t + 2); WAIT_VMCNT(10); }
       else if (left == 1) { WAIT_VMCNT(4); }
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) { aoff[ks] ^= 32768; boff[ks] ^= 32768; }
+      toggle();
       quad(1, 0);
     }
     if (wm == 0) bar();
-    if (PERSIST && (KT & 1)) {              // the next tile starts in buffer 0 again
-#pragma unroll
-      for (int ks = 0; ks < 4; ++ks) { aoff[ks] ^= 32768; boff[ks] ^= 32768; }
+    if (PERSIST && (KT & 1)) toggle();              // the next tile starts in buffer 0 again
     }
   } else {
   // wait for the first K stage.  After a prefetch the epilogue's own loads and stores are in flight as well and
@@ -706,14 +762,18 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restric
 
 template <int MODE>
 hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W, int m_base, int M, int Nout, int K,
-                       const EpiParams<bf16_t>& ep, int slots, int cus, int ksplit) {
+                       const EpiParams<bf16_t>& ep, int slots, int cus, int ksplit, bool forced) {
   if (cfg == kRowsCfg) {
     const RowsPlan plan = gemm_rows_plan(cus, MODE, M - m_base, Nout, K);
     return launch_gemm_rows_bf16(st, plan, MODE, A, W, m_base, M, Nout, K, ep);
   }
+  // configuration 1 in its lower height; 9 is that height by force
+  const bool low = cfg == 9 || (cfg == 1 && !forced &&
+                                alternating_rows(cus, MODE, M - m_base, Nout, K, ep.part ? ep.part_floats : 0) == 192);
+  if (cfg == 9) cfg = 1;
   if constexpr (MODE == EPI_RESIDUAL) {
     // see k_slices; the scratch buffer holds 4 x rows x C floats, hence Nout == C
-    if ((cfg == 1 || cfg == 2 || cfg == 5 || cfg == 6) && ep.part && Nout == ep.C && Nout % 8 == 0) {
+    if (((cfg == 1 && !low) || cfg == 2 || cfg == 5 || cfg == 6) && ep.part && Nout == ep.C && Nout % 8 == 0) {
       const int bm = cfg == 5 ? 128 : cfg == 6 ? 192 : 256, bn = cfg == 1 ? 256 : 128;
       const int tiles = ((M - m_base + bm - 1) / bm) * ((Nout + bn - 1) / bn);
       const int ks = k_slices(cus, MODE, tiles, M - m_base, Nout, K, ep.part_floats, ksplit);
@@ -743,6 +803,8 @@ hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W
     else
       return hipErrorInvalidValue;
   }
+  if constexpr (MODE != EPI_ENTROPY)
+    if (low) return launch_cfg<192, 256, 2, 4, 64, 2, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
   switch (cfg) {
     case 1: return launch_cfg<256, 256, 2, 4, 64, 2, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
     case 5: return launch_cfg<128, 128, 2, 4, 64, 3, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
@@ -759,7 +821,7 @@ hipError_t launch_mode(const nova_ctx* ctx, hipStream_t st, const bf16_t* A, con
     const int cus = ctx ? ctx->num_cus : 256;
     const hipError_t e = launch_part<MODE>(st, p.cfg[i], A, W, p.m_base[i], p.m_end[i], Nout, K, ep,
                                            (ctx && ctx->gemm_persist == 0) ? 0 : cus, cus,
-                                           ctx ? ctx->gemm_ksplit : -1);
+                                           ctx ? ctx->gemm_ksplit : -1, forced_tile(ctx));
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

@@ -61,7 +61,11 @@ inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K)
 }
 
 // Tile configurations (NOVA_GEMM_CFG forces one, for tuning; numbers without a kernel mean 2):
-//   1: 256x256x64, 8 waves of 128x64 that alternate between the matrix cores and LDS
+//   1: 256x256x64, 8 waves of 128x64 that alternate between the matrix cores and LDS, or 192x256x64, the same with waves of
+//      96x64, where the model prices that lower: more of the CUs busy in a round that 256 x 256 tiles fill by half (us, weights
+//      from memory, 256 x 256 or the best plan without it / 192 x 256: 4096 rows, K = 2304, 2304 features 51.2 / 46.0, K = 9216
+//      166 / 154; 4915 rows of C = 2048, output 51.1 / 43.8, down 163 / 140; 1229 rows, K = 2304, 9216 features 57.5 / 52.8).
+//      Never cut in K: four slices of it lose to slices of the smaller tiles (1046 rows, K = 5632, 1408 features 38.7 / 33.3)
 //   2: 256x128x64, 8 waves of 64x64, 3 stages
 //   6: 192x128x64, 8 waves of 96x32, 3 stages: one round where 256x128 leaves too many CUs idle and 128x128 needs a
 //      second round (1640 rows, K = 1024, 3072 features 17.3 -> 15.7 us; 1100 rows, 4096 features 19.2 -> 16.2)
@@ -70,6 +74,7 @@ inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K)
 //   5: 128x128x64, 8 waves of 64x32, 3 stages, one workgroup per CU (two waves per SIMD hide the LDS waits that
 //      four waves of 64x64 expose: 3-10 % faster at every shape measured)
 //   7: the few-rows kernels of gemm_rows_bf16.hip (chosen by gemm_rows_plan, not by force)
+//   9: 192x256x64 by force (a plan calls it 1; not for a prediction head)
 // Without a forced choice the launcher prices 1, 2, 5 and 6 with a model fitted to measurements on MI355X (300 ... 6144
 // rows, widths C of 640 ... 2304, outputs of C, 3C and 4C features, K = C and 4C): a launch takes rounds of one tile
 // per CU; a round costs a fixed time (first loads, epilogue) and a time per element of K that grows with the share of
@@ -79,7 +84,7 @@ inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K)
 // fit leaves out).  A fit to launches that find their weights in L2 makes a single round of 256 x 256 tiles too dear
 // against two of smaller ones, which fetch the weights more often: 0.25 %, and blocks up to 7 % slower (1500 rows,
 // C = 1920 / 2048 226 / 237 us, with this one 212 / 228; 1800 rows, C = 1024 126 and 120).
-constexpr int kNumCfgs = 7;
+constexpr int kNumCfgs = 10;
 constexpr int kRowsCfg = 7;
 
 struct Candidate {
@@ -91,13 +96,17 @@ struct Candidate {
 static const Candidate kCands[] = {{1, 256, 256, 3.5, 5.4, 1.8, 0.01806, -0.00115, 0.00630},
                                    {2, 256, 128, 2.4, 3.1, 0.7, 0.00974, -0.00010, 0.00433},
                                    {6, 192, 128, 2.5, 2.7, 0.6, 0.00778, 0.00189, 0.00153},
-                                   {5, 128, 128, 2.2, 1.1, 0.1, 0.00649, 0.00120, 0.00165}};
+                                   {5, 128, 128, 2.2, 1.1, 0.1, 0.00649, 0.00120, 0.00165},
+                                   {1, 192, 256, 4.6, 5.3, 1.6, 0.01280, 0.00100, 0.00420}};
+inline bool low_tile(const Candidate& c) { return c.cfg == 1 && c.bm == 192; }
+// The lower height is for projections: a prediction head's rows are many, and full rounds want the 256 x 256 tile.
+inline bool tile_takes(const Candidate& c, int mode) { return !low_tile(c) || mode != EPI_ENTROPY; }
 
 // Up to this K the lanes' 32-bit offsets into a tile do: 255 rows of 2 K bytes and the offset along K stay below 2^31.
 // Beyond it configuration 2 takes 64-bit addresses, K slices among them, and stands in for 1, 5 and 6; the staggered ones
 // (3, 4) of a prediction head always do.  The FFN down projection gets there with few features and a wide FFN.
 constexpr int kNearK = 1 << 21;
-inline bool tile_fits(int cfg, int K) { return (cfg != 1 && cfg != 5 && cfg != 6) || K <= kNearK; }
+inline bool tile_fits(int cfg, int K) { return (cfg != 1 && cfg != 5 && cfg != 6 && cfg != 9) || K <= kNearK; }
 inline bool far_tile(int K) { return K > kNearK; }
 
 // K slices of a launch of `tiles` tiles (the FFN down projection once few tokens are kept: a long K and a narrow
@@ -114,7 +123,7 @@ inline int k_slices(int cus, int mode, int tiles, int64_t rows, int Nout, int K,
 // Modelled time (seconds) of one launch over M rows with candidate c.
 inline double model_time(const Candidate& c, int slots, int mode, int M, int Nout, int K, int64_t part_floats) {
   const int tiles = ((M + c.bm - 1) / c.bm) * ((Nout + c.bn - 1) / c.bn);
-  const int ks = k_slices(slots, mode, tiles, M, Nout, K, part_floats, -1);
+  const int ks = low_tile(c) ? 1 : k_slices(slots, mode, tiles, M, Nout, K, part_floats, -1);
   const int full = tiles * ks / slots, rest = tiles * ks % slots;
   const double f = (double)rest / slots, fixed = c.round + (mode == EPI_GELU || mode == EPI_GELU_TANH ? c.gelu : 0.0);
   double t = c.launch + full * (fixed + K / ks * (c.k0 + c.k1 + c.k3));
@@ -137,8 +146,27 @@ inline double rows_time(const RowsPlan& p, int cus, int rows, int Nout, int K) {
   return 2.1e-6 + bytes / 75e9 + (double)Nout * K / 5e12;
 }
 
+inline bool forced_tile(const nova_ctx* ctx) {
+  return ctx && ctx->gemm_cfg >= 0 && ctx->gemm_cfg < kNumCfgs && ctx->gemm_cfg != kRowsCfg;
+}
+
+// Rows of a tile of configuration 1: the height that the model prices lower.
+inline int alternating_rows(int slots, int mode, int M, int Nout, int K, int64_t part_floats) {
+  int bm = 256;
+  double best = 1e30;
+  for (const Candidate& c : kCands) {
+    if (c.cfg != 1 || !tile_takes(c, mode)) continue;
+    const double t = model_time(c, slots, mode, M, Nout, K, part_floats);
+    if (t < best) { best = t; bm = c.bm; }
+  }
+  return bm;
+}
+
 inline int pick_cfg(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64_t part_floats, double* t_out = nullptr) {
-  if (ctx && ctx->gemm_cfg >= 0 && ctx->gemm_cfg < kNumCfgs) return tile_fits(ctx->gemm_cfg, K) ? ctx->gemm_cfg : 2;
+  if (forced_tile(ctx)) {
+    const bool has = tile_fits(ctx->gemm_cfg, K) && (mode != EPI_ENTROPY || ctx->gemm_cfg < kRowsCfg);
+    return has ? ctx->gemm_cfg : 2;
+  }
   if (mode == EPI_ENTROPY) {
     if (M <= 64) return 3;
     if (narrow_tiles(M, Nout, K)) return 4;
@@ -157,7 +185,7 @@ inline int pick_cfg(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64
   const bool wide = mode == EPI_ENTROPY && (int64_t)M * ((Nout + 127) / 128) > room && (int64_t)M * ((Nout + 255) / 256) <= room;
   for (const Candidate& c : kCands) {
     if (wide && c.bn < 256) continue;
-    if (!tile_fits(c.cfg, K)) continue;
+    if (!tile_fits(c.cfg, K) || !tile_takes(c, mode)) continue;
     const double t = model_time(c, slots, mode, M, Nout, K, part_floats);
     if (t < best_t) { best_t = t; best = c.cfg; }
   }
@@ -176,12 +204,11 @@ inline Plan plan_rows(const nova_ctx* ctx, int mode, int M, int Nout, int K, int
   Plan p;
   double t_single = 1e30;
   p.n = 1; p.m_base[0] = 0; p.m_end[0] = M; p.cfg[0] = pick_cfg(ctx, mode, M, Nout, K, part_floats, &t_single);
-  const bool forced = ctx && ctx->gemm_cfg >= 0 && ctx->gemm_cfg < kNumCfgs;
-  if (forced || mode == EPI_ENTROPY || M <= 512 || (ctx && ctx->gemm_parts == 0)) return p;   // one launch
+  if (forced_tile(ctx) || mode == EPI_ENTROPY || M <= 512 || (ctx && ctx->gemm_parts == 0)) return p;   // one launch
   const int slots = ctx ? ctx->num_cus : 256;
   double best = t_single * 0.97;                          // a second launch has to pay for itself
   for (const Candidate& c : kCands) {
-    if (!tile_fits(c.cfg, K)) continue;
+    if (!tile_fits(c.cfg, K) || !tile_takes(c, mode)) continue;
     const int tiles_n = (Nout + c.bn - 1) / c.bn;
     for (int rounds = 1;; ++rounds) {                     // rounds of the first part
       const int64_t m1_all = (int64_t)rounds * slots / tiles_n * c.bm;

@@ -1,0 +1,42 @@
+"""GPU parity of the projection tiles that stand in where others leave CUs idle (csrc/gemm_bf16.hip, by force) against the
+oracle where their K loops and edges change: one, two, three and an odd number of K steps, rows and features that end inside
+a tile and on its edge, gated residuals, more tiles than compute units (a workgroup then walks several, each starting in the
+first LDS buffer).  Tolerance: bf16 tensors max|d| / max|ref| <= 2e-2, as everywhere (the products and
+their sums are fp32)."""
+import pytest
+import torch
+
+import workloads as WL
+
+pytestmark = pytest.mark.gpu
+TILES = {"192x256": "9"}
+
+
+@pytest.fixture(params=list(TILES.values()), ids=list(TILES))
+def hx(request, monkeypatch):
+    import harness
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU and the built libnova.so (no fallback)")
+    from paper_2602_01345_amd import Nova
+    monkeypatch.setenv("NOVA_GEMM_CFG", request.param)
+    monkeypatch.setattr(harness, "_NOVA", Nova(0))     # the knob is read when a context is created
+    return harness
+
+
+def _block(B, grid, P, C, heads):
+    return WL.Workload("shapes", "bf16", B=B, C=C, heads=heads, L=1, V=64, keep_hi=.5, keep_lo=.5,
+                       scales=(WL.Scale(grid=grid, prev_grid=max(grid - 2, 1), kv_len=P),), seed=23)
+
+
+@pytest.mark.parametrize("C,heads,k", [(64, 1, 1), (64, 1, 191), (128, 2, 192), (192, 3, 193), (320, 5, 64), (640, 5, 289)])
+@pytest.mark.parametrize("variant", [None, frozenset({"ada"})], ids=["base", "gated"])
+def test_k_steps_and_edges(hx, C, heads, k, variant):
+    print(f"tile shapes C={C} k={k} {variant}", flush=True)
+    wl = _block(2, 17, 40, C, heads)
+    hx.check_block(hx.make_host_block(wl, 0, k=k, variant=variant), hx.BF16_TOL)
+
+
+def test_several_tiles_per_workgroup_with_an_odd_number_of_k_steps(hx):
+    print("tile shapes C=832 M=6480", flush=True)      # 13 K steps
+    wl = _block(16, 21, 30, 832, 13)
+    hx.check_block(hx.make_host_block(wl, 0, k=405), hx.BF16_TOL, rows=[0, 7, 15])
