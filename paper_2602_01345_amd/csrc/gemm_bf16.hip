@@ -803,8 +803,10 @@ hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W
     else
       return hipErrorInvalidValue;
   }
-  if constexpr (MODE != EPI_ENTROPY)
+  if constexpr (MODE != EPI_ENTROPY) {
     if (low) return launch_cfg<192, 256, 2, 4, 64, 2, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
+    if (cfg == 8) return launch_cfg<128, 64, 4, 2, 64, 6, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
+  }
   switch (cfg) {
     case 1: return launch_cfg<256, 256, 2, 4, 64, 2, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
     case 5: return launch_cfg<128, 128, 2, 4, 64, 3, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);

@@ -74,8 +74,12 @@ inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K)
 //   5: 128x128x64, 8 waves of 64x32, 3 stages, one workgroup per CU (two waves per SIMD hide the LDS waits that
 //      four waves of 64x64 expose: 3-10 % faster at every shape measured)
 //   7: the few-rows kernels of gemm_rows_bf16.hip (chosen by gemm_rows_plan, not by force)
+//   8: 128x64x64, 8 waves of 32x32, 6 stages (with 3: K = 2304 18.6 us in place of 16.3): a narrow output of some 800 ... 2000
+//      rows, which 128x128 tiles spread over half of the CUs (us, weights from memory, 128x128 / 128x64: 820 rows, 2304 features
+//      out of K = 2304 21.4 / 16.3, 700 rows of 2048 17.9 / 14.5, 1640 rows of 1024 10.4 / 9.4, 2000 rows, K = 2560, 640
+//      features 20.4 / 17.2).  A second round of it loses (2458 rows of 1024 10.9 / 17.0)
 //   9: 192x256x64 by force (a plan calls it 1; not for a prediction head)
-// Without a forced choice the launcher prices 1, 2, 5 and 6 with a model fitted to measurements on MI355X (300 ... 6144
+// Without a forced choice the launcher prices 1, 2, 5, 6 and 8 with a model fitted to measurements on MI355X (300 ... 6144
 // rows, widths C of 640 ... 2304, outputs of C, 3C and 4C features, K = C and 4C): a launch takes rounds of one tile
 // per CU; a round costs a fixed time (first loads, epilogue) and a time per element of K that grows with the share of
 // the CUs that are busy (they share L2, memory and power).  Fitted for the choice, not for the times, to whole blocks
@@ -97,16 +101,22 @@ static const Candidate kCands[] = {{1, 256, 256, 3.5, 5.4, 1.8, 0.01806, -0.0011
                                    {2, 256, 128, 2.4, 3.1, 0.7, 0.00974, -0.00010, 0.00433},
                                    {6, 192, 128, 2.5, 2.7, 0.6, 0.00778, 0.00189, 0.00153},
                                    {5, 128, 128, 2.2, 1.1, 0.1, 0.00649, 0.00120, 0.00165},
+                                   {8, 128, 64, 2.2, 2.3, 0.2, 0.00490, 0.00030, 0.00040},
                                    {1, 192, 256, 4.6, 5.3, 1.6, 0.01280, 0.00100, 0.00420}};
 inline bool low_tile(const Candidate& c) { return c.cfg == 1 && c.bm == 192; }
-// The lower height is for projections: a prediction head's rows are many, and full rounds want the 256 x 256 tile.
-inline bool tile_takes(const Candidate& c, int mode) { return !low_tile(c) || mode != EPI_ENTROPY; }
+// 128 x 64 and the lower height are for projections: a prediction head's rows are many, and full rounds want the 256 x 256
+// tile.  A long K leaves 128 x 64 to the tiles that are cut in K: uncut it would gain 2 ... 7 % at 1200 ... 2000 rows of
+// K = 4096, 1024 features (2048 rows 30.1 / 28.1 us) and lose elsewhere (820 rows, K = 8192, 2048 features 43.9 / 48.8).
+inline bool tile_takes(const Candidate& c, int mode, int K) {
+  if (c.cfg == 8) return mode != EPI_ENTROPY && K < 4096;
+  return !low_tile(c) || mode != EPI_ENTROPY;
+}
 
 // Up to this K the lanes' 32-bit offsets into a tile do: 255 rows of 2 K bytes and the offset along K stay below 2^31.
 // Beyond it configuration 2 takes 64-bit addresses, K slices among them, and stands in for 1, 5 and 6; the staggered ones
 // (3, 4) of a prediction head always do.  The FFN down projection gets there with few features and a wide FFN.
 constexpr int kNearK = 1 << 21;
-inline bool tile_fits(int cfg, int K) { return (cfg != 1 && cfg != 5 && cfg != 6 && cfg != 9) || K <= kNearK; }
+inline bool tile_fits(int cfg, int K) { return (cfg != 1 && cfg != 5 && cfg != 6 && cfg != 8 && cfg != 9) || K <= kNearK; }
 inline bool far_tile(int K) { return K > kNearK; }
 
 // K slices of a launch of `tiles` tiles (the FFN down projection once few tokens are kept: a long K and a narrow
@@ -155,7 +165,7 @@ inline int alternating_rows(int slots, int mode, int M, int Nout, int K, int64_t
   int bm = 256;
   double best = 1e30;
   for (const Candidate& c : kCands) {
-    if (c.cfg != 1 || !tile_takes(c, mode)) continue;
+    if (c.cfg != 1 || !tile_takes(c, mode, K)) continue;
     const double t = model_time(c, slots, mode, M, Nout, K, part_floats);
     if (t < best) { best = t; bm = c.bm; }
   }
@@ -185,7 +195,7 @@ inline int pick_cfg(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64
   const bool wide = mode == EPI_ENTROPY && (int64_t)M * ((Nout + 127) / 128) > room && (int64_t)M * ((Nout + 255) / 256) <= room;
   for (const Candidate& c : kCands) {
     if (wide && c.bn < 256) continue;
-    if (!tile_fits(c.cfg, K) || !tile_takes(c, mode)) continue;
+    if (!tile_fits(c.cfg, K) || !tile_takes(c, mode, K)) continue;
     const double t = model_time(c, slots, mode, M, Nout, K, part_floats);
     if (t < best_t) { best_t = t; best = c.cfg; }
   }
@@ -208,7 +218,7 @@ inline Plan plan_rows(const nova_ctx* ctx, int mode, int M, int Nout, int K, int
   const int slots = ctx ? ctx->num_cus : 256;
   double best = t_single * 0.97;                          // a second launch has to pay for itself
   for (const Candidate& c : kCands) {
-    if (!tile_fits(c.cfg, K) || !tile_takes(c, mode)) continue;
+    if (!tile_fits(c.cfg, K) || !tile_takes(c, mode, K)) continue;
     const int tiles_n = (Nout + c.bn - 1) / c.bn;
     for (int rounds = 1;; ++rounds) {                     // rounds of the first part
       const int64_t m1_all = (int64_t)rounds * slots / tiles_n * c.bm;

@@ -1,5 +1,5 @@
 """GPU parity of the projection tiles that stand in where others leave CUs idle (csrc/gemm_bf16.hip, by force) against the
-oracle where their K loops and edges change: one, two, three and an odd number of K steps, rows and features that end inside
+oracle where their K loops and edges change: one, two, three and more K steps than stages, an odd number, rows and features that end inside
 a tile and on its edge, gated residuals, more tiles than compute units (a workgroup then walks several, each starting in the
 first LDS buffer).  Tolerance: bf16 tensors max|d| / max|ref| <= 2e-2, as everywhere (the products and
 their sums are fp32)."""
@@ -9,7 +9,7 @@ import torch
 import workloads as WL
 
 pytestmark = pytest.mark.gpu
-TILES = {"192x256": "9"}
+TILES = {"192x256": "9", "128x64": "8"}
 
 
 @pytest.fixture(params=list(TILES.values()), ids=list(TILES))
@@ -28,7 +28,7 @@ def _block(B, grid, P, C, heads):
                        scales=(WL.Scale(grid=grid, prev_grid=max(grid - 2, 1), kv_len=P),), seed=23)
 
 
-@pytest.mark.parametrize("C,heads,k", [(64, 1, 1), (64, 1, 191), (128, 2, 192), (192, 3, 193), (320, 5, 64), (640, 5, 289)])
+@pytest.mark.parametrize("C,heads,k", [(64, 1, 1), (64, 1, 191), (128, 2, 192), (192, 3, 193), (320, 5, 64), (448, 7, 129), (640, 5, 289)])
 @pytest.mark.parametrize("variant", [None, frozenset({"ada"})], ids=["base", "gated"])
 def test_k_steps_and_edges(hx, C, heads, k, variant):
     print(f"tile shapes C={C} k={k} {variant}", flush=True)
