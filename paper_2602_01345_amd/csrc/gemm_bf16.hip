@@ -809,7 +809,10 @@ hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W
   }
   switch (cfg) {
     case 1: return launch_cfg<256, 256, 2, 4, 64, 2, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
-    case 5: return launch_cfg<128, 128, 2, 4, 64, 3, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
+    case 5:
+      if constexpr (MODE != EPI_ENTROPY)
+        if (K >= kDeepK) return launch_cfg<128, 128, 2, 4, 64, 4, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
+      return launch_cfg<128, 128, 2, 4, 64, 3, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
     case 6: return launch_cfg<192, 128, 2, 4, 64, 3, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
     default: return launch_cfg<256, 128, 4, 2, 64, 3, false, MODE>(st, A, W, m_base, M, Nout, K, ep, slots);
   }

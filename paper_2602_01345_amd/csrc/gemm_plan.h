@@ -71,8 +71,10 @@ inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K)
 //      second round (1640 rows, K = 1024, 3072 features 17.3 -> 15.7 us; 1100 rows, 4096 features 19.2 -> 16.2)
 //   3: 64x32x64, 2 waves of 32x32, 6 stages, staggered K walk          (head entropy only, M <= 64)
 //   4: 128x32x64, 4 waves of 32x32, 4 stages, staggered K walk         (head entropy only, M <= 256 or 512)
-//   5: 128x128x64, 8 waves of 64x32, 3 stages, one workgroup per CU (two waves per SIMD hide the LDS waits that
-//      four waves of 64x64 expose: 3-10 % faster at every shape measured)
+//   5: 128x128x64, 8 waves of 64x32, 3 stages or, from K = kDeepK on, 4, one workgroup per CU (two waves per SIMD hide the LDS
+//      waits that four waves of 64x64 expose: 3-10 % faster at every shape measured).  Three / four stages, us, weights from
+//      memory: 900 rows, K = 2304, 2304 features 21.6 / 19.5, 6912 features 44.4 / 42.0; 520 rows, K = 2048, 6144 features
+//      20.7 / 19.9; but K = 1536 13.0 / 13.2, K = 1024 10.1 / 10.4 (five: nowhere better than four)
 //   7: the few-rows kernels of gemm_rows_bf16.hip (chosen by gemm_rows_plan, not by force)
 //   8: 128x64x64, 8 waves of 32x32, 6 stages (with 3: K = 2304 18.6 us in place of 16.3): a narrow output of some 800 ... 2000
 //      rows, which 128x128 tiles spread over half of the CUs (us, weights from memory, 128x128 / 128x64: 820 rows, 2304 features
@@ -90,6 +92,7 @@ inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K)
 // C = 1920 / 2048 226 / 237 us, with this one 212 / 228; 1800 rows, C = 1024 126 and 120).
 constexpr int kNumCfgs = 10;
 constexpr int kRowsCfg = 7;
+constexpr int kDeepK = 2048;
 
 struct Candidate {
   int cfg, bm, bn;

@@ -40,3 +40,13 @@ def test_several_tiles_per_workgroup_with_an_odd_number_of_k_steps(hx):
     print("tile shapes C=832 M=6480", flush=True)      # 13 K steps
     wl = _block(16, 21, 30, 832, 13)
     hx.check_block(hx.make_host_block(wl, 0, k=405), hx.BF16_TOL, rows=[0, 7, 15])
+
+
+def test_128_x_128_with_a_long_k(monkeypatch):
+    """From K = 2048 on that tile has one more stage."""
+    import harness as hx
+    from paper_2602_01345_amd import Nova
+    monkeypatch.setenv("NOVA_GEMM_CFG", "5")
+    monkeypatch.setattr(hx, "_NOVA", Nova(0))
+    print("tile shapes C=2048 128 x 128", flush=True)
+    hx.check_block(hx.make_host_block(_block(1, 13, 40, 2048, 16), 0, k=129), hx.BF16_TOL)
