@@ -33,13 +33,6 @@ hipError_t launch_block_bf16(nova_ctx* ctx, hipStream_t st, const nova_block_sha
   const int ada_pitch = 6 * C;
   auto ada_row = [&](int j) { return ada ? ada + (int64_t)j * C : nullptr; };
 
-  hipError_t e;
-  {
-    StageTimer t(ctx, st, NOVA_STAGE_GATHER_LN);
-    e = launch_gather_ln(st, NOVA_BF16, x, idx, M, s.k, s.N, C, ada_row(0), ada_row(1), ada_pitch, u, rc.k_rows);
-  }
-  if (e != hipSuccess) return e;
-
   EpiParams<bf16_t> ep = {};
   ep.C = C; ep.heads = s.heads; ep.dh = dh; ep.cap = s.kv_capacity; ep.P = s.kv_len; ep.k = s.k;
   ep.idx = idx; ep.Ntok = s.N;
@@ -48,13 +41,32 @@ hipError_t launch_block_bf16(nova_ctx* ctx, hipStream_t st, const nova_block_sha
   ep.part = reinterpret_cast<float*>(ws.part_o);          // free once attention is done: K-slice sums of the projections back to C
   ep.part_floats = ws.part_floats;
 
+  hipError_t e;
+  // LayerNorm in front of a projection of src: few rows without modulation are normalised by the projection itself, others
+  // by a launch of their own into u.  Returns the projection's operand.
+  auto layer_norm = [&](const bf16_t* src, const int32_t* src_idx, const bf16_t* shift, const bf16_t* scale, int32_t* kv_next,
+                        int mode, int Nout) -> const bf16_t* {
+    ep.kv_next = kv_next;
+    e = hipSuccess;
+    if (!shift && gemm_takes_norm(ctx, mode, M, Nout, C)) return src;
+    e = launch_gather_ln(st, NOVA_BF16, src, src_idx, M, s.k, s.N, C, shift, scale, ada_pitch, u, rc.k_rows, rc.kv_rows, kv_next,
+                         s.kv_len);
+    return u;
+  };
+  const bf16_t* in;
+  {
+    StageTimer t(ctx, st, NOVA_STAGE_GATHER_LN);
+    in = layer_norm(x, idx, ada_row(0), ada_row(1), nullptr, EPI_QKV, 3 * C);
+  }
+  if (e != hipSuccess) return e;
+
   // the attention kernel takes its query rows multiplied by (score scale * log2 e); unit-length queries get the
   // factor when they are rescaled (a factor before that would cancel)
   ep.bias = static_cast<const bf16_t*>(w.b_qkv); ep.out = q; ep.ldo = C; ep.kc = kc; ep.vc = vc;
   ep.q_scale = var.qk_norm ? 1.0f : kAttnLog2e / sqrtf((float)dh);
   {
     StageTimer t(ctx, st, NOVA_STAGE_QKV);
-    e = launch_gemm_bf16(ctx, st, EPI_QKV, u, w.w_qkv, M, 3 * C, C, ep);
+    e = launch_gemm_bf16(ctx, st, EPI_QKV, in, w.w_qkv, M, 3 * C, C, ep, in != u);
     if (e == hipSuccess && var.qk_norm)
       e = launch_qk_norm(st, NOVA_BF16, q, kc, var.qk_scale, kAttnLog2e, s.B, s.k, C, s.heads, s.kv_capacity, s.kv_len,
                          rc.k_rows, rc.kv_rows);
@@ -79,11 +91,11 @@ hipError_t launch_block_bf16(nova_ctx* ctx, hipStream_t st, const nova_block_sha
     // cross-attention sub-layer over the condition tokens: LN -> query projection -> attention over the
     // text keys / values -> output projection added to x1 in place (each output element is read and
     // written by the same thread)
-    e = launch_gather_ln(st, NOVA_BF16, x1, nullptr, M, s.k, s.N, C, nullptr, nullptr, 0, u, rc.k_rows);
-    if (e != hipSuccess) return e;
     ep.bias = static_cast<const bf16_t*>(var.b_cq); ep.out = q; ep.ldo = C; ep.gate = nullptr;
     ep.q_scale = kAttnLog2e / sqrtf((float)dh);
-    e = launch_gemm_bf16(ctx, st, EPI_PLAIN, u, var.w_cq, M, C, C, ep);
+    in = layer_norm(x1, nullptr, nullptr, nullptr, nullptr, EPI_PLAIN, C);
+    if (e != hipSuccess) return e;
+    e = launch_gemm_bf16(ctx, st, EPI_PLAIN, in, var.w_cq, M, C, C, ep, in != u);
     if (e != hipSuccess) return e;
     e = launch_attention_bf16(ctx, st, q, var.k_text, var.v_text, s.B, s.k, C, s.heads, var.text_capacity,
                               var.text_len, attn, reinterpret_cast<float*>(ws.part_o),
@@ -93,17 +105,17 @@ hipError_t launch_block_bf16(nova_ctx* ctx, hipStream_t st, const nova_block_sha
     e = launch_gemm_bf16(ctx, st, EPI_RESIDUAL, attn, var.w_co, M, C, C, ep);
     if (e != hipSuccess) return e;
   }
+  const int up = var.gelu_tanh ? EPI_GELU_TANH : EPI_GELU;
   {
     StageTimer t(ctx, st, NOVA_STAGE_LN2);
-    e = launch_gather_ln(st, NOVA_BF16, x1, nullptr, M, s.k, s.N, C, ada_row(3), ada_row(4), ada_pitch, u, rc.k_rows,
-                         rc.kv_rows, rc.kv_next, s.kv_len);
+    in = layer_norm(x1, nullptr, ada_row(3), ada_row(4), rc.kv_next, up, F);
   }
   if (e != hipSuccess) return e;
 
   ep.bias = static_cast<const bf16_t*>(w.b_fc1); ep.out = hid; ep.ldo = F; ep.gate = nullptr;
   {
     StageTimer t(ctx, st, NOVA_STAGE_FFN1);
-    e = launch_gemm_bf16(ctx, st, var.gelu_tanh ? EPI_GELU_TANH : EPI_GELU, u, w.w_fc1, M, F, C, ep);
+    e = launch_gemm_bf16(ctx, st, up, in, w.w_fc1, M, F, C, ep, in != u);
   }
   if (e != hipSuccess) return e;
 

@@ -46,6 +46,8 @@ __device__ __forceinline__ void fill_lds(const bf16_t* base, char* dst, uint32_t
       __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(base), 0, 0x7FFFFFFF, 0x00020000), (lptr_t)dst, 16, lane_off, off, 0, 0);
 }
 
+constexpr float kNormEps = 1e-6f;          // of the LayerNorms
+
 // Per-image keep counts (the reduction ratios of Sec. 3.3, "Dual-Linkage Acceleration", are per instance): the
 // kept rows of image b are slots [0, k_b) of its kpitch-row segment, and it holds its own number of prior K/V rows.
 // Null pointers mean "uniform": every image keeps kpitch rows / holds P prior rows.  Values are clamped, so a

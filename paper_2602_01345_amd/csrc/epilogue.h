@@ -49,6 +49,8 @@ struct EpiParams {
   // bf16 kernels: div_inv(k) and log2(dh), set by launch_gemm_bf16
   uint32_t k_inv;
   int dh_log2;
+  // projections that normalise their rows: where to write the per-image cache lengths after the block, or nullptr
+  int32_t* kv_next;
 
   // image (and slot in it) of a kept-token row
   __device__ __forceinline__ int image(int row, int& slot) const { return div_by(row, k, k_inv, slot); }

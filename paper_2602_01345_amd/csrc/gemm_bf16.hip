@@ -820,7 +820,9 @@ hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W
 
 template <int MODE>
 hipError_t launch_mode(const nova_ctx* ctx, hipStream_t st, const bf16_t* A, const bf16_t* W, int M, int Nout,
-                       int K, const EpiParams<bf16_t>& ep) {
+                       int K, const EpiParams<bf16_t>& ep, bool norm) {
+  if (norm)
+    return launch_gemm_rows_bf16(st, gemm_norm_plan(ctx ? ctx->num_cus : 256, MODE, M, Nout, K), MODE, A, W, 0, M, Nout, K, ep, true);
   const Plan p = plan_rows(ctx, MODE, M, Nout, K, ep.part ? ep.part_floats : 0);
   for (int i = 0; i < p.n; ++i) {
     const int cus = ctx ? ctx->num_cus : 256;
@@ -843,20 +845,24 @@ int gemm_bf16_tile_cols(const nova_ctx* ctx, int M, int Nout, int K) {
   }
 }
 
+bool gemm_takes_norm(const nova_ctx* ctx, int mode, int M, int Nout, int K) {
+  return !forced_tile(ctx) && gemm_norm_plan(ctx ? ctx->num_cus : 256, mode, M, Nout, K).rg > 0;
+}
+
 hipError_t launch_gemm_bf16(const nova_ctx* ctx, hipStream_t st, int mode, const void* A, const void* W, int M,
-                            int Nout, int K, const EpiParams<bf16_t>& params) {
+                            int Nout, int K, const EpiParams<bf16_t>& params, bool norm) {
   EpiParams<bf16_t> ep = params;
   ep.k_inv = ep.k > 0 ? div_inv(ep.k) : 0;
   ep.dh_log2 = ep.dh == 128 ? 7 : 6;
   const bf16_t* a = static_cast<const bf16_t*>(A);
   const bf16_t* w = static_cast<const bf16_t*>(W);
   switch (mode) {
-    case EPI_QKV: return launch_mode<EPI_QKV>(ctx, st, a, w, M, Nout, K, ep);
-    case EPI_ATTN_OUT: return launch_mode<EPI_ATTN_OUT>(ctx, st, a, w, M, Nout, K, ep);
-    case EPI_GELU: return launch_mode<EPI_GELU>(ctx, st, a, w, M, Nout, K, ep);
-    case EPI_GELU_TANH: return launch_mode<EPI_GELU_TANH>(ctx, st, a, w, M, Nout, K, ep);
-    case EPI_PLAIN: return launch_mode<EPI_PLAIN>(ctx, st, a, w, M, Nout, K, ep);
-    case EPI_ENTROPY: return launch_mode<EPI_ENTROPY>(ctx, st, a, w, M, Nout, K, ep);
-    default: return launch_mode<EPI_RESIDUAL>(ctx, st, a, w, M, Nout, K, ep);
+    case EPI_QKV: return launch_mode<EPI_QKV>(ctx, st, a, w, M, Nout, K, ep, norm);
+    case EPI_ATTN_OUT: return launch_mode<EPI_ATTN_OUT>(ctx, st, a, w, M, Nout, K, ep, norm);
+    case EPI_GELU: return launch_mode<EPI_GELU>(ctx, st, a, w, M, Nout, K, ep, norm);
+    case EPI_GELU_TANH: return launch_mode<EPI_GELU_TANH>(ctx, st, a, w, M, Nout, K, ep, norm);
+    case EPI_PLAIN: return launch_mode<EPI_PLAIN>(ctx, st, a, w, M, Nout, K, ep, norm);
+    case EPI_ENTROPY: return launch_mode<EPI_ENTROPY>(ctx, st, a, w, M, Nout, K, ep, norm);
+    default: return launch_mode<EPI_RESIDUAL>(ctx, st, a, w, M, Nout, K, ep, norm);
   }
 }

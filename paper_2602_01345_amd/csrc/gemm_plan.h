@@ -6,7 +6,8 @@
 #include "epilogue.h"
 #include "nova_internal.h"
 
-// Tile of the few-rows kernels for `rows` rows, or rg = 0 where the shared-ring kernels are faster.
+// Tile of the few-rows kernels for `rows` rows, or rg = 0 where the shared-ring kernels are faster.  norm: for a projection
+// that normalises its rows itself (gemm_norm_plan).
 //  * A tile of rg groups of eight rows and ng groups of eight features loads (rg + ng) groups and computes rg ng, so of
 //    the tiles that give every CU one workgroup the one nearest to a square loads least: the rule is the fewest groups
 //    on the busiest CU.  Against the narrowest tile over all rows at once (us, weights from HBM): 64 rows, Nout = 1024,
@@ -35,16 +36,16 @@
   T(1, 1, 4, 4, 2) T(1, 1, 8, 4, 2) T(1, 2, 4, 4, 2) T(1, 4, 4, 4, 2) T(2, 1, 4, 4, 2) \
   T(2, 2, 4, 4, 2) T(2, 4, 4, 3, 2) T(4, 2, 4, 3, 2) T(4, 4, 4, 2, 2) T(4, 8, 4, 2, 1) \
   T(8, 4, 4, 2, 1) T(8, 8, 4, 2, 1) T(8, 8, 4, 1, 2)
-inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K) {
+inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K, bool norm = false) {
   RowsPlan best = {};
   if (mode == EPI_ENTROPY || Nout % 64 != 0) return best;
-  const bool weights_only = rows <= 8 && (Nout <= 8 * num_cus || (K > 1536 && Nout % (8 * num_cus) == 0 && Nout <= 32 * num_cus));
+  const bool weights_only = !norm && rows <= 8 && (Nout <= 8 * num_cus || (K > 1536 && Nout % (8 * num_cus) == 0 && Nout <= 32 * num_cus));
   const bool tall = K >= 4096 || (K >= 1536 && Nout >= 1536);
   const int max_per_cu = mode == EPI_RESIDUAL || rows > 512 ? 1 : 2;
   int64_t least = INT64_MAX;
   auto consider = [&](const RowsPlan& t, int fit) {
     if ((int64_t)std::max(t.rg, t.ng) * 16 * K > 1 << 30) return;                    // see the last rule above
-    if (t.rg * t.ng == 1 ? t.kw != (K > 2048 ? 8 : 4) : weights_only) return;       // a long K over twice the waves
+    if (t.rg * t.ng == 1 ? norm || t.kw != (K > 2048 ? 8 : 4) : weights_only) return;       // a long K over twice the waves
     const int64_t wgs = (int64_t)((rows + 8 * t.rg - 1) / (8 * t.rg)) * (Nout / (8 * t.ng));
     const int64_t per_cu = (wgs + num_cus - 1) / num_cus;
     if (rows > 64 && per_cu > std::min(fit, max_per_cu)) return;                     // up to 64 rows: in turns
@@ -58,6 +59,26 @@ inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K)
   NOVA_ROWS_TILES(CONSIDER)
 #undef CONSIDER
   return best;
+}
+
+// Few rows that the projection normalises itself (rg = 0: a launch of its own does it).
+//  * Every workgroup normalises its tile's rows again, on one wave per SIMD: some 0.6 us of vector work with 8 rows of 1024, 1.4
+//    with 16, against 2.8 us of a launch.  Two norms, us per block in a graph, B images (separate / in the projection): C = 1024
+//    1 row 22.5 / 19.6, 8 rows 23.4 / 19.8, 16 rows 26.6 / 25.3, 32 rows 27.7 / 26.8, 48 rows 29.0 / 29.1; C = 512 1 ... 16 rows
+//    -1.8 ... -2.6, 48 rows 23.8 / 22.2; C = 1536 8 rows 32.6 / 28.7, 32 rows 42.3 / 42.4; C = 2304 8 rows 46.5 / 43.7, 16 rows
+//    54.4 / 54.3; tiles of 32 rows normalise for 2.5 ... 3.5 us and gain nothing (C = 1024, 36 ... 100 rows: 0 ... +2 us).
+//  * Up to eight rows no more workgroups than CUs: three or four small ones per CU would each normalise (C = 2048, 1 / 8 rows
+//    37.0 / 39.7 with separate norms, 36.6 / 38.7 with the norm in 768 and 1024 small workgroups, 34.6 / 36.2 in wider tiles).
+//  * A wave holds its rows in registers, 512 elements at a time up to kNormMaxK; a K of 64 per wave at least.
+constexpr int kNormMaxGroups = 2, kNormMaxRows = 32, kNormMaxK = 2560;
+inline size_t gemm_norm_lds(const RowsPlan& p, int K) { return (size_t)p.rg * 16 * K + (size_t)p.kw * p.s * p.ng * 1024 + 1024; }
+inline RowsPlan gemm_norm_plan(int num_cus, int mode, int rows, int Nout, int K) {
+  RowsPlan p = {};
+  if (rows > kNormMaxRows || K > kNormMaxK) return p;
+  if (mode != EPI_QKV && mode != EPI_GELU && mode != EPI_GELU_TANH && mode != EPI_PLAIN) return p;
+  p = gemm_rows_plan(num_cus, mode, rows, Nout, K, true);
+  if (p.rg > kNormMaxGroups || K < 64 * p.kw) p.rg = 0;
+  return p;
 }
 
 // Tile configurations (NOVA_GEMM_CFG forces one, for tuning; numbers without a kernel mean 2):

@@ -17,9 +17,14 @@
 //    lane offset and a scalar, no accumulation registers to move out of.
 //  * The epilogue works on eight consecutive features of one row per thread, rows fastest, so that value-cache
 //    columns (key index minor) are written in runs of rows; its bias and residual are requested before the K walk.
+//  * Up to 32 rows a projection that starts from a LayerNorm takes it along (NORM): the norm's own launch is 2.8 us of which
+//    half is starting and ending, and its rows are a latency that the weights' covers (a block of one / eight rows of 1024 in
+//    a graph 22.6 / 23.5 -> 19.4 / 20.1 us).
 // Measured in a graph, weights from HBM (us; with the divisions and 64-row tiles whatever the width / now / a stream of the
 // same bytes): K = 1024, Nout = 1024 / 3072 / 4096, one row 3.1 / 4.2 / 4.5 -> 2.7 / 3.6 / 3.9 (- / 2.9 / 3.3), 64 rows
 // 4.3 / 5.9 / 6.1 -> 3.0 / 4.9 / 5.1; K = 4096, Nout = 1024, one row 4.8 -> 4.4, 64 rows 9.3 -> 6.7.
+#include <type_traits>
+
 #include "common.h"
 #include "epilogue.h"
 #include "gemm_plan.h"
@@ -45,19 +50,35 @@ __device__ __forceinline__ f32x4v mfma16(bf16x8 a, bf16x8 b, f32x4v c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
+// LDS of a kernel: of a fixed size, or with the rows of A in front, as long as K has it
+template <bool DYNAMIC, int BYTES>
+__device__ __forceinline__ char* rows_lds() {
+  if constexpr (DYNAMIC) {
+    extern __shared__ __attribute__((aligned(1024))) char dyn[];
+    return dyn;
+  } else {
+    __shared__ __attribute__((aligned(1024))) char fixed[BYTES];
+    return fixed;
+  }
+}
+
 // RG, NG: groups of eight rows / features of a tile (an MFMA tile is 16 x 16: with an odd count its other half is
-// whatever lies in LDS behind and is never used); KW: waves; S: units in flight per wave
-template <int RG, int NG, int KW, int S, int MODE>
-__global__ __launch_bounds__(KW* 64) __attribute__((amdgpu_waves_per_eu(KW * S * (NG + RG) <= 79 ? 2 : 1))) void gemm_rows_kernel(
+// whatever lies in LDS behind and is never used); KW: waves; S: units in flight per wave.
+// NORM: A's rows are gathered and normalised here (see normalise), then lie in LDS whole, and the waves' rings hold
+// weights only.
+template <int RG, int NG, int KW, int S, int MODE, bool NORM>
+__global__ __launch_bounds__(KW* 64) __attribute__((amdgpu_waves_per_eu(!NORM && KW * S * (NG + RG) <= 79 ? 2 : 1))) void gemm_rows_kernel(
     const bf16_t* __restrict__ A, const bf16_t* __restrict__ W, int M, int Nout, int K, int m_base, EpiParams<bf16_t> ep) {
   constexpr int MT = (RG + 1) / 2, NF = (NG + 1) / 2;
   constexpr int ROWS = MT * 16, LROWS = RG * 8, COLS = NG * 8, NT = KW * 64;
   constexpr int COL8 = COLS / 8;                         // eight-feature groups per row: one thread each in the epilogue
-  constexpr int LPU = NG + RG;                       // 1 KB load instructions per unit
-  constexpr int SLOT = (NG + RG) * 1024;                 // rows 8 .. 15 of an odd group count are whatever follows: never used
+  constexpr int LPU = NORM ? NG : NG + RG;               // 1 KB load instructions per unit
+  constexpr int SLOT = LPU * 1024;                       // rows 8 .. 15 of an odd group count are whatever follows: never used
   constexpr int NO = (ROWS * COL8 + NT - 1) / NT;        // of which a thread takes this many
   static_assert(S * LPU < 64, "vmcnt is a 6-bit counter");
-  __shared__ __attribute__((aligned(1024))) char lds[KW * S * SLOT + 1024];
+  static_assert(S * SLOT >= ROWS * NF * 16 * 4, "a wave's partial sums take the place of its ring");
+  char* const a_lds = rows_lds<NORM, KW * S * SLOT + 1024>();
+  char* const lds = a_lds + (NORM ? RG * 16 * K : 0);
 
   // all arguments in one round trip, not one per branch below that needs some
   asm volatile("" ::"s"(A), "s"(W), "s"(M), "s"(Nout), "s"(K), "s"(m_base), "s"(ep.bias), "s"(ep.out),
@@ -65,13 +86,22 @@ __global__ __launch_bounds__(KW* 64) __attribute__((amdgpu_waves_per_eu(KW * S *
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n0 = blockIdx.x * COLS, m0 = m_base + blockIdx.y * LROWS;
+  auto advance_kv = [&]() {
+    // per-image cache lengths after this block: prior rows + kept rows (the up-projection: everything that reads the old
+    // lengths has run, so the output may be the input array)
+    if (!NORM || !ep.kv_next || blockIdx.x != 0 || blockIdx.y != 0) return;
+    for (int b = tid; b * ep.k < M; b += NT) ep.kv_next[b] = image_prior(ep.kv_rows, b, ep.P) + image_count(ep.k_rows, b, ep.k);
+  };
   if (ep.k_rows) {
     // per-image keep counts: a tile without a live row has nothing to compute (the whole workgroup leaves together)
     const int m_hi = min(m0 + LROWS, M);
     bool live = false;
     for (int b = ep.image(m0); b * ep.k < m_hi; ++b)
       live = live || max(m0 - b * ep.k, 0) < image_count(ep.k_rows, b, ep.k);
-    if (!live) return;
+    if (!live) {
+      advance_kv();
+      return;
+    }
   }
 
   // ---- fills: instruction j of a unit drops 8 rows x 128 bytes into LDS; slot p of row r holds chunk p ^ ((r >> 1) & 7)
@@ -89,14 +119,100 @@ __global__ __launch_bounds__(KW* 64) __attribute__((amdgpu_waves_per_eu(KW * S *
     oa[j] = (uint32_t)min(r, M - 1 - m0) * (uint32_t)(2 * K) + ((lp ^ ((r >> 1) & 7)) << 4);
   }
   char* mine_lds = lds + wave * (S * SLOT);
-  auto issue = [&](int i) {
-    char* d = mine_lds + (i % S) * SLOT;
+  auto issue_at = [&](int slot, int i) {
+    char* d = mine_lds + slot * SLOT;
     const uint32_t k0 = (uint32_t)(wave + i * KW) * 128;
 #pragma unroll
     for (int j = 0; j < NG; ++j) fill_lds(Wb, d + j * 1024, ow[j & 1], k0 + (uint32_t)(j * 16 * K));
+    if constexpr (!NORM) {
 #pragma unroll
-    for (int j = 0; j < RG; ++j) fill_lds(Ab, d + (NG + j) * 1024, oa[j], k0);
+      for (int j = 0; j < RG; ++j) fill_lds(Ab, d + (NG + j) * 1024, oa[j], k0);
+    }
   };
+  // ---- NORM: wave w takes rows w, w + KW, ... of the tile, a row per wave as in norm.hip and with its sums in the same
+  // order, so that the bits are those of its output.  The rows are requested in front of the weights, whose latency then
+  // covers the sums.  NU: 512 elements a time per row, the last ones perhaps fewer.
+  auto normalise = [&](auto nu_tag) {
+    constexpr int NU = decltype(nu_tag)::value, NR = LROWS / KW;
+    constexpr bool GATHER = MODE == EPI_QKV;
+    const bool last = ((NU - 1) * 64 + lane) * 8 < K;    // whether this lane has elements in the last vector of a row
+    int m[NR], image[NR], slot[NR], token[NR], count[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      m[i] = min(m0 + wave + i * KW, M - 1);             // rows past the last one: the last one, never stored
+      image[i] = ep.image(m[i], slot[i]);
+      count[i] = ep.k;
+    }
+    if (ep.k_rows) {
+#pragma unroll
+      for (int i = 0; i < NR; ++i) count[i] = image_count(ep.k_rows, image[i], ep.k);
+    }
+    if constexpr (GATHER) {
+#pragma unroll
+      for (int i = 0; i < NR; ++i) token[i] = ep.idx[m[i]];
+    }
+    bf16x8 x[NR][NU];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const int64_t row = GATHER ? (int64_t)image[i] * ep.Ntok + min(max(token[i], 0), ep.Ntok - 1) : m[i];
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+        x[i][u] = *reinterpret_cast<const bf16x8*>(A + row * K + (u + 1 < NU || last ? u * 64 + lane : lane) * 8);
+    }
+    // the weights behind the rows, gathered ones too (in front of them: 0.6 us slower), and without branches, so that the
+    // wait for the rows is not one for everything: with few units the last one comes twice
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < S; ++i) issue_at(i, min(i, n_units - 1));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    float mean[NR], rstd[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      float sum = 0.f;
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sum += u + 1 < NU || last ? (float)x[i][u][e] : 0.f;
+      mean[i] = wave_sum(sum) / (float)K;
+    }
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      float sq = 0.f;
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          const float d = u + 1 < NU || last ? (float)x[i][u][e] - mean[i] : 0.f;
+          sq = fmaf(d, d, sq);
+        }
+      rstd[i] = 1.0f / sqrtf(wave_sum(sq) / (float)K + kNormEps);
+    }
+#pragma unroll
+    for (int i = 0; i < NR; ++i) {
+      const int r = wave + i * KW;
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const int c = u * 64 + lane;                     // chunk of eight elements: unit c / 8, slot as the fills have it
+        bf16x8 o;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = (bf16_t)(((float)x[i][u][e] - mean[i]) * rstd[i]);
+        if (slot[i] >= count[i]) {                       // a slot past its image's keep count: zeros
+#pragma unroll
+          for (int e = 0; e < 8; ++e) o[e] = (bf16_t)0.f;
+        }
+        if (u + 1 < NU || last)
+          *reinterpret_cast<bf16x8*>(a_lds + (c >> 3) * (RG * 1024) + r * 128 + (((c & 7) ^ ((r >> 1) & 7)) << 4)) = o;
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(0xC07F);                  // lgkmcnt(0), and a bare barrier: the weights stay in flight
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  static_assert(!NORM || LROWS % KW == 0, "rows split over the waves");
+  auto issue = [&](int i) { issue_at(i % S, i); };
   // This thread's outputs: row m0 + o % ROWS, features n0 + 8 (o / ROWS) .. for o = tid, tid + NT, ...  Their bias,
   // residual and gate are requested behind the first units; only the gathered residual's index, which its address
   // waits for, goes ahead of them.  (vmcnt counts in order: the waits below are then for a few loads more than needed.)
@@ -112,7 +228,17 @@ __global__ __launch_bounds__(KW* 64) __attribute__((amdgpu_waves_per_eu(KW * S *
   asm volatile("" ::: "memory");
 #pragma unroll
   for (int i = 0; i < S; ++i)
-    if (i < n_units) issue(i);
+    if (!NORM && i < n_units) issue(i);
+  if constexpr (NORM) {
+    switch ((K + 511) / 512) {
+      case 1: normalise(std::integral_constant<int, 1>{}); break;
+      case 2: normalise(std::integral_constant<int, 2>{}); break;
+      case 3: normalise(std::integral_constant<int, 3>{}); break;
+      case 4: normalise(std::integral_constant<int, 4>{}); break;
+      default: normalise(std::integral_constant<int, kNormMaxK / 512>{}); break;
+    }
+    advance_kv();
+  }
   asm volatile("" ::: "memory");
 #pragma unroll
   for (int q = 0; q < NO; ++q) {
@@ -155,7 +281,8 @@ __global__ __launch_bounds__(KW* 64) __attribute__((amdgpu_waves_per_eu(KW * S *
 #pragma unroll
       for (int f = 0; f < NF; ++f) wf[s][f] = *reinterpret_cast<const bf16x8*>(d + f * 2048 + off[s]);
 #pragma unroll
-      for (int t = 0; t < MT; ++t) af[s][t] = *reinterpret_cast<const bf16x8*>(d + NG * 1024 + t * 2048 + off[s]);
+      for (int t = 0; t < MT; ++t)
+        af[s][t] = *reinterpret_cast<const bf16x8*>((NORM ? a_lds + (wave + i * KW) * (RG * 1024) : d + NG * 1024) + t * 2048 + off[s]);
     }
     if (i + S < n_units) {
       __builtin_amdgcn_s_waitcnt(0xC07F);                // lgkmcnt(0): the slot has been read
@@ -235,19 +362,25 @@ __global__ __launch_bounds__(KW* 64) __attribute__((amdgpu_waves_per_eu(KW * S *
   }
 }
 
-template <int RG, int NG, int KW, int S, int MODE>
+template <int RG, int NG, int KW, int S, int MODE, bool NORM>
 hipError_t go(hipStream_t st, const bf16_t* A, const bf16_t* W, int m_base, int M, int Nout, int K,
               const EpiParams<bf16_t>& ep) {
   const dim3 grid(Nout / (NG * 8), (M - m_base + RG * 8 - 1) / (RG * 8));
-  gemm_rows_kernel<RG, NG, KW, S, MODE><<<grid, KW * 64, 0, st>>>(A, W, M, Nout, K, m_base, ep);
+  const size_t lds = NORM ? gemm_norm_lds({RG, NG, KW, S}, K) : 0;
+  gemm_rows_kernel<RG, NG, KW, S, MODE, NORM><<<grid, KW * 64, lds, st>>>(A, W, M, Nout, K, m_base, ep);
   return hipGetLastError();
 }
 
 template <int MODE>
 hipError_t by_plan(hipStream_t st, const RowsPlan& p, const bf16_t* A, const bf16_t* W, int m_base, int M, int Nout, int K,
-                   const EpiParams<bf16_t>& ep) {
-#define GO(RG, NG, KW, S, FIT) \
-  if (p.rg == RG && p.ng == NG && p.kw == KW && p.s == S) return go<RG, NG, KW, S, MODE>(st, A, W, m_base, M, Nout, K, ep);
+                   const EpiParams<bf16_t>& ep, bool norm) {
+  constexpr bool TAKES_NORM = MODE == EPI_QKV || MODE == EPI_GELU || MODE == EPI_GELU_TANH || MODE == EPI_PLAIN;
+#define GO(RG, NG, KW, S, FIT)                                                                                       \
+  if (p.rg == RG && p.ng == NG && p.kw == KW && p.s == S) {                                                          \
+    if constexpr (TAKES_NORM && RG <= kNormMaxGroups)                                                                \
+      if (norm) return go<RG, NG, KW, S, MODE, true>(st, A, W, m_base, M, Nout, K, ep);                              \
+    return norm ? hipErrorInvalidValue : go<RG, NG, KW, S, MODE, false>(st, A, W, m_base, M, Nout, K, ep);           \
+  }
   NOVA_ROWS_TILES(GO)
 #undef GO
   return hipErrorInvalidValue;
@@ -256,14 +389,14 @@ hipError_t by_plan(hipStream_t st, const RowsPlan& p, const bf16_t* A, const bf1
 }  // namespace
 
 hipError_t launch_gemm_rows_bf16(hipStream_t st, const RowsPlan& p, int mode, const bf16_t* A, const bf16_t* W, int m_base,
-                                 int M, int Nout, int K, const EpiParams<bf16_t>& ep) {
+                                 int M, int Nout, int K, const EpiParams<bf16_t>& ep, bool norm) {
   switch (mode) {
-    case EPI_QKV: return by_plan<EPI_QKV>(st, p, A, W, m_base, M, Nout, K, ep);
-    case EPI_ATTN_OUT: return by_plan<EPI_ATTN_OUT>(st, p, A, W, m_base, M, Nout, K, ep);
-    case EPI_GELU: return by_plan<EPI_GELU>(st, p, A, W, m_base, M, Nout, K, ep);
-    case EPI_GELU_TANH: return by_plan<EPI_GELU_TANH>(st, p, A, W, m_base, M, Nout, K, ep);
-    case EPI_PLAIN: return by_plan<EPI_PLAIN>(st, p, A, W, m_base, M, Nout, K, ep);
-    case EPI_RESIDUAL: return by_plan<EPI_RESIDUAL>(st, p, A, W, m_base, M, Nout, K, ep);
+    case EPI_QKV: return by_plan<EPI_QKV>(st, p, A, W, m_base, M, Nout, K, ep, norm);
+    case EPI_ATTN_OUT: return by_plan<EPI_ATTN_OUT>(st, p, A, W, m_base, M, Nout, K, ep, norm);
+    case EPI_GELU: return by_plan<EPI_GELU>(st, p, A, W, m_base, M, Nout, K, ep, norm);
+    case EPI_GELU_TANH: return by_plan<EPI_GELU_TANH>(st, p, A, W, m_base, M, Nout, K, ep, norm);
+    case EPI_PLAIN: return by_plan<EPI_PLAIN>(st, p, A, W, m_base, M, Nout, K, ep, norm);
+    case EPI_RESIDUAL: return by_plan<EPI_RESIDUAL>(st, p, A, W, m_base, M, Nout, K, ep, norm);
     default: return hipErrorInvalidValue;
   }
 }

@@ -10,7 +10,6 @@
 namespace {
 
 constexpr int kWavesPerBlock = 4;
-constexpr float kEps = 1e-6f;
 
 // U: vectors per lane, a row of at most U * 64 vectors is kept in registers (every count up to eight has its kernel: with
 // modulation eight vectors are 96 registers); 0: any row, three passes
@@ -85,7 +84,7 @@ __global__ __launch_bounds__(kWavesPerBlock* NOVA_WAVE) void gather_ln_kernel(
 #pragma unroll
         for (int e = 0; e < VN; ++e) { float d = v[u].get(e) - mean; sq = fmaf(d, d, sq); }
       }
-    const float rstd = 1.0f / sqrtf(wave_sum(sq) / (float)C + kEps);
+    const float rstd = 1.0f / sqrtf(wave_sum(sq) / (float)C + kNormEps);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int vi = u * NOVA_WAVE + lane;
@@ -117,7 +116,7 @@ __global__ __launch_bounds__(kWavesPerBlock* NOVA_WAVE) void gather_ln_kernel(
 #pragma unroll
     for (int e = 0; e < VN; ++e) { float d = v.get(e) - mean; sq = fmaf(d, d, sq); }
   }
-  const float rstd = 1.0f / sqrtf(wave_sum(sq) / (float)C + kEps);
+  const float rstd = 1.0f / sqrtf(wave_sum(sq) / (float)C + kNormEps);
   if (shift) {          // modulation vectors of image m / k (both given or neither)
     const T* sh = shift + (int64_t)image * mod_pitch;
     const T* sc = scale + (int64_t)image * mod_pitch;

@@ -117,15 +117,17 @@ hipError_t launch_block_f32(nova_ctx* ctx, hipStream_t st, const nova_block_shap
                             float* kc, float* vc, float* y, const BlockWorkspace& ws);
 // gemm_bf16.hip: out = epilogue(A W^T) on the matrix cores; mode is an EpiMode
 template <typename T> struct EpiParams;
+// norm: A's rows are normalised on the way (only where gemm_takes_norm), in mode EPI_QKV gathered through ep.idx as well
+bool gemm_takes_norm(const nova_ctx* ctx, int mode, int M, int Nout, int K);
 hipError_t launch_gemm_bf16(const nova_ctx* ctx, hipStream_t st, int mode, const void* A, const void* W, int M,
-                            int Nout, int K, const EpiParams<__bf16>& ep);
+                            int Nout, int K, const EpiParams<__bf16>& ep, bool norm = false);
 // gemm_rows_bf16.hip: the same for few rows [m_base, M), by a plan of gemm_plan.h.  The plan's rg is 0 where the shape is
 // better served by gemm_bf16.hip
 struct RowsPlan {
   int rg, ng, kw, s;       // groups of 8 rows / 8 features per tile, waves, units in flight per wave
 };
 hipError_t launch_gemm_rows_bf16(hipStream_t st, const RowsPlan& plan, int mode, const __bf16* A, const __bf16* W, int m_base,
-                                 int M, int Nout, int K, const EpiParams<__bf16>& ep);
+                                 int M, int Nout, int K, const EpiParams<__bf16>& ep, bool norm = false);
 int gemm_bf16_tile_cols(const nova_ctx* ctx, int M, int Nout, int K);
 size_t head_entropy_workspace_bytes(int M, int V);
 hipError_t launch_head_entropy(const nova_ctx* ctx, hipStream_t st, const void* hidden, const void* w_head,

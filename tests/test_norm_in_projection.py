@@ -1,0 +1,47 @@
+"""GPU parity of the few-rows projections that normalise their rows themselves (csrc/gemm_rows_bf16.hip) against the oracle:
+row counts around their tiles and around the last count they take, widths at the ends of the range and with a last vector
+that only some lanes hold, per-image keep counts (dead slots, an image without rows, cache lengths written by the launch),
+the unmodulated variants.  Tolerance: bf16 tensors max|d| / max|ref| <= 2e-2, as everywhere: the norm is the separate
+kernel's, bit for bit."""
+import pytest
+import torch
+
+import workloads as WL
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hx():
+    import harness
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU and the built libnova.so (no fallback)")
+    return harness
+
+
+def _block(B, grid, P, C, heads):
+    return WL.Workload("norm", "bf16", B=B, C=C, heads=heads, L=1, V=64, keep_hi=.5, keep_lo=.5,
+                       scales=(WL.Scale(grid=grid, prev_grid=max(grid - 2, 1), kv_len=P),), seed=29)
+
+
+# below, at and inside the range of K (256 ... 2560), 512-element vectors whole and in part
+@pytest.mark.parametrize("C,heads", [(192, 3), (256, 4), (576, 9), (1024, 8), (1600, 25), (2496, 39), (2560, 20), (2624, 41)])
+@pytest.mark.parametrize("M", [1, 9, 32, 33])
+def test_widths_and_row_counts(hx, C, heads, M):
+    print(f"norm in projection C={C} M={M}", flush=True)
+    hx.check_block(hx.make_host_block(_block(1, 6, 20, C, heads), 0, k=M), hx.BF16_TOL)
+
+
+@pytest.mark.parametrize("k_rows,kv_rows", [([5, 0, 1, 7], [20, 3, 0, 11]), ([0, 0, 8, 0], [0, 20, 1, 2]), ([0, 0, 0, 1], [4, 4, 4, 4])])
+@pytest.mark.parametrize("C,heads", [(320, 5), (1024, 8)])
+def test_per_image_counts(hx, C, heads, k_rows, kv_rows):
+    print(f"norm in projection, counts {k_rows} C={C}", flush=True)
+    hx.check_block_rows(hx.make_host_block(_block(4, 6, 20, C, heads), 0), k_rows, kv_rows, hx.BF16_TOL, kpitch=8)
+
+
+@pytest.mark.parametrize("variant", [{"gelu_tanh", "cross", "qk_norm"}, {"ada", "cross"}], ids=lambda v: "+".join(sorted(v)))
+@pytest.mark.parametrize("M", [3, 16])
+def test_variants(hx, variant, M):
+    """Modulated norms keep their own launch, the one in front of the cross-attention has no modulation."""
+    print(f"norm in projection {sorted(variant)} M={M}", flush=True)
+    hx.check_block(hx.make_host_block(_block(1, 6, 20, 512, 8), 0, k=M, variant=variant), hx.BF16_TOL)
