@@ -12,22 +12,30 @@ namespace {
 constexpr int kTile = 16;
 constexpr int kStepK = 64;                 // elements of K per step
 constexpr int kPitch = kStepK + 4;         // 16-byte reads of sixteen rows hit all banks once
+constexpr int kNormMaxK = 256;             // NORM: a thread holds a sixteenth of a row
 
 // out[m][n] = sum_k A[m][k] * W[n][k]  (+ epilogue); A [M, K] row-major, W [Nout, K] row-major.
 // One thread per output element, K in ascending order.  These launches are a few workgroups that wait for memory: the
 // next 64 elements of K are requested before the current ones are used, so K = 256 costs one exposed latency and four
 // pairs of barriers where steps of 16 cost sixteen of each (128 x 64, K = 256: 9.9 -> 5.4 us).
-template <int MODE>
+// NORM: the rows of A are normalised here (in mode EPI_QKV gathered through ep.idx as well), the sixteen threads of a row
+// holding it, and lie in LDS whole.  Every workgroup of a row tile does it again, while its weights are on the way, which
+// never cost as much as the norm's own launch: block and merge in a graph, us, C = 64, 128 / 512 rows 31.7 / 37.9 -> 27.3 /
+// 32.2, C = 192, 128 / 1024 rows 43.7 / 101.7 -> 38.4 / 97.0, C = 256, 85 / 3900 / 15600 rows 47.6 / 468 / 1830 -> 42.8 / 464
+// / 1787.
+template <int MODE, bool NORM>
 __global__ __launch_bounds__(kTile* kTile) void gemm_f32_kernel(const float* __restrict__ A,
                                                                 const float* __restrict__ W, int M, int Nout,
                                                                 int K, EpiParams<float> ep) {
-  __shared__ __attribute__((aligned(16))) float As[kTile][kPitch];
+  constexpr int PitchA = NORM ? kNormMaxK + 4 : kPitch;
+  __shared__ __attribute__((aligned(16))) float As[kTile][PitchA];
   __shared__ __attribute__((aligned(16))) float Ws[kTile][kPitch];
   const int tx = threadIdx.x % kTile, ty = threadIdx.x / kTile;
   const int row = blockIdx.y * kTile + ty;
   const int col = blockIdx.x * kTile + tx;
   const int wr = blockIdx.x * kTile + ty;            // the weight row this thread loads for the tile
-  const float* ap = A + (int64_t)min(row, M - 1) * K;
+  const int m = min(row, M - 1), image = NORM ? m / ep.k : 0;
+  const float* ap = A + (NORM && MODE == EPI_QKV ? (int64_t)image * ep.Ntok + min(max(ep.idx[m], 0), ep.Ntok - 1) : m) * (int64_t)K;
   const float* wp = W + (int64_t)min(wr, Nout - 1) * K;
   constexpr int NL = kStepK / kTile;
   float a[NL], w[NL];
@@ -35,23 +43,50 @@ __global__ __launch_bounds__(kTile* kTile) void gemm_f32_kernel(const float* __r
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
       const int kk = k0 + tx + i * kTile;
-      a[i] = kk < K ? ap[kk] : 0.f;
+      if (!NORM) a[i] = kk < K ? ap[kk] : 0.f;
       w[i] = kk < K ? wp[kk] : 0.f;
     }
   };
-  request(0);
+  if constexpr (NORM) {
+    constexpr int NE = kNormMaxK / kTile;
+    float x[NE];
+#pragma unroll
+    for (int i = 0; i < NE; ++i) x[i] = tx + i * kTile < K ? ap[tx + i * kTile] : 0.f;
+    request(0);
+    float sum = 0.f, sq = 0.f;
+#pragma unroll
+    for (int i = 0; i < NE; ++i) sum += x[i];
+    const float mean = row16_sum(sum) / (float)K;
+#pragma unroll
+    for (int i = 0; i < NE; ++i) {
+      const float d = tx + i * kTile < K ? x[i] - mean : 0.f;
+      sq = fmaf(d, d, sq);
+    }
+    const float rstd = 1.0f / sqrtf(row16_sum(sq) / (float)K + kNormEps);
+    // zeros behind the row's end and in a slot past its image's keep count
+    const bool live = m - image * ep.k < image_count(ep.k_rows, image, ep.k);
+#pragma unroll
+    for (int i = 0; i < NE; ++i)
+      As[ty][tx + i * kTile] = live && tx + i * kTile < K ? (x[i] - mean) * rstd : 0.f;
+    // per-image cache lengths after this block (the up-projection: everything that reads the old ones has run)
+    if (ep.kv_next && blockIdx.x == 0 && blockIdx.y == 0)
+      for (int b = threadIdx.x; b * ep.k < M; b += kTile * kTile)
+        ep.kv_next[b] = image_prior(ep.kv_rows, b, ep.P) + image_count(ep.k_rows, b, ep.k);
+  } else {
+    request(0);
+  }
   float acc = 0.f;
   for (int k0 = 0; k0 < K; k0 += kStepK) {
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-      As[ty][tx + i * kTile] = a[i];
+      if (!NORM) As[ty][tx + i * kTile] = a[i];
       Ws[ty][tx + i * kTile] = w[i];
     }
     __syncthreads();
     if (k0 + kStepK < K) request(k0 + kStepK);
 #pragma unroll
     for (int i = 0; i < kStepK; i += 4) {
-      const f32x4 av = *reinterpret_cast<const f32x4*>(&As[ty][i]), wv = *reinterpret_cast<const f32x4*>(&Ws[tx][i]);
+      const f32x4 av = *reinterpret_cast<const f32x4*>(&As[ty][NORM ? k0 + i : i]), wv = *reinterpret_cast<const f32x4*>(&Ws[tx][i]);
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc = fmaf(av[e], wv[e], acc);
     }
@@ -149,10 +184,10 @@ __global__ __launch_bounds__(kAttnWaves* NOVA_WAVE) void attention_f32_kernel(co
 // LDS of attention_f32_kernel: the scores, and dh floats or what the waves exchange
 size_t attention_f32_lds(int kv_total, int dh) { return (size_t)(kv_total + std::max(dh, 2 * kAttnWaves)) * sizeof(float); }
 
-template <int MODE>
+template <int MODE, bool NORM = false>
 void gemm(hipStream_t st, const float* A, const float* W, int M, int Nout, int K, const EpiParams<float>& ep) {
   dim3 grid((Nout + kTile - 1) / kTile, (M + kTile - 1) / kTile);
-  gemm_f32_kernel<MODE><<<grid, kTile * kTile, 0, st>>>(A, W, M, Nout, K, ep);
+  gemm_f32_kernel<MODE, NORM><<<grid, kTile * kTile, 0, st>>>(A, W, M, Nout, K, ep);
 }
 
 }  // namespace
@@ -172,23 +207,34 @@ hipError_t launch_block_f32(nova_ctx* ctx, hipStream_t st, const nova_block_shap
   const int ada_pitch = 6 * C;
   auto ada_row = [&](int j) { return ada ? ada + (int64_t)j * C : nullptr; };
 
-  hipError_t e;
-  {
-    StageTimer t(ctx, st, NOVA_STAGE_GATHER_LN);
-    e = launch_gather_ln(st, NOVA_F32, x, idx, M, s.k, s.N, C, ada_row(0), ada_row(1), ada_pitch, u, rc.k_rows);
-  }
-  if (e != hipSuccess) return e;
-
   EpiParams<float> ep = {};
   ep.C = C; ep.heads = s.heads; ep.dh = dh; ep.cap = s.kv_capacity; ep.P = s.kv_len; ep.k = s.k;
   ep.k_rows = rc.k_rows; ep.kv_rows = rc.kv_rows;
   ep.idx = idx; ep.Ntok = s.N;
   ep.gate_pitch = ada_pitch;
 
+  hipError_t e = hipSuccess;
+  // LayerNorm of src in front of a projection: short rows without modulation are the projection's, others go through u
+  auto layer_norm = [&](const float* src, const int32_t* src_idx, const float* shift, const float* scale,
+                        int32_t* kv_next) -> const float* {
+    ep.kv_next = kv_next;
+    if (!shift && C <= kNormMaxK) return src;
+    e = launch_gather_ln(st, NOVA_F32, src, src_idx, M, s.k, s.N, C, shift, scale, ada_pitch, u, rc.k_rows, rc.kv_rows, kv_next,
+                         s.kv_len);
+    return u;
+  };
+  const float* in;
+  {
+    StageTimer t(ctx, st, NOVA_STAGE_GATHER_LN);
+    in = layer_norm(x, idx, ada_row(0), ada_row(1), nullptr);
+  }
+  if (e != hipSuccess) return e;
+
   ep.bias = static_cast<const float*>(w.b_qkv); ep.out = q; ep.ldo = C; ep.kc = kc; ep.vc = vc;
   {
     StageTimer t(ctx, st, NOVA_STAGE_QKV);
-    gemm<EPI_QKV>(st, u, static_cast<const float*>(w.w_qkv), M, 3 * C, C, ep);
+    if (in != u) gemm<EPI_QKV, true>(st, in, static_cast<const float*>(w.w_qkv), M, 3 * C, C, ep);
+    else gemm<EPI_QKV>(st, u, static_cast<const float*>(w.w_qkv), M, 3 * C, C, ep);
     if (var.qk_norm) {
       e = launch_qk_norm(st, NOVA_F32, q, kc, var.qk_scale, 1.0f, s.B, s.k, C, s.heads, s.kv_capacity, s.kv_len,
                          rc.k_rows, rc.kv_rows);
@@ -212,10 +258,11 @@ hipError_t launch_block_f32(nova_ctx* ctx, hipStream_t st, const nova_block_shap
   }
   if (var.w_cq) {
     // cross-attention sub-layer over the condition tokens (see block_bf16.hip)
-    e = launch_gather_ln(st, NOVA_F32, x1, nullptr, M, s.k, s.N, C, nullptr, nullptr, 0, u, rc.k_rows);
+    in = layer_norm(x1, nullptr, nullptr, nullptr, nullptr);
     if (e != hipSuccess) return e;
     ep.bias = static_cast<const float*>(var.b_cq); ep.out = q; ep.ldo = C; ep.gate = nullptr;
-    gemm<EPI_PLAIN>(st, u, static_cast<const float*>(var.w_cq), M, C, C, ep);
+    if (in != u) gemm<EPI_PLAIN, true>(st, in, static_cast<const float*>(var.w_cq), M, C, C, ep);
+    else gemm<EPI_PLAIN>(st, u, static_cast<const float*>(var.w_cq), M, C, C, ep);
     const size_t lds_t = attention_f32_lds(var.text_len, dh);
     attention_f32_kernel<<<dim3(M, s.heads), kAttnWaves * NOVA_WAVE, lds_t, st>>>(
         q, static_cast<const float*>(var.k_text), static_cast<const float*>(var.v_text), s.k, C, s.heads, dh,
@@ -225,16 +272,18 @@ hipError_t launch_block_f32(nova_ctx* ctx, hipStream_t st, const nova_block_shap
   }
   {
     StageTimer t(ctx, st, NOVA_STAGE_LN2);
-    e = launch_gather_ln(st, NOVA_F32, x1, nullptr, M, s.k, s.N, C, ada_row(3), ada_row(4), ada_pitch, u, rc.k_rows,
-                         rc.kv_rows, rc.kv_next, s.kv_len);
+    in = layer_norm(x1, nullptr, ada_row(3), ada_row(4), rc.kv_next);
   }
   if (e != hipSuccess) return e;
 
   ep.bias = static_cast<const float*>(w.b_fc1); ep.out = hid; ep.ldo = F; ep.gate = nullptr;
   {
     StageTimer t(ctx, st, NOVA_STAGE_FFN1);
-    if (var.gelu_tanh) gemm<EPI_GELU_TANH>(st, u, static_cast<const float*>(w.w_fc1), M, F, C, ep);
-    else gemm<EPI_GELU>(st, u, static_cast<const float*>(w.w_fc1), M, F, C, ep);
+    const float* w1 = static_cast<const float*>(w.w_fc1);
+    if (in != u && var.gelu_tanh) gemm<EPI_GELU_TANH, true>(st, in, w1, M, F, C, ep);
+    else if (in != u) gemm<EPI_GELU, true>(st, in, w1, M, F, C, ep);
+    else if (var.gelu_tanh) gemm<EPI_GELU_TANH>(st, u, w1, M, F, C, ep);
+    else gemm<EPI_GELU>(st, u, w1, M, F, C, ep);
   }
 
   ep.bias = static_cast<const float*>(w.b_fc2); ep.out = y; ep.ldo = C; ep.res = x1; ep.gate = ada_row(5);

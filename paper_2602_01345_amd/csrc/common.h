@@ -70,6 +70,13 @@ template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ float dpp_or(float v, float identity) {
   return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(identity), __float_as_int(v), CTRL, ROW_MASK, 0xF, false));
 }
+// (of each sixteen lanes, in all of them)
+__device__ __forceinline__ float row16_sum(float v) {
+  v += dpp_or<0xB1, 0xF>(v, 0.0f);
+  v += dpp_or<0x4E, 0xF>(v, 0.0f);
+  v += dpp_or<0x141, 0xF>(v, 0.0f);
+  return v + dpp_or<0x140, 0xF>(v, 0.0f);
+}
 __device__ __forceinline__ float wave_sum(float v) {
   v += dpp_or<0xB1, 0xF>(v, 0.0f);          // quad_perm [1,0,3,2]
   v += dpp_or<0x4E, 0xF>(v, 0.0f);          // quad_perm [2,3,0,1]

@@ -1,8 +1,8 @@
-"""GPU parity of the few-rows projections that normalise their rows themselves (csrc/gemm_rows_bf16.hip) against the oracle:
+"""GPU parity of the projections that normalise their rows themselves (csrc/gemm_rows_bf16.hip, block_f32.hip) against the oracle:
 row counts around their tiles and around the last count they take, widths at the ends of the range and with a last vector
 that only some lanes hold, per-image keep counts (dead slots, an image without rows, cache lengths written by the launch),
 the unmodulated variants.  Tolerance: bf16 tensors max|d| / max|ref| <= 2e-2, as everywhere: the norm is the separate
-kernel's, bit for bit."""
+kernel's, bit for bit.  fp32 as everywhere 2e-5: the row's sum is one over sixteen lanes instead of 64."""
 import pytest
 import torch
 
@@ -45,3 +45,21 @@ def test_variants(hx, variant, M):
     """Modulated norms keep their own launch, the one in front of the cross-attention has no modulation."""
     print(f"norm in projection {sorted(variant)} M={M}", flush=True)
     hx.check_block(hx.make_host_block(_block(1, 6, 20, 512, 8), 0, k=M, variant=variant), hx.BF16_TOL)
+
+
+# fp32: rows of up to 256, a sixteenth per thread (multiples of four, not of sixteen), around the 16-row tiles
+@pytest.mark.parametrize("C,heads", [(4, 1), (60, 3), (252, 9), (256, 8), (260, 10)])
+@pytest.mark.parametrize("M", [1, 16, 17, 36])
+def test_fp32_widths_and_row_counts(hx, C, heads, M):
+    print(f"norm in projection fp32 C={C} M={M}", flush=True)
+    wl = WL.Workload("norm", "f32", B=1, C=C, heads=heads, L=1, V=64, keep_hi=.5, keep_lo=.5,
+                     scales=(WL.Scale(grid=6, prev_grid=4, kv_len=20),), seed=31)
+    hx.check_block(hx.make_host_block(wl, 0, k=M), hx.F32_TOL)
+
+
+@pytest.mark.parametrize("variant", [{"gelu_tanh", "cross", "qk_norm"}, {"ada", "cross"}], ids=lambda v: "+".join(sorted(v)))
+def test_fp32_variants(hx, variant):
+    print(f"norm in projection fp32 {sorted(variant)}", flush=True)
+    wl = WL.Workload("norm", "f32", B=2, C=48, heads=3, L=1, V=64, keep_hi=.5, keep_lo=.5,
+                     scales=(WL.Scale(grid=6, prev_grid=4, kv_len=20),), seed=31)
+    hx.check_block(hx.make_host_block(wl, 0, k=19, variant=variant), hx.F32_TOL)
