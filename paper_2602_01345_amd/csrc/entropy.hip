@@ -147,6 +147,44 @@ __global__ __launch_bounds__(kMeanThreads) void row_mean_kernel(MeanBatch<NB> ba
   batch.mean[blockIdx.y][blockIdx.x] = t / (float)rows_per_batch;
 }
 
+// Entropies and mean of images of a few regular rows in one launch: a workgroup per image, a wave per row, then the first
+// wave takes the mean in row_mean_kernel's order, so its bits.  Of two launches most is start and end (bf16, V = 4096, us in a
+// graph, two / one: 1 row 5.3 / 3.8, 8 images of 4 rows 6.1 / 4.2, 16 of 9 6.1 / 5.7; a call from the host 7.9 / 5.5).  Up to
+// one row per SIMD at any V (V = 32768, 4 rows 20.1 / 18.4); beyond, the rows share the CU's vector units: 16 of 16 rows 6.1 /
+// 7.0, V = 16384, 9 rows 12.2 / 16.5, but V = 512, 16 rows 4.4 / 3.1.  Hence kFewElements an image.
+constexpr int kFewRows = kMeanThreads / NOVA_WAVE, kFewElements = 40960;
+template <typename T, int CH>
+__global__ __launch_bounds__(kMeanThreads) void entropy_few_rows_kernel(const T* __restrict__ logits, float* __restrict__ H,
+                                                                        float* __restrict__ mean, int rows_per_batch, int nchunk,
+                                                                        int64_t stride) {
+  __shared__ float hs[kFewRows];
+  const int lane = threadIdx.x & (NOVA_WAVE - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / NOVA_WAVE);   // the launch has a wave per row
+  const int64_t row0 = (int64_t)blockIdx.x * rows_per_batch;
+  walk_rows<T, CH>(logits, row0 + wave, (int64_t)1, (int64_t)1, nchunk, stride, lane, [&](int64_t row, float h) {
+    if (lane == 0) { H[row] = h; hs[wave] = h; }
+  });
+  __syncthreads();
+  if (wave != 0) return;
+  const float s = wave_sum(lane < rows_per_batch ? hs[min(lane, kFewRows - 1)] : 0.0f);
+  if (lane == 0) mean[blockIdx.x] = s / (float)rows_per_batch;
+}
+
+// Whether that kernel took the call
+template <typename T>
+bool launch_few_rows(hipStream_t st, const void* logits, int64_t rows_per_batch, int batch, int V, int64_t stride, float* H, float* mean) {
+  constexpr int VN = Vec16<T>::N;
+  if (rows_per_batch > kFewRows || (rows_per_batch > 4 && rows_per_batch * V > kFewElements) || (reinterpret_cast<uintptr_t>(logits) & 15) != 0 || (stride * (int64_t)sizeof(T)) % 16 != 0 ||
+      V % (NOVA_WAVE * VN) != 0)
+    return false;
+  const int sweeps = V / (NOVA_WAVE * VN), n = (int)rows_per_batch;
+  const T* p = static_cast<const T*>(logits);
+  if (sweeps % 4 == 0) entropy_few_rows_kernel<T, 4><<<batch, n * NOVA_WAVE, 0, st>>>(p, H, mean, n, sweeps / 4, stride);
+  else if (sweeps % 2 == 0) entropy_few_rows_kernel<T, 2><<<batch, n * NOVA_WAVE, 0, st>>>(p, H, mean, n, sweeps / 2, stride);
+  else entropy_few_rows_kernel<T, 1><<<batch, n * NOVA_WAVE, 0, st>>>(p, H, mean, n, sweeps, stride);
+  return true;
+}
+
 // `n` tensors of the same shape and alignment, at most NB
 template <typename T, int NB>
 void launch_t(hipStream_t st, int num_cus, int n, const void* const* logits, int64_t rows, int V, int64_t stride, float* const* H) {
@@ -192,6 +230,12 @@ hipError_t launch_entropy(hipStream_t st, int num_cus, int n, const void* const*
     int run = 1;
     const bool aligned = (reinterpret_cast<uintptr_t>(logits[i]) & 15) == 0;
     while (run < kMaxBatch && i + run < n && ((reinterpret_cast<uintptr_t>(logits[i + run]) & 15) == 0) == aligned) ++run;
+    if (run == 1 && mean &&
+        (dtype == NOVA_BF16 ? launch_few_rows<bf16_t>(st, logits[i], rows_per_batch, batch, V, stride, H[i], mean[i])
+                            : launch_few_rows<float>(st, logits[i], rows_per_batch, batch, V, stride, H[i], mean[i]))) {
+      ++i;
+      continue;
+    }
     auto go = [&](auto one, auto many) { run == 1 ? one() : many(); };
     if (dtype == NOVA_BF16)
       go([&] { launch_t<bf16_t, 1>(st, num_cus, 1, logits + i, rows, V, stride, H + i); },

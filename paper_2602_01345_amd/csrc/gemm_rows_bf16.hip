@@ -377,7 +377,7 @@ hipError_t by_plan(hipStream_t st, const RowsPlan& p, const bf16_t* A, const bf1
   constexpr bool TAKES_NORM = MODE == EPI_QKV || MODE == EPI_GELU || MODE == EPI_GELU_TANH || MODE == EPI_PLAIN;
 #define GO(RG, NG, KW, S, FIT)                                                                                       \
   if (p.rg == RG && p.ng == NG && p.kw == KW && p.s == S) {                                                          \
-    if constexpr (TAKES_NORM && RG <= kNormMaxGroups)                                                                \
+    if constexpr (TAKES_NORM && RG <= kNormMaxGroups && RG * NG > 1)                                                 \
       if (norm) return go<RG, NG, KW, S, MODE, true>(st, A, W, m_base, M, Nout, K, ep);                              \
     return norm ? hipErrorInvalidValue : go<RG, NG, KW, S, MODE, false>(st, A, W, m_base, M, Nout, K, ep);           \
   }

@@ -1,0 +1,30 @@
+"""Entropies and mean of images of up to 16 regular rows in one launch (csrc/entropy.hip) against the launches of many rows,
+which a list of two tensors takes: the same bits, at the row counts and sizes where the kernel starts and ends and for
+logits with ties, -inf and NaN."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("B,N", [(1, 1), (3, 4), (2, 15), (5, 16), (2, 17)])
+@pytest.mark.parametrize("V", [512, 1000, 1024, 2560, 6144, 32768])
+def test_same_bits_as_the_launches_of_many_rows(dtype, B, N, V):
+    from paper_2602_01345_amd import Nova
+    print(f"entropy few rows B={B} N={N} V={V} {dtype}", flush=True)
+    n = Nova(0)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(V + N)
+    x = (torch.randn((B, N, V), generator=g, device="cuda") * 5).to(dtype)
+    x[0, 0, 1:V:3] = x[0, 0, 0]
+    x[-1, -1, 5:V // 2] = -float("inf")
+    if N > 3:
+        x[0, 2, V - 1] = float("nan")
+    H = [torch.full((B, N), 7.0, device="cuda") for _ in range(3)]
+    m = [torch.full((B,), 7.0, device="cuda") for _ in range(3)]
+    n.entropy(x, H[0], m[0])
+    n.entropy_blocks([x, x], H[1:], m[1:])
+    for h, s in zip(H[1:], m[1:]):
+        assert torch.equal(H[0].view(torch.int32), h.view(torch.int32)) and torch.equal(m[0].view(torch.int32), s.view(torch.int32))
+    assert bool(torch.isnan(m[0][0])) == (N > 3) and bool(torch.isfinite(m[0][-1])) == (B > 1 or N <= 3)
