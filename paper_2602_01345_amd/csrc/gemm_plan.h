@@ -71,6 +71,8 @@ inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K,
 //    37.0 / 39.7 with separate norms, 36.6 / 38.7 with the norm in 768 and 1024 small workgroups, 34.6 / 36.2 in wider tiles).
 //  * A wave holds its rows in registers, 512 elements at a time up to kNormMaxK; a K of 64 per wave at least.
 constexpr int kNormMaxGroups = 2, kNormMaxRows = 32, kNormMaxK = 2560;
+// Vector of eight elements that a lane reads as its u-th of a row: the row's last one for lanes past its end
+constexpr int norm_vector(int u, int lane, int K) { return u * 64 + lane < K / 8 ? u * 64 + lane : K / 8 - 1; }
 inline size_t gemm_norm_lds(const RowsPlan& p, int K) { return (size_t)p.rg * 16 * K + (size_t)p.kw * p.s * p.ng * 1024 + 1024; }
 inline RowsPlan gemm_norm_plan(int num_cus, int mode, int rows, int Nout, int K) {
   RowsPlan p = {};

@@ -157,7 +157,7 @@ __global__ __launch_bounds__(KW* 64) __attribute__((amdgpu_waves_per_eu(!NORM &&
       const int64_t row = GATHER ? (int64_t)image[i] * ep.Ntok + min(max(token[i], 0), ep.Ntok - 1) : m[i];
 #pragma unroll
       for (int u = 0; u < NU; ++u)
-        x[i][u] = *reinterpret_cast<const bf16x8*>(A + row * K + (u + 1 < NU || last ? u * 64 + lane : lane) * 8);
+        x[i][u] = *reinterpret_cast<const bf16x8*>(A + row * K + (u + 1 < NU ? u * 64 + lane : norm_vector(u, lane, K)) * 8);
     }
     // the weights behind the rows, gathered ones too (in front of them: 0.6 us slower), and without branches, so that the
     // wait for the rows is not one for everything: with few units the last one comes twice

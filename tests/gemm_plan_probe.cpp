@@ -2,14 +2,35 @@
 // mode M Nout K part_floats gemm_cfg gemm_parts gemm_ksplit on standard input, for every part of the plan
 // rows:cfg:tiles:slices:reach, the few-rows kernels, which do not cut K, as rows:7:workgroups:1:reach:rg:ng:kw:s.  Reach:
 // the byte offsets into a tile end below it (its rows of 2 K bytes), 0 where the kernel takes 64-bit addresses instead.
+// With the argument "norm": for every K that a projection normalises itself, "K first end missing", the elements of a
+// row that the lanes of its wave read (first ... end - 1) and how many of the row none of them reads.
 #include <algorithm>
 #include <cstdio>
+#include <cstring>
+#include <vector>
 
 #include "gemm_plan.h"
 
 size_t head_entropy_static_capacity() { return NOVA_HEAD_ENTROPY_STATIC_BYTES; }
 
-int main() {
+static void norm_reads() {
+  for (int K = 64; K <= kNormMaxK; K += 64) {
+    std::vector<char> read(K, 0);
+    int first = K, end = 0;
+    for (int u = 0; u < (K + 511) / 512; ++u)
+      for (int lane = 0; lane < 64; ++lane)
+        for (int e = 0; e < 8; ++e) {
+          const int at = norm_vector(u, lane, K) * 8 + e;
+          first = std::min(first, at);
+          end = std::max(end, at + 1);
+          if (at >= 0 && at < K) read[at] = 1;
+        }
+    printf("%d %d %d %d\n", K, first, end, (int)std::count(read.begin(), read.end(), 0));
+  }
+}
+
+int main(int argc, char** argv) {
+  if (argc > 1 && !strcmp(argv[1], "norm")) return norm_reads(), 0;
   long long part;
   int mode, M, Nout, K, cfg, parts, ksplit;
   while (scanf("%d %d %d %d %lld %d %d %d", &mode, &M, &Nout, &K, &part, &cfg, &parts, &ksplit) == 8) {

@@ -33,6 +33,7 @@ def plan(tmp_path_factory):
         return {(mode, *(int(v) for v in p.split(":")[5:])) for (mode, _), line in zip(asked, r.stdout.split("\n"))
                 for p in line.split() if p.split(":")[1] == "7"}
     ask.few_rows_tiles = few_rows_tiles
+    ask.exe = exe
     return ask
 
 
@@ -62,6 +63,15 @@ def test_no_launch_leaves_its_32_bit_offsets(plan, M, Nout, K):
             assert K <= 1 << 21 or all(p[1] == 7 or p[4] == 0 for p in parts), (cfg, ksplit, parts)
             cut += any(p[3] > 1 for p in parts)
     assert cut or 2 * M * Nout > _part_floats(M, Nout)
+
+
+def test_a_projection_that_normalises_reads_its_rows_and_no_more(plan):
+    """Rows shorter than the 512 elements that a wave reads at a time among them: the last row of the activations ends where
+    the caller's memory may end."""
+    r = subprocess.run([plan.exe, "norm"], text=True, check=True, capture_output=True)
+    rows = [[int(v) for v in line.split()] for line in r.stdout.splitlines()]
+    assert [row[0] for row in rows] == list(range(64, 2561, 64))
+    assert all((first, end, missing) == (0, K, 0) for K, first, end, missing in rows), rows
 
 
 @pytest.mark.parametrize("K,few", [(1 << 23, True), ((1 << 23) + 2048, True), (1 << 26, True), ((1 << 26) + 64, False)])
