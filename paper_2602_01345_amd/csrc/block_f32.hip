@@ -48,26 +48,45 @@ __global__ __launch_bounds__(kTile* kTile) void gemm_f32_kernel(const float* __r
     }
   };
   if constexpr (NORM) {
-    constexpr int NE = kNormMaxK / kTile;
-    float x[NE];
+    // four vectors of a row per thread, summed as a wave of norm.hip does it, which has one per lane: the bits are its bits
+    constexpr int NV = kNormMaxK / (4 * kTile);
+    f32x4 x[NV];
 #pragma unroll
-    for (int i = 0; i < NE; ++i) x[i] = tx + i * kTile < K ? ap[tx + i * kTile] : 0.f;
-    request(0);
-    float sum = 0.f, sq = 0.f;
-#pragma unroll
-    for (int i = 0; i < NE; ++i) sum += x[i];
-    const float mean = row16_sum(sum) / (float)K;
-#pragma unroll
-    for (int i = 0; i < NE; ++i) {
-      const float d = tx + i * kTile < K ? x[i] - mean : 0.f;
-      sq = fmaf(d, d, sq);
+    for (int j = 0; j < NV; ++j) {
+      const int at = (j * kTile + tx) * 4;
+      x[j] = at < K ? *reinterpret_cast<const f32x4*>(ap + at) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    const float rstd = 1.0f / sqrtf(row16_sum(sq) / (float)K + kNormEps);
+    request(0);
+    float part[NV];
+    auto row_sum = [&]() {
+#pragma unroll
+      for (int j = 0; j < NV; ++j) part[j] = row16_sum(part[j]);
+      return (part[3] + part[2]) + (part[1] + part[0]);
+    };
+    static_assert(NV == 4, "as many as a wave has rows of sixteen lanes");
+#pragma unroll
+    for (int j = 0; j < NV; ++j) part[j] = ((x[j][0] + x[j][1]) + x[j][2]) + x[j][3];
+    const float mean = row_sum() / (float)K;
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+      part[j] = 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float d = (j * kTile + tx) * 4 < K ? x[j][e] - mean : 0.f;
+        part[j] = fmaf(d, d, part[j]);
+      }
+    }
+    const float rstd = 1.0f / sqrtf(row_sum() / (float)K + kNormEps);
     // zeros behind the row's end and in a slot past its image's keep count
     const bool live = m - image * ep.k < image_count(ep.k_rows, image, ep.k);
 #pragma unroll
-    for (int i = 0; i < NE; ++i)
-      As[ty][tx + i * kTile] = live && tx + i * kTile < K ? (x[i] - mean) * rstd : 0.f;
+    for (int j = 0; j < NV; ++j) {
+      const int at = (j * kTile + tx) * 4;
+      f32x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = live && at < K ? (x[j][e] - mean) * rstd : 0.f;
+      *reinterpret_cast<f32x4*>(&As[ty][at]) = o;
+    }
     // per-image cache lengths after this block (the up-projection: everything that reads the old ones has run)
     if (ep.kv_next && blockIdx.x == 0 && blockIdx.y == 0)
       for (int b = threadIdx.x; b * ep.k < M; b += kTile * kTile)

@@ -2,7 +2,10 @@
 row counts around their tiles and around the last count they take, widths at the ends of the range and with a last vector
 that only some lanes hold, per-image keep counts (dead slots, an image without rows, cache lengths written by the launch),
 the unmodulated variants.  Tolerance: bf16 tensors max|d| / max|ref| <= 2e-2, as everywhere: the norm is the separate
-kernel's, bit for bit.  fp32 as everywhere 2e-5: the row's sum is one over sixteen lanes instead of 64."""
+kernel's, bit for bit (held to that by blocks whose modulation, zeros and ones, leaves the norm a launch of its own).  fp32 as
+everywhere 2e-5."""
+import dataclasses
+
 import pytest
 import torch
 
@@ -63,3 +66,30 @@ def test_fp32_variants(hx, variant):
     wl = WL.Workload("norm", "f32", B=2, C=48, heads=3, L=1, V=64, keep_hi=.5, keep_lo=.5,
                      scales=(WL.Scale(grid=6, prev_grid=4, kv_len=20),), seed=31)
     hx.check_block(hx.make_host_block(wl, 0, k=19, variant=variant), hx.F32_TOL)
+
+
+def _outputs(hx, hb):
+    runner, st, x = hx.to_gpu(hb)
+    runner.run_block(st, x)
+    torch.cuda.synchronize()
+    return st.y_kept, st.k_cache, st.v_cache, st.out
+
+
+def _neutral_ada(hb):
+    """The block with a modulation that changes no bit: shifts and scales of zero, gates of one."""
+    ada = torch.zeros((hb.wl.B, 6, hb.wl.C), dtype=WL.torch_dtype(hb.wl.dtype))
+    ada[:, 2] = ada[:, 5] = 1.0
+    return dataclasses.replace(hb, variant={**(hb.variant or {}), "ada": ada})
+
+
+@pytest.mark.parametrize("C,heads", [(4, 1), (60, 3), (64, 4), (192, 12), (252, 9), (256, 8)])
+@pytest.mark.parametrize("variant", [None, {"gelu_tanh"}], ids=["erf", "tanh"])
+def test_fp32_bits_of_the_separate_norm(hx, C, heads, variant):
+    """Rows of a mean of three deviations: what another order of a row's sums would lose most of."""
+    print(f"norm in projection fp32 bits C={C}", flush=True)
+    wl = WL.Workload("norm", "f32", B=1, C=C, heads=heads, L=1, V=64, keep_hi=.5, keep_lo=.5,
+                     scales=(WL.Scale(grid=6, prev_grid=4, kv_len=20),), seed=37)
+    hb = hx.make_host_block(wl, 0, k=36, variant=variant)
+    hb.x += 3.0
+    for got, ref in zip(_outputs(hx, hb), _outputs(hx, _neutral_ada(hb))):
+        assert torch.equal(got, ref)
