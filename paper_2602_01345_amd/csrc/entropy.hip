@@ -149,10 +149,9 @@ __global__ __launch_bounds__(kMeanThreads) void row_mean_kernel(MeanBatch<NB> ba
 
 // Entropies and mean of images of a few regular rows in one launch: a workgroup per image, a wave per row, then the first
 // wave takes the mean in row_mean_kernel's order, so its bits.  Of two launches most is start and end (bf16, V = 4096, us in a
-// graph, two / one: 1 row 5.3 / 3.8, 8 images of 4 rows 6.1 / 4.2, 16 of 9 6.1 / 5.7; a call from the host 7.9 / 5.5).  Up to
-// one row per SIMD at any V (V = 32768, 4 rows 20.1 / 18.4); beyond, the rows share the CU's vector units: 16 of 16 rows 6.1 /
-// 7.0, V = 16384, 9 rows 12.2 / 16.5, but V = 512, 16 rows 4.4 / 3.1.  Hence kFewElements an image.
-constexpr int kFewRows = kMeanThreads / NOVA_WAVE, kFewElements = 40960;
+// graph, two / one: 1 row 5.3 / 3.8, 8 images of 4 rows 6.1 / 4.2, 16 of 9 6.1 / 5.7; a call from the host 7.9 / 5.5), which
+// entropy_core.h: one_launch decides by.
+static_assert(kFewRows == kMeanThreads / NOVA_WAVE);
 template <typename T, int CH>
 __global__ __launch_bounds__(kMeanThreads) void entropy_few_rows_kernel(const T* __restrict__ logits, float* __restrict__ H,
                                                                         float* __restrict__ mean, int rows_per_batch, int nchunk,
@@ -172,12 +171,11 @@ __global__ __launch_bounds__(kMeanThreads) void entropy_few_rows_kernel(const T*
 
 // Whether that kernel took the call
 template <typename T>
-bool launch_few_rows(hipStream_t st, const void* logits, int64_t rows_per_batch, int batch, int V, int64_t stride, float* H, float* mean) {
-  constexpr int VN = Vec16<T>::N;
-  if (rows_per_batch > kFewRows || (rows_per_batch > 4 && rows_per_batch * V > kFewElements) || (reinterpret_cast<uintptr_t>(logits) & 15) != 0 || (stride * (int64_t)sizeof(T)) % 16 != 0 ||
-      V % (NOVA_WAVE * VN) != 0)
-    return false;
-  const int sweeps = V / (NOVA_WAVE * VN), n = (int)rows_per_batch;
+bool launch_few_rows(hipStream_t st, int num_cus, const void* logits, int64_t rows_per_batch, int batch, int V, int64_t stride,
+                     float* H, float* mean) {
+  const int sweeps = regular_sweeps<T>(logits, V, stride);
+  if (sweeps == 0 || !one_launch<T>(num_cus, rows_per_batch, batch, V)) return false;
+  const int n = (int)rows_per_batch;
   const T* p = static_cast<const T*>(logits);
   if (sweeps % 4 == 0) entropy_few_rows_kernel<T, 4><<<batch, n * NOVA_WAVE, 0, st>>>(p, H, mean, n, sweeps / 4, stride);
   else if (sweeps % 2 == 0) entropy_few_rows_kernel<T, 2><<<batch, n * NOVA_WAVE, 0, st>>>(p, H, mean, n, sweeps / 2, stride);
@@ -188,21 +186,19 @@ bool launch_few_rows(hipStream_t st, const void* logits, int64_t rows_per_batch,
 // `n` tensors of the same shape and alignment, at most NB
 template <typename T, int NB>
 void launch_t(hipStream_t st, int num_cus, int n, const void* const* logits, int64_t rows, int V, int64_t stride, float* const* H) {
-  constexpr int VN = Vec16<T>::N;
   EntropyBatch<NB> batch = {};
   for (int i = 0; i < n; ++i) { batch.logits[i] = logits[i]; batch.H[i] = H[i]; }
-  const int vec_ok = ((reinterpret_cast<uintptr_t>(logits[0]) & 15) == 0) && ((stride * (int64_t)sizeof(T)) % 16 == 0);
-  const int per_sweep = NOVA_WAVE * VN;            // elements one 16-byte vector per lane covers
   const int64_t per_row = (rows + kWavesPerBlock - 1) / kWavesPerBlock;
-  if (vec_ok && V % per_sweep == 0) {
+  if (const int sweeps = regular_sweeps<T>(logits[0], V, stride)) {
     // at most kWavesPerSimd resident waves per SIMD over all tensors, each walking several rows
     const int64_t max_blocks = std::max<int64_t>((int64_t)num_cus * 4 * kWavesPerSimd / kWavesPerBlock / n, 1);
     const dim3 grid((unsigned)std::min<int64_t>(per_row, max_blocks), n);
-    const int sweeps = V / per_sweep, block = kWavesPerBlock * NOVA_WAVE;
+    const int block = kWavesPerBlock * NOVA_WAVE;
     if (sweeps % 4 == 0) entropy_kernel<T, 4, NB><<<grid, block, 0, st>>>(batch, rows, sweeps / 4, stride);
     else if (sweeps % 2 == 0) entropy_kernel<T, 2, NB><<<grid, block, 0, st>>>(batch, rows, sweeps / 2, stride);
     else entropy_kernel<T, 1, NB><<<grid, block, 0, st>>>(batch, rows, sweeps, stride);
   } else {
+    const int vec_ok = aligned_rows<T>(logits[0], stride);
     const dim3 grid((unsigned)per_row, n);
     entropy_generic_kernel<T, 8, NB><<<grid, kWavesPerBlock * NOVA_WAVE, 0, st>>>(batch, rows, V, stride, vec_ok);
   }
@@ -231,8 +227,8 @@ hipError_t launch_entropy(hipStream_t st, int num_cus, int n, const void* const*
     const bool aligned = (reinterpret_cast<uintptr_t>(logits[i]) & 15) == 0;
     while (run < kMaxBatch && i + run < n && ((reinterpret_cast<uintptr_t>(logits[i + run]) & 15) == 0) == aligned) ++run;
     if (run == 1 && mean &&
-        (dtype == NOVA_BF16 ? launch_few_rows<bf16_t>(st, logits[i], rows_per_batch, batch, V, stride, H[i], mean[i])
-                            : launch_few_rows<float>(st, logits[i], rows_per_batch, batch, V, stride, H[i], mean[i]))) {
+        (dtype == NOVA_BF16 ? launch_few_rows<bf16_t>(st, num_cus, logits[i], rows_per_batch, batch, V, stride, H[i], mean[i])
+                            : launch_few_rows<float>(st, num_cus, logits[i], rows_per_batch, batch, V, stride, H[i], mean[i]))) {
       ++i;
       continue;
     }

@@ -185,13 +185,36 @@ __device__ __forceinline__ void walk_rows(const T* __restrict__ logits, int64_t 
   }
 }
 
-// Chunk size for regular rows: V / (elements of one 16-byte vector per lane) sweeps per row, split into nchunk chunks
-// of CH sweeps.  Returns 0 when the rows are not regular (V not a multiple of a sweep, or unaligned).
+// Whether rows of `stride` elements all start at 16 bytes
+template <typename T>
+__host__ inline bool aligned_rows(const void* logits, int64_t stride) {
+  return (reinterpret_cast<uintptr_t>(logits) & 15) == 0 && (stride * (int64_t)sizeof(T)) % 16 == 0;
+}
+
+// Sweeps (one 16-byte vector per lane) of a regular row, which go into chunks of CH of them; 0 when the rows are not regular
+// (V not a multiple of a sweep, or unaligned).
 template <typename T>
 __host__ inline int regular_sweeps(const void* logits, int V, int64_t stride) {
   constexpr int VN = Vec16<T>::N;
-  const bool vec_ok = ((reinterpret_cast<uintptr_t>(logits) & 15) == 0) && ((stride * (int64_t)sizeof(T)) % 16 == 0);
-  return (vec_ok && V % (NOVA_WAVE * VN) == 0) ? V / (NOVA_WAVE * VN) : 0;
+  return aligned_rows<T>(logits, stride) && V % (NOVA_WAVE * VN) == 0 ? V / (NOVA_WAVE * VN) : 0;
+}
+
+// Whether images of a few regular rows and their means are one launch, a workgroup per image and a wave per row, or two.
+//  * Up to one row per SIMD at any V (bf16, V = 32768, 4 rows, us in a graph, two / one 20.1 / 18.4); beyond, the rows share the
+//    CU's vector units: 16 images of 16 rows of 4096 6.1 / 7.0, of 9 rows of 16384 12.2 / 16.5, but V = 512, 16 rows 4.4 / 3.1.
+//    Hence kFewElements an image.
+//  * Any number of images (of 4096: 1 row, V = 512 11.9 / 4.3; 4 rows, V = 4096 38.8 / 27.3) but where the kernel of four
+//    vectors a lane has more than kBusyElements an image, or in bf16 more than eight waves: a CU then holds one workgroup at a
+//    time.  bf16, V = 4096, 9 rows of 256 / 257 / 300 / 520 / 1024 / 4096 images 9.7 / 9.8 / 10.2 / 14.1 / 22.4 / 71 in two
+//    launches, 7.5 / 10.5 / 11.3 / 16.7 / 24.7 / 88 in one; V = 8192, 5 rows of 800 19.1 / 19.9; fp32, V = 6144, 6 rows of 300
+//    13.0 / 14.0.
+constexpr int kFewRows = 16, kFewElements = 40960, kBusyElements = 32768;
+template <typename T>
+__host__ inline bool one_launch(int num_cus, int64_t rows_per_batch, int batch, int V) {
+  if (rows_per_batch > kFewRows || (rows_per_batch > 4 && rows_per_batch * V > kFewElements)) return false;
+  const bool four_vectors = V % (4 * NOVA_WAVE * Vec16<T>::N) == 0;
+  const bool one_per_cu = (sizeof(T) == 2 && rows_per_batch > 8) || (rows_per_batch > 4 && rows_per_batch * V > kBusyElements);
+  return batch <= num_cus || !four_vectors || !one_per_cu;
 }
 
 }  // namespace entropy_core

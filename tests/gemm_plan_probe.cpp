@@ -4,11 +4,13 @@
 // the byte offsets into a tile end below it (its rows of 2 K bytes), 0 where the kernel takes 64-bit addresses instead.
 // With the argument "norm": for every K that a projection normalises itself, "K first end missing", the elements of a
 // row that the lanes of its wave read (first ... end - 1) and how many of the row none of them reads.
+// With the argument "entropy": of every request of bytes rows images V, 1 where entropies and means are one launch, else 0.
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <vector>
 
+#include "entropy_core.h"
 #include "gemm_plan.h"
 
 size_t head_entropy_static_capacity() { return NOVA_HEAD_ENTROPY_STATIC_BYTES; }
@@ -29,8 +31,15 @@ static void norm_reads() {
   }
 }
 
+static void entropy_launches() {
+  int bytes, rows, batch, V;
+  while (scanf("%d %d %d %d", &bytes, &rows, &batch, &V) == 4)
+    printf("%d\n", bytes == 2 ? entropy_core::one_launch<bf16_t>(256, rows, batch, V) : entropy_core::one_launch<float>(256, rows, batch, V));
+}
+
 int main(int argc, char** argv) {
   if (argc > 1 && !strcmp(argv[1], "norm")) return norm_reads(), 0;
+  if (argc > 1 && !strcmp(argv[1], "entropy")) return entropy_launches(), 0;
   long long part;
   int mode, M, Nout, K, cfg, parts, ksplit;
   while (scanf("%d %d %d %d %lld %d %d %d", &mode, &M, &Nout, &K, &part, &cfg, &parts, &ksplit) == 8) {

@@ -11,6 +11,17 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("B,N", [(1, 1), (3, 4), (2, 15), (5, 16), (2, 17)])
 @pytest.mark.parametrize("V", [512, 1000, 1024, 2560, 6144, 32768])
 def test_same_bits_as_the_launches_of_many_rows(dtype, B, N, V):
+    _check(dtype, B, N, V)
+
+
+# as many images as compute units and one more
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("B,N,V", [(B, N, V) for B in (256, 257) for N, V in ((1, 512), (8, 4096), (9, 4096), (5, 8192), (16, 2048))])
+def test_many_images(dtype, B, N, V):
+    _check(dtype, B, N, V)
+
+
+def _check(dtype, B, N, V):
     from paper_2602_01345_amd import Nova
     print(f"entropy few rows B={B} N={N} V={V} {dtype}", flush=True)
     n = Nova(0)

@@ -74,6 +74,17 @@ def test_a_projection_that_normalises_reads_its_rows_and_no_more(plan):
     assert all((first, end, missing) == (0, K, 0) for K, first, end, missing in rows), rows
 
 
+def test_entropies_of_many_images_with_their_means(plan):
+    """Sizes where one launch takes up to 24 % longer than two (0), and neighbours of them where it takes less (1)."""
+    sizes = {(2, 9, 256, 4096): 1, (2, 9, 257, 4096): 0, (2, 9, 4096, 4096): 0, (2, 8, 800, 4096): 1, (2, 9, 3000, 2048): 0,
+             (2, 16, 3000, 2048): 0, (2, 16, 3000, 2560): 1, (2, 9, 3000, 1536): 1, (2, 5, 256, 8192): 1, (2, 5, 800, 8192): 0,
+             (2, 4, 4096, 4096): 1, (2, 4, 2048, 32768): 1, (4, 9, 2048, 2048): 1, (4, 6, 256, 6144): 1,
+             (4, 6, 300, 6144): 0, (2, 16, 1, 2560): 1, (2, 16, 1, 4096): 0, (4, 16, 1, 4096): 0, (2, 17, 1, 512): 0}
+    r = subprocess.run([plan.exe, "entropy"], input="".join("%d %d %d %d\n" % s for s in sizes), text=True, check=True,
+                       capture_output=True)
+    assert [int(v) for v in r.stdout.split()] == list(sizes.values())
+
+
 @pytest.mark.parametrize("K,few", [(1 << 23, True), ((1 << 23) + 2048, True), (1 << 26, True), ((1 << 26) + 64, False)])
 def test_few_rows_keep_their_kernels_while_a_tile_fits(plan, K, few):
     """Eight rows of 2 K bytes are within 32-bit offsets up to K = 2^26: no reason to leave the few-rows kernels before."""
