@@ -44,20 +44,17 @@ hipError_t launch_block_bf16(nova_ctx* ctx, hipStream_t st, const nova_block_sha
   hipError_t e;
   // LayerNorm in front of a projection of src: few rows without modulation are normalised by the projection itself, others
   // by a launch of their own into u.  Returns the projection's operand.
-  auto layer_norm = [&](const bf16_t* src, const int32_t* src_idx, const bf16_t* shift, const bf16_t* scale, int32_t* kv_next,
-                        int mode, int Nout) -> const bf16_t* {
+  auto layer_norm = [&](int stage, const bf16_t* src, const int32_t* src_idx, const bf16_t* shift, const bf16_t* scale,
+                        int32_t* kv_next, int mode, int Nout) -> const bf16_t* {
     ep.kv_next = kv_next;
     e = hipSuccess;
     if (!shift && gemm_takes_norm(ctx, mode, M, Nout, C)) return src;
+    StageTimer t(stage < 0 ? nullptr : ctx, st, stage);
     e = launch_gather_ln(st, NOVA_BF16, src, src_idx, M, s.k, s.N, C, shift, scale, ada_pitch, u, rc.k_rows, rc.kv_rows, kv_next,
                          s.kv_len);
     return u;
   };
-  const bf16_t* in;
-  {
-    StageTimer t(ctx, st, NOVA_STAGE_GATHER_LN);
-    in = layer_norm(x, idx, ada_row(0), ada_row(1), nullptr, EPI_QKV, 3 * C);
-  }
+  const bf16_t* in = layer_norm(NOVA_STAGE_GATHER_LN, x, idx, ada_row(0), ada_row(1), nullptr, EPI_QKV, 3 * C);
   if (e != hipSuccess) return e;
 
   // the attention kernel takes its query rows multiplied by (score scale * log2 e); unit-length queries get the
@@ -93,7 +90,7 @@ hipError_t launch_block_bf16(nova_ctx* ctx, hipStream_t st, const nova_block_sha
     // written by the same thread)
     ep.bias = static_cast<const bf16_t*>(var.b_cq); ep.out = q; ep.ldo = C; ep.gate = nullptr;
     ep.q_scale = kAttnLog2e / sqrtf((float)dh);
-    in = layer_norm(x1, nullptr, nullptr, nullptr, nullptr, EPI_PLAIN, C);
+    in = layer_norm(-1, x1, nullptr, nullptr, nullptr, nullptr, EPI_PLAIN, C);
     if (e != hipSuccess) return e;
     e = launch_gemm_bf16(ctx, st, EPI_PLAIN, in, var.w_cq, M, C, C, ep, in != u);
     if (e != hipSuccess) return e;
@@ -106,10 +103,7 @@ hipError_t launch_block_bf16(nova_ctx* ctx, hipStream_t st, const nova_block_sha
     if (e != hipSuccess) return e;
   }
   const int up = var.gelu_tanh ? EPI_GELU_TANH : EPI_GELU;
-  {
-    StageTimer t(ctx, st, NOVA_STAGE_LN2);
-    in = layer_norm(x1, nullptr, ada_row(3), ada_row(4), rc.kv_next, up, F);
-  }
+  in = layer_norm(NOVA_STAGE_LN2, x1, nullptr, ada_row(3), ada_row(4), rc.kv_next, up, F);
   if (e != hipSuccess) return e;
 
   ep.bias = static_cast<const bf16_t*>(w.b_fc1); ep.out = hid; ep.ldo = F; ep.gate = nullptr;

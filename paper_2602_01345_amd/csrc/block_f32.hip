@@ -234,19 +234,16 @@ hipError_t launch_block_f32(nova_ctx* ctx, hipStream_t st, const nova_block_shap
 
   hipError_t e = hipSuccess;
   // LayerNorm of src in front of a projection: short rows without modulation are the projection's, others go through u
-  auto layer_norm = [&](const float* src, const int32_t* src_idx, const float* shift, const float* scale,
+  auto layer_norm = [&](int stage, const float* src, const int32_t* src_idx, const float* shift, const float* scale,
                         int32_t* kv_next) -> const float* {
     ep.kv_next = kv_next;
     if (!shift && C <= kNormMaxK) return src;
+    StageTimer t(stage < 0 ? nullptr : ctx, st, stage);
     e = launch_gather_ln(st, NOVA_F32, src, src_idx, M, s.k, s.N, C, shift, scale, ada_pitch, u, rc.k_rows, rc.kv_rows, kv_next,
                          s.kv_len);
     return u;
   };
-  const float* in;
-  {
-    StageTimer t(ctx, st, NOVA_STAGE_GATHER_LN);
-    in = layer_norm(x, idx, ada_row(0), ada_row(1), nullptr);
-  }
+  const float* in = layer_norm(NOVA_STAGE_GATHER_LN, x, idx, ada_row(0), ada_row(1), nullptr);
   if (e != hipSuccess) return e;
 
   ep.bias = static_cast<const float*>(w.b_qkv); ep.out = q; ep.ldo = C; ep.kc = kc; ep.vc = vc;
@@ -277,7 +274,7 @@ hipError_t launch_block_f32(nova_ctx* ctx, hipStream_t st, const nova_block_shap
   }
   if (var.w_cq) {
     // cross-attention sub-layer over the condition tokens (see block_bf16.hip)
-    in = layer_norm(x1, nullptr, nullptr, nullptr, nullptr);
+    in = layer_norm(-1, x1, nullptr, nullptr, nullptr, nullptr);
     if (e != hipSuccess) return e;
     ep.bias = static_cast<const float*>(var.b_cq); ep.out = q; ep.ldo = C; ep.gate = nullptr;
     if (in != u) gemm<EPI_PLAIN, true>(st, in, static_cast<const float*>(var.w_cq), M, C, C, ep);
@@ -289,10 +286,7 @@ hipError_t launch_block_f32(nova_ctx* ctx, hipStream_t st, const nova_block_shap
     ep.bias = static_cast<const float*>(var.b_co); ep.out = x1; ep.ldo = C; ep.res = x1;
     gemm<EPI_RESIDUAL>(st, attn, static_cast<const float*>(var.w_co), M, C, C, ep);
   }
-  {
-    StageTimer t(ctx, st, NOVA_STAGE_LN2);
-    in = layer_norm(x1, nullptr, ada_row(3), ada_row(4), rc.kv_next);
-  }
+  in = layer_norm(NOVA_STAGE_LN2, x1, nullptr, ada_row(3), ada_row(4), rc.kv_next);
   if (e != hipSuccess) return e;
 
   ep.bias = static_cast<const float*>(w.b_fc1); ep.out = hid; ep.ldo = F; ep.gate = nullptr;

@@ -68,6 +68,25 @@ def test_fp32_variants(hx, variant):
     hx.check_block(hx.make_host_block(wl, 0, k=19, variant=variant), hx.F32_TOL)
 
 
+@pytest.mark.parametrize("dtype,C,heads,M,own", [("bf16", 1024, 8, 8, 0), ("bf16", 1024, 8, 36, 1), ("f32", 64, 4, 8, 0),
+                                                 ("f32", 260, 10, 8, 1)])
+@pytest.mark.parametrize("variant", [None, {"ada", "cross"}], ids=["base", "ada"])
+def test_stages_count_the_launches_made(hx, dtype, C, heads, M, own, variant):
+    print(f"norm in projection, stages {dtype} C={C} M={M} {variant}", flush=True)
+    from paper_2602_01345_amd.binding import STAGES
+    wl = dataclasses.replace(_block(1, 6, 20, C, heads), dtype=dtype)
+    hb, n = hx.make_host_block(wl, 0, k=M, variant=variant), hx.nova()
+    runner, st, x = hx.to_gpu(hb)
+    n.profile_stages(range(len(STAGES)))
+    try:
+        runner.run_block(st, x)
+    finally:
+        n.profile_stages([])
+    torch.cuda.synchronize()
+    got = {name: n.profile_collect(i)[1] for i, name in enumerate(STAGES)}
+    assert got == {**dict.fromkeys(got, 1), **dict.fromkeys(("gather_ln", "ln2"), 1 if variant else own)}
+
+
 def _outputs(hx, hb):
     runner, st, x = hx.to_gpu(hb)
     runner.run_block(st, x)
