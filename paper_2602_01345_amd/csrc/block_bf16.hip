@@ -11,6 +11,7 @@
 // sequences them on the caller's stream.
 #include "common.h"
 #include "epilogue.h"
+#include "gemm_plan.h"
 #include "nova_internal.h"
 
 hipError_t launch_block_bf16(nova_ctx* ctx, hipStream_t st, const nova_block_shape& s,

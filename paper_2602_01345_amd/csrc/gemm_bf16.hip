@@ -761,22 +761,20 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const float* __restric
 }
 
 template <int MODE>
-hipError_t launch_part(hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W, int m_base, int M, int Nout, int K,
-                       const EpiParams<bf16_t>& ep, int slots, int cus, int ksplit, bool forced) {
+hipError_t launch_part(const nova_ctx* ctx, hipStream_t st, int cfg, const bf16_t* A, const bf16_t* W, int m_base, int M, int Nout,
+                       int K, const EpiParams<bf16_t>& ep) {
+  const int cus = ctx ? ctx->num_cus : 256, slots = ctx && ctx->gemm_persist == 0 ? 0 : cus;
   if (cfg == kRowsCfg) {
     const RowsPlan plan = gemm_rows_plan(cus, MODE, M - m_base, Nout, K);
     return launch_gemm_rows_bf16(st, plan, MODE, A, W, m_base, M, Nout, K, ep);
   }
-  // configuration 1 in its lower height; 9 is that height by force
-  const bool low = cfg == 9 || (cfg == 1 && !forced &&
-                                alternating_rows(cus, MODE, M - m_base, Nout, K, ep.part ? ep.part_floats : 0) == 192);
-  if (cfg == 9) cfg = 1;
+  const bool low = low_launch(ctx, cfg, MODE, M - m_base, Nout, K, ep.part ? ep.part_floats : 0);
   if constexpr (MODE == EPI_RESIDUAL) {
     // see k_slices; the scratch buffer holds 4 x rows x C floats, hence Nout == C
-    if (((cfg == 1 && !low) || cfg == 2 || cfg == 5 || cfg == 6) && ep.part && Nout == ep.C && Nout % 8 == 0) {
+    if (cut_in_k(cfg, low) && ep.part && Nout == ep.C && Nout % 8 == 0) {
       const int bm = cfg == 5 ? 128 : cfg == 6 ? 192 : 256, bn = cfg == 1 ? 256 : 128;
       const int tiles = ((M - m_base + bm - 1) / bm) * ((Nout + bn - 1) / bn);
-      const int ks = k_slices(cus, MODE, tiles, M - m_base, Nout, K, ep.part_floats, ksplit);
+      const int ks = k_slices(cus, MODE, tiles, M - m_base, Nout, K, ep.part_floats, ctx ? ctx->gemm_ksplit : -1);
       if (ks > 1) {
         hipError_t e;
         if (far_tile(K)) e = launch_cfg<256, 128, 4, 2, 64, 3, false, EPI_PARTIAL, true>(st, A, W, m_base, M, Nout, K, ep, 0, ks);
@@ -825,10 +823,7 @@ hipError_t launch_mode(const nova_ctx* ctx, hipStream_t st, const bf16_t* A, con
     return launch_gemm_rows_bf16(st, gemm_norm_plan(ctx ? ctx->num_cus : 256, MODE, M, Nout, K), MODE, A, W, 0, M, Nout, K, ep, true);
   const Plan p = plan_rows(ctx, MODE, M, Nout, K, ep.part ? ep.part_floats : 0);
   for (int i = 0; i < p.n; ++i) {
-    const int cus = ctx ? ctx->num_cus : 256;
-    const hipError_t e = launch_part<MODE>(st, p.cfg[i], A, W, p.m_base[i], p.m_end[i], Nout, K, ep,
-                                           (ctx && ctx->gemm_persist == 0) ? 0 : cus, cus,
-                                           ctx ? ctx->gemm_ksplit : -1, forced_tile(ctx));
+    const hipError_t e = launch_part<MODE>(ctx, st, p.cfg[i], A, W, p.m_base[i], p.m_end[i], Nout, K, ep);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -843,10 +838,6 @@ int gemm_bf16_tile_cols(const nova_ctx* ctx, int M, int Nout, int K) {
     case 3: case 4: return 32;
     default: return 128;
   }
-}
-
-bool gemm_takes_norm(const nova_ctx* ctx, int mode, int M, int Nout, int K) {
-  return !forced_tile(ctx) && gemm_norm_plan(ctx ? ctx->num_cus : 256, mode, M, Nout, K).rg > 0;
 }
 
 hipError_t launch_gemm_bf16(const nova_ctx* ctx, hipStream_t st, int mode, const void* A, const void* W, int M,

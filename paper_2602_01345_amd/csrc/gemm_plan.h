@@ -186,6 +186,11 @@ inline bool forced_tile(const nova_ctx* ctx) {
   return ctx && ctx->gemm_cfg >= 0 && ctx->gemm_cfg < kNumCfgs && ctx->gemm_cfg != kRowsCfg;
 }
 
+// Whether a projection behind a LayerNorm without modulation normalises its rows itself.
+inline bool gemm_takes_norm(const nova_ctx* ctx, int mode, int M, int Nout, int K) {
+  return !forced_tile(ctx) && gemm_norm_plan(ctx ? ctx->num_cus : 256, mode, M, Nout, K).rg > 0;
+}
+
 // Rows of a tile of configuration 1: the height that the model prices lower.
 inline int alternating_rows(int slots, int mode, int M, int Nout, int K, int64_t part_floats) {
   int bm = 256;
@@ -197,6 +202,13 @@ inline int alternating_rows(int slots, int mode, int M, int Nout, int K, int64_t
   }
   return bm;
 }
+
+// Whether a launch of configuration cfg is of 192 x 256 tiles, and whether it can be cut in K.
+inline bool low_launch(const nova_ctx* ctx, int cfg, int mode, int rows, int Nout, int K, int64_t part_floats) {
+  if (cfg == 9) return true;
+  return cfg == 1 && !forced_tile(ctx) && alternating_rows(ctx ? ctx->num_cus : 256, mode, rows, Nout, K, part_floats) == 192;
+}
+inline bool cut_in_k(int cfg, bool low) { return (cfg == 1 && !low) || cfg == 2 || cfg == 5 || cfg == 6; }
 
 inline int pick_cfg(const nova_ctx* ctx, int mode, int M, int Nout, int K, int64_t part_floats, double* t_out = nullptr) {
   if (forced_tile(ctx)) {

@@ -117,8 +117,8 @@ hipError_t launch_block_f32(nova_ctx* ctx, hipStream_t st, const nova_block_shap
                             float* kc, float* vc, float* y, const BlockWorkspace& ws);
 // gemm_bf16.hip: out = epilogue(A W^T) on the matrix cores; mode is an EpiMode
 template <typename T> struct EpiParams;
-// norm: A's rows are normalised on the way (only where gemm_takes_norm), in mode EPI_QKV gathered through ep.idx as well
-bool gemm_takes_norm(const nova_ctx* ctx, int mode, int M, int Nout, int K);
+// norm: A's rows are normalised on the way (only where gemm_plan.h: gemm_takes_norm), in mode EPI_QKV gathered through ep.idx
+// as well
 hipError_t launch_gemm_bf16(const nova_ctx* ctx, hipStream_t st, int mode, const void* A, const void* W, int M,
                             int Nout, int K, const EpiParams<__bf16>& ep, bool norm = false);
 // gemm_rows_bf16.hip: the same for few rows [m_base, M), by a plan of gemm_plan.h.  The plan's rg is 0 where the shape is

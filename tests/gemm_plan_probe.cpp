@@ -1,7 +1,9 @@
 // Prints what csrc/gemm_plan.h plans on 256 compute units (tests/test_gemm_plan.py): one line per request of
 // mode M Nout K part_floats gemm_cfg gemm_parts gemm_ksplit on standard input, for every part of the plan
-// rows:cfg:tiles:slices:reach, the few-rows kernels, which do not cut K, as rows:7:workgroups:1:reach:rg:ng:kw:s.  Reach:
-// the byte offsets into a tile end below it (its rows of 2 K bytes), 0 where the kernel takes 64-bit addresses instead.
+// rows:cfg:tiles:slices:reach:bm:bn (tile rows and columns), the few-rows kernels, which do not cut K, as
+// rows:7:workgroups:1:reach:rg:ng:kw:s, all rows in a projection that normalises them with ":norm" behind it.  Reach: the byte
+// offsets into a tile end below it (its rows of 2 K bytes), 0 where the kernel takes 64-bit addresses instead.  A mode with 16
+// added has a LayerNorm without modulation in front.
 // With the argument "norm": for every K that a projection normalises itself, "K first end missing", the elements of a
 // row that the lanes of its wave read (first ... end - 1) and how many of the row none of them reads.
 // With the argument "entropy": of every request of bytes rows images V, 1 where entropies and means are one launch, else 0.
@@ -47,21 +49,33 @@ int main(int argc, char** argv) {
     c.num_cus = 256;
     c.gemm_cfg = cfg;
     c.gemm_parts = parts;
+    c.gemm_ksplit = ksplit;
+    auto few_rows = [&](const RowsPlan& r, int rows, const char* norm) {
+      printf("%d:7:%d:1:%lld:%d:%d:%d:%d%s ", rows, (rows + 8 * r.rg - 1) / (8 * r.rg) * (Nout / (8 * r.ng)),
+             8LL * std::max(r.rg, r.ng) * 2 * K, r.rg, r.ng, r.kw, r.s, norm);
+    };
+    const bool norm = mode >= 16 && gemm_takes_norm(&c, mode & 15, M, Nout, K);
+    mode &= 15;
+    if (norm) {
+      few_rows(gemm_norm_plan(256, mode, M, Nout, K), M, ":norm");
+      printf("\n");
+      continue;
+    }
     const Plan p = plan_rows(&c, mode, M, Nout, K, part);
     for (int i = 0; i < p.n; ++i) {
       const int rows = p.m_end[i] - p.m_base[i];
       if (p.cfg[i] == kRowsCfg) {
-        const RowsPlan r = gemm_rows_plan(256, mode, rows, Nout, K);
-        printf("%d:7:%d:1:%lld:%d:%d:%d:%d ", rows, (rows + 8 * r.rg - 1) / (8 * r.rg) * (Nout / (8 * r.ng)),
-               8LL * std::max(r.rg, r.ng) * 2 * K, r.rg, r.ng, r.kw, r.s);
+        few_rows(gemm_rows_plan(256, mode, rows, Nout, K), rows, "");
         continue;
       }
+      const bool low = low_launch(&c, p.cfg[i], mode, rows, Nout, K, part);
       const Candidate* t = &kCands[1];
       for (const Candidate& q : kCands)
-        if (q.cfg == p.cfg[i]) t = &q;
+        if (low ? low_tile(q) : q.cfg == p.cfg[i] && !low_tile(q)) t = &q;
       const int tiles = (rows + t->bm - 1) / t->bm * ((Nout + t->bn - 1) / t->bn);
-      printf("%d:%d:%d:%d:%lld ", rows, p.cfg[i], tiles, k_slices(256, mode, tiles, rows, Nout, K, part, ksplit),
-             far_tile(K) ? 0 : 2LL * std::max(t->bm, t->bn) * K);
+      const int slices = cut_in_k(p.cfg[i], low) ? k_slices(256, mode, tiles, rows, Nout, K, part, ksplit) : 1;
+      printf("%d:%d:%d:%d:%lld:%d:%d ", rows, p.cfg[i], tiles, slices, far_tile(K) ? 0 : 2LL * std::max(t->bm, t->bn) * K, t->bm,
+             t->bn);
     }
     printf("\n");
   }

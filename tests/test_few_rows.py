@@ -27,9 +27,10 @@ def _block(B, grid, P, C, heads):
 AROUND_THE_TILES = [(64, 1), (320, 5), (1024, 8)], [1, 8, 9, 16, 17, 32, 33, 64, 65, 129, 257]
 WIDTHS = [(2048, 16, 5), (2048, 16, 12), (2048, 16, 30), (2048, 16, 50), (2048, 16, 100), (1920, 30, 72), (512, 8, 511),
           (1024, 8, 512)]
-# tiles that the widths above do not reach, or not in every projection: 8 x 32, 16 x 32, 32 x 64, 64 x 64 with one unit in flight
+# tiles that the widths above do not reach, or not in every projection: 8 x 32 (of more rows than a projection normalises itself),
+# 16 x 32, 32 x 64, 64 x 64 with one unit in flight
 OTHER_TILES = [(1152, 18, 1), (1152, 18, 8), (1536, 24, 7), (1536, 24, 165), (704, 11, 87), (384, 6, 330), (2112, 33, 5),
-               (2112, 33, 9), (2112, 33, 451), (2304, 36, 213)]
+               (2112, 33, 9), (2112, 33, 451), (2304, 36, 213), (384, 6, 36), (384, 6, 50)]
 BEYOND_512 = [(1024, 8, 257), (1024, 8, 511), (512, 8, 600)]
 SIZES = ([(C, M) for C, _ in AROUND_THE_TILES[0] for M in AROUND_THE_TILES[1]] + [(C, M) for C, _, M in WIDTHS + OTHER_TILES] +
          [(C, 2 * k) for C, _, k in BEYOND_512])

@@ -1,9 +1,10 @@
 """GPU parity of the projections that normalise their rows themselves (csrc/gemm_rows_bf16.hip, block_f32.hip) against the oracle:
-row counts around their tiles and around the last count they take, widths at the ends of the range and with a last vector
-that only some lanes hold, per-image keep counts (dead slots, an image without rows, cache lengths written by the launch),
-the unmodulated variants.  Tolerance: bf16 tensors max|d| / max|ref| <= 2e-2, as everywhere: the norm is the separate
-kernel's, bit for bit (held to that by blocks whose modulation, zeros and ones, leaves the norm a launch of its own).  fp32 as
-everywhere 2e-5."""
+row counts around their tiles of 8 and 16 rows and around the last one they take (16 in wide projections, which pick tiles of 32
+rows beyond, else 24 or 32), widths at the ends of the range and with a last vector that only some lanes hold, every tile in
+every projection that picks it (tests/test_gemm_plan.py holds the sizes to that), per-image keep counts (dead slots, an image
+without rows, cache lengths written by the launch), the unmodulated variants.  Tolerance: bf16 tensors max|d| / max|ref| <=
+2e-2, as everywhere; fp32 2e-5.  The norm's bits are those of the separate kernel: an image alone, whose projections normalise,
+against the same image among others, whose do not, and fp32 blocks against blocks with a modulation of zeros and ones."""
 import dataclasses
 
 import pytest
@@ -28,11 +29,47 @@ def _block(B, grid, P, C, heads):
 
 
 # below, at and inside the range of K (256 ... 2560), 512-element vectors whole and in part
-@pytest.mark.parametrize("C,heads", [(192, 3), (256, 4), (576, 9), (1024, 8), (1600, 25), (2496, 39), (2560, 20), (2624, 41)])
-@pytest.mark.parametrize("M", [1, 9, 32, 33])
+WIDTHS = [(192, 3), (256, 4), (576, 9), (1024, 8), (1600, 25), (2496, 39), (2560, 20), (2624, 41)]
+ROWS = [1, 9, 16, 17, 32, 33]
+
+
+@pytest.mark.parametrize("C,heads", WIDTHS)
+@pytest.mark.parametrize("M", ROWS)
 def test_widths_and_row_counts(hx, C, heads, M):
     print(f"norm in projection C={C} M={M}", flush=True)
     hx.check_block(hx.make_host_block(_block(1, 6, 20, C, heads), 0, k=M), hx.BF16_TOL)
+
+
+# every tile in front of the cross-attention and of the tanh form
+CROSS = [(512, 8, 3), (576, 9, 13), (1088, 17, 26), (1536, 12, 3), (1792, 28, 9), (2112, 33, 17), (704, 11, 17)]
+
+
+@pytest.mark.parametrize("C,heads,M", CROSS)
+def test_cross_attention_and_tanh(hx, C, heads, M):
+    print(f"norm in projection, cross C={C} M={M}", flush=True)
+    hx.check_block(hx.make_host_block(_block(1, 6, 20, C, heads), 0, k=M, variant={"gelu_tanh", "cross"}), hx.BF16_TOL)
+
+
+# images of k rows, and as many of them as make a separate launch of the norm
+AMONG_OTHERS = [(256, 4, 1, 33), (512, 8, 26, 2), (1088, 17, 26, 2), (1600, 25, 9, 4), (1792, 28, 9, 4), (2112, 33, 17, 2),
+                (2304, 36, 8, 5), (2560, 20, 16, 3)]
+
+
+@pytest.mark.parametrize("C,heads,k,B", AMONG_OTHERS)
+@pytest.mark.parametrize("variant", [None, {"gelu_tanh", "cross"}], ids=["base", "cross"])
+def test_bits_of_the_separate_norm(hx, monkeypatch, C, heads, k, B, variant):
+    print(f"norm in projection, bits C={C} k={k} {variant}", flush=True)
+    from paper_2602_01345_amd import Nova
+    monkeypatch.setenv("NOVA_ATTN_SPLIT", "1")           # keys of an item are not cut, whatever the number of items
+    monkeypatch.setattr(hx, "_NOVA", Nova(0))
+    hb = hx.make_host_block(_block(B, 6, 20, C, heads), 0, k=k, variant=variant)
+    first = {f.name: getattr(hb, f.name)[:1] for f in dataclasses.fields(hb) if f.name in ("logits", "x", "k_prior", "v_prior", "cache_prev")}
+    if variant:
+        cross = {n: t[:1] if n in ("k_text", "v_text") else t for n, t in hb.variant["cross"].items()}
+        first["variant"] = {**hb.variant, "cross": cross}
+    alone = dataclasses.replace(hb, wl=dataclasses.replace(hb.wl, B=1), **first)
+    for got, ref in zip(_outputs(hx, alone), _outputs(hx, hb)):
+        assert torch.equal(got[0], ref[0])
 
 
 @pytest.mark.parametrize("k_rows,kv_rows", [([5, 0, 1, 7], [20, 3, 0, 11]), ([0, 0, 8, 0], [0, 20, 1, 2]), ([0, 0, 0, 1], [4, 4, 4, 4])])

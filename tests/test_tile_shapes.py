@@ -1,7 +1,7 @@
-"""GPU parity of the projection tiles that stand in where others leave CUs idle (csrc/gemm_bf16.hip, by force) against the
-oracle where their K loops and edges change: one, two, three and more K steps than stages, an odd number, rows and features that end inside
+"""GPU parity of the projection tiles that stand in where others leave CUs idle (csrc/gemm_bf16.hip) against the oracle, by force
+where their K loops and edges change: one, two, three and more K steps than stages, an odd number, rows and features that end inside
 a tile and on its edge, gated residuals, more tiles than compute units (a workgroup then walks several, each starting in the
-first LDS buffer).  Tolerance: bf16 tensors max|d| / max|ref| <= 2e-2, as everywhere (the products and
+first LDS buffer), and at sizes where the plan chooses them, for all rows and for the first or last of two launches.  Tolerance: bf16 tensors max|d| / max|ref| <= 2e-2, as everywhere (the products and
 their sums are fp32)."""
 import pytest
 import torch
@@ -50,3 +50,17 @@ def test_128_x_128_with_a_long_k(monkeypatch):
     monkeypatch.setattr(hx, "_NOVA", Nova(0))
     print("tile shapes C=2048 128 x 128", flush=True)
     hx.check_block(hx.make_host_block(_block(1, 13, 40, 2048, 16), 0, k=129), hx.BF16_TOL)
+
+
+# C, heads, images, kept tokens, image compared, and (projection: 0 QKV, 1 output, 2 up, 3 down; launch of it; tile) of its rows
+CHOSEN = [(704, 11, 6, 249, 5, [(1, 0, 128, 64), (3, 0, 128, 64)]), (768, 12, 2, 257, 1, [(0, 0, 128, 64), (2, 0, 128, 64)]),
+          (1344, 21, 14, 425, 13, [(0, 0, 192, 256), (3, 0, 192, 256)]), (2304, 36, 8, 512, 3, [(1, 0, 192, 256), (3, 0, 192, 256)]),
+          (1984, 31, 7, 404, 6, [(0, 1, 192, 256), (2, 0, 192, 256)]), (2368, 37, 4, 418, 3, [(0, 0, 192, 256), (2, 1, 192, 256)]),
+          (960, 15, 9, 667, 8, [(0, 1, 128, 64), (2, 0, 192, 256)]), (960, 15, 11, 518, 0, [(0, 0, 128, 64)])]
+
+
+@pytest.mark.parametrize("C,heads,B,k,image,tiles", CHOSEN)
+def test_sizes_where_the_plan_chooses_them(C, heads, B, k, image, tiles):
+    import harness as hx
+    print(f"tile shapes chosen C={C} M={B * k}", flush=True)
+    hx.check_block(hx.make_host_block(_block(B, 27, 30, C, heads), 0, k=k), hx.BF16_TOL, rows=[image])
