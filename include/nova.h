@@ -365,8 +365,8 @@ int nova_layer_ratio(nova_ctx* ctx, void* stream, const float* mean_entropy, flo
  * needed).  nova_profile_collect waits for all recorded events, returns the summed elapsed
  * milliseconds and the launch count of `stage` (host pointers, either may be NULL) and
  * releases that stage's events.  A mask of 0 switches timing off (the default).
- * A LayerNorm that the projection behind it takes along (no modulation, bf16: up to 32 rows, fp32: C <= 256) is no launch of
- * its own: its stage counts none, and its time is part of the projection's.
+ * A LayerNorm that the projection behind it takes along (no modulation; bf16: few rows, at most 32; fp32: C <= 256) is no
+ * launch of its own: its stage counts none, and its time is part of the projection's.
  */
 enum {
   NOVA_STAGE_ENTROPY = 0,   /* nova_entropy kernel                                  */

@@ -63,12 +63,15 @@ inline RowsPlan gemm_rows_plan(int num_cus, int mode, int rows, int Nout, int K,
 
 // Few rows that the projection normalises itself (rg = 0: a launch of its own does it).
 //  * Every workgroup normalises its tile's rows again, on one wave per SIMD: some 0.6 us of vector work with 8 rows of 1024, 1.4
-//    with 16, against 2.8 us of a launch.  Two norms, us per block in a graph, B images (separate / in the projection): C = 1024
-//    1 row 22.5 / 19.6, 8 rows 23.4 / 19.8, 16 rows 26.6 / 25.3, 32 rows 27.7 / 26.8, 48 rows 29.0 / 29.1; C = 512 1 ... 16 rows
-//    -1.8 ... -2.6, 48 rows 23.8 / 22.2; C = 1536 8 rows 32.6 / 28.7, 32 rows 42.3 / 42.4; C = 2304 8 rows 46.5 / 43.7, 16 rows
-//    54.4 / 54.3; tiles of 32 rows normalise for 2.5 ... 3.5 us and gain nothing (C = 1024, 36 ... 100 rows: 0 ... +2 us).
-//  * Up to eight rows no more workgroups than CUs: three or four small ones per CU would each normalise (C = 2048, 1 / 8 rows
-//    37.0 / 39.7 with separate norms, 36.6 / 38.7 with the norm in 768 and 1024 small workgroups, 34.6 / 36.2 in wider tiles).
+//    with 16, against 2.8 us of a launch.  Two norms, us per block in a graph (separate / in the projection): C = 1024 1 row
+//    22.4 / 19.6, 8 rows 23.4 / 19.9, 16 rows 26.9 / 26.2, 32 rows 28.0 / 26.6; C = 512 16 rows 22.6 / 19.7, 32 rows 23.2 /
+//    21.5; C = 2048 8 rows 39.1 / 35.3, 16 rows 45.7 / 43.4; C = 2560 1 row 47.3 / 45.0, 8 rows 51.9 / 48.2, 16 rows 60.6 / 60.0
+//    (QKV alone).  Tiles of 32 rows normalise for 2.5 ... 3.5 us and gain nothing (C = 1024, 36 ... 100 rows: 0 ... +2 us).
+//    So tiles of 8 or 16 rows: any projection of up to 8 rows, of up to 16 but for 8192 features and more, which get taller
+//    tiles, and of up to 32 of the narrower ones (QKV to C = 1344, up to 1024, cross-attention query to 2048; 256 CUs).
+//  * Up to eight rows not the smallest tiles: three or four workgroups per CU would each normalise (C = 2048, 1 / 8 rows
+//    37.0 / 39.7 with separate norms, 36.6 / 38.7 with the norm in 768 and 1024 workgroups of 8 x 8, 34.6 / 36.2 in wider tiles).
+//    Up projections of more than 8192 features are still 528 ... 640 workgroups of 8 x 16 (C = 2112 ... 2560 above).
 //  * A wave holds its rows in registers, 512 elements at a time up to kNormMaxK; a K of 64 per wave at least.
 constexpr int kNormMaxGroups = 2, kNormMaxRows = 32, kNormMaxK = 2560;
 // Vector of eight elements that a lane reads as its u-th of a row: the row's last one for lanes past its end
@@ -97,7 +100,7 @@ inline RowsPlan gemm_norm_plan(int num_cus, int mode, int rows, int Nout, int K)
 //   5: 128x128x64, 8 waves of 64x32, 3 stages or, from K = kDeepK on, 4, one workgroup per CU (two waves per SIMD hide the LDS
 //      waits that four waves of 64x64 expose: 3-10 % faster at every shape measured).  Three / four stages, us, weights from
 //      memory: 900 rows, K = 2304, 2304 features 21.6 / 19.5, 6912 features 44.4 / 42.0; 520 rows, K = 2048, 6144 features
-//      20.7 / 19.9; but K = 1536 13.0 / 13.2, K = 1024 10.1 / 10.4 (five: nowhere better than four)
+//      20.7 / 19.9; but K = 1536 13.0 / 13.2, K = 1024 10.1 / 10.4 (five: nowhere better than four).  K slices of it have 3
 //   7: the few-rows kernels of gemm_rows_bf16.hip (chosen by gemm_rows_plan, not by force)
 //   8: 128x64x64, 8 waves of 32x32, 6 stages (with 3: K = 2304 18.6 us in place of 16.3): a narrow output of some 800 ... 2000
 //      rows, which 128x128 tiles spread over half of the CUs (us, weights from memory, 128x128 / 128x64: 820 rows, 2304 features
@@ -107,12 +110,16 @@ inline RowsPlan gemm_norm_plan(int num_cus, int mode, int rows, int Nout, int K)
 // Without a forced choice the launcher prices 1, 2, 5, 6 and 8 with a model fitted to measurements on MI355X (300 ... 6144
 // rows, widths C of 640 ... 2304, outputs of C, 3C and 4C features, K = C and 4C): a launch takes rounds of one tile
 // per CU; a round costs a fixed time (first loads, epilogue) and a time per element of K that grows with the share of
-// the CUs that are busy (they share L2, memory and power).  Fitted for the choice, not for the times, to whole blocks
-// whose weights come from memory as a model's do, with and without K slices and in one launch or two: what it chooses is
-// 0.08 % of the block's time from the best on average, 4 % at worst (426 sizes; 0.1 % and 7 % on the half of them that a
-// fit leaves out).  A fit to launches that find their weights in L2 makes a single round of 256 x 256 tiles too dear
-// against two of smaller ones, which fetch the weights more often: 0.25 %, and blocks up to 7 % slower (1500 rows,
-// C = 1920 / 2048 226 / 237 us, with this one 212 / 228; 1800 rows, C = 1024 126 and 120).
+// the CUs that are busy (they share L2, memory and power).  The prices of 256x256, 2, 6 and of 5 with three stages at any K are
+// fitted for the choice, not for the times, to whole blocks whose weights come from memory as a model's do, with and without
+// K slices and in one launch or two: what they chose among themselves was 0.08 % of the block's time from the best on
+// average, 4 % at worst (426 sizes; 0.1 % and 7 % on the half of them that a fit leaves out).  192x256 and 8 are priced beside
+// them from launches of their own, not in one fit: a block of 160 sizes (513 ... 6000 rows, C = 512 ... 2304) that the two, or
+// the fourth stage of 5, change takes 0.972 of its time without on average, 0.89 at best, 1.015 at worst (C = 1600, 4928 rows
+// 380 / 386 us; single launches 1.03 at worst: 5984 rows, K = 5376, 1344 features 89.8 / 92.6).  A fit to launches that find their weights in L2
+// makes a single round of 256 x 256 tiles too dear against two of smaller ones, which fetch the weights more often: 0.25 %,
+// and blocks up to 7 % slower (1500 rows, C = 1920 / 2048 226 / 237 us, with this one 212 / 228; 1800 rows, C = 1024 126 and
+// 120).
 constexpr int kNumCfgs = 10;
 constexpr int kRowsCfg = 7;
 constexpr int kDeepK = 2048;

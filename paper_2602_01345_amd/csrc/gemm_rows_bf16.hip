@@ -17,9 +17,9 @@
 //    lane offset and a scalar, no accumulation registers to move out of.
 //  * The epilogue works on eight consecutive features of one row per thread, rows fastest, so that value-cache
 //    columns (key index minor) are written in runs of rows; its bias and residual are requested before the K walk.
-//  * Up to 32 rows a projection that starts from a LayerNorm takes it along (NORM): the norm's own launch is 2.8 us of which
-//    half is starting and ending, and its rows are a latency that the weights' covers (a block of one / eight rows of 1024 in
-//    a graph 22.6 / 23.5 -> 19.4 / 20.1 us).
+//  * In tiles of 8 or 16 rows, K of 256 ... 2560 and at most 32 rows (gemm_norm_plan), a projection behind a LayerNorm without
+//    modulation takes it along (NORM): the norm's own launch is 2.8 us of which half is starting and ending, and its rows are
+//    a latency that the weights' covers (a block of one / eight rows of 1024 in a graph 22.4 / 23.4 -> 19.6 / 19.9 us).
 // Measured in a graph, weights from HBM (us; with the divisions and 64-row tiles whatever the width / now / a stream of the
 // same bytes): K = 1024, Nout = 1024 / 3072 / 4096, one row 3.1 / 4.2 / 4.5 -> 2.7 / 3.6 / 3.9 (- / 2.9 / 3.3), 64 rows
 // 4.3 / 5.9 / 6.1 -> 3.0 / 4.9 / 5.1; K = 4096, Nout = 1024, one row 4.8 -> 4.4, 64 rows 9.3 -> 6.7.
