@@ -116,10 +116,10 @@ inline RowsPlan gemm_norm_plan(int num_cus, int mode, int rows, int Nout, int K)
 // average, 4 % at worst (426 sizes; 0.1 % and 7 % on the half of them that a fit leaves out).  192x256 and 8 are priced beside
 // them from launches of their own, not in one fit: a block of 160 sizes (513 ... 6000 rows, C = 512 ... 2304) that the two, or
 // the fourth stage of 5, change takes 0.972 of its time without on average, 0.89 at best, 1.015 at worst (C = 1600, 4928 rows
-// 380 / 386 us; single launches 1.03 at worst: 5984 rows, K = 5376, 1344 features 89.8 / 92.6).  A fit to launches that find their weights in L2
-// makes a single round of 256 x 256 tiles too dear against two of smaller ones, which fetch the weights more often: 0.25 %,
-// and blocks up to 7 % slower (1500 rows, C = 1920 / 2048 226 / 237 us, with this one 212 / 228; 1800 rows, C = 1024 126 and
-// 120).
+// 380 / 386 us; single launches 1.03 at worst: 5984 rows, K = 5376, 1344 features 89.8 / 92.6).  A fit to launches that find
+// their weights in L2 makes a single round of 256 x 256 tiles too dear against two of smaller ones, which fetch the weights
+// more often: 0.25 %, and blocks up to 7 % slower (1500 rows, C = 1920 / 2048 226 / 237 us, with this one 212 / 228; 1800 rows,
+// C = 1024 126 and 120).
 constexpr int kNumCfgs = 10;
 constexpr int kRowsCfg = 7;
 constexpr int kDeepK = 2048;
